@@ -36,14 +36,36 @@ constexpr int kStatsWaves = 4;        // waves per workgroup
 // Row id of a workgroup: grid.y carries the low part, grid.z the rest (grid.y <= 65535).
 constexpr int kRowsPerGridY = 32768;
 
-// A 16-byte load, optionally marked as streaming (nontemporal).  Streaming loads reach a higher
-// rate on a pass over logits that are larger than the caches, but leave nothing behind for the
-// kernels that follow; STREAM is chosen per entry point by how much of the rows those re-read.
+// A 16-byte load at any element address (the type says so to the compiler, which then relies on
+// the unaligned access that the amdhsa target guarantees for global memory: the same instruction
+// as an aligned load, at most one cache line more per wave).  Optionally marked as streaming
+// (nontemporal): streaming loads reach a higher rate on a pass over logits that are larger than
+// the caches, but leave nothing behind for the kernels that follow; STREAM is chosen per entry
+// point by how much of the rows those re-read.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 template <bool STREAM>
 __device__ __forceinline__ u32x4 load16(const void *p) {
-  if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-  else return *reinterpret_cast<const u32x4 *>(p);
+  if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(p));
+  else return *reinterpret_cast<const u32x4_any *>(p);
+}
+
+template <bool BF16>
+constexpr int kPer16 = BF16 ? 8 : 4;    // logits in 16 bytes
+
+// The 16 bytes of logits that a load16 brought, as floats.
+template <bool BF16>
+__device__ __forceinline__ void unpack16(const u32x4 w, float *x) {
+  const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if constexpr (BF16) {
+      x[2 * k] = __uint_as_float(ww[k] << 16);
+      x[2 * k + 1] = __uint_as_float(ww[k] & 0xffff0000u);
+    } else {
+      x[k] = __uint_as_float(ww[k]);
+    }
+  }
 }
 
 // exp((x - M) / temperature) for one element, argument in two pieces so that its error stays
@@ -112,7 +134,8 @@ __device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t row, fl
   }
 }
 
-template <bool BF16, bool VEC, bool STREAM>
+// WIDE: a row holds at least one 16-byte piece (V >= 8 bf16 or 4 fp32 logits).
+template <bool BF16, bool WIDE, bool STREAM>
 __global__ __launch_bounds__(kStatsWaves *kWave) void row_stats_kernel(RowSet rs, int32_t V,
                                                                        int32_t nparts, int64_t nrows,
                                                                        float c, StatPart *parts,
@@ -136,37 +159,37 @@ __global__ __launch_bounds__(kStatsWaves *kWave) void row_stats_kernel(RowSet rs
   const void *rowp = row_base(rs, row, BF16);
   const int32_t e0 = part * kPartElems;
 
+  // 16-byte loads, all issued before the first use; each instruction covers 1 KiB of the row.
+  // Rows need no alignment (see load16).  In the last part of a row, pieces that would cross its
+  // end are read where the row's last 16 bytes lie instead, and what belongs to the piece before
+  // (or to no piece) is masked: no branch, every load in flight, nothing read past the row.
+  // (Element by element such parts took 12.9 us where whole parts take 3.7: V = 20 011, 75 rows.)
   float x[32];
-  if (VEC && e0 + kPartElems <= V) {
-    // interior part of an aligned row: 16-byte loads, all issued before the first use;
-    // each load instruction covers 1 KiB of the row
-    if constexpr (BF16) {
-      const uint4 *src = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(rowp) + e0);
-      u32x4 w[4];
+  if constexpr (WIDE) {
+    constexpr int per = kPer16<BF16>, nv = 32 / per;
+    const char *src = reinterpret_cast<const char *>(rowp);
+    constexpr int esz = BF16 ? 2 : 4;
+    u32x4 w[nv];
+    if (e0 + kPartElems <= V) {
+      src += (int64_t) e0 * esz;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = load16<STREAM>(src + j * kWave + lane);
+      for (int j = 0; j < nv; ++j) w[j] = load16<STREAM>(src + (j * kWave + lane) * 16);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t ww[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          x[j * 8 + 2 * k] = __uint_as_float(ww[k] << 16);
-          x[j * 8 + 2 * k + 1] = __uint_as_float(ww[k] & 0xffff0000u);
-        }
-      }
+      for (int j = 0; j < nv; ++j) unpack16<BF16>(w[j], x + j * per);
     } else {
-      const float4 *src = reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(rowp) + e0);
-      u32x4 w[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) w[j] = load16<STREAM>(src + j * kWave + lane);
+      for (int j = 0; j < nv; ++j)
+        w[j] = load16<STREAM>(src + (int64_t) min(e0 + (j * kWave + lane) * per, V - per) * esz);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        x[j * 4] = __uint_as_float(w[j].x); x[j * 4 + 1] = __uint_as_float(w[j].y);
-        x[j * 4 + 2] = __uint_as_float(w[j].z); x[j * 4 + 3] = __uint_as_float(w[j].w);
+      for (int j = 0; j < nv; ++j) {
+        unpack16<BF16>(w[j], x + j * per);
+        const int32_t over = e0 + (j * kWave + lane) * per - (V - per);   // elements to mask, if any
+#pragma unroll
+        for (int k = 0; k < per; ++k)
+          if (k < over) x[j * per + k] = -INFINITY;
       }
     }
   } else {
-    // the ragged last part of a row, or rows that are not 16-byte aligned: element loads
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
       const int32_t e = e0 + j * kWave + lane;
@@ -234,23 +257,21 @@ __device__ __forceinline__ RowStat merge_row(const StatPart *parts, int64_t row,
 
 constexpr int kTokensPerThread = 8;    // consecutive tokens a thread of the table kernels handles
 
-// Eight consecutive logits of a row as floats; VEC: one (bf16) or two (fp32) 16-byte loads.
-template <bool BF16, bool VEC>
+// The table kernels work on eight consecutive tokens per thread, at any alignment.  A thread whose
+// eight would cross the end of the row takes the row's last eight instead (slice_start): it repeats
+// what its neighbour does for some of them and stores the same values.  WIDE: V >= 8.
+template <bool WIDE>
+__device__ __forceinline__ int32_t slice_start(int32_t t, int32_t V) {
+  return WIDE ? min(t, V - 8) : t;
+}
+
+// Eight consecutive logits of a row as floats: one (bf16) or two (fp32) 16-byte loads.
+template <bool BF16, bool WIDE>
 __device__ __forceinline__ void load8(const void *row, int32_t t, int32_t V, float *x) {
-  if (VEC && t + 8 <= V) {
-    if constexpr (BF16) {
-      const uint4 w = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(row) + t);
-      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        x[2 * k] = __uint_as_float(ww[k] << 16);
-        x[2 * k + 1] = __uint_as_float(ww[k] & 0xffff0000u);
-      }
-    } else {
-      const float4 a = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(row) + t);
-      const float4 b = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(row) + t + 4);
-      x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-    }
+  if constexpr (WIDE) {
+    const char *src = reinterpret_cast<const char *>(row) + (int64_t) t * (BF16 ? 2 : 4);
+    unpack16<BF16>(load16<false>(src), x);
+    if constexpr (!BF16) unpack16<BF16>(load16<false>(src + 16), x + 4);
   } else {
 #pragma unroll
     for (int k = 0; k < 8; ++k) x[k] = (t + k < V) ? logit_at<BF16>(row, t + k) : -INFINITY;
@@ -259,27 +280,32 @@ __device__ __forceinline__ void load8(const void *row, int32_t t, int32_t V, flo
 
 // Divisors of eight consecutive tokens: their multiplicities, or 1 with mult == NULL (general
 // weights: the per-entry weight is applied by the gather instead).
-template <bool VEC>
+template <bool WIDE>
 __device__ __forceinline__ void load8_mult(const int32_t *mult, int32_t t, int32_t V, float *m) {
   if (!mult) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) m[k] = 1.f;
-  } else if (VEC && t + 8 <= V) {
-    const int4 a = *reinterpret_cast<const int4 *>(mult + t);
-    const int4 b = *reinterpret_cast<const int4 *>(mult + t + 4);
-    m[0] = (float) a.x; m[1] = (float) a.y; m[2] = (float) a.z; m[3] = (float) a.w;
-    m[4] = (float) b.x; m[5] = (float) b.y; m[6] = (float) b.z; m[7] = (float) b.w;
+  } else if constexpr (WIDE) {
+    const u32x4 a = load16<false>(mult + t), b = load16<false>(mult + t + 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { m[k] = (float) (int32_t) a[k]; m[4 + k] = (float) (int32_t) b[k]; }
   } else {
 #pragma unroll
     for (int k = 0; k < 8; ++k) m[k] = (t + k < V) ? (float) mult[t + k] : 1.f;
   }
 }
 
-template <bool VEC>
+// Four floats at any float address (a row of the table starts at a multiple of V).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+template <bool WIDE>
 __device__ __forceinline__ void store8(float *out, int32_t t, int32_t V, const float *v) {
-  if (VEC && t + 8 <= V) {
-    *reinterpret_cast<float4 *>(out + t) = make_float4(v[0], v[1], v[2], v[3]);
-    *reinterpret_cast<float4 *>(out + t + 4) = make_float4(v[4], v[5], v[6], v[7]);
+  if constexpr (WIDE) {
+    f32x4_any a, b;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { a[k] = v[k]; b[k] = v[4 + k]; }
+    *reinterpret_cast<f32x4_any *>(out + t) = a;
+    *reinterpret_cast<f32x4_any *>(out + t + 4) = b;
   } else {
 #pragma unroll
     for (int k = 0; k < 8; ++k)
@@ -427,8 +453,7 @@ __device__ void accept_phase(AcceptShared &sh, const AcceptArgs &a, int b, bool 
 //   rejected (i* < K):  delta[t] = (q_{i*}(t) - p_{i*}(t)) / N(t)
 //   bonus    (i* = K):  delta[t] =  q_K(t) / N(t)
 // Workgroup s = 0 also writes the sequence's outputs, row statistics and counters.
-// VEC: rows, mult and the table are 16-byte aligned and V is a multiple of 8.
-template <bool BF16, bool VEC>
+template <bool BF16, bool WIDE>
 __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs a, int32_t nsplit,
                                                                       float c_lo, float *table) {
   __shared__ AcceptShared sh;
@@ -443,8 +468,8 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs
   // the multiplicities of this thread's first two slices do not depend on the decision row:
   // they are asked for before the accept scan
   float m_a[8], m_b[8];
-  if (first < V) load8_mult<VEC>(mult, first, V, m_a);
-  if (first + stride < V) load8_mult<VEC>(mult, first + stride, V, m_b);
+  if (first < V) load8_mult<WIDE>(mult, slice_start<WIDE>(first, V), V, m_a);
+  if (first + stride < V) load8_mult<WIDE>(mult, slice_start<WIDE>(first + stride, V), V, m_b);
   accept_phase<BF16>(sh, a, b, split == 0);
 
   // 4. this workgroup's share of the table on the decision row: slices split, split + nsplit, ...
@@ -471,27 +496,28 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs
   };
   float *out = table + (int64_t) b * V;
   // two slices per turn, so that the loads of the second are in flight behind the first
-  for (int32_t t = first; t < V; t += 2 * stride) {
-    const int32_t t2 = t + stride;
+  for (int32_t at = first; at < V; at += 2 * stride) {
+    const bool two = at + stride < V;
+    const int32_t t = slice_start<WIDE>(at, V), t2 = slice_start<WIDE>(at + stride, V);
     float xt[8], xd[8], m[8], v[8], xt2[8], xd2[8], m2[8];
-    load8<BF16, VEC>(trow, t, V, xt);
-    if (rejected) load8<BF16, VEC>(drow, t, V, xd);
-    if (t2 < V) {
-      load8<BF16, VEC>(trow, t2, V, xt2);
-      if (rejected) load8<BF16, VEC>(drow, t2, V, xd2);
+    load8<BF16, WIDE>(trow, t, V, xt);
+    if (rejected) load8<BF16, WIDE>(drow, t, V, xd);
+    if (two) {
+      load8<BF16, WIDE>(trow, t2, V, xt2);
+      if (rejected) load8<BF16, WIDE>(drow, t2, V, xd2);
     }
-    if (t == first) {
+    if (at == first) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) { m[k] = m_a[k]; m2[k] = m_b[k]; }
     } else {
-      load8_mult<VEC>(mult, t, V, m);
-      if (t2 < V) load8_mult<VEC>(mult, t2, V, m2);
+      load8_mult<WIDE>(mult, t, V, m);
+      if (two) load8_mult<WIDE>(mult, t2, V, m2);
     }
     delta8(xt, xd, m, v);
-    store8<VEC>(out, t, V, v);
-    if (t2 < V) {
+    store8<WIDE>(out, t, V, v);
+    if (two) {
       delta8(xt2, xd2, m2, v);
-      store8<VEC>(out, t2, V, v);
+      store8<WIDE>(out, t2, V, v);
     }
   }
 }
@@ -621,31 +647,35 @@ struct Logits32 {
   }
 };
 
-// Tokens e0 .. e0+31 of a row; tokens at or beyond V read as -inf.
-template <bool BF16, bool VEC>
+// Tokens e0 .. e0+31 of a row; tokens at or beyond V read as -inf.  A lane wholly inside the row
+// uses 16-byte loads at any alignment; one that crosses its end reads element by element, at
+// addresses clamped into the row so that its 32 loads are in flight together.
+template <bool BF16>
 __device__ __forceinline__ void load32(const void *row, int32_t e0, int32_t V, Logits32<BF16> &r) {
   constexpr int nvec = BF16 ? 4 : 8;
-  if (VEC && e0 + 32 <= V) {
-    const uint4 *src = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(row) +
-                                                       (size_t) e0 * (BF16 ? 2 : 4));
+  if (e0 + 32 <= V) {
+    const char *src = reinterpret_cast<const char *>(row) + (size_t) e0 * (BF16 ? 2 : 4);
 #pragma unroll
     for (int i = 0; i < nvec; ++i) {
-      const uint4 q = src[i];
+      const u32x4 q = load16<false>(src + 16 * i);
       r.w[4 * i] = q.x; r.w[4 * i + 1] = q.y; r.w[4 * i + 2] = q.z; r.w[4 * i + 3] = q.w;
     }
   } else {
     const uint32_t ninf = BF16 ? 0xff80u : 0xff800000u;
+    uint32_t bits[32];
 #pragma unroll
     for (int k = 0; k < 32; ++k) {
-      uint32_t bits = ninf;
-      if (e0 + k < V) {
-        if constexpr (BF16) bits = reinterpret_cast<const uint16_t *>(row)[e0 + k];
-        else bits = reinterpret_cast<const uint32_t *>(row)[e0 + k];
-      }
+      const int32_t e = min(e0 + k, V - 1);
+      if constexpr (BF16) bits[k] = reinterpret_cast<const uint16_t *>(row)[e];
+      else bits[k] = reinterpret_cast<const uint32_t *>(row)[e];
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+      const uint32_t b = e0 + k < V ? bits[k] : ninf;
       if constexpr (BF16) {
-        if (k & 1) r.w[k >> 1] |= bits << 16; else r.w[k >> 1] = bits;
+        if (k & 1) r.w[k >> 1] |= b << 16; else r.w[k >> 1] = b;
       } else {
-        r.w[k] = bits;
+        r.w[k] = b;
       }
     }
   }
@@ -655,7 +685,7 @@ __device__ __forceinline__ void load32(const void *row, int32_t e0, int32_t V, L
 // part (each lane sums 32 consecutive tokens), then the token among that lane's 32, which are
 // handed to 32 lanes through `redo` (32 words of LDS private to the calling wave).
 // *near: the draw is within 1e-6 of an inner edge of the token's bin.
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ int32_t draw_token(const PartMasses &pm, uint32_t *redo, const void *trow, int32_t V,
                               int32_t nparts, float c, double u, int lane, bool *near) {
   const WavePick pp = wave_inverse_cdf(nparts, [&](int32_t p) { return pm.Zp[p]; }, u, lane);
@@ -664,7 +694,7 @@ __device__ int32_t draw_token(const PartMasses &pm, uint32_t *redo, const void *
   const float t = pm.tp[p];
   const int32_t e0 = p * kPartElems + lane * 32;
   Logits32<BF16> raw;
-  load32<BF16, VEC>(trow, e0, V, raw);
+  load32<BF16>(trow, e0, V, raw);
   // the same expression row_stats summed
   auto mass = [&](float x) -> float {
     return x > -INFINITY ? __builtin_amdgcn_exp2f(fmaf(x, c, -t)) : 0.f;
@@ -709,7 +739,7 @@ __device__ int32_t draw_token(const PartMasses &pm, uint32_t *redo, const void *
   return y;
 }
 
-template <bool BF16, bool VEC>
+template <bool BF16>
 __global__ __launch_bounds__(kAcceptThreads) void accept_thin_kernel(
     AcceptArgs a, const int32_t *tok_ptr, const int32_t *tok_groups, const float *tok_weights,
     int32_t *trials, int32_t max_trials) {
@@ -752,7 +782,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_thin_kernel(
       const TrialDraws d = philox_trial(a.seed, a.offset, (uint32_t) b, (uint32_t) istar,
                                         (uint32_t) trial);
       bool near_y = false;
-      const int32_t y = draw_token<BF16, VEC>(th.pm, th.redo[wave], trow, V, a.nparts, a.c,
+      const int32_t y = draw_token<BF16>(th.pm, th.redo[wave], trow, V, a.nparts, a.c,
                                               (double) d.u_y, lane, &near_y);
       const int32_t e0 = tok_ptr[y], n = tok_ptr[y + 1] - e0;
       bool near_e = false;
@@ -822,7 +852,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_thin_kernel(
 // of the membership entries of x.
 // =============================================================================================
 
-template <bool BF16, bool VEC>
+template <bool BF16>
 __global__ __launch_bounds__(kWave) void propose_kernel(
     RowSet rs, int32_t V, int32_t K, int32_t pos0, int32_t nparts, float c, const StatPart *parts,
     const int32_t *tok_ptr, const int32_t *tok_groups, const float *tok_weights, uint64_t seed,
@@ -842,7 +872,7 @@ __global__ __launch_bounds__(kWave) void propose_kernel(
   split_row(row, K, rs.inv_npos0, b, i);
   const ProposalDraws d = philox_proposal(seed, offset, (uint32_t) b, (uint32_t) (pos0 + i));
   bool near = false;
-  const int32_t x = draw_token<BF16, VEC>(pm, redo, row_base(rs, row, BF16), V, nparts, c,
+  const int32_t x = draw_token<BF16>(pm, redo, row_base(rs, row, BF16), V, nparts, c,
                                           (double) d.u_x, lane, &near);
   const int32_t e0 = tok_ptr[x], n = tok_ptr[x + 1] - e0;
   bool near_e = false;
@@ -865,7 +895,7 @@ constexpr int kTableThreads = 256;
 constexpr int kTableTokens = kTableThreads * kTokensPerThread;    // tokens per workgroup
 
 // group_probs: w[r][t] = softmax(row r)[t] / N(t) for a batch of rows starting at row0.
-template <bool BF16, bool VEC>
+template <bool BF16, bool WIDE>
 __global__ __launch_bounds__(kTableThreads) void weights_kernel(
     RowSet rs, int32_t V, int32_t nparts, int32_t nct, int64_t row0, float c, float c_hi,
     float c_lo, const StatPart *parts, const int32_t *mult, float *table) {
@@ -877,18 +907,19 @@ __global__ __launch_bounds__(kTableThreads) void weights_kernel(
     if (threadIdx.x == 0) sh = s;
   }
   __syncthreads();
-  const int32_t t = (blockIdx.x % nct) * kTableTokens + threadIdx.x * kTokensPerThread;
-  if (t >= V) return;
+  const int32_t at = (blockIdx.x % nct) * kTableTokens + threadIdx.x * kTokensPerThread;
+  if (at >= V) return;
+  const int32_t t = slice_start<WIDE>(at, V);
   const RowStat s = sh;
   const double iz = 1.0 / s.Z;
   const void *rowp = row_base(rs, row, BF16);
   float x[8], m[8], v[8];
-  load8<BF16, VEC>(rowp, t, V, x);
-  load8_mult<VEC>(mult, t, V, m);
+  load8<BF16, WIDE>(rowp, t, V, x);
+  load8_mult<WIDE>(mult, t, V, m);
 #pragma unroll
   for (int k = 0; k < 8; ++k)
     v[k] = (float) ((double) exp_rel(x[k], s.M, c_hi, c_lo) * iz) * __builtin_amdgcn_rcpf(m[k]);
-  store8<VEC>(table + (int64_t) local * V, t, V, v);
+  store8<WIDE>(table + (int64_t) local * V, t, V, v);
 }
 
 // =============================================================================================
@@ -1478,7 +1509,12 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
               (const __attribute__((address_space(1))) void *) (s4 + k0 + lane),
               (__attribute__((address_space(3))) void *) (tab + 4 * k0), 16, 0, 0);
     } else {
-      for (int32_t k = threadIdx.x; k < tl; k += kGatherThreads) tab[k] = src[t0 + k];
+      // rows that do not start on 16 bytes: the same with 4 bytes per lane
+      for (int32_t k0 = wave * kWave; k0 < tl; k0 += kGatherThreads)
+        if (k0 + lane < tl)
+          __builtin_amdgcn_global_load_lds(
+              (const __attribute__((address_space(1))) void *) (src + t0 + k0 + lane),
+              (__attribute__((address_space(3))) void *) (tab + k0), 4, 0, 0);
     }
     if (threadIdx.x < kBanks) tab[tile_len + threadIdx.x] = 0.f;   // the padding slots
     // The wave's blocks of this tile are walked side by side: turn s takes step s of every block
@@ -1504,7 +1540,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     fetch(bufX, 0, 0);
     uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];
     load_desc(h + 1, nsteps, noffs);
-    if (direct) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's part of the tile has landed
+    __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
 #pragma unroll
     for (int q0 = 0; q0 < kMaxBlocksPerWave; q0 += kSide) {
@@ -1582,14 +1618,6 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
 // Launchers.
 // =============================================================================================
 
-static inline bool rows_vector_aligned(const RowSet &rs, bool bf16) {
-  const int64_t per16 = bf16 ? 8 : 4;   // elements in 16 bytes
-  auto ok = [&](const void *p, int64_t bs, int64_t ps) {
-    return p == nullptr || (((uintptr_t) p & 15) == 0 && bs % per16 == 0 && ps % per16 == 0);
-  };
-  return ok(rs.base0, rs.bs0, rs.ps0) && ok(rs.base1, rs.bs1, rs.ps1);
-}
-
 int32_t stats_nparts(int32_t V) { return (V + kPartElems - 1) / kPartElems; }
 
 hipError_t launch_row_stats(const RowSet &rs, bool bf16, int32_t V, int64_t nrows, float c,
@@ -1607,26 +1635,20 @@ hipError_t launch_row_stats(const RowSet &rs, bool bf16, int32_t V, int64_t nrow
   const int64_t slots = nrows + probe_y;                    // values of (z, y) the grid must hold
   const unsigned gz = (unsigned) ((slots + kRowsPerGridY - 1) / kRowsPerGridY);
   const dim3 grid(gx, (unsigned) std::min<int64_t>(slots, kRowsPerGridY), gz), block(kStatsWaves * kWave);
-  const bool vec = rows_vector_aligned(rs, bf16);
+  const bool wide = V >= (bf16 ? kPer16<true> : kPer16<false>);
   auto launch = [&](auto kernel) {
     kernel<<<grid, block, 0, stream>>>(rs, V, nparts, nrows, c, parts, pa, probe_y);
   };
   if (bf16) {
-    if (!vec) launch(row_stats_kernel<true, false, false>);
+    if (!wide) launch(row_stats_kernel<true, false, false>);
     else if (streaming) launch(row_stats_kernel<true, true, true>);
     else launch(row_stats_kernel<true, true, false>);
   } else {
-    if (!vec) launch(row_stats_kernel<false, false, false>);
+    if (!wide) launch(row_stats_kernel<false, false, false>);
     else if (streaming) launch(row_stats_kernel<false, true, true>);
     else launch(row_stats_kernel<false, true, false>);
   }
   return hipGetLastError();
-}
-
-static inline bool table_vector_ok(const RowSet &rs, bool bf16, int32_t V, const int32_t *mult,
-                                   const float *table) {
-  return rows_vector_aligned(rs, bf16) && V % 8 == 0 && ((uintptr_t) mult & 15) == 0 &&
-         ((uintptr_t) table & 15) == 0;
 }
 
 // Workgroups per sequence in the accept + delta kernel: enough to give every compute unit one,
@@ -1640,7 +1662,7 @@ hipError_t launch_accept_delta(const AcceptArgs &a, bool bf16, int32_t B, float 
                                hipStream_t stream) {
   const int32_t nsplit = accept_nsplit(a.V, B);
   const dim3 grid((unsigned) ((int64_t) B * nsplit));
-  const bool vec = table_vector_ok(a.rs, bf16, a.V, a.mult, table);
+  const bool vec = a.V >= 8;
 #define PCG_LAUNCH_AD(BF, VE) \
   accept_delta_kernel<BF, VE><<<grid, kAcceptThreads, 0, stream>>>(a, nsplit, c_lo, table)
   if (bf16) { if (vec) PCG_LAUNCH_AD(true, true); else PCG_LAUNCH_AD(true, false); }
@@ -1652,13 +1674,10 @@ hipError_t launch_accept_delta(const AcceptArgs &a, bool bf16, int32_t B, float 
 hipError_t launch_accept_thin(const AcceptArgs &a, bool bf16, int32_t B, const int32_t *tok_ptr,
                               const int32_t *tok_groups, const float *tok_weights, int32_t *trials,
                               int32_t max_trials, hipStream_t stream) {
-  const bool vec = rows_vector_aligned(a.rs, bf16) && a.V % 8 == 0;
-#define PCG_LAUNCH_AT(BF, VE)                                                                \
-  accept_thin_kernel<BF, VE><<<B, kAcceptThreads, 0, stream>>>(a, tok_ptr, tok_groups,        \
-                                                               tok_weights, trials, max_trials)
-  if (bf16) { if (vec) PCG_LAUNCH_AT(true, true); else PCG_LAUNCH_AT(true, false); }
-  else { if (vec) PCG_LAUNCH_AT(false, true); else PCG_LAUNCH_AT(false, false); }
-#undef PCG_LAUNCH_AT
+  auto launch = [&](auto kernel) {
+    kernel<<<B, kAcceptThreads, 0, stream>>>(a, tok_ptr, tok_groups, tok_weights, trials, max_trials);
+  };
+  if (bf16) launch(accept_thin_kernel<true>); else launch(accept_thin_kernel<false>);
   return hipGetLastError();
 }
 
@@ -1669,16 +1688,13 @@ hipError_t launch_propose(const RowSet &rs, bool bf16, int32_t V, int32_t K, int
                           const float *tok_weights, uint64_t seed, uint64_t offset,
                           int32_t *prop_tokens, int32_t *prop_groups, pcg_diag *diag,
                           hipStream_t stream) {
-  const bool vec = rows_vector_aligned(rs, bf16) && V % 8 == 0;
   const int32_t nparts = stats_nparts(V);
   const unsigned grid = (unsigned) rs.nrows0;
-#define PCG_LAUNCH_PR(BF, VE)                                                                     \
-  propose_kernel<BF, VE><<<grid, kWave, 0, stream>>>(rs, V, K, pos0, nparts, c, parts, tok_ptr,   \
-                                                     tok_groups, tok_weights, seed, offset,       \
-                                                     prop_tokens, prop_groups, diag)
-  if (bf16) { if (vec) PCG_LAUNCH_PR(true, true); else PCG_LAUNCH_PR(true, false); }
-  else { if (vec) PCG_LAUNCH_PR(false, true); else PCG_LAUNCH_PR(false, false); }
-#undef PCG_LAUNCH_PR
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, kWave, 0, stream>>>(rs, V, K, pos0, nparts, c, parts, tok_ptr, tok_groups, tok_weights,
+                                       seed, offset, prop_tokens, prop_groups, diag);
+  };
+  if (bf16) launch(propose_kernel<true>); else launch(propose_kernel<false>);
   return hipGetLastError();
 }
 
@@ -1688,7 +1704,7 @@ hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int6
   const int32_t nct = (g.V + kTableTokens - 1) / kTableTokens;
   const dim3 grid((unsigned) ((int64_t) nct * nrows));
   const int32_t nparts = stats_nparts(g.V);
-  const bool vec = table_vector_ok(rs, bf16, g.V, g.mult, table);
+  const bool vec = g.V >= 8;
   // with general weights the table is the plain probability: the gather applies the weights
   const int32_t *mult = g.weights ? nullptr : g.mult;
 #define PCG_LAUNCH_WEIGHTS(BF, VE)                                                             \

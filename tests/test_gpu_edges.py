@@ -1,0 +1,67 @@
+"""Sizes at the edges of what the kernels' tiles, parts and dispatch rules cover, each against the
+oracle (whole outputs exact except on draws it flags; group probabilities within 1e-5).  Run with
+``-m gpu`` on an MI355X."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2511_13732_amd as pcg
+import workloads as W
+from parity import (as_oracle_logits, compare_thinning, compare_verify, group_probs_error, oracle_groups,
+                    run_both, run_both_thinning)
+from test_gpu_propose import compare_proposals
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_at(x: torch.Tensor, off: int) -> torch.Tensor:
+    """The same rows as a view that starts `off` elements into a larger buffer, rows `off` apart."""
+    B, n, V = x.shape
+    big = torch.full((B, n, V + off), 9.0, dtype=x.dtype, device="cuda")
+    big[:, :, off:] = x.cuda()
+    return big[:, :, off:]
+
+
+def check_step(V, G, size, B, K, dtype, off=0, layout="prepared", chunk_groups=0, weighted=False, seed=0,
+               thinning=True, sigma=4.0):
+    print(f"V={V} G={G} size={size} B={B} K={K} {dtype} off={off} {layout} {chunk_groups} w={weighted}", flush=True)
+    rp, mem = W.random_groups(V, G, 1, size, seed=seed + V)
+    og = oracle_groups(V, rp, mem)
+    w = W.random_weights(og.V, og.members, seed) if weighted else None
+    if weighted:
+        og = oracle.with_weights(og, w)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=layout == "prepared", chunk_groups=chunk_groups,
+                             reverse=True, weights=w)
+    rev = oracle.reverse_index(og)
+    rng = np.random.default_rng([V, G, B, K, seed])
+    tgt = (sigma * rng.standard_normal((B, K + 1, V))).astype(np.float32)
+    dft = (tgt[:, :K] + rng.standard_normal((B, K, V))).astype(np.float32)
+    tgt, dft = torch.from_numpy(tgt), torch.from_numpy(dft)
+    if dtype == "bf16":
+        tgt, dft = tgt.to(torch.bfloat16), dft.to(torch.bfloat16)
+    tgt, dft = rows_at(tgt, off), rows_at(dft, off)
+    pref = oracle.propose(og, rev, as_oracle_logits(dft), temperature=0.9, seed=3, offset=1, nthreads=8)
+    if thinning:
+        tok, grp = pcg.propose(dg, dft, temperature=0.9, seed=3, offset=1)
+        assert compare_proposals(tok, grp, pref, og).tolerated <= 1
+    for step in range(2):
+        gpu, ref, _, diag = run_both(V, rp, mem, tgt, dft, pref.tokens, pref.groups, temperature=0.9, seed=3,
+                                     offset=step, dg=dg, og=og, nthreads=8)
+        assert compare_verify(gpu, ref, og, pref.tokens, pref.groups).tolerated <= 1
+        assert diag["sequences"] == B and diag["accepted_total"] == int(gpu.accept_len.sum())
+        if thinning:
+            g2, trials, r2, _ = run_both_thinning(V, tgt, dft, pref.tokens, pref.groups, dg=dg, og=og, rev=rev,
+                                                  temperature=0.9, seed=3, offset=step, nthreads=8)
+            assert compare_thinning(g2, trials, r2, og, pref.tokens, pref.groups).tolerated <= 1
+    out = pcg.group_probs(dg, tgt[:, 0], 0.9)
+    assert group_probs_error(out, oracle.group_probs(og, as_oracle_logits(tgt[:, 0]), 0.9)) <= 1e-5
+
+
+# rows of less than one 16-byte piece, of one, around a part of 2048, and around several; every
+# start inside 16 bytes
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V,off", [(3, 0), (4, 1), (7, 0), (8, 3), (9, 5), (33, 7), (2040, 1), (2047, 0),
+                                   (2049, 2), (2055, 3), (6143, 6), (8193, 1), (20011, 7)])
+def test_ragged_rows(V, off, dtype):
+    check_step(V, max(1, V // 3), min(V, 9), 3, 2, dtype, off=off)
