@@ -1388,30 +1388,37 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(FinalizeArgs fa
 // ---------------------------------------------------------------------------------------------
 // The same sum read from the prepared layout (pcg_prepared): no cross-lane reduction and no
 // address arithmetic beyond a shift.  A workgroup owns one chunk of consecutive groups of one
-// table row.  Wave w owns the blocks block_of(q, w), q = 0..3, of the chunk and walks them side
-// by side; lane l handles each block's 4 groups r*64 + l -- the same 16 groups in every tile
-// pass, so their running sums stay in registers.  One 16-byte load per lane brings 2 slots for
+// table row.  Wave w owns the blocks block_of(q, w), q = 0..3, of the chunk and walks them one
+// after the other; lane l handles each block's 4 groups r*64 + l -- the same 16 groups in every
+// tile pass, so their running sums stay in registers.  One 16-byte load per lane brings 2 slots for
 // each of a block's 4 groups.  Results are put back into group order through LDS.  Without CSUM
 // they leave with coalesced stores; with CSUM (the residual of pcg_verify, Eq. 8) only totals of
 // max(0, .) leave, in double and summed in a fixed order: one per run of kRunGroups consecutive
 // groups and one for the chunk.
 // ---------------------------------------------------------------------------------------------
 
+// One step of a block: 8 slots per lane, two for each of its 4 groups.  All eight reads are issued
+// before the first sum waits for one (left to itself the compiler, short of registers, lets each
+// addition wait for its own read).
 __device__ __forceinline__ void gather_step(const float *tab, const uint4 w, float *acc) {
-  acc[0] += tab[w.x & 0xffffu]; acc[1] += tab[w.y & 0xffffu];
-  acc[2] += tab[w.z & 0xffffu]; acc[3] += tab[w.w & 0xffffu];
-  acc[0] += tab[w.x >> 16]; acc[1] += tab[w.y >> 16];
-  acc[2] += tab[w.z >> 16]; acc[3] += tab[w.w >> 16];
+  const float a0 = tab[w.x & 0xffffu], a1 = tab[w.y & 0xffffu], a2 = tab[w.z & 0xffffu], a3 = tab[w.w & 0xffffu];
+  const float b0 = tab[w.x >> 16], b1 = tab[w.y >> 16], b2 = tab[w.z >> 16], b3 = tab[w.w >> 16];
+  __builtin_amdgcn_sched_barrier(0);
+  acc[0] += a0; acc[1] += a1; acc[2] += a2; acc[3] += a3;
+  acc[0] += b0; acc[1] += b1; acc[2] += b2; acc[3] += b3;
 }
 
 // The same with general weights (Eq. 4): every slot comes with its w_{k,t}, 8 floats per lane
 // and step next to the 8 slots.
-__device__ __forceinline__ void gather_step_w(const float *tab, const uint4 s, const float4 a,
-                                              const float4 b, float *acc) {
-  acc[0] = fmaf(tab[s.x & 0xffffu], a.x, acc[0]); acc[1] = fmaf(tab[s.y & 0xffffu], a.z, acc[1]);
-  acc[2] = fmaf(tab[s.z & 0xffffu], b.x, acc[2]); acc[3] = fmaf(tab[s.w & 0xffffu], b.z, acc[3]);
-  acc[0] = fmaf(tab[s.x >> 16], a.y, acc[0]); acc[1] = fmaf(tab[s.y >> 16], a.w, acc[1]);
-  acc[2] = fmaf(tab[s.z >> 16], b.y, acc[2]); acc[3] = fmaf(tab[s.w >> 16], b.w, acc[3]);
+__device__ __forceinline__ void gather_step_w(const float *tab, const uint4 s, const float4 wa,
+                                              const float4 wb, float *acc) {
+  const float a0 = tab[s.x & 0xffffu], a1 = tab[s.y & 0xffffu], a2 = tab[s.z & 0xffffu], a3 = tab[s.w & 0xffffu];
+  const float b0 = tab[s.x >> 16], b1 = tab[s.y >> 16], b2 = tab[s.z >> 16], b3 = tab[s.w >> 16];
+  __builtin_amdgcn_sched_barrier(0);
+  acc[0] = fmaf(a0, wa.x, acc[0]); acc[1] = fmaf(a1, wa.z, acc[1]);
+  acc[2] = fmaf(a2, wb.x, acc[2]); acc[3] = fmaf(a3, wb.z, acc[3]);
+  acc[0] = fmaf(b0, wa.y, acc[0]); acc[1] = fmaf(b1, wa.w, acc[1]);
+  acc[2] = fmaf(b2, wb.y, acc[2]); acc[3] = fmaf(b3, wb.w, acc[3]);
 }
 
 // One step of one block as it comes from memory: 8 slots and, with weights, their 8 weights.
@@ -1490,7 +1497,16 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     }
   };
   uint32_t steps[kMaxBlocksPerWave], offs[kMaxBlocksPerWave];
+  uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];
   load_desc(0, steps, offs);
+  // Steps in flight per wave.  A wave used to keep one step of each of its blocks in flight, so
+  // one left with a single long block (or none beside it) waited for the L2 on every step: 17.0 us
+  // at B = 1, V = 65 536 against 13.4 with this ring, 57.5 against 46.3 at B = 128, V = 32 768 with
+  // groups of 1 to 128, 27.4 against 25.2 at B = 64, V = 65 536.  Six steps spill with weights and
+  // change nothing without; eight spill (27.8 us).
+  constexpr int kRing = WEIGHTED ? 2 : 4;
+  GatherStep<WEIGHTED> ring[kRing];
+  bool filled = false, follows = false;               // ring holds the first steps of this / the next tile
 
   for (int h = 0; h < ntiles; ++h) {
     const int32_t t0 = h * tile_len;
@@ -1517,47 +1533,75 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
               (__attribute__((address_space(3))) void *) (tab + k0), 4, 0, 0);
     }
     if (threadIdx.x < kBanks) tab[tile_len + threadIdx.x] = 0.f;   // the padding slots
-    // The wave's blocks of this tile are walked side by side: turn s takes step s of every block
-    // that has one (kSide blocks at a time: all four, or two when weights travel along), so one
-    // loop with fixed registers serves them all; while a turn is gathered the next one is on its
-    // way (a block that has run out re-reads its last step, which keeps every load in bounds and
-    // the number of loads in flight the same on every turn).  The first turn and the next tile's
-    // descriptors are asked for while the tile is still on its way into LDS.
-    constexpr int kSide = WEIGHTED ? 2 : kMaxBlocksPerWave;
-    GatherStep<WEIGHTED> bufX[kSide], bufY[kSide];
-    uint32_t last[kMaxBlocksPerWave];                 // a block's last step (0 for a block without any)
-#pragma unroll
-    for (int q = 0; q < kMaxBlocksPerWave; ++q)
-      last[q] = __builtin_amdgcn_readfirstlane(steps[q] > 0 ? steps[q] - 1 : 0u);
-    auto fetch = [&](GatherStep<WEIGHTED> (&dst)[kSide], int q0, uint32_t turn) {
-#pragma unroll
-      for (int j = 0; j < kSide; ++j) {
-        const uint32_t k = min(turn, last[q0 + j]);                         // scalar
-        // a scalar base and the lane as the only vector part: no address arithmetic per load
-        dst[j].load(data + ((size_t) offs[q0 + j] + (size_t) k * kWave), wdata + 2 * ((size_t) offs[q0 + j] + (size_t) k * kWave), lane);
-      }
-    };
-    fetch(bufX, 0, 0);
-    uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];
+    // The wave walks its blocks one after the other, reading their steps through a ring of kRing
+    // registers sets that is always kRing steps ahead: slot i takes the steps i, i + kRing, ... of
+    // a block, and once the block has none left, step i of the wave's next block (in the last
+    // block of a tile: of the next tile's first), so the stream of slots never waits at a block's
+    // or a tile's end.  The next tile's descriptors and, in the first tile, the first steps are asked
+    // for while the tile is still on its way into LDS.
     load_desc(h + 1, nsteps, noffs);
+    uint32_t succ_off[kMaxBlocksPerWave], succ_last[kMaxBlocksPerWave];   // what follows each block
+    uint32_t first_off = 0, first_steps = 0;          // the first block of this tile that has steps
+    {
+      uint32_t so = 0, sn = 0;
+#pragma unroll
+      for (int q = kMaxBlocksPerWave - 1; q >= 0; --q)
+        if (nsteps[q] > 0) { so = noffs[q]; sn = nsteps[q]; }
+      follows = sn > 0;
+#pragma unroll
+      for (int q = kMaxBlocksPerWave - 1; q >= 0; --q) {
+        // nothing follows: the block's own first steps are read again, and not used
+        succ_off[q] = sn > 0 ? so : offs[q];
+        succ_last[q] = (sn > 0 ? sn : max(steps[q], 1u)) - 1;
+        if (steps[q] > 0) { so = first_off = offs[q]; sn = first_steps = steps[q]; }
+      }
+    }
+    // a scalar base and the lane as the only vector part: no address arithmetic per load
+    auto load = [&](GatherStep<WEIGHTED> &slot, uint32_t unit) {
+      const uint32_t u = __builtin_amdgcn_readfirstlane(unit);
+      slot.load(data + u, wdata + 2 * (size_t) u, lane);
+    };
+    if (!filled && first_steps > 0) {
+#pragma unroll
+      for (int i = 0; i < kRing; ++i) load(ring[i], first_off + min((uint32_t) i, first_steps - 1) * kWave);
+    }
+    if (first_steps > 0) filled = follows;
     __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
 #pragma unroll
-    for (int q0 = 0; q0 < kMaxBlocksPerWave; q0 += kSide) {
-      uint32_t turns = 0;
+    for (int q = 0; q < kMaxBlocksPerWave; ++q) {
+      const uint32_t n = steps[q];                    // uniform over the wave, as everything below
+      float *a = acc + q * kLaneGroups;
+      auto next = [&](int i) { return succ_off[q] + min((uint32_t) i, succ_last[q]) * kWave; };
+      if (n >= (uint32_t) kRing) {
+        uint32_t t = 0;
+        for (; t + kRing <= n; t += kRing) {
 #pragma unroll
-      for (int j = 0; j < kSide; ++j) turns = max(turns, steps[q0 + j]);
-      if (q0 > 0) fetch(bufX, q0, 0);
-      for (uint32_t t = 0; t < turns; t += 2) {
-        fetch(bufY, q0, t + 1);
+          for (int i = 0; i < kRing; ++i) {
+            ring[i].apply(tab, a);
+            const uint32_t k = t + i + kRing;
+            load(ring[i], k < n ? offs[q] + k * kWave : next(i));
+          }
+        }
 #pragma unroll
-        for (int j = 0; j < kSide; ++j)
-          if (t < steps[q0 + j]) bufX[j].apply(tab, acc + (q0 + j) * kLaneGroups);      // uniform
-        if (t + 1 >= turns) break;
-        fetch(bufX, q0, t + 2);
+        for (int i = 0; i < kRing - 1; ++i) {
+          if (t + i < n) {
+            ring[i].apply(tab, a);
+            load(ring[i], next(i));
+          }
+        }
+      } else if (n > 0) {
+        // a short block: the slots it has no step for pass to its successor first
 #pragma unroll
-        for (int j = 0; j < kSide; ++j)
-          if (t + 1 < steps[q0 + j]) bufY[j].apply(tab, acc + (q0 + j) * kLaneGroups);  // uniform
+        for (int i = 1; i < kRing; ++i)
+          if ((uint32_t) i >= n) load(ring[i], next(i));
+#pragma unroll
+        for (int i = 0; i < kRing - 1; ++i) {
+          if ((uint32_t) i < n) {
+            ring[i].apply(tab, a);
+            load(ring[i], next(i));
+          }
+        }
       }
     }
 #pragma unroll

@@ -65,3 +65,13 @@ def check_step(V, G, size, B, K, dtype, off=0, layout="prepared", chunk_groups=0
                                    (2049, 2), (2055, 3), (6143, 6), (8193, 1), (20011, 7)])
 def test_ragged_rows(V, off, dtype):
     check_step(V, max(1, V // 3), min(V, 9), 3, 2, dtype, off=off)
+
+
+# the prepared gather: blocks with fewer steps than it keeps in flight, blocks without any in some
+# tile (or in all), one to three tiles, one to four blocks per wave, with and without weights
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("V,G,size,chunk", [(900, 4096, 1, 4096), (5000, 700, 40, 4096), (45000, 5000, 3, 4096),
+                                            (45001, 300, 400, 8192), (45000, 17000, 9, 16384),
+                                            (90002, 9000, 2, 12288), (81400, 40000, 5, 16384)])
+def test_prepared_gather_blocks(V, G, size, chunk, weighted):
+    check_step(V, G, size, 2, 2, "bf16", chunk_groups=chunk, weighted=weighted, thinning=False)
