@@ -206,7 +206,8 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
     if (r0 == 0) { tm.end(kStageTable); tm.begin(kStageGather); }
     e = groups->prepared
             ? launch_gather_prepared(*groups, n, table, out + r0 * groups->G, nullptr, nullptr, stream)
-            : launch_gather(*groups, n, false, table, out + r0 * groups->G, stream);
+            : launch_gather(*groups, csr_shape(groups->V, groups->G, groups->nnz, n, 256), n, table,
+                            out + r0 * groups->G, nullptr, 0, nullptr, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (r0 == 0) tm.end(kStageGather);
   }
@@ -377,16 +378,28 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
     return hip_fail(e);
   tm.end(kStageAccept);
   tm.begin(kStageGather);
-  const bool prepared = groups->prepared != nullptr;
-  e = prepared ? launch_gather_prepared(*groups, B, table, R, csum, runs, stream)
-               : launch_gather(*groups, B, true, table, R, stream);
+  int32_t nchunks, chunk_groups;
+  int64_t csum_stride;
+  if (groups->prepared) {
+    csum_stride = nchunks = groups->prepared_info->nchunks;
+    chunk_groups = groups->prepared_info->chunk_groups;
+    e = launch_gather_prepared(*groups, B, table, R, csum, runs, stream);
+  } else {
+    // The CSR gather may cut a row finer than csum has room for; its chunk totals then go where the
+    // sequence's row parts were, which nothing reads after the accept scan.
+    const int64_t room = (groups->G + kChunkStep - 1) / kChunkStep;
+    const int64_t parts_room = (2 * K + 1) * (int64_t) nparts * (sizeof(StatPart) / sizeof(double));
+    const CsrShape shape = csr_shape(V, groups->G, groups->nnz, B, std::max(room, parts_room));
+    nchunks = shape.nchunks;
+    chunk_groups = shape.chunk_groups;
+    csum_stride = nchunks <= room ? room : parts_room;
+    if (nchunks > room) csum = (double *) parts;
+    e = launch_gather(*groups, shape, B, table, nullptr, csum, csum_stride, runs, stream);
+  }
   if (e != hipSuccess) return hip_fail(e);
   tm.end(kStageGather);
   tm.begin(kStageFinalize);
-  if ((e = launch_finalize(fa, bf16, *groups, B, prepared ? csum : nullptr,
-                           prepared ? runs : nullptr,
-                           prepared ? groups->prepared_info->nchunks : 1,
-                           prepared ? groups->prepared_info->chunk_groups : groups->G, stream)) !=
+  if ((e = launch_finalize(fa, bf16, *groups, B, csum, csum_stride, runs, nchunks, chunk_groups, stream)) !=
       hipSuccess)
     return hip_fail(e);
   tm.end(kStageFinalize);

@@ -38,14 +38,23 @@ hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int6
                           int32_t nrows, float c, float c_hi, float c_lo, const StatPart *parts,
                           float *table, hipStream_t stream);
 
-hipError_t launch_gather(const pcg_groups &g, int32_t nrows, bool clamp, const float *table,
-                         float *out, hipStream_t stream);
+// How the CSR gather cuts `nrows` rows: lanes per group, chunks of consecutive groups (a multiple of
+// kRunGroups; no more of them than max_chunks or ceil(G / kMaxChunkGroups)), tiles of the vocabulary.
+struct CsrShape {
+  int32_t width, nchunks, chunk_groups, ntiles, tile_len;
+};
+CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max_chunks);
+
+// With csum (and runs): no sums, only the clamped totals per chunk (row r's at csum + r * csum_stride)
+// and per run of kRunGroups groups; otherwise every sum to out.
+hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, const float *table, float *out,
+                         double *csum, int64_t csum_stride, double *runs, hipStream_t stream);
 
 hipError_t launch_gather_prepared(const pcg_groups &g, int32_t nrows, const float *table, float *out,
                                   double *csum, double *runs, hipStream_t stream);
 
 hipError_t launch_finalize(const FinalizeArgs &fa, bool bf16, const pcg_groups &g, int32_t B,
-                           const double *csum, const double *runs, int32_t nchunks,
+                           const double *csum, int64_t csum_stride, const double *runs, int32_t nchunks,
                            int32_t chunk_groups, hipStream_t stream);
 
 // Remembers a HIP error for pcg_last_hip_error and returns PCG_ERR_HIP.

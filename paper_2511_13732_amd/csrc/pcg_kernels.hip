@@ -9,10 +9,10 @@
 //                 the table delta[t] = (q(t) - p(t)) / N(t) (q(t) / N(t) on the bonus row), so
 //                 that T[g] - D[g] = sum of delta over G_g
 //   gather        the overlap-aware segmented gather-sum of that table over the membership
-//                 (Eq. 5, Eq. 8), table tiles staged in LDS.  From the prepared layout, inside
-//                 pcg_verify, no sum leaves the kernel: only fp64 totals of max(0, .) per run of
-//                 16 consecutive groups and per chunk.  From the CSR (and in pcg_group_probs,
-//                 which wants them) every sum is written.
+//                 (Eq. 5, Eq. 8), table tiles staged in LDS, from the prepared layout or the CSR.
+//                 Inside pcg_verify no sum leaves the kernel: only fp64 totals of max(0, .) per
+//                 run of 16 consecutive groups and per chunk.  pcg_group_probs has every sum
+//                 written.
 //   finalize      per sequence: the chunk and the run that hold u * total, the run's 16 sums
 //                 formed again, the group by inverse CDF, then the token inside it (Eq. 10)
 // pcg_group_probs runs row_stats, a weights kernel (q(t) / N(t)) and the same gather;
@@ -23,6 +23,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace pcg {
 
@@ -76,23 +77,20 @@ __device__ __forceinline__ float exp_rel(float x, float M, float c_hi, float c_l
   return d == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(fmaf(d, c_hi, d * c_lo));
 }
 
-// The probe of target row `row` = (b, i), i < K, by one wave: T_i[g] and D_i[g] of the proposed
+// The probe of target row (b, i), i < K, by one wave: T_i[g] and D_i[g] of the proposed
 // group g (Eq. 5), each relative to the group's own largest logit.  A chain of four dependent
 // loads (proposal -> group -> members -> logits) that needs no row statistic, which is why it
 // rides along with the statistics pass instead of waiting for it.
 template <bool BF16>
-__device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t row, float c, int lane) {
-  int64_t b;
-  int32_t i;
-  split_row(row, rs.npos0, rs.inv_npos0, b, i);
+__device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t b, int32_t i, float c, int lane,
+                          Probe *out) {
   const int32_t K = pa.K;
-  if (i >= K) return;                                   // the bonus row has no proposal
   const int32_t g = pa.prop_groups[b * K + i];
   const bool ok = g >= 0 && g < pa.G;
   double at = 0.0, ad = 0.0;
   float mt = -INFINITY, md = -INFINITY;
   if (ok) {
-    const void *trow = row_base(rs, row, BF16);
+    const void *trow = row_base(rs, b * (K + 1) + i, BF16);
     const void *drow = row_base(rs, rs.nrows0 + b * K + i, BF16);
     const int32_t beg = pa.row_ptr[g], end = pa.row_ptr[g + 1];
     // the first 64 members stay in registers; longer groups take a second trip
@@ -130,35 +128,14 @@ __device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t row, fl
   if (lane == 0) {
     Probe p;
     p.Tp = at; p.Dp = ad; p.Tref = mt; p.Dref = md; p.bad = !ok; p.pad = 0;
-    pa.out[b * K + i] = p;
+    *out = p;
   }
 }
 
+// The statistics of elements e0 .. e0 + kPartElems - 1 of a row by one wave; valid in its last lane.
 // WIDE: a row holds at least one 16-byte piece (V >= 8 bf16 or 4 fp32 logits).
 template <bool BF16, bool WIDE, bool STREAM>
-__global__ __launch_bounds__(kStatsWaves *kWave) void row_stats_kernel(RowSet rs, int32_t V,
-                                                                       int32_t nparts, int64_t nrows,
-                                                                       float c, StatPart *parts,
-                                                                       ProbeArgs pa, int64_t probe_slots) {
-  const int lane = threadIdx.x & (kWave - 1);
-  // everything that selects the data is wave-uniform: keep it in scalar registers
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // grid planes (z) continue the count of y: slot runs over the probe slots, then the rows
-  const int64_t slot = (int64_t) blockIdx.z * kRowsPerGridY + blockIdx.y;
-  if (slot < probe_slots) {
-    // The first probe_slots values (launched only with probes) are not rows of logits: each wave
-    // of their workgroups forms the probe of one target row.  They are dealt out first, so the
-    // chains of dependent loads behind the probes run while the rest of the grid streams.
-    const int64_t prow = (slot * gridDim.x + blockIdx.x) * kStatsWaves + wave;
-    if (prow < rs.nrows0) probe_row<BF16>(rs, pa, prow, c, lane);
-    return;
-  }
-  const int32_t part = blockIdx.x * kStatsWaves + wave;
-  const int64_t row = slot - probe_slots;
-  if (part >= nparts || row >= nrows) return;   // whole wave leaves together
-  const void *rowp = row_base(rs, row, BF16);
-  const int32_t e0 = part * kPartElems;
-
+__device__ __forceinline__ StatPart part_stats(const void *rowp, int32_t e0, int32_t V, float c, int lane) {
   // 16-byte loads, all issued before the first use; each instruction covers 1 KiB of the row.
   // Rows need no alignment (see load16).  In the last part of a row, pieces that would cross its
   // end are read where the row's last 16 bytes lie instead, and what belongs to the piece before
@@ -220,14 +197,41 @@ __global__ __launch_bounds__(kStatsWaves *kWave) void row_stats_kernel(RowSet rs
   }
   double z = (double) ((s0 + s1) + (s2 + s3));
   if (m == -INFINITY) z = 0.0;   // (-inf) - (-inf) is NaN: an all -inf part holds no mass
-  z = subwave_sum<64>(z);
-  if (lane == kWave - 1) {
-    StatPart sp;
-    sp.z = z;
-    sp.m = m;
-    sp.t = t;
-    parts[row * nparts + part] = sp;
+  StatPart sp;
+  sp.z = subwave_sum<64>(z);
+  sp.m = m;
+  sp.t = t;
+  return sp;
+}
+
+template <bool BF16, bool WIDE, bool STREAM>
+__global__ __launch_bounds__(kStatsWaves *kWave) void row_stats_kernel(RowSet rs, int32_t V,
+                                                                       int32_t nparts, int64_t nrows,
+                                                                       float c, StatPart *parts,
+                                                                       ProbeArgs pa, int64_t probe_slots) {
+  const int lane = threadIdx.x & (kWave - 1);
+  // everything that selects the data is wave-uniform: keep it in scalar registers
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // grid planes (z) continue the count of y: slot runs over the probe slots, then the rows
+  const int64_t slot = (int64_t) blockIdx.z * kRowsPerGridY + blockIdx.y;
+  if (slot < probe_slots) {
+    // The first probe_slots values (launched only with probes) are not rows of logits: each wave
+    // of their workgroups forms the probe of one target row.  They are dealt out first, so the
+    // chains of dependent loads behind the probes run while the rest of the grid streams.
+    const int64_t prow = (slot * gridDim.x + blockIdx.x) * kStatsWaves + wave;
+    if (prow >= rs.nrows0) return;
+    int64_t b;
+    int32_t i;
+    split_row(prow, rs.npos0, rs.inv_npos0, b, i);
+    if (i < pa.K) probe_row<BF16>(rs, pa, b, i, c, lane, pa.out + b * pa.K + i);   // the bonus row has none
+    return;
   }
+  const int32_t part = blockIdx.x * kStatsWaves + wave;
+  const int64_t row = slot - probe_slots;
+  if (part >= nparts || row >= nrows) return;   // whole wave leaves together
+  const void *rowp = row_base(rs, row, BF16);
+  const StatPart sp = part_stats<BF16, WIDE, STREAM>(rowp, part * kPartElems, V, c, lane);
+  if (lane == kWave - 1) parts[row * nparts + part] = sp;
 }
 
 // Merge the parts of one row inside a wave: every lane returns the row's (M, Z).
@@ -330,9 +334,7 @@ struct AcceptShared {
 
 // Statistics of one row from its parts, by the 16 lanes of one DPP row (sub = lane & 15); four
 // rows are merged per wave at once.  Every lane of the 16 returns the result.
-__device__ __forceinline__ RowStat merge_row16(const StatPart *parts, int64_t row, int32_t nparts,
-                                               float c, int sub) {
-  const StatPart *rp = parts + row * nparts;
+__device__ __forceinline__ RowStat merge_row16(const StatPart *rp, int32_t nparts, float c, int sub) {
   // a lane's first two parts stay in registers (rows of up to 65 536 logits: all of them), so
   // that the maximum and the sum need one trip to memory, not two
   constexpr int kKeep = 2;
@@ -368,19 +370,20 @@ __device__ __forceinline__ RowStat merge_row16(const StatPart *parts, int64_t ro
 
 // The accept scan of sequence b (Algorithm 1 up to the first rejection) by one workgroup of
 // kAcceptThreads.  On return sh.istar, sh.st_t and sh.st_d are valid for every thread; with
-// `writer` the sequence's outputs, row statistics and counters are written.
-template <bool BF16>
-__device__ void accept_phase(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
+// `writer` the sequence's outputs and counters are written, and its row statistics if a.rowstat is
+// given.  probes: the sequence's K probes; parts_t, parts_d: the parts of its target and draft rows.
+__device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs &a, int b, bool writer,
+                                             const Probe *probes, const StatPart *parts_t,
+                                             const StatPart *parts_d) {
   const int K = a.K;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   constexpr int nw = kAcceptThreads / kWave;
-  const int64_t B = a.rs.nrows0 / (K + 1);
   // The probes of the proposed groups were formed by the statistics pass; the first wave fetches
   // them (one position per lane), the others merge the row statistics.
   const int nprobe = 1;
   if (wave == 0) {
     for (int i = lane; i < K; i += kWave) {
-      const Probe p = a.probes[(int64_t) b * K + i];
+      const Probe p = probes[i];
       sh.Tp[i] = p.Tp; sh.Dp[i] = p.Dp; sh.Tref[i] = p.Tref; sh.Dref[i] = p.Dref;
       sh.bad[i] = p.bad;
       sh.pgrp[i] = a.prop_groups[(int64_t) b * K + i];
@@ -392,11 +395,12 @@ __device__ void accept_phase(AcceptShared &sh, const AcceptArgs &a, int b, bool 
     const int sub = lane & 15;
     for (int r = (wave - nprobe) * 4 + (lane >> 4); r < 2 * K + 1; r += (nw - nprobe) * 4) {
       const bool is_t = r <= K;
-      const int64_t row = is_t ? (int64_t) b * (K + 1) + r : B * (K + 1) + (int64_t) b * K + (r - K - 1);
-      const RowStat s = merge_row16(a.parts, row, a.nparts, a.c, sub);
+      const int i = is_t ? r : r - K - 1;
+      const RowStat s = merge_row16((is_t ? parts_t : parts_d) + (int64_t) i * a.nparts, a.nparts, a.c, sub);
       if (sub == 0) {
-        if (writer) a.rowstat[row] = s;
-        if (is_t) sh.st_t[r] = s; else sh.st_d[r - K - 1] = s;
+        if (writer && a.rowstat)
+          a.rowstat[is_t ? (int64_t) b * (K + 1) + i : a.rs.nrows0 + (int64_t) b * K + i] = s;
+        if (is_t) sh.st_t[i] = s; else sh.st_d[i] = s;
       }
     }
   }
@@ -447,6 +451,31 @@ __device__ void accept_phase(AcceptShared &sh, const AcceptArgs &a, int b, bool 
   __syncthreads();
 }
 
+// The same on the probes and parts that the statistics pass left in memory.
+__device__ __forceinline__ void accept_phase_stored(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
+  accept_phase(sh, a, b, writer, a.probes + (int64_t) b * a.K,
+               a.parts + (int64_t) b * (a.K + 1) * a.nparts,
+               a.parts + (a.rs.nrows0 + (int64_t) b * a.K) * a.nparts);
+}
+
+// The table entries of eight tokens on a decision row (statistics st; draft sd if it was rejected).
+__device__ __forceinline__ void delta8(const float *xt, const float *xd, const float *m, bool rejected,
+                                       const RowStat &st, const RowStat &sd, double izt, double izd,
+                                       float c, float c_lo, float *v) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const float et = exp_rel(xt[k], st.M, c, c_lo);
+    // two rounded products and a rounded difference (no fused multiply-add), so that
+    // identical target and draft rows give exactly zero
+    double diff = __dmul_rn((double) et, izt);
+    if (rejected) {
+      const float ed = exp_rel(xd[k], sd.M, c, c_lo);
+      diff = __dsub_rn(diff, __dmul_rn((double) ed, izd));
+    }
+    v[k] = (float) diff * __builtin_amdgcn_rcpf(m[k]);   // N(t) is a small integer: 1 ulp, a tenth of a division's cost
+  }
+}
+
 // accept + delta.  Workgroup (b, s) runs the whole accept scan of sequence b -- every one of
 // the sequence's workgroups does, so that none has to wait for another -- and then writes its
 // slices of the table the gather sums over, on the decision row i* = accept_len[b]:
@@ -470,7 +499,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs
   float m_a[8], m_b[8];
   if (first < V) load8_mult<WIDE>(mult, slice_start<WIDE>(first, V), V, m_a);
   if (first + stride < V) load8_mult<WIDE>(mult, slice_start<WIDE>(first + stride, V), V, m_b);
-  accept_phase<BF16>(sh, a, b, split == 0);
+  accept_phase_stored(sh, a, b, split == 0);
 
   // 4. this workgroup's share of the table on the decision row: slices split, split + nsplit, ...
   const int32_t istar = sh.istar;
@@ -480,19 +509,8 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs
   const RowStat st = sh.st_t[istar];
   const RowStat sd = sh.st_d[rejected ? istar : 0];
   const double izt = 1.0 / st.Z, izd = rejected ? 1.0 / sd.Z : 0.0;
-  auto delta8 = [&](const float *xt, const float *xd, const float *m, float *v) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float et = exp_rel(xt[k], st.M, c, c_lo);
-      // two rounded products and a rounded difference (no fused multiply-add), so that
-      // identical target and draft rows give exactly zero
-      double diff = __dmul_rn((double) et, izt);
-      if (rejected) {
-        const float ed = exp_rel(xd[k], sd.M, c, c_lo);
-        diff = __dsub_rn(diff, __dmul_rn((double) ed, izd));
-      }
-      v[k] = (float) diff * __builtin_amdgcn_rcpf(m[k]);   // N(t) is a small integer: 1 ulp, a tenth of a division's cost
-    }
+  auto delta = [&](const float *xt, const float *xd, const float *m, float *v) {
+    delta8(xt, xd, m, rejected, st, sd, izt, izd, c, c_lo, v);
   };
   float *out = table + (int64_t) b * V;
   // two slices per turn, so that the loads of the second are in flight behind the first
@@ -513,10 +531,10 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs
       load8_mult<WIDE>(mult, t, V, m);
       if (two) load8_mult<WIDE>(mult, t2, V, m2);
     }
-    delta8(xt, xd, m, v);
+    delta(xt, xd, m, v);
     store8<WIDE>(out, t, V, v);
     if (two) {
-      delta8(xt2, xd2, m2, v);
+      delta(xt2, xd2, m2, v);
       store8<WIDE>(out, t2, V, v);
     }
   }
@@ -746,7 +764,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_thin_kernel(
   __shared__ AcceptShared sh;
   __shared__ ThinShared th;
   const int b = blockIdx.x;
-  accept_phase<BF16>(sh, a, b, true);
+  accept_phase_stored(sh, a, b, true);
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t K = a.K, V = a.V, istar = sh.istar;
@@ -927,79 +945,206 @@ __global__ __launch_bounds__(kTableThreads) void weights_kernel(
 // =============================================================================================
 
 
+// One tile of a table row, global memory -> LDS directly: every load of the tile is in flight at once
+// and none passes through a register (a wave's instruction fills 64 pieces in lane order, which is
+// the table's own order).  16 bytes per lane, or 4 where the row or the tile does not start on 16
+// bytes.  The caller waits (vmcnt) and meets the other waves.  tab: 16-byte aligned.
+__device__ __forceinline__ void stage_tile(float *tab, const float *src, int32_t tl, int tid) {
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if ((((uintptr_t) src | (uintptr_t) (4 * tl)) & 15) == 0) {        // uniform
+    const float4 *s4 = reinterpret_cast<const float4 *>(src);
+    const int32_t n4 = tl >> 2;
+    for (int32_t k0 = wave * kWave; k0 < n4; k0 += kGatherThreads)
+      if (k0 + lane < n4)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *) (s4 + k0 + lane),
+            (__attribute__((address_space(3))) void *) (tab + 4 * k0), 16, 0, 0);
+  } else {
+    for (int32_t k0 = wave * kWave; k0 < tl; k0 += kGatherThreads)
+      if (k0 + lane < tl)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *) (src + k0 + lane),
+            (__attribute__((address_space(3))) void *) (tab + k0), 4, 0, 0);
+  }
+}
+
+// A workgroup's sums, from LDS to memory: 16 bytes at a time where both sides allow it.
+__device__ __forceinline__ void store_sums(float *dst, const float *sums, int32_t ng) {
+  if ((((uintptr_t) dst | (uintptr_t) ng) & 15) == 0 && (ng & 3) == 0) {
+    for (int32_t i = 4 * threadIdx.x; i < ng; i += 4 * kGatherThreads)
+      *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(sums + i);
+  } else {
+    for (int32_t i = threadIdx.x; i < ng; i += kGatherThreads) dst[i] = sums[i];
+  }
+}
+
+// Sums over the groups [g_begin, g_end) of the table tile tab[0 .. tl) = tokens [t0, t0 + tl), read
+// straight from the CSR by a workgroup of kGatherThreads; sink(g, sum) is called by one lane per
+// group.  tab[zero] must read 0.  W lanes share a group, each taking four consecutive entries with
+// one 16-byte load (kept inside the nnz entries of the array; what lies outside the group is sent to
+// the zero slot); a sub-wave works on kInFlight groups at a time, and while it sums them the
+// entries of its next ones and the bounds of those after them are on their way.
+template <int W, bool WEIGHTED, typename Sink>
+__device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t t0, int32_t tl, int32_t g_begin,
+                                         int32_t g_end, const int32_t *row_ptr, const int32_t *members,
+                                         int32_t nnz, const float *weights, Sink sink) {
+  constexpr int kInFlight = 4;
+  constexpr int nsub = kGatherThreads / W;
+  constexpr int kPass = nsub * kInFlight;           // groups per turn of the workgroup
+  const int sub = threadIdx.x / W, sl = threadIdx.x % W;
+  struct Bounds { int32_t beg[kInFlight], end[kInFlight]; };
+  struct Entries { u32x4 m[kInFlight], w[kInFlight]; };
+  auto bounds = [&](int32_t gb, Bounds &r) {
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) {
+      const int32_t g = min(gb + u * nsub + sub, g_end - 1);
+      r.beg[u] = row_ptr[g];
+      r.end[u] = row_ptr[g + 1];
+    }
+  };
+  auto load4 = [&](const void *p, int32_t j) -> u32x4 {
+    const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
+    if (nnz >= 4) return load16<false>(q + min(j, nnz - 4));
+    u32x4 r = {0, 0, 0, 0};                         // fewer than four entries in all
+    for (int k = 0; k < 4; ++k) {
+      const int32_t at = nnz - 4 + k;
+      if (at >= 0) r[k] = q[at];
+    }
+    return r;
+  };
+  auto entries = [&](const Bounds &r, Entries &e) {
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) {
+      const int32_t j = r.beg[u] + 4 * sl;
+      e.m[u] = load4(members, j);
+      if constexpr (WEIGHTED) e.w[u] = load4(weights, j);
+    }
+  };
+  // what the four entries loaded for position j add to a sum: those from j on, inside the group
+  auto add4 = [&](const u32x4 m, const u32x4 w, int32_t j, int32_t end, float acc) {
+    const int32_t at = min(j, nnz - 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int32_t t = (int32_t) m[k] - t0;
+      const bool mine = at + k >= j && at + k < end && (uint32_t) t < (uint32_t) tl;
+      const float v = tab[mine ? t : zero];
+      if constexpr (WEIGHTED) acc = fmaf(v, __uint_as_float(w[k]), acc);
+      else acc += v;
+    }
+    return acc;
+  };
+  Bounds now, after;
+  Entries e;
+  bounds(g_begin, now);
+  entries(now, e);
+  bounds(min(g_begin + kPass, g_end - 1), after);
+  for (int32_t gb = g_begin; gb < g_end; gb += kPass) {
+    Entries en;
+    Bounds later;
+    if (gb + kPass < g_end) {                       // uniform over the workgroup
+      entries(after, en);
+      bounds(min(gb + 2 * kPass, g_end - 1), later);
+    }
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) {
+      float acc = add4(e.m[u], e.w[u], now.beg[u] + 4 * sl, now.end[u], 0.f);
+      for (int32_t j = now.beg[u] + 4 * (sl + W); j < now.end[u]; j += 4 * W) {   // longer than one trip
+        const u32x4 m = load4(members, j);
+        u32x4 w = m;
+        if constexpr (WEIGHTED) w = load4(weights, j);
+        acc = add4(m, w, j, now.end[u], acc);
+      }
+      acc = subwave_sum<W>(acc);
+      const int32_t g = gb + u * nsub + sub;
+      if (g < g_end && sl == W - 1) sink(g, acc);
+    }
+    now = after;
+    after = later;
+    e = en;
+  }
+}
+
+// Totals of max(0, sum) per run of kRunGroups groups (to runs) and over all ng sums of a workgroup
+// (to *total), in double and in a fixed order; sums: 16-byte aligned LDS, readable up to the next
+// multiple of 4.  Four neighbouring lanes cover one run, four groups each.
+__device__ __forceinline__ void run_totals(const float *sums, int32_t ng, double *runs, double *total) {
+  __shared__ double wsum[kGatherWaves];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+  const float4 *sums4 = reinterpret_cast<const float4 *>(sums);
+  double part = 0.0;
+#pragma unroll
+  for (int j = 0; j < kMaxChunkGroups / (4 * kGatherThreads); ++j) {
+    const int32_t i4 = threadIdx.x + j * kGatherThreads;
+    const int32_t g = 4 * i4;
+    double s = 0.0;
+    if (g < ng) {
+      const float4 v = sums4[i4];
+      s = ((double) fmaxf(v.x, 0.f) + (g + 1 < ng ? (double) fmaxf(v.y, 0.f) : 0.0)) +
+          ((g + 2 < ng ? (double) fmaxf(v.z, 0.f) : 0.0) + (g + 3 < ng ? (double) fmaxf(v.w, 0.f) : 0.0));
+    }
+    s = subwave_sum<4>(s);
+    if ((lane & 3) == 0 && g < ng) {
+      runs[i4 >> 2] = s;
+      part += s;
+    }
+  }
+  part = subwave_sum<64>(part);
+  if (lane == kWave - 1) wsum[wave] = part;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < kGatherWaves; ++w) t += wsum[w];
+    *total = t;
+  }
+}
+
 // Workgroup id -> (row, chunk).  Workgroups are dealt to the 8 XCDs round-robin by id, so all
 // chunks of one row are given ids that are equal mod 8: they then share that XCD's L2 for the
 // table row and none other holds it.
-template <int W, bool CLAMP>
+// LDS holds a tile of the table (tile_len tokens, the zero slot behind it) and the chunk's sums
+// (groups_per_chunk, a multiple of 4).  CSUM: only run and chunk totals leave, as from the prepared
+// gather; otherwise every sum.
+// Bound by the L2, which hands every row its own copy of the members (4 bytes an entry, once per
+// tile).  One entry per lane and load, with every pass waiting for its bounds, then its entries, took
+// 28.3 us at V = 16 384, 32 members, 32 rows, and 13.2 us to scan the sums; this takes 14.6, and 7.6 to
+// locate the draw (V = 65 536, 64 rows: 450 us and 51 us before, 197 and 9 now).
+template <int W, bool CSUM, bool WEIGHTED>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
-    int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t groups_per_chunk,
-    int32_t ntiles, int32_t tile_len, const int32_t *row_ptr, const int32_t *members,
-    const float *weights, const float *table, float *out) {
-  __shared__ float tab[kTileMax];
+    int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t groups_per_chunk, int32_t ntiles,
+    int32_t tile_len, int32_t nnz, const int32_t *row_ptr, const int32_t *members, const float *weights,
+    const float *table, float *out, double *csum, int64_t csum_stride, double *runs) {
+  __shared__ __attribute__((aligned(16))) float lds[kTileMax];
+  float *sums = lds, *tab = lds + groups_per_chunk;
   const int xcd = blockIdx.x & 7;
   const int y = blockIdx.x >> 3;
   const int r = xcd + 8 * (y / nchunks);
   const int chunk = y % nchunks;
   if (r >= nrows) return;   // whole workgroup leaves together, before any barrier
   const float *src = table + (int64_t) r * V;
-  float *dst = out + (int64_t) r * G;
   const int32_t g_begin = chunk * groups_per_chunk;
-  const int32_t g_end = min(G, g_begin + groups_per_chunk);
-  constexpr int nsub = kGatherThreads / W;          // groups in flight per workgroup pass
-  const int sub = threadIdx.x / W, sl = threadIdx.x % W;
-
+  const int32_t ng = min(groups_per_chunk, G - g_begin);
   for (int tile = 0; tile < ntiles; ++tile) {
     const int32_t t0 = tile * tile_len;
     const int32_t tl = min(tile_len, V - t0);
     if (tl <= 0) break;                             // uniform: no tile starts past the row
     if (tile > 0) __syncthreads();                  // everyone is done reading the old tile
-    for (int32_t k = threadIdx.x; k < tl; k += kGatherThreads) tab[k] = src[t0 + k];
+    stage_tile(tab, src + t0, tl, threadIdx.x);
+    if (threadIdx.x == 0) tab[tile_len] = 0.f;
+    __builtin_amdgcn_s_waitcnt(0x0f70);             // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
-    // Every lane of a wave runs the same number of passes, so the DPP reduction below is
-    // always executed by full waves.  A sub-wave takes kInFlight groups per pass, so that their
-    // chains of dependent loads (row_ptr -> members -> table) overlap.
-    constexpr int kInFlight = 8;
-    for (int32_t gb = g_begin; gb < g_end; gb += nsub * kInFlight) {
-      int32_t beg[kInFlight], end[kInFlight], mem[kInFlight];
-      float wt[kInFlight], acc[kInFlight];
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {
-        const int32_t g = gb + u * nsub + sub;
-        const bool valid = g < g_end;
-        beg[u] = valid ? row_ptr[g] : 0;
-        end[u] = valid ? row_ptr[g + 1] : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {       // first trip of each group
-        const int32_t j = beg[u] + sl;
-        const bool has = j < end[u];
-        mem[u] = has ? members[j] : -1;
-        wt[u] = has && weights ? weights[j] : 1.f;
-      }
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {
-        const uint32_t t = (uint32_t) (mem[u] - t0);
-        acc[u] = 0.f;
-        if (mem[u] >= 0 && t < (uint32_t) tl) acc[u] = weights ? tab[t] * wt[u] : tab[t];
-      }
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {       // groups longer than the sub-wave
-        for (int32_t j = beg[u] + sl + W; j < end[u]; j += W) {
-          const uint32_t t = (uint32_t) (members[j] - t0);
-          if (t < (uint32_t) tl) acc[u] += weights ? tab[t] * weights[j] : tab[t];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {
-        const int32_t g = gb + u * nsub + sub;
-        float a = subwave_sum<W>(acc[u]);
-        if (g < g_end && sl == W - 1) {
-          if (tile > 0) a += dst[g];                // partial sum of the earlier tiles
-          if (CLAMP && tile == ntiles - 1) a = fmaxf(a, 0.f);
-          dst[g] = a;
-        }
-      }
-    }
+    csr_sums<W, WEIGHTED>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
+                          [&](int32_t g, float a) {
+                            // the same lane in every tile: no other touches this sum
+                            sums[g - g_begin] = tile > 0 ? sums[g - g_begin] + a : a;
+                          });
+  }
+  __syncthreads();
+  if constexpr (CSUM) {
+    run_totals(sums, ng, runs + ((int64_t) r * nchunks + chunk) * (groups_per_chunk / kRunGroups),
+               csum + r * csum_stride + chunk);
+  } else {
+    store_sums(out + (int64_t) r * G + g_begin, sums, ng);
   }
 }
 
@@ -1142,23 +1287,12 @@ __device__ __forceinline__ bool near_edge(const CdfPick &p, double u) {
   return near_lo || near_hi;
 }
 
-// The last step of a sequence, by one whole workgroup of NT threads.  After the CSR gather
-// (csum == NULL) R holds the gathered sums T[g] - D[g] (T[g] on a bonus row), clamped here on
-// read, and all of it is scanned.  After the prepared gather (csum, runs != NULL) there are no
-// sums, only the totals of max(0, .) over chunks of chunk_groups consecutive groups and over runs
-// of kRunGroups: the chunk and the run that hold the draw are located from them, and the run's
-// sums are formed again here.
+// The token inside the chosen group (Eq. 10) and the sequence's last outputs, by one whole workgroup
+// of NT threads; pg: the group draw (total mass <= 0: the fallback to T of this row).
 template <bool BF16, int NT>
-__device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, int b,
-                                  const double *csum, const double *runs, int32_t nchunks,
-                                  int32_t chunk_groups) {
+__device__ void finish_sequence(const FinalizeArgs &fa, int32_t G, int b, int32_t istar, const void *trow,
+                                const RowStat &st, const Uniforms &u, CdfPick pg) {
   const int32_t K = fa.K;
-  const int32_t istar = fa.accept_len[b];
-  const int64_t trow_id = (int64_t) b * (K + 1) + istar;
-  const void *trow = row_base(fa.rs, trow_id, BF16);
-  const RowStat st = fa.rowstat[trow_id];
-  const Uniforms u = philox_uniforms(fa.seed, fa.offset, (uint32_t) b, (uint32_t) istar);
-  float *Rb = fa.R + (int64_t) b * G;
   const int32_t *row_ptr = fa.row_ptr, *members = fa.members, *mult = fa.mult;
   const float *wts = fa.weights;
   const double cd = fa.cd;
@@ -1170,22 +1304,125 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
     return wts ? e * (double) wts[j] / st.Z : e / (st.Z * (double) mult[t]);
   };
 
+  bool fallback = false;
+  if (!(pg.total > 0.0) || pg.index < 0) {
+    // Residual total <= 0 (cannot happen in exact arithmetic): draw from T of this row instead.
+    fallback = true;
+    float *Rb = fa.R + (int64_t) b * G;
+    for (int32_t g = threadIdx.x; g < G; g += NT) {
+      double s = 0.0;
+      for (int32_t j = row_ptr[g]; j < row_ptr[g + 1]; ++j) s += weight(j);
+      Rb[g] = (float) s;
+    }
+    __syncthreads();
+    pg = block_inverse_cdf<NT>(G, [&](int32_t g) { return (double) Rb[g]; }, (double) u.grp);
+  }
+  const int32_t gs = pg.index < 0 ? 0 : pg.index;
+
+  const int32_t beg = row_ptr[gs], end = row_ptr[gs + 1];
+  CdfPick pt;
+  constexpr int kTokRounds = 4;          // entries per lane the one-wave path keeps in registers
+  if (end - beg <= kTokRounds * kWave) {
+    // The token inside the group (Eq. 10) by the first wave alone: every entry's mass is loaded
+    // once, all loads in flight together, and kept in registers for the total and for the scan.
+    if (threadIdx.x < kWave) {
+      const int lane = threadIdx.x;
+      const int32_t n = end - beg;
+      double w[kTokRounds];
+#pragma unroll
+      for (int c = 0; c < kTokRounds; ++c) {
+        const int32_t j = c * kWave + lane;
+        w[c] = j < n ? weight(beg + j) : 0.0;
+        if (!(w[c] > 0.0)) w[c] = 0.0;
+      }
+      double total = 0.0;
+#pragma unroll
+      for (int c = 0; c < kTokRounds; ++c) total += wave_sum(w[c]);      // ascending, 64 at a time
+      pt.index = -1; pt.total = total; pt.lo = pt.hi = 0.0;
+      const double goal = (double) u.tok * total;
+      double base = 0.0, last_v = 0.0;
+      int32_t last = -1;
+      bool done = false;
+#pragma unroll
+      for (int c = 0; c < kTokRounds; ++c) {
+        if (done || c * kWave >= n) continue;                            // uniform
+        const double inc = wave_scan(w[c]);
+        const unsigned long long pos = __ballot(w[c] > 0.0);
+        if (pos) {
+          const int hl = 63 - __clzll((long long) pos);
+          last = c * kWave + hl;
+          last_v = read_lane(w[c], hl);
+        }
+        const unsigned long long hit = __ballot(w[c] > 0.0 && base + inc > goal);
+        if (hit) {
+          const int l = __ffsll((long long) hit) - 1;
+          pt.index = c * kWave + l;
+          pt.hi = base + read_lane(inc, l);
+          pt.lo = pt.hi - read_lane(w[c], l);
+          done = true;
+        } else {
+          base += read_lane(inc, kWave - 1);
+        }
+      }
+      if (!done && last >= 0) {          // rounding at the top end: the last entry that has mass
+        pt.index = last; pt.hi = total; pt.lo = total - last_v;
+      }
+    }
+  } else {
+    pt = block_inverse_cdf<NT>(end - beg, [&](int32_t j) { return weight(beg + j); }, (double) u.tok);
+  }
+  if (threadIdx.x == 0) {
+    fa.out_groups[(int64_t) b * (K + 1) + istar] = gs;
+    fa.out_tokens[(int64_t) b * (K + 1) + istar] = pt.index < 0 ? -1 : members[beg + pt.index];
+    if (fa.diag) {
+      if (pg.index >= 0 && near_edge(pg, (double) u.grp)) atomicAdd(&fa.diag->near_group, 1u);
+      if (pt.index >= 0 && near_edge(pt, (double) u.tok)) atomicAdd(&fa.diag->near_token, 1u);
+      if (fallback) atomicAdd(&fa.diag->residual_fallback, 1u);
+    }
+  }
+}
+
+// The last step of a sequence, by one whole workgroup of NT threads.  The gather left no sums, only
+// the totals of max(0, T[g] - D[g]) (T[g] on a bonus row) over chunks of chunk_groups consecutive
+// groups and over runs of kRunGroups: the chunk and the run that hold the draw are located from
+// them, and the run's sums are formed again here.
+template <bool BF16, int NT>
+__device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, int b,
+                                  const double *csum, int64_t csum_stride, const double *runs,
+                                  int32_t nchunks, int32_t chunk_groups) {
+  const int32_t K = fa.K;
+  const int32_t istar = fa.accept_len[b];
+  const int64_t trow_id = (int64_t) b * (K + 1) + istar;
+  const void *trow = row_base(fa.rs, trow_id, BF16);
+  const RowStat st = fa.rowstat[trow_id];
+  const Uniforms u = philox_uniforms(fa.seed, fa.offset, (uint32_t) b, (uint32_t) istar);
+  const int32_t *row_ptr = fa.row_ptr, *members = fa.members, *mult = fa.mult;
+  const float *wts = fa.weights;
+  const double cd = fa.cd;
+
+  // residual total and the chunk that holds u * total, from the per-chunk sums (ascending), 64 side by
+  // side; every wave does the same
   CdfPick pg;
-  if (csum) {
-    // residual total and the chunk that holds u * total, from the per-chunk sums (ascending)
-    const double *cs = csum + (int64_t) b * nchunks;
-    double S = 0.0;
-    for (int32_t c = 0; c < nchunks; ++c) S += cs[c];
+  {
+    const double *cs = csum + b * csum_stride;
+    const int ln = threadIdx.x & (kWave - 1);
+    const double cs0 = ln < nchunks ? cs[ln] : 0.0;
+    double S = wave_sum(cs0);
+    for (int32_t c0 = kWave; c0 < nchunks; c0 += kWave) S += wave_sum(c0 + ln < nchunks ? cs[c0 + ln] : 0.0);
     const double goal = (double) u.grp * S;
     double cum = 0.0, base = 0.0;
     int32_t cstar = -1;
-    for (int32_t c = 0; c < nchunks; ++c) {
-      const double v = cs[c];
-      if (!(v > 0.0)) continue;
-      cstar = c;
-      base = cum;
-      if (cum + v > goal) break;
-      cum += v;
+    for (int32_t c0 = 0; c0 < nchunks; c0 += kWave) {
+      const double v = c0 == 0 ? cs0 : (c0 + ln < nchunks ? cs[c0 + ln] : 0.0);
+      const double inc = wave_scan(v);
+      const unsigned long long pos = __ballot(v > 0.0), hit = __ballot(v > 0.0 && cum + inc > goal);
+      if (pos) {
+        const int l = hit ? __ffsll((long long) hit) - 1 : 63 - __clzll((long long) pos);
+        cstar = c0 + l;
+        base = cum + (read_lane(inc, l) - read_lane(v, l));
+      }
+      if (hit) break;
+      cum += read_lane(inc, kWave - 1);
     }
     pg.index = -1; pg.total = S; pg.lo = pg.hi = 0.0;
     if (S > 0.0 && cstar >= 0) {
@@ -1293,96 +1530,19 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
         }
       }
     }
-  } else {
-    pg = block_inverse_cdf<NT>(G, [&](int32_t g) { return (double) fmaxf(Rb[g], 0.f); },
-                               (double) u.grp);
   }
-  bool fallback = false;
-  if (!(pg.total > 0.0) || pg.index < 0) {
-    // Residual total <= 0 (cannot happen in exact arithmetic): draw from T of this row instead.
-    fallback = true;
-    for (int32_t g = threadIdx.x; g < G; g += NT) {
-      double s = 0.0;
-      for (int32_t j = row_ptr[g]; j < row_ptr[g + 1]; ++j) s += weight(j);
-      Rb[g] = (float) s;
-    }
-    __syncthreads();
-    pg = block_inverse_cdf<NT>(G, [&](int32_t g) { return (double) Rb[g]; }, (double) u.grp);
-  }
-  const int32_t gs = pg.index < 0 ? 0 : pg.index;
-
-  const int32_t beg = row_ptr[gs], end = row_ptr[gs + 1];
-  CdfPick pt;
-  constexpr int kTokRounds = 4;          // entries per lane the one-wave path keeps in registers
-  if (end - beg <= kTokRounds * kWave) {
-    // The token inside the group (Eq. 10) by the first wave alone: every entry's mass is loaded
-    // once, all loads in flight together, and kept in registers for the total and for the scan.
-    if (threadIdx.x < kWave) {
-      const int lane = threadIdx.x;
-      const int32_t n = end - beg;
-      double w[kTokRounds];
-#pragma unroll
-      for (int c = 0; c < kTokRounds; ++c) {
-        const int32_t j = c * kWave + lane;
-        w[c] = j < n ? weight(beg + j) : 0.0;
-        if (!(w[c] > 0.0)) w[c] = 0.0;
-      }
-      double total = 0.0;
-#pragma unroll
-      for (int c = 0; c < kTokRounds; ++c) total += wave_sum(w[c]);      // ascending, 64 at a time
-      pt.index = -1; pt.total = total; pt.lo = pt.hi = 0.0;
-      const double goal = (double) u.tok * total;
-      double base = 0.0, last_v = 0.0;
-      int32_t last = -1;
-      bool done = false;
-#pragma unroll
-      for (int c = 0; c < kTokRounds; ++c) {
-        if (done || c * kWave >= n) continue;                            // uniform
-        const double inc = wave_scan(w[c]);
-        const unsigned long long pos = __ballot(w[c] > 0.0);
-        if (pos) {
-          const int hl = 63 - __clzll((long long) pos);
-          last = c * kWave + hl;
-          last_v = read_lane(w[c], hl);
-        }
-        const unsigned long long hit = __ballot(w[c] > 0.0 && base + inc > goal);
-        if (hit) {
-          const int l = __ffsll((long long) hit) - 1;
-          pt.index = c * kWave + l;
-          pt.hi = base + read_lane(inc, l);
-          pt.lo = pt.hi - read_lane(w[c], l);
-          done = true;
-        } else {
-          base += read_lane(inc, kWave - 1);
-        }
-      }
-      if (!done && last >= 0) {          // rounding at the top end: the last entry that has mass
-        pt.index = last; pt.hi = total; pt.lo = total - last_v;
-      }
-    }
-  } else {
-    pt = block_inverse_cdf<NT>(end - beg, [&](int32_t j) { return weight(beg + j); }, (double) u.tok);
-  }
-  if (threadIdx.x == 0) {
-    fa.out_groups[(int64_t) b * (K + 1) + istar] = gs;
-    fa.out_tokens[(int64_t) b * (K + 1) + istar] = pt.index < 0 ? -1 : members[beg + pt.index];
-    if (fa.diag) {
-      if (pg.index >= 0 && near_edge(pg, (double) u.grp)) atomicAdd(&fa.diag->near_group, 1u);
-      if (pt.index >= 0 && near_edge(pt, (double) u.tok)) atomicAdd(&fa.diag->near_token, 1u);
-      if (fallback) atomicAdd(&fa.diag->residual_fallback, 1u);
-    }
-  }
+  finish_sequence<BF16, NT>(fa, G, b, istar, trow, st, u, pg);
 }
 
-// One workgroup per sequence.  csum / nchunks / chunk_groups describe the chunk totals the
-// prepared gather wrote (csum == NULL after the CSR gather: the whole range is scanned).
+// One workgroup per sequence.  csum, runs, nchunks, chunk_groups: the totals as the gather wrote them.
 template <bool BF16>
 __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(FinalizeArgs fa, int32_t V,
                                                                  int32_t G, const double *csum,
+                                                                 int64_t csum_stride,
                                                                  const double *runs,
                                                                  int32_t nchunks,
                                                                  int32_t chunk_groups) {
-  finalize_sequence<BF16, kFinalThreads>(fa, V, G, blockIdx.x, csum, runs, nchunks, chunk_groups);
+  finalize_sequence<BF16, kFinalThreads>(fa, V, G, blockIdx.x, csum, csum_stride, runs, nchunks, chunk_groups);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1447,6 +1607,112 @@ struct GatherStep<true> {
   }
 };
 
+// First unit and number of steps of a wave's blocks in one tile of one chunk (dsc; NULL: none).
+__device__ __forceinline__ void load_desc(const uint32_t *dsc, int bpc, int wave,
+                                          uint32_t (&steps)[kMaxBlocksPerWave],
+                                          uint32_t (&offs)[kMaxBlocksPerWave]) {
+#pragma unroll
+  for (int q = 0; q < kMaxBlocksPerWave; ++q) {
+    const int bl = block_of(q, wave);
+    steps[q] = 0;
+    offs[q] = 0;
+    if (dsc && bl < bpc) {                            // uniform over the wave: scalar registers
+      steps[q] = __builtin_amdgcn_readfirstlane(dsc[2 * bl + 1]);
+      offs[q] = __builtin_amdgcn_readfirstlane(dsc[2 * bl]);
+    }
+  }
+}
+
+// A wave's way through its blocks, one after the other.  The steps come through a ring of registers
+// that is always kRing steps ahead: slot i takes the steps i, i + kRing, ... of a block, and once the
+// block has none left, step i of the wave's next block (in the last block of a tile: of the next
+// tile's first), so that the stream never waits at a block's or a tile's end.
+template <bool WEIGHTED>
+struct SlotStream {
+  // Steps in flight per wave.  A wave used to keep one step of each of its blocks in flight, so
+  // one left with a single long block (or none beside it) waited for the L2 on every step: 17.0 us
+  // at B = 1, V = 65 536 against 13.4 with this ring, 57.5 against 46.3 at B = 128, V = 32 768 with
+  // groups of 1 to 128, 27.4 against 25.2 at B = 64, V = 65 536.  Six steps spill with weights and
+  // change nothing without; eight spill (27.8 us).
+  static constexpr int kRing = WEIGHTED ? 2 : 4;
+  GatherStep<WEIGHTED> ring[kRing];
+  bool filled = false;                                // the ring holds the first steps of the coming tile
+  uint32_t steps[kMaxBlocksPerWave], offs[kMaxBlocksPerWave];             // this tile's blocks
+  uint32_t succ_off[kMaxBlocksPerWave], succ_last[kMaxBlocksPerWave];     // what follows each of them
+
+  // a scalar base and the lane as the only vector part: no address arithmetic per load
+  __device__ __forceinline__ void load(int i, uint32_t unit, const uint4 *data, const float4 *wdata, int lane) {
+    const uint32_t u = __builtin_amdgcn_readfirstlane(unit);
+    ring[i].load(data + u, wdata + 2 * (size_t) u, lane);
+  }
+
+  // Before a tile (steps, offs set): finds what follows each block, nsteps / noffs being the next
+  // tile's, and fills the ring unless the tile before has done so.
+  __device__ __forceinline__ void begin(const uint32_t (&nsteps)[kMaxBlocksPerWave],
+                                        const uint32_t (&noffs)[kMaxBlocksPerWave], const uint4 *data,
+                                        const float4 *wdata, int lane) {
+    uint32_t so = 0, sn = 0, first_off = 0, first_steps = 0;
+#pragma unroll
+    for (int q = kMaxBlocksPerWave - 1; q >= 0; --q)
+      if (nsteps[q] > 0) { so = noffs[q]; sn = nsteps[q]; }
+    const bool follows = sn > 0;
+#pragma unroll
+    for (int q = kMaxBlocksPerWave - 1; q >= 0; --q) {
+      // nothing follows: the block's own first steps are read again, and not used
+      succ_off[q] = sn > 0 ? so : offs[q];
+      succ_last[q] = (sn > 0 ? sn : max(steps[q], 1u)) - 1;
+      if (steps[q] > 0) { so = first_off = offs[q]; sn = first_steps = steps[q]; }
+    }
+    if (!filled && first_steps > 0) {
+#pragma unroll
+      for (int i = 0; i < kRing; ++i)
+        load(i, first_off + min((uint32_t) i, first_steps - 1) * kWave, data, wdata, lane);
+    }
+    if (first_steps > 0) filled = follows;
+  }
+
+  // Adds the tile's entries to the wave's sums.
+  __device__ __forceinline__ void walk(const float *tab, const uint4 *data, const float4 *wdata, int lane,
+                                       float *acc) {
+#pragma unroll
+    for (int q = 0; q < kMaxBlocksPerWave; ++q) {
+      const uint32_t n = steps[q];                    // uniform over the wave, as everything below
+      float *a = acc + q * kLaneGroups;
+      auto next = [&](int i) { return succ_off[q] + min((uint32_t) i, succ_last[q]) * kWave; };
+      if (n >= (uint32_t) kRing) {
+        uint32_t t = 0;
+        for (; t + kRing <= n; t += kRing) {
+#pragma unroll
+          for (int i = 0; i < kRing; ++i) {
+            ring[i].apply(tab, a);
+            const uint32_t k = t + i + kRing;
+            load(i, k < n ? offs[q] + k * kWave : next(i), data, wdata, lane);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < kRing - 1; ++i) {
+          if (t + i < n) {
+            ring[i].apply(tab, a);
+            load(i, next(i), data, wdata, lane);
+          }
+        }
+      } else if (n > 0) {
+        // a short block: the slots it has no step for pass to its successor first
+#pragma unroll
+        for (int i = 1; i < kRing; ++i)
+          if ((uint32_t) i >= n) load(i, next(i), data, wdata, lane);
+#pragma unroll
+        for (int i = 0; i < kRing - 1; ++i) {
+          if ((uint32_t) i < n) {
+            ring[i].apply(tab, a);
+            load(i, next(i), data, wdata, lane);
+          }
+        }
+      }
+    }
+  }
+};
+
 template <bool CSUM, bool WEIGHTED>
 __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t chunk_groups, int32_t ntiles,
@@ -1455,7 +1721,6 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     const float4 *__restrict__ wdata, const float *__restrict__ table, float *__restrict__ out,
     double *__restrict__ csum, double *__restrict__ runs) {
   __shared__ __attribute__((aligned(16))) float tab[kTileMax];
-  __shared__ double wsum[kGatherWaves];
   const int xcd = blockIdx.x & 7;
   const int y = blockIdx.x >> 3;
   const int r = xcd + 8 * (y / nchunks);
@@ -1482,130 +1747,26 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     }
   }
 
-  // descriptors (first unit and number of steps) of this wave's blocks in tile h
-  auto load_desc = [&](int h, uint32_t (&steps)[kMaxBlocksPerWave], uint32_t (&offs)[kMaxBlocksPerWave]) {
-    const uint32_t *dsc = desc + ((size_t) (chunk * ntiles + h) * bpc) * 2;
-#pragma unroll
-    for (int q = 0; q < kMaxBlocksPerWave; ++q) {
-      const int bl = block_of(q, wave);
-      steps[q] = 0;
-      offs[q] = 0;
-      if (bl < bpc && h < ntiles) {                   // uniform over the wave: scalar registers
-        steps[q] = __builtin_amdgcn_readfirstlane(dsc[2 * bl + 1]);
-        offs[q] = __builtin_amdgcn_readfirstlane(dsc[2 * bl]);
-      }
-    }
-  };
-  uint32_t steps[kMaxBlocksPerWave], offs[kMaxBlocksPerWave];
-  uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];
-  load_desc(0, steps, offs);
-  // Steps in flight per wave.  A wave used to keep one step of each of its blocks in flight, so
-  // one left with a single long block (or none beside it) waited for the L2 on every step: 17.0 us
-  // at B = 1, V = 65 536 against 13.4 with this ring, 57.5 against 46.3 at B = 128, V = 32 768 with
-  // groups of 1 to 128, 27.4 against 25.2 at B = 64, V = 65 536.  Six steps spill with weights and
-  // change nothing without; eight spill (27.8 us).
-  constexpr int kRing = WEIGHTED ? 2 : 4;
-  GatherStep<WEIGHTED> ring[kRing];
-  bool filled = false, follows = false;               // ring holds the first steps of this / the next tile
+  const uint32_t *dsc = desc + (size_t) chunk * ntiles * bpc * 2;
+  uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];      // the next tile's blocks
+  SlotStream<WEIGHTED> stream;
+  load_desc(dsc, bpc, wave, stream.steps, stream.offs);
 
   for (int h = 0; h < ntiles; ++h) {
     const int32_t t0 = h * tile_len;
     const int32_t tl = min(tile_len, V - t0);
     if (h > 0) __syncthreads();                       // everyone is done reading the old tile
-    const bool direct = ((V | tl) & 3) == 0;          // rows and tiles are 16-byte aligned
-    if (direct) {
-      // global memory -> LDS directly, 16 bytes per lane: every load of the tile is in flight at
-      // once and none passes through a register (a wave's instruction fills 1 KiB in lane order,
-      // which is the table's own order)
-      const float4 *s4 = reinterpret_cast<const float4 *>(src + t0);
-      const int32_t n4 = tl >> 2;
-      for (int32_t k0 = wave * kWave; k0 < n4; k0 += kGatherThreads)
-        if (k0 + lane < n4)
-          __builtin_amdgcn_global_load_lds(
-              (const __attribute__((address_space(1))) void *) (s4 + k0 + lane),
-              (__attribute__((address_space(3))) void *) (tab + 4 * k0), 16, 0, 0);
-    } else {
-      // rows that do not start on 16 bytes: the same with 4 bytes per lane
-      for (int32_t k0 = wave * kWave; k0 < tl; k0 += kGatherThreads)
-        if (k0 + lane < tl)
-          __builtin_amdgcn_global_load_lds(
-              (const __attribute__((address_space(1))) void *) (src + t0 + k0 + lane),
-              (__attribute__((address_space(3))) void *) (tab + k0), 4, 0, 0);
-    }
+    stage_tile(tab, src + t0, tl, threadIdx.x);
     if (threadIdx.x < kBanks) tab[tile_len + threadIdx.x] = 0.f;   // the padding slots
-    // The wave walks its blocks one after the other, reading their steps through a ring of kRing
-    // registers sets that is always kRing steps ahead: slot i takes the steps i, i + kRing, ... of
-    // a block, and once the block has none left, step i of the wave's next block (in the last
-    // block of a tile: of the next tile's first), so the stream of slots never waits at a block's
-    // or a tile's end.  The next tile's descriptors and, in the first tile, the first steps are asked
-    // for while the tile is still on its way into LDS.
-    load_desc(h + 1, nsteps, noffs);
-    uint32_t succ_off[kMaxBlocksPerWave], succ_last[kMaxBlocksPerWave];   // what follows each block
-    uint32_t first_off = 0, first_steps = 0;          // the first block of this tile that has steps
-    {
-      uint32_t so = 0, sn = 0;
-#pragma unroll
-      for (int q = kMaxBlocksPerWave - 1; q >= 0; --q)
-        if (nsteps[q] > 0) { so = noffs[q]; sn = nsteps[q]; }
-      follows = sn > 0;
-#pragma unroll
-      for (int q = kMaxBlocksPerWave - 1; q >= 0; --q) {
-        // nothing follows: the block's own first steps are read again, and not used
-        succ_off[q] = sn > 0 ? so : offs[q];
-        succ_last[q] = (sn > 0 ? sn : max(steps[q], 1u)) - 1;
-        if (steps[q] > 0) { so = first_off = offs[q]; sn = first_steps = steps[q]; }
-      }
-    }
-    // a scalar base and the lane as the only vector part: no address arithmetic per load
-    auto load = [&](GatherStep<WEIGHTED> &slot, uint32_t unit) {
-      const uint32_t u = __builtin_amdgcn_readfirstlane(unit);
-      slot.load(data + u, wdata + 2 * (size_t) u, lane);
-    };
-    if (!filled && first_steps > 0) {
-#pragma unroll
-      for (int i = 0; i < kRing; ++i) load(ring[i], first_off + min((uint32_t) i, first_steps - 1) * kWave);
-    }
-    if (first_steps > 0) filled = follows;
+    // The next tile's descriptors and, in the first tile, the first steps are asked for while the
+    // tile is still on its way into LDS.
+    load_desc(h + 1 < ntiles ? dsc + (size_t) (h + 1) * bpc * 2 : nullptr, bpc, wave, nsteps, noffs);
+    stream.begin(nsteps, noffs, data, wdata, lane);
     __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
+    stream.walk(tab, data, wdata, lane, acc);
 #pragma unroll
-    for (int q = 0; q < kMaxBlocksPerWave; ++q) {
-      const uint32_t n = steps[q];                    // uniform over the wave, as everything below
-      float *a = acc + q * kLaneGroups;
-      auto next = [&](int i) { return succ_off[q] + min((uint32_t) i, succ_last[q]) * kWave; };
-      if (n >= (uint32_t) kRing) {
-        uint32_t t = 0;
-        for (; t + kRing <= n; t += kRing) {
-#pragma unroll
-          for (int i = 0; i < kRing; ++i) {
-            ring[i].apply(tab, a);
-            const uint32_t k = t + i + kRing;
-            load(ring[i], k < n ? offs[q] + k * kWave : next(i));
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < kRing - 1; ++i) {
-          if (t + i < n) {
-            ring[i].apply(tab, a);
-            load(ring[i], next(i));
-          }
-        }
-      } else if (n > 0) {
-        // a short block: the slots it has no step for pass to its successor first
-#pragma unroll
-        for (int i = 1; i < kRing; ++i)
-          if ((uint32_t) i >= n) load(ring[i], next(i));
-#pragma unroll
-        for (int i = 0; i < kRing - 1; ++i) {
-          if ((uint32_t) i < n) {
-            ring[i].apply(tab, a);
-            load(ring[i], next(i));
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < kMaxBlocksPerWave; ++q) { steps[q] = nsteps[q]; offs[q] = noffs[q]; }
+    for (int q = 0; q < kMaxBlocksPerWave; ++q) { stream.steps[q] = nsteps[q]; stream.offs[q] = noffs[q]; }
   }
 
   // back into group order through LDS, then coalesced stores
@@ -1615,46 +1776,14 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     if (where[j] != 0xFFFFu) tab[where[j]] = acc[j];
   __syncthreads();
   if constexpr (!CSUM) {
-    float *dst = out + (int64_t) r * G + g0;
-    if ((((uintptr_t) dst | (uintptr_t) ng) & 15) == 0 && (ng & 3) == 0) {      // 16 bytes at a time
-      for (int32_t i = 4 * threadIdx.x; i < ng; i += 4 * kGatherThreads)
-        *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(tab + i);
-    } else {
-      for (int32_t i = threadIdx.x; i < ng; i += kGatherThreads) dst[i] = tab[i];
-    }
+    store_sums(out + (int64_t) r * G + g0, tab, ng);
   } else {
     // The caller draws one group by inverse CDF over max(0, sum).  It does not need the sums
-    // themselves for that, only where the running total crosses its threshold: the workgroup
-    // leaves the totals of runs of kRunGroups consecutive groups (fp64, fixed order) and the
-    // chunk's total; the few sums of the run that holds the crossing are formed again by the
-    // caller.  Four neighbouring lanes cover one run, four groups each.
-    const float4 *tab4 = reinterpret_cast<const float4 *>(tab);
-    double *rp = runs + ((int64_t) r * nchunks + chunk) * (chunk_groups / kRunGroups);
-    double part = 0.0;
-#pragma unroll
-    for (int j = 0; j < kMaxChunkGroups / (4 * kGatherThreads); ++j) {
-      const int32_t i4 = threadIdx.x + j * kGatherThreads;
-      const int32_t g = 4 * i4;
-      double s = 0.0;
-      if (g < ng) {
-        const float4 v = tab4[i4];
-        s = ((double) fmaxf(v.x, 0.f) + (g + 1 < ng ? (double) fmaxf(v.y, 0.f) : 0.0)) +
-            ((g + 2 < ng ? (double) fmaxf(v.z, 0.f) : 0.0) + (g + 3 < ng ? (double) fmaxf(v.w, 0.f) : 0.0));
-      }
-      s = subwave_sum<4>(s);
-      if ((lane & 3) == 0 && g < ng) {
-        rp[i4 >> 2] = s;
-        part += s;
-      }
-    }
-    part = subwave_sum<64>(part);
-    if (lane == kWave - 1) wsum[wave] = part;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int w = 0; w < kGatherWaves; ++w) t += wsum[w];
-      csum[(int64_t) r * nchunks + chunk] = t;
-    }
+    // themselves for that, only where the running total crosses its threshold: the totals of runs of
+    // kRunGroups consecutive groups and the chunk's; the few sums of the run that holds the
+    // crossing are formed again by the caller.
+    run_totals(tab, ng, runs + ((int64_t) r * nchunks + chunk) * (chunk_groups / kRunGroups),
+               csum + (int64_t) r * nchunks + chunk);
   }
 }
 
@@ -1760,47 +1889,49 @@ hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int6
   return hipGetLastError();
 }
 
-template <int W>
-static void gather_dispatch(bool clamp, dim3 grid, hipStream_t stream, int32_t V, int32_t G,
-                            int32_t nrows, int32_t nchunks, int32_t gpc, int32_t ntiles,
-                            int32_t tile_len, const int32_t *row_ptr, const int32_t *members,
-                            const float *weights, const float *table, float *out) {
-  if (clamp)
-    gather_kernel<W, true><<<grid, kGatherThreads, 0, stream>>>(
-        V, G, nrows, nchunks, gpc, ntiles, tile_len, row_ptr, members, weights, table, out);
-  else
-    gather_kernel<W, false><<<grid, kGatherThreads, 0, stream>>>(
-        V, G, nrows, nchunks, gpc, ntiles, tile_len, row_ptr, members, weights, table, out);
+CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max_chunks) {
+  CsrShape p;
+  // Lanes per group: enough for a group of mean size in one trip of four entries a lane, 2 to 16
+  // (fewer lanes leave long groups to one lane's loop, more leave lanes idle).
+  const double mean = (double) nnz / (double) G;
+  p.width = 2;
+  while (p.width < 16 && 4 * p.width < mean) p.width *= 2;
+  // Chunks per row: a workgroup for every compute unit, each with at least one pass of groups, at most
+  // kMaxChunkGroups and, where that allows it, at most max_chunks.
+  const int64_t pass = 4 * (kGatherThreads / p.width);
+  int64_t nchunks = std::min<int64_t>({(256 + nrows - 1) / nrows, max_chunks, (G + pass - 1) / pass});
+  nchunks = std::max<int64_t>(nchunks, ((int64_t) G + kMaxChunkGroups - 1) / kMaxChunkGroups);
+  int64_t gpc = (G + nchunks - 1) / nchunks;
+  gpc = (gpc + kRunGroups - 1) / kRunGroups * kRunGroups;
+  p.chunk_groups = (int32_t) gpc;
+  p.nchunks = (int32_t) ((G + gpc - 1) / gpc);
+  // LDS: the chunk's sums, then as much of the table row as fits (a tile and its zero slot)
+  const int32_t room = (kTileMax - p.chunk_groups - 64) / 64 * 64;
+  p.ntiles = (V + room - 1) / room;
+  p.tile_len = std::min(room, ((V + p.ntiles - 1) / p.ntiles + 63) / 64 * 64);
+  return p;
 }
 
-hipError_t launch_gather(const pcg_groups &g, int32_t nrows, bool clamp, const float *table,
-                         float *out, hipStream_t stream) {
+hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, const float *table, float *out,
+                         double *csum, int64_t csum_stride, double *runs, hipStream_t stream) {
   if (nrows == 0) return hipSuccess;
-  // lanes per group: the smallest power of two >= the mean group size, within [4, 64]
-  const double mean = (double) g.nnz / (double) g.G;
-  int W = 4;
-  while (W < 64 && W < mean) W *= 2;
-  const int nsub = kGatherThreads / W;
-  // enough chunks per row to give every CU a workgroup, but no chunk below one pass
-  int32_t nchunks = (256 + nrows - 1) / nrows;
-  const int32_t max_chunks = (g.G + nsub - 1) / nsub;
-  if (nchunks > max_chunks) nchunks = max_chunks;
-  if (nchunks < 1) nchunks = 1;
-  int32_t gpc = (g.G + nchunks - 1) / nchunks;
-  gpc = (gpc + nsub - 1) / nsub * nsub;
-  nchunks = (g.G + gpc - 1) / gpc;
-  const int32_t ntiles = (g.V + kTileMax - 1) / kTileMax;
-  int32_t tile_len = (g.V + ntiles - 1) / ntiles;
-  tile_len = (tile_len + 63) / 64 * 64;
-  if (tile_len > kTileMax) tile_len = kTileMax;
   const int32_t rows8 = (nrows + 7) / 8;
-  const dim3 grid((unsigned) (8 * rows8 * nchunks));
-  switch (W) {
-    case 4: gather_dispatch<4>(clamp, grid, stream, g.V, g.G, nrows, nchunks, gpc, ntiles, tile_len, g.row_ptr, g.members, g.weights, table, out); break;
-    case 8: gather_dispatch<8>(clamp, grid, stream, g.V, g.G, nrows, nchunks, gpc, ntiles, tile_len, g.row_ptr, g.members, g.weights, table, out); break;
-    case 16: gather_dispatch<16>(clamp, grid, stream, g.V, g.G, nrows, nchunks, gpc, ntiles, tile_len, g.row_ptr, g.members, g.weights, table, out); break;
-    case 32: gather_dispatch<32>(clamp, grid, stream, g.V, g.G, nrows, nchunks, gpc, ntiles, tile_len, g.row_ptr, g.members, g.weights, table, out); break;
-    default: gather_dispatch<64>(clamp, grid, stream, g.V, g.G, nrows, nchunks, gpc, ntiles, tile_len, g.row_ptr, g.members, g.weights, table, out); break;
+  const dim3 grid((unsigned) (8 * rows8 * p.nchunks));
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, p.nchunks, p.chunk_groups, p.ntiles, p.tile_len,
+                                                (int32_t) g.nnz, g.row_ptr, g.members, g.weights, table, out,
+                                                csum, csum_stride, runs);
+  };
+  auto pick = [&](auto width) {
+    constexpr int W = decltype(width)::value;
+    if (g.weights) { if (csum) launch(gather_kernel<W, true, true>); else launch(gather_kernel<W, false, true>); }
+    else { if (csum) launch(gather_kernel<W, true, false>); else launch(gather_kernel<W, false, false>); }
+  };
+  switch (p.width) {
+    case 2: pick(std::integral_constant<int, 2>{}); break;
+    case 4: pick(std::integral_constant<int, 4>{}); break;
+    case 8: pick(std::integral_constant<int, 8>{}); break;
+    default: pick(std::integral_constant<int, 16>{}); break;
   }
   return hipGetLastError();
 }
@@ -1834,12 +1965,12 @@ hipError_t launch_gather_prepared(const pcg_groups &g, int32_t nrows, const floa
 }
 
 hipError_t launch_finalize(const FinalizeArgs &fa, bool bf16, const pcg_groups &g, int32_t B,
-                           const double *csum, const double *runs, int32_t nchunks,
+                           const double *csum, int64_t csum_stride, const double *runs, int32_t nchunks,
                            int32_t chunk_groups, hipStream_t stream) {
-  if (bf16)
-    finalize_kernel<true><<<B, kFinalThreads, 0, stream>>>(fa, g.V, g.G, csum, runs, nchunks, chunk_groups);
-  else
-    finalize_kernel<false><<<B, kFinalThreads, 0, stream>>>(fa, g.V, g.G, csum, runs, nchunks, chunk_groups);
+  auto launch = [&](auto kernel) {
+    kernel<<<B, kFinalThreads, 0, stream>>>(fa, g.V, g.G, csum, csum_stride, runs, nchunks, chunk_groups);
+  };
+  if (bf16) launch(finalize_kernel<true>); else launch(finalize_kernel<false>);
   return hipGetLastError();
 }
 

@@ -75,3 +75,13 @@ def test_ragged_rows(V, off, dtype):
                                             (90002, 9000, 2, 12288), (81400, 40000, 5, 16384)])
 def test_prepared_gather_blocks(V, G, size, chunk, weighted):
     check_step(V, G, size, 2, 2, "bf16", chunk_groups=chunk, weighted=weighted, thinning=False)
+
+
+# the CSR gather: fewer than four entries, every number of lanes per group, groups longer than one trip
+# and empty ones, one to four tiles, more chunks than the chunk totals have room for, few and many rows
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("V,G,size,B", [(3, 1, 3, 1), (5, 1, 5, 3), (700, 900, 6, 1), (700, 900, 14, 300),
+                                        (3000, 2500, 29, 5), (9000, 400, 90, 2), (20000, 40000, 8, 2),
+                                        (45003, 20001, 17, 1), (81000, 300, 700, 3), (100003, 3000, 60, 12)])
+def test_csr_gather(V, G, size, B, weighted):
+    check_step(V, G, size, B, 2, "bf16", layout="csr", weighted=weighted, thinning=False)
