@@ -472,7 +472,8 @@ int pcg_groups_prepare_weights_host(int32_t V, int32_t G, const int32_t *row_ptr
  * unused entries 0), the number of calls (HOST) and returns PCG_OK.  At most `max_calls`
  * calls are recorded; later ones run unrecorded.  Stage names: pcg_stage_name(i).  The stage
  * "event_overhead" is an empty event pair recorded at the start of each call: the time an
- * event pair adds, which is included in every other stage's figure.
+ * event pair adds, which is included in every other stage's figure.  A step that is small enough
+ * to run as one kernel is recorded under "gather"; its other stages then read as event_overhead.
  * Not thread-safe; one profile at a time.
  */
 int pcg_profile_begin(int32_t max_calls);

@@ -369,6 +369,20 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
 
   StageTimer tm(stream);
   hipError_t e;
+  if (small_step_fits(*groups, B, K)) {
+    AcceptArgs small = aa;
+    small.parts = nullptr;              // everything between the phases stays in LDS
+    small.probes = nullptr;
+    small.rowstat = nullptr;
+    // one kernel: recorded under gather; the stages it has absorbed are empty event pairs
+    for (Stage st : {kStageStats, kStageAccept}) { tm.begin(st); tm.end(st); }
+    tm.begin(kStageGather);
+    if ((e = launch_small_step(small, fa, pa, *groups, bf16, B, stream)) != hipSuccess) return hip_fail(e);
+    tm.end(kStageGather);
+    tm.begin(kStageFinalize);
+    tm.end(kStageFinalize);
+    return PCG_OK;
+  }
   tm.begin(kStageStats);
   // streaming pass: only the rejected position's two rows (2 of 2K+1) are read again
   if ((e = launch_row_stats(rs, bf16, V, rows, f.c, true, parts, stream, &pa)) != hipSuccess) return hip_fail(e);

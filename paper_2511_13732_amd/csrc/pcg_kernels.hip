@@ -15,6 +15,8 @@
 //                 written.
 //   finalize      per sequence: the chunk and the run that hold u * total, the run's 16 sums
 //                 formed again, the group by inverse CDF, then the token inside it (Eq. 10)
+// A step that is small, or has many sequences of moderate size, runs as one kernel instead
+// (small_step): one workgroup per sequence does all of the above with everything in LDS.
 // pcg_group_probs runs row_stats, a weights kernel (q(t) / N(t)) and the same gather;
 // pcg_verify_thinning runs row_stats and accept_thin; pcg_propose runs row_stats and propose.
 #include "pcg_kernels.h"
@@ -132,48 +134,63 @@ __device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t b, int3
   }
 }
 
-// The statistics of elements e0 .. e0 + kPartElems - 1 of a row by one wave; valid in its last lane.
+// A wave's share of a row on its way: elements e0 .. e0 + kPartElems - 1.
 // WIDE: a row holds at least one 16-byte piece (V >= 8 bf16 or 4 fp32 logits).
+// 16-byte loads, all issued before the first use; each instruction covers 1 KiB of the row.  Rows
+// need no alignment (see load16).  In the last part of a row, pieces that would cross its end are
+// read where the row's last 16 bytes lie instead, and what belongs to the piece before (or to no
+// piece) is masked: no branch, every load in flight, nothing read past the row.  (Element by element
+// such parts took 12.9 us where whole parts take 3.7: V = 20 011, 75 rows.)
 template <bool BF16, bool WIDE, bool STREAM>
-__device__ __forceinline__ StatPart part_stats(const void *rowp, int32_t e0, int32_t V, float c, int lane) {
-  // 16-byte loads, all issued before the first use; each instruction covers 1 KiB of the row.
-  // Rows need no alignment (see load16).  In the last part of a row, pieces that would cross its
-  // end are read where the row's last 16 bytes lie instead, and what belongs to the piece before
-  // (or to no piece) is masked: no branch, every load in flight, nothing read past the row.
-  // (Element by element such parts took 12.9 us where whole parts take 3.7: V = 20 011, 75 rows.)
-  float x[32];
-  if constexpr (WIDE) {
-    constexpr int per = kPer16<BF16>, nv = 32 / per;
-    const char *src = reinterpret_cast<const char *>(rowp);
-    constexpr int esz = BF16 ? 2 : 4;
-    u32x4 w[nv];
-    if (e0 + kPartElems <= V) {
-      src += (int64_t) e0 * esz;
+struct RowPart {
+  static constexpr int per = kPer16<BF16>, nv = 32 / per;
+  u32x4 w[WIDE ? nv : 1];
+  float e[WIDE ? 1 : 32];
+
+  __device__ __forceinline__ void load(const void *rowp, int32_t e0, int32_t V, int lane) {
+    if constexpr (WIDE) {
+      const char *src = reinterpret_cast<const char *>(rowp);
+      constexpr int esz = BF16 ? 2 : 4;
+      if (e0 + kPartElems <= V) {
+        src += (int64_t) e0 * esz;
 #pragma unroll
-      for (int j = 0; j < nv; ++j) w[j] = load16<STREAM>(src + (j * kWave + lane) * 16);
+        for (int j = 0; j < nv; ++j) w[j] = load16<STREAM>(src + (j * kWave + lane) * 16);
+      } else {
 #pragma unroll
-      for (int j = 0; j < nv; ++j) unpack16<BF16>(w[j], x + j * per);
+        for (int j = 0; j < nv; ++j)
+          w[j] = load16<STREAM>(src + (int64_t) min(e0 + (j * kWave + lane) * per, V - per) * esz);
+      }
     } else {
 #pragma unroll
-      for (int j = 0; j < nv; ++j)
-        w[j] = load16<STREAM>(src + (int64_t) min(e0 + (j * kWave + lane) * per, V - per) * esz);
-#pragma unroll
-      for (int j = 0; j < nv; ++j) {
-        unpack16<BF16>(w[j], x + j * per);
-        const int32_t over = e0 + (j * kWave + lane) * per - (V - per);   // elements to mask, if any
-#pragma unroll
-        for (int k = 0; k < per; ++k)
-          if (k < over) x[j * per + k] = -INFINITY;
+      for (int j = 0; j < 32; ++j) {
+        const int32_t at = e0 + j * kWave + lane;
+        e[j] = (at < V) ? logit_at<BF16>(rowp, at) : -INFINITY;
       }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const int32_t e = e0 + j * kWave + lane;
-      x[j] = (e < V) ? logit_at<BF16>(rowp, e) : -INFINITY;
     }
   }
 
+  __device__ __forceinline__ void get(float (&x)[32], int32_t e0, int32_t V, int lane) const {
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int j = 0; j < nv; ++j) unpack16<BF16>(w[j], x + j * per);
+      if (e0 + kPartElems > V) {
+#pragma unroll
+        for (int j = 0; j < nv; ++j) {
+          const int32_t over = e0 + (j * kWave + lane) * per - (V - per);   // elements to mask, if any
+#pragma unroll
+          for (int k = 0; k < per; ++k)
+            if (k < over) x[j * per + k] = -INFINITY;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 32; ++j) x[j] = e[j];
+    }
+  }
+};
+
+// The statistics of a wave's 32 logits per lane; valid in its last lane.
+__device__ __forceinline__ StatPart part_stats(const float (&x)[32], float c) {
   float m0 = fmaxf(x[0], x[1]), m1 = fmaxf(x[2], x[3]);
 #pragma unroll
   for (int j = 4; j < 32; j += 4) {
@@ -230,8 +247,20 @@ __global__ __launch_bounds__(kStatsWaves *kWave) void row_stats_kernel(RowSet rs
   const int64_t row = slot - probe_slots;
   if (part >= nparts || row >= nrows) return;   // whole wave leaves together
   const void *rowp = row_base(rs, row, BF16);
-  const StatPart sp = part_stats<BF16, WIDE, STREAM>(rowp, part * kPartElems, V, c, lane);
+  RowPart<BF16, WIDE, STREAM> raw;
+  float x[32];
+  raw.load(rowp, part * kPartElems, V, lane);
+  raw.get(x, part * kPartElems, V, lane);
+  const StatPart sp = part_stats(x, c);
   if (lane == kWave - 1) parts[row * nparts + part] = sp;
+}
+
+// Meets the other waves of the workgroup once this wave's LDS accesses are done, without the fence of
+// __syncthreads(), which would also wait for every load still in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // Merge the parts of one row inside a wave: every lane returns the row's (M, Z).
@@ -372,6 +401,16 @@ __device__ __forceinline__ RowStat merge_row16(const StatPart *rp, int32_t npart
 // kAcceptThreads.  On return sh.istar, sh.st_t and sh.st_d are valid for every thread; with
 // `writer` the sequence's outputs and counters are written, and its row statistics if a.rowstat is
 // given.  probes: the sequence's K probes; parts_t, parts_d: the parts of its target and draft rows.
+// FETCHED: the proposals and their accept uniforms are in sh already (accept_fetch).
+__device__ __forceinline__ void accept_fetch(AcceptShared &sh, const AcceptArgs &a, int b, int lane) {
+  for (int i = lane; i < a.K; i += kWave) {
+    sh.pgrp[i] = a.prop_groups[(int64_t) b * a.K + i];
+    sh.ptok[i] = a.prop_tokens[(int64_t) b * a.K + i];
+    sh.uacc[i] = philox_uniforms(a.seed, a.offset, (uint32_t) b, (uint32_t) i).acc;
+  }
+}
+
+template <bool FETCHED>
 __device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs &a, int b, bool writer,
                                              const Probe *probes, const StatPart *parts_t,
                                              const StatPart *parts_d) {
@@ -386,10 +425,8 @@ __device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs 
       const Probe p = probes[i];
       sh.Tp[i] = p.Tp; sh.Dp[i] = p.Dp; sh.Tref[i] = p.Tref; sh.Dref[i] = p.Dref;
       sh.bad[i] = p.bad;
-      sh.pgrp[i] = a.prop_groups[(int64_t) b * K + i];
-      sh.ptok[i] = a.prop_tokens[(int64_t) b * K + i];
-      sh.uacc[i] = philox_uniforms(a.seed, a.offset, (uint32_t) b, (uint32_t) i).acc;
     }
+    if constexpr (!FETCHED) accept_fetch(sh, a, b, lane);
   } else {
     // row statistics of this sequence's 2K+1 rows, four rows per wave at a time
     const int sub = lane & 15;
@@ -404,7 +441,7 @@ __device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs 
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
 
   // Both chains have met.  One wave, one position per lane (K <= 64): normalise the probe,
   // take the accept test, and find the first rejection with a ballot; the draft token stands
@@ -448,12 +485,12 @@ __device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs 
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 // The same on the probes and parts that the statistics pass left in memory.
 __device__ __forceinline__ void accept_phase_stored(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
-  accept_phase(sh, a, b, writer, a.probes + (int64_t) b * a.K,
+  accept_phase<false>(sh, a, b, writer, a.probes + (int64_t) b * a.K,
                a.parts + (int64_t) b * (a.K + 1) * a.nparts,
                a.parts + (a.rs.nrows0 + (int64_t) b * a.K) * a.nparts);
 }
@@ -1607,6 +1644,15 @@ struct GatherStep<true> {
   }
 };
 
+// The prepared layout as the kernels see it.
+struct PreparedView {
+  const uint32_t *desc;
+  const uint16_t *perm;
+  const uint4 *data;
+  const float4 *wdata;
+  int32_t nchunks, chunk_groups, ntiles, tile_len, blocks_per_chunk;
+};
+
 // First unit and number of steps of a wave's blocks in one tile of one chunk (dsc; NULL: none).
 __device__ __forceinline__ void load_desc(const uint32_t *dsc, int bpc, int wave,
                                           uint32_t (&steps)[kMaxBlocksPerWave],
@@ -1715,11 +1761,13 @@ struct SlotStream {
 
 template <bool CSUM, bool WEIGHTED>
 __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
-    int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t chunk_groups, int32_t ntiles,
-    int32_t tile_len, int32_t bpc, const uint32_t *__restrict__ desc,
-    const uint16_t *__restrict__ perm, const uint4 *__restrict__ data,
-    const float4 *__restrict__ wdata, const float *__restrict__ table, float *__restrict__ out,
-    double *__restrict__ csum, double *__restrict__ runs) {
+    int32_t V, int32_t G, int32_t nrows, PreparedView p, const float *__restrict__ table,
+    float *__restrict__ out, double *__restrict__ csum, double *__restrict__ runs) {
+  const int32_t nchunks = p.nchunks, chunk_groups = p.chunk_groups, ntiles = p.ntiles, tile_len = p.tile_len;
+  const int32_t bpc = p.blocks_per_chunk;
+  const uint4 *__restrict__ data = p.data;
+  const float4 *__restrict__ wdata = p.wdata;
+  const uint16_t *__restrict__ perm = p.perm;
   __shared__ __attribute__((aligned(16))) float tab[kTileMax];
   const int xcd = blockIdx.x & 7;
   const int y = blockIdx.x >> 3;
@@ -1747,7 +1795,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     }
   }
 
-  const uint32_t *dsc = desc + (size_t) chunk * ntiles * bpc * 2;
+  const uint32_t *dsc = p.desc + (size_t) chunk * ntiles * bpc * 2;
   uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];      // the next tile's blocks
   SlotStream<WEIGHTED> stream;
   load_desc(dsc, bpc, wave, stream.steps, stream.offs);
@@ -1755,7 +1803,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
   for (int h = 0; h < ntiles; ++h) {
     const int32_t t0 = h * tile_len;
     const int32_t tl = min(tile_len, V - t0);
-    if (h > 0) __syncthreads();                       // everyone is done reading the old tile
+    if (h > 0) lds_barrier();                         // everyone is done reading the old tile
     stage_tile(tab, src + t0, tl, threadIdx.x);
     if (threadIdx.x < kBanks) tab[tile_len + threadIdx.x] = 0.f;   // the padding slots
     // The next tile's descriptors and, in the first tile, the first steps are asked for while the
@@ -1785,6 +1833,225 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     run_totals(tab, ng, runs + ((int64_t) r * nchunks + chunk) * (chunk_groups / kRunGroups),
                csum + (int64_t) r * nchunks + chunk);
   }
+}
+
+// =============================================================================================
+// small step: one workgroup runs a sequence's whole step, the statistics of its 2K + 1 rows, the
+// accept scan, the table, the sums of all groups and the draws, without leaving the compute unit.
+// Four launches cost about 5 us each whatever the size (the launch, a trip to memory for what the
+// kernel before has written, a drain); here the parts, the probes, the table and the sums pass
+// through LDS, and what is left is the chain of loads proposal -> members -> logits and group ->
+// members -> logits.  Bound by latency: at V = 4096, K = 8 the rows and probes take 7.7 us (34 parts
+// and 8 probes on 16 waves), the accept scan 1.7, the table 1.3, the sums 2.8, the draws 3.2; the whole
+// call 23.8 -> 19.8 us at B = 8, and 22.8 -> 13.5 at V = 1024, K = 4, B = 1.
+// =============================================================================================
+
+constexpr int kSmallTokens = 16384;    // table entries in LDS: 64 KB
+constexpr int kSmallGroups = 16384;    // sums in LDS: 64 KB
+constexpr int kSmallParts = 512;       // row parts (2048 logits each) of a sequence: 8 KB
+
+// Where the sums come from.
+constexpr int kSumsPrepared = 0, kSumsPreparedWeighted = 1, kSumsCsr = 2, kSumsCsrWeighted = 3;
+
+// Inverse CDF over max(0, sums[0 .. n)) (LDS, 16-byte aligned, n <= kSmallGroups) by a workgroup of
+// 1024 threads, four neighbouring groups a thread and turn: first index whose running sum exceeds
+// u * total.  All threads get the result.
+__device__ CdfPick pick_group(const float *sums, int32_t n, double u) {
+  constexpr int kTurns = kSmallGroups / (4 * kGatherThreads);
+  static_assert(kTurns * kGatherWaves <= kWave, "one lane per total");
+  __shared__ double wtot[kTurns * kGatherWaves];
+  __shared__ CdfPick res;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+  const int turns = (n + 4 * kGatherThreads - 1) / (4 * kGatherThreads);     // uniform
+  double mine[kTurns], inc[kTurns];
+#pragma unroll
+  for (int k = 0; k < kTurns; ++k) {
+    mine[k] = inc[k] = 0.0;
+    if (k < turns) {
+      const int32_t g = 4 * (k * kGatherThreads + tid);
+      if (g < n) {
+        const float4 v = *reinterpret_cast<const float4 *>(sums + g);
+        mine[k] = ((double) fmaxf(v.x, 0.f) + (g + 1 < n ? (double) fmaxf(v.y, 0.f) : 0.0)) +
+                  ((g + 2 < n ? (double) fmaxf(v.z, 0.f) : 0.0) + (g + 3 < n ? (double) fmaxf(v.w, 0.f) : 0.0));
+      }
+      inc[k] = wave_scan(mine[k]);
+    }
+    if (lane == kWave - 1) wtot[k * kGatherWaves + wave] = inc[k];
+  }
+  __syncthreads();
+  // every wave finds the wave and turn that hold the crossing; rounding at the top end may leave
+  // none: the last that has mass
+  const double tot = lane < kTurns * kGatherWaves ? wtot[lane] : 0.0;
+  const double upto = wave_scan(tot);
+  const double total = read_lane(upto, kWave - 1), goal = u * total;
+  const unsigned long long pos = __ballot(tot > 0.0), hit = __ballot(tot > 0.0 && upto > goal);
+  if (!pos) {
+    CdfPick r;
+    r.index = -1; r.total = total; r.lo = r.hi = 0.0;
+    return r;                                       // the same in every thread
+  }
+  const int at = hit ? __ffsll((long long) hit) - 1 : 63 - __clzll((long long) pos);
+  if (wave == at % kGatherWaves) {                  // uniform over the wave
+    const double before = read_lane(upto, at) - read_lane(tot, at);
+    double my_mine = 0.0, my_inc = 0.0;
+#pragma unroll
+    for (int k = 0; k < kTurns; ++k)
+      if (k == at / kGatherWaves) { my_mine = mine[k]; my_inc = inc[k]; }
+    const unsigned long long has = __ballot(my_mine > 0.0);
+    const unsigned long long over = hit ? __ballot(my_mine > 0.0 && before + my_inc > goal) : 0;
+    const int l = over ? __ffsll((long long) over) - 1 : 63 - __clzll((long long) has);
+    if (lane == l) {                                // walks its four groups
+      const int32_t g0 = 4 * (at / kGatherWaves * kGatherThreads + tid);
+      double cum = before + (my_inc - my_mine), last_v = 0.0;
+      int32_t pick = -1;
+      bool done = false;
+      for (int j = 0; j < 4; ++j) {
+        const double v = g0 + j < n ? (double) fmaxf(sums[g0 + j], 0.f) : 0.0;
+        if (!done && v > 0.0) {
+          pick = g0 + j;
+          last_v = v;
+          cum += v;
+          done = cum > goal;
+        }
+      }
+      res.index = pick;
+      res.total = total;
+      res.hi = hit ? cum : total;
+      res.lo = res.hi - last_v;
+    }
+  }
+  __syncthreads();
+  return res;
+}
+
+template <bool BF16, int SUMS>
+__global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a, FinalizeArgs fa, ProbeArgs pa,
+                                                                    PreparedView p, int32_t nnz) {
+  static_assert(kAcceptThreads == kGatherThreads, "one workgroup plays both parts");
+  __shared__ AcceptShared sh;
+  __shared__ StatPart parts[kSmallParts];
+  __shared__ Probe probes[PCG_MAX_K];
+  __shared__ __attribute__((aligned(16))) float tab[kSmallTokens + kBanks];
+  __shared__ __attribute__((aligned(16))) float sums[kSmallGroups];
+  __shared__ int next_item;
+  constexpr bool kWeighted = SUMS == kSumsPreparedWeighted || SUMS == kSumsCsrWeighted;
+  const int b = blockIdx.x;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const RowSet &rs = a.rs;
+  const int32_t V = a.V, G = a.G, K = a.K;
+
+  // the first multiplicities and the first blocks of slots do not depend on any row
+  const int32_t first = threadIdx.x * kTokensPerThread;
+  float m[8];
+  if (first < V) load8_mult<true>(kWeighted ? nullptr : a.mult, slice_start<true>(first, V), V, m);
+  SlotStream<kWeighted> stream;
+  if constexpr (SUMS <= kSumsPreparedWeighted) load_desc(p.desc, p.blocks_per_chunk, wave, stream.steps, stream.offs);
+
+  // Row parts and probes, handed to whichever wave is free: the probes, chains of dependent loads,
+  // first; a wave asks for its next part before it works on the one that has come.
+  if (threadIdx.x == 0) next_item = kGatherWaves;
+  lds_barrier();
+  if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
+  const int32_t nitems = K + (2 * K + 1) * a.nparts;
+  auto take = [&]() {
+    int32_t n = 0;
+    if (lane == 0) n = atomicAdd(&next_item, 1);
+    return (int32_t) __builtin_amdgcn_readfirstlane(n);
+  };
+  int32_t item = wave;
+  while (item < K) {
+    probe_row<BF16>(rs, pa, b, item, a.c, lane, probes + item);
+    item = take();
+  }
+  RowPart<BF16, true, false> raw;       // cached: the decision rows are read again
+  auto ask = [&](int32_t it) {
+    const int32_t r = (it - K) / a.nparts, part = (it - K) % a.nparts;
+    const int64_t row = r <= K ? (int64_t) b * (K + 1) + r : rs.nrows0 + (int64_t) b * K + (r - K - 1);
+    raw.load(row_base(rs, row, BF16), part * kPartElems, V, lane);
+  };
+  if (item < nitems) ask(item);
+  while (item < nitems) {
+    float x[32];
+    raw.get(x, ((item - K) % a.nparts) * kPartElems, V, lane);
+    const int32_t next = take();
+    if (next < nitems) ask(next);
+    const StatPart sp = part_stats(x, a.c);
+    if (lane == kWave - 1) parts[item - K] = sp;
+    item = next;
+  }
+  // the first chunk's slots and the places of its sums: on their way through the accept scan
+  uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];
+  uint16_t where[kMaxAcc];
+  auto ask_chunk = [&](int32_t chunk) {
+    load_desc(chunk + 1 < p.nchunks ? p.desc + (size_t) (chunk + 1) * p.blocks_per_chunk * 2 : nullptr,
+              p.blocks_per_chunk, wave, nsteps, noffs);
+    stream.begin(nsteps, noffs, p.data, p.wdata, lane);
+#pragma unroll
+    for (int j = 0; j < kMaxAcc; ++j) {
+      const int bl = block_of(j / kLaneGroups, wave);
+      where[j] = bl < p.blocks_per_chunk
+                     ? p.perm[((size_t) chunk * p.blocks_per_chunk + bl) * kBlockGroups + (j % kLaneGroups) * kWave + lane]
+                     : (uint16_t) 0xFFFFu;
+    }
+  };
+  if constexpr (SUMS <= kSumsPreparedWeighted) ask_chunk(0);
+  lds_barrier();
+  accept_phase<true>(sh, a, b, true, probes, parts, parts + (K + 1) * a.nparts);
+
+  // the table on the decision row, straight into LDS
+  const int32_t istar = sh.istar;
+  const bool rejected = istar < K;
+  const void *trow = row_base(rs, (int64_t) b * (K + 1) + istar, BF16);
+  const void *drow = row_base(rs, rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0), BF16);
+  const RowStat st = sh.st_t[istar];
+  const RowStat sd = sh.st_d[rejected ? istar : 0];
+  const double izt = 1.0 / st.Z, izd = rejected ? 1.0 / sd.Z : 0.0;
+  for (int32_t at = first; at < V; at += kAcceptTokens) {
+    const int32_t t = slice_start<true>(at, V);
+    float xt[8], xd[8], v[8];
+    load8<BF16, true>(trow, t, V, xt);
+    if (rejected) load8<BF16, true>(drow, t, V, xd);
+    if (at != first) load8_mult<true>(kWeighted ? nullptr : a.mult, t, V, m);
+    delta8(xt, xd, m, rejected, st, sd, izt, izd, a.c, fa.c_lo, v);
+    if ((t & 3) == 0) {
+      *reinterpret_cast<float4 *>(tab + t) = make_float4(v[0], v[1], v[2], v[3]);
+      *reinterpret_cast<float4 *>(tab + t + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) tab[t + k] = v[k];
+    }
+  }
+
+  // the sums of all groups
+  if constexpr (SUMS <= kSumsPreparedWeighted) {
+    if (threadIdx.x < kBanks) tab[p.tile_len + threadIdx.x] = 0.f;
+    lds_barrier();                                  // the table is complete
+    for (int32_t chunk = 0; chunk < p.nchunks; ++chunk) {
+      float acc[kMaxAcc];
+#pragma unroll
+      for (int j = 0; j < kMaxAcc; ++j) acc[j] = 0.f;
+      if (chunk > 0) {
+#pragma unroll
+        for (int q = 0; q < kMaxBlocksPerWave; ++q) { stream.steps[q] = nsteps[q]; stream.offs[q] = noffs[q]; }
+        ask_chunk(chunk);
+      }
+      stream.walk(tab, p.data, p.wdata, lane, acc);
+#pragma unroll
+      for (int j = 0; j < kMaxAcc; ++j)
+        if (where[j] != 0xFFFFu) sums[chunk * p.chunk_groups + where[j]] = acc[j];
+    }
+  } else {
+    if (threadIdx.x == 0) tab[V] = 0.f;
+    lds_barrier();
+    csr_sums<4, kWeighted>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights,
+                           [&](int32_t g, float s) { sums[g] = s; });
+  }
+  lds_barrier();
+
+  const Uniforms u = philox_uniforms(fa.seed, fa.offset, (uint32_t) b, (uint32_t) istar);
+  const CdfPick pg = pick_group(sums, G, (double) u.grp);
+  finish_sequence<BF16, kAcceptThreads>(fa, G, b, istar, trow, st, u, pg);
 }
 
 // =============================================================================================
@@ -1936,31 +2203,72 @@ hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, 
   return hipGetLastError();
 }
 
+static PreparedView prepared_view(const pcg_groups &g) {
+  const pcg_prepared &p = *g.prepared_info;
+  const char *blob = reinterpret_cast<const char *>(g.prepared);
+  PreparedView v;
+  v.desc = reinterpret_cast<const uint32_t *>(blob + p.off_desc);
+  v.perm = reinterpret_cast<const uint16_t *>(blob + p.off_perm);
+  v.data = reinterpret_cast<const uint4 *>(blob + p.off_data);
+  // general weights are read from the blob (the caller's checks made sure it holds them)
+  v.wdata = g.weights ? reinterpret_cast<const float4 *>(blob + p.off_weights) : nullptr;
+  v.nchunks = p.nchunks;
+  v.chunk_groups = p.chunk_groups;
+  v.ntiles = p.ntiles;
+  v.tile_len = p.tile_len;
+  v.blocks_per_chunk = p.blocks_per_chunk;
+  return v;
+}
+
 hipError_t launch_gather_prepared(const pcg_groups &g, int32_t nrows, const float *table, float *out,
                                   double *csum, double *runs, hipStream_t stream) {
   if (nrows == 0) return hipSuccess;
-  const pcg_prepared &p = *g.prepared_info;
-  const char *blob = reinterpret_cast<const char *>(g.prepared);
-  const uint32_t *desc = reinterpret_cast<const uint32_t *>(blob + p.off_desc);
-  const uint16_t *perm = reinterpret_cast<const uint16_t *>(blob + p.off_perm);
-  const uint4 *data = reinterpret_cast<const uint4 *>(blob + p.off_data);
+  const PreparedView p = prepared_view(g);
   const int32_t rows8 = (nrows + 7) / 8;
   const dim3 grid((unsigned) (8 * rows8 * p.nchunks));
-  // general weights are read from the blob (the caller's checks made sure it holds them)
-  const float4 *wdata =
-      g.weights ? reinterpret_cast<const float4 *>(blob + p.off_weights) : nullptr;
   auto launch = [&](auto kernel) {
-    kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, p.nchunks, p.chunk_groups,
-                                                p.ntiles, p.tile_len, p.blocks_per_chunk, desc,
-                                                perm, data, wdata, table, out, csum, runs);
+    kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, p, table, out, csum, runs);
   };
-  if (wdata) {
+  if (g.weights) {
     if (csum) launch(gather_prepared_kernel<true, true>);
     else launch(gather_prepared_kernel<false, true>);
   } else {
     if (csum) launch(gather_prepared_kernel<true, false>);
     else launch(gather_prepared_kernel<false, false>);
   }
+  return hipGetLastError();
+}
+
+bool small_step_fits(const pcg_groups &g, int32_t B, int32_t K) {
+  // what the kernel's LDS and its row loads can take
+  const int64_t row_parts = (2 * (int64_t) K + 1) * stats_nparts(g.V);
+  if (g.V < 8 || g.V > kSmallTokens || g.G > kSmallGroups || row_parts > kSmallParts) return false;
+  if (g.prepared && (g.prepared_info->ntiles != 1 || g.prepared_info->tile_len > kSmallTokens)) return false;
+  if (B > 256) return false;                        // one workgroup per compute unit at a time
+  // Where one compute unit per sequence is the faster way.  From 144 sequences on it keeps the chip
+  // busy and always is (B = 256, K = 8: V = 1024 25.1 -> 16.8 us, 16 384 60.1 -> 47.1).  With few
+  // sequences the four kernels take 18 to 25 us whatever the size and spread one sequence over many
+  // compute units, so it has to be small: 8 items (probes and row parts) cost it about 1 us, as do 32 K
+  // entries and 2.5 K tokens.  B = 1, K = 8, members each: V = 4096, 16: 21.3 -> 19.0 us (load 71);
+  // V = 2048, 100: 26.0 -> 20.3 (82); V = 4096, 32, fp32: 22.8 -> 20.5 (88); V = 8192, 16: 21.5 -> 26.6
+  // (135).  From the CSR the crossing is earlier: V = 1024 19.3 -> 14.6 (32), V = 4096, K = 4
+  // 18.9 -> 19.0 (51).
+  const int64_t load = K + row_parts + g.nnz / 4096 + g.V / 320;
+  return B >= 144 || load <= (g.prepared ? 90 : 50);
+}
+
+hipError_t launch_small_step(const AcceptArgs &a, const FinalizeArgs &fa, const ProbeArgs &pa,
+                             const pcg_groups &g, bool bf16, int32_t B, hipStream_t stream) {
+  const PreparedView p = g.prepared ? prepared_view(g) : PreparedView{};
+  auto launch = [&](auto kernel) {
+    kernel<<<B, kAcceptThreads, 0, stream>>>(a, fa, pa, p, (int32_t) g.nnz);
+  };
+  auto pick = [&](auto is_bf16) {
+    constexpr bool BF = decltype(is_bf16)::value;
+    if (g.prepared) { if (g.weights) launch(small_step_kernel<BF, kSumsPreparedWeighted>); else launch(small_step_kernel<BF, kSumsPrepared>); }
+    else { if (g.weights) launch(small_step_kernel<BF, kSumsCsrWeighted>); else launch(small_step_kernel<BF, kSumsCsr>); }
+  };
+  if (bf16) pick(std::true_type{}); else pick(std::false_type{});
   return hipGetLastError();
 }
 
