@@ -37,19 +37,84 @@ __device__ __forceinline__ uint16_t round_to_bf16(double x) {
   return (uint16_t) ((pick >> 16) | (__double_as_longlong(x) < 0 ? 0x8000u : 0u));
 }
 
-// norms (may be NULL) receives ||emb[v]|| in double.
+// The same for x = e / norm, with inv = 1 / norm: the product is off by less than an fp32 ulp, so its
+// fp32 image decides the rounding unless it lies within two ulps of the middle between two bfloat16
+// values; only then is the quotient formed.
+__device__ __forceinline__ uint16_t quotient_to_bf16(double e, double norm, double inv) {
+  const uint32_t u = __float_as_uint((float) (e * inv));
+  const uint32_t low = u & 0xffffu;
+  if (low - 0x7ffeu <= 4u) return round_to_bf16(e / norm);
+  return (uint16_t) ((u + 0x8000u) >> 16);
+}
+
+__device__ __forceinline__ double bf16_value(uint16_t b) { return (double) __uint_as_float((uint32_t) b << 16); }
+
+// EXACT: norms receives ||emb[v]|| in double, and *worst (a non-negative float as its bits) the
+// largest ||unit_bf16[v] - emb[v] / ||emb[v]|| ||, how far rounding has moved a unit vector.
+// One wave per token; its row (up to kRowRegs * 256 elements, d a multiple of 4) stays in registers
+// between the norm and the quotients.  Bound by memory: 268 MB of embeddings and 134 MB of unit
+// vectors at 65 536 x 1024 take 80 us (175 with 4-byte loads, the row read twice and a
+// division in double per element).
+template <bool EXACT>
 __global__ __launch_bounds__(256) void asg_normalize_kernel(const float *emb, int32_t V, int32_t d,
-                                                            uint16_t *unit, double *norms) {
+                                                            uint16_t *unit, double *norms, uint32_t *worst) {
+  constexpr int kRowRegs = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t v = (int64_t) blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
   if (v >= V) return;                       // whole waves leave together
   const float *e = emb + v * d;
-  double ss = 0.0;
-  for (int32_t k = lane; k < d; k += kWave) ss += (double) e[k] * (double) e[k];
-  const double norm = sqrt(wave_sum(ss));
-  if (norms && lane == 0) norms[v] = norm;
-  for (int32_t k = lane; k < d; k += kWave)
-    unit[v * d + k] = norm > 0.0 ? round_to_bf16((double) e[k] / norm) : (uint16_t) 0;
+  uint16_t *out = unit + v * d;
+  double ss = 0.0, err = 0.0;
+  const bool wide = d % 4 == 0 && d <= kRowRegs * 4 * kWave && (((uintptr_t) e | (uintptr_t) (2 * (uintptr_t) out)) & 15) == 0;
+  if (wide) {                               // uniform over the wave
+    float4 x[kRowRegs];
+#pragma unroll
+    for (int i = 0; i < kRowRegs; ++i) {
+      const int32_t k = 4 * (lane + i * kWave);
+      x[i] = k < d ? *reinterpret_cast<const float4 *>(e + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int i = 0; i < kRowRegs; ++i)
+      ss += ((double) x[i].x * (double) x[i].x + (double) x[i].y * (double) x[i].y) +
+            ((double) x[i].z * (double) x[i].z + (double) x[i].w * (double) x[i].w);
+    const double norm = sqrt(wave_sum(ss)), inv = norm > 0.0 ? 1.0 / norm : 0.0;
+    if (EXACT && lane == 0) norms[v] = norm;
+#pragma unroll
+    for (int i = 0; i < kRowRegs; ++i) {
+      const int32_t k = 4 * (lane + i * kWave);
+      if (k >= d) continue;
+      const float xs[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+      uint16_t q[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        q[j] = norm > 0.0 ? quotient_to_bf16((double) xs[j], norm, inv) : (uint16_t) 0;
+        if constexpr (EXACT) {
+          const double off = bf16_value(q[j]) - (double) xs[j] * inv;
+          err += off * off;
+        }
+      }
+      *reinterpret_cast<uint2 *>(out + k) =
+          make_uint2((uint32_t) q[0] | (uint32_t) q[1] << 16, (uint32_t) q[2] | (uint32_t) q[3] << 16);
+    }
+  } else {
+    for (int32_t k = lane; k < d; k += kWave) ss += (double) e[k] * (double) e[k];
+    const double norm = sqrt(wave_sum(ss)), inv = norm > 0.0 ? 1.0 / norm : 0.0;
+    if (EXACT && lane == 0) norms[v] = norm;
+    for (int32_t k = lane; k < d; k += kWave) {
+      const uint16_t q = norm > 0.0 ? quotient_to_bf16((double) e[k], norm, inv) : (uint16_t) 0;
+      out[k] = q;
+      if constexpr (EXACT) {
+        const double off = bf16_value(q) - (double) e[k] * inv;
+        err += off * off;
+      }
+    }
+  }
+  if constexpr (EXACT) {
+    // rounded up; read before the atomic, since 65 536 atomics on one word would take their time.  A row
+    // with a NaN or an infinity has no cosine above any threshold and must not widen the band.
+    const uint32_t mine = __float_as_uint(__double2float_ru(sqrt(wave_sum(err)) * (1.0 + 0x1p-40)));
+    if (lane == 0 && mine < 0x7f800000u && mine > __atomic_load_n(worst, __ATOMIC_RELAXED)) atomicMax(worst, mine);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -112,12 +177,27 @@ __device__ __forceinline__ void bare_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// EXACT: pairs above theta are candidates, and those not above theta_hi are marked kAsgUnsure
-// for asg_refine_kernel (theta and theta_hi bracket the threshold of Eq. 1 by the rounding band).
+// How far the fp32-accumulated dot product of two bf16-rounded unit vectors can lie from the cosine of
+// the vectors they were rounded from, if rounding moved neither by more than e: the exact dot product
+// of the rounded ones lies within 2 e + e^2 (Cauchy-Schwarz), and the d additions in fp32 add at most
+// d 2^-23 of the vectors' lengths (a rounding, or a truncation, of each partial sum).  2^-20 covers
+// the roundings of this expression and of the threshold plus or minus it.
+__device__ __forceinline__ float asg_rounding_band(int32_t d, float e) {
+  return (2.f * e + e * e) + (float) d * 0x1p-23f * (1.f + e) * (1.f + e) + 0x1p-20f;
+}
+
+// EXACT: pairs above theta minus the rounding band are candidates, and those not above theta plus
+// the band are marked kAsgUnsure for asg_refine_kernel.
 template <bool EXACT>
 __global__ __launch_bounds__(kSimThreads) void asg_similarity_kernel(
-    const uint16_t *__restrict__ unit, int32_t V, int32_t d, float theta, float theta_hi,
+    const uint16_t *__restrict__ unit, int32_t V, int32_t d, float theta, const uint32_t *worst,
     int32_t cap, int32_t *count, int32_t *cand) {
+  float theta_hi = theta;
+  if constexpr (EXACT) {
+    const float band = asg_rounding_band(d, __uint_as_float(*worst));
+    theta_hi = theta + band;
+    theta = theta - band;
+  }
   // Workgroups go to the 8 XCDs round-robin; the 32 that run together on one XCD take a patch of
   // 16 x 2 tiles (measured: 5.0 ms against 5.2 for 8 x 4 and 5.7 for 4 x 8), so that they find each
   // other's rows in their L2.
@@ -297,59 +377,93 @@ __global__ __launch_bounds__(kSimThreads) void asg_similarity_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact form: one wave per token settles the members marked kAsgUnsure by Eq. (1) itself -- the
-// dot product of the two float32 embeddings and their norms, all in double, strict > theta --
-// and closes the gaps in the token's list.  The dot product is summed in the same order for
-// (t, v) and (v, t), so both tokens reach the same decision.  A list that did not fit into cap
-// stays undecided: its count stays above cap and the call reports PCG_ERR_CAPACITY.
+// Exact form: the pairs marked kAsgUnsure are settled by Eq. (1) itself -- the dot product of the two
+// float32 embeddings and their norms, all in double, strict > theta.  A pair stands in both tokens'
+// lists; the wave of its smaller token decides it and writes the outcome into both: the plain token
+// id, or kAsgRemoved (asg_sort_kernel closes the gaps).  No two waves write the same entry, and a
+// wave's own pairs are those with a larger token, whatever has happened to the others it reads.
+// The wave's own row stays in registers (up to kRowRegs * 256 elements), the other's comes from
+// memory: bound by the gather of those rows, 4 d bytes a pair.  65 536 x 1024, 0.7 M undecided pairs:
+// 1711 us when both tokens' waves computed each pair and read both rows for it, now 476.
+// Lists that did not fit into cap stay undecided: their count stays above cap and the call reports
+// PCG_ERR_CAPACITY.
 // ---------------------------------------------------------------------------------------------
+constexpr uint32_t kAsgRemoved = 0xffffffffu;
+
 __global__ __launch_bounds__(256) void asg_refine_kernel(const float *__restrict__ emb,
                                                          const double *__restrict__ norms, int32_t V,
                                                          int32_t d, double theta, int32_t cap,
-                                                         int32_t *count, int32_t *cand) {
+                                                         const int32_t *count, int32_t *cand) {
+  constexpr int kRowRegs = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int32_t t = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
   if (t >= V) return;                       // whole waves leave together
   const int32_t found = count[t];
+  if (found > cap) return;
   int32_t *row = cand + (int64_t) t * cap;
-  if (found > cap) {
-    // undecided, but plain token ids again: the kernels that follow index with them
-    for (int32_t k = lane; k < cap; k += kWave) row[k] = (int32_t) ((uint32_t) row[k] & ~kAsgUnsure);
-    return;
-  }
   const float *et = emb + (int64_t) t * d;
   const double nt = norms[t];
-  int32_t kept_total = 0;
+  float4 own[kRowRegs];                     // d is a multiple of 64
+#pragma unroll
+  for (int i = 0; i < kRowRegs; ++i) {
+    const int32_t k = 4 * (lane + i * kWave);
+    own[i] = k < d ? *reinterpret_cast<const float4 *>(et + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  auto product = [](const float4 a, const float4 b) {
+    return ((double) a.x * (double) b.x + (double) a.y * (double) b.y) +
+           ((double) a.z * (double) b.z + (double) a.w * (double) b.w);
+  };
+  auto fetch = [&](int32_t v, float4 (&o)[kRowRegs]) {
+    const float *ev = emb + (int64_t) v * d;
+#pragma unroll
+    for (int i = 0; i < kRowRegs; ++i) {
+      const int32_t k = 4 * (lane + i * kWave);
+      o[i] = k < d ? *reinterpret_cast<const float4 *>(ev + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
   for (int32_t c0 = 0; c0 < found; c0 += kWave) {
     const int32_t k = c0 + lane;
-    bool keep = k < found;
-    const uint32_t raw = keep ? (uint32_t) row[k] : 0u;
+    const uint32_t raw = k < found ? (uint32_t) row[k] : 0u;
     const int32_t entry = (int32_t) (raw & ~kAsgUnsure);
-    unsigned long long unsure = __ballot(keep && (raw & kAsgUnsure) != 0);
-    while (unsure) {                                   // uniform over the wave
-      const int l = __ffsll((long long) unsure) - 1;
-      unsure &= unsure - 1;
+    unsigned long long mine = __ballot(raw != kAsgRemoved && (raw & kAsgUnsure) != 0 && entry > t);
+    if (mine == 0) continue;                           // uniform over the wave, as everything below
+    bool member = false;
+    int l = __ffsll((long long) mine) - 1;
+    float4 o[kRowRegs];
+    fetch(__builtin_amdgcn_readlane(entry, l), o);
+    const unsigned long long all = mine;
+    while (true) {
+      mine &= mine - 1;
       const int32_t v = __builtin_amdgcn_readlane(entry, l);
-      const float *ev = emb + (int64_t) v * d;
-      double dot = 0.0;
-      for (int32_t j = 4 * lane; j < d; j += 4 * kWave) {       // d is a multiple of 64
-        const float4 a = *reinterpret_cast<const float4 *>(et + j);
-        const float4 b = *reinterpret_cast<const float4 *>(ev + j);
-        dot += ((double) a.x * (double) b.x + (double) a.y * (double) b.y) +
-               ((double) a.z * (double) b.z + (double) a.w * (double) b.w);
+      float4 cur[kRowRegs];
+#pragma unroll
+      for (int i = 0; i < kRowRegs; ++i) cur[i] = o[i];
+      int ln = 0;
+      if (mine) {                                      // the next row is on its way behind this one
+        ln = __ffsll((long long) mine) - 1;
+        fetch(__builtin_amdgcn_readlane(entry, ln), o);
       }
+      double dot = 0.0;
+#pragma unroll
+      for (int i = 0; i < kRowRegs; ++i) dot += product(own[i], cur[i]);
+      for (int32_t j = 4 * (lane + kRowRegs * kWave); j < d; j += 4 * kWave)
+        dot += product(*reinterpret_cast<const float4 *>(et + j),
+                       *reinterpret_cast<const float4 *>(emb + (int64_t) v * d + j));
       dot = wave_sum(dot);
       const double nv = norms[v];
       const double cosine = (nt > 0.0 && nv > 0.0) ? dot / (nt * nv) : 0.0;
-      if (lane == l && !(cosine > theta)) keep = false;
+      const bool is_member = cosine > theta;
+      if (lane == l) member = is_member;
+      // the same pair in the other token's list
+      const int32_t theirs = min(count[v], cap);
+      int32_t *other = cand + (int64_t) v * cap;
+      for (int32_t j = lane; j < theirs; j += kWave)
+        if ((uint32_t) other[j] == ((uint32_t) t | kAsgUnsure)) other[j] = is_member ? t : (int32_t) kAsgRemoved;
+      if (!mine) break;
+      l = ln;
     }
-    const unsigned long long kept = __ballot(keep);
-    const int32_t pos = kept_total + __popcll(kept & ((1ull << lane) - 1ull));
-    // positions written here lie below c0 + 64, positions read later at or above it
-    if (keep) row[pos] = entry;
-    kept_total += __popcll(kept);
+    if ((all >> lane) & 1ull) row[k] = member ? entry : (int32_t) kAsgRemoved;
   }
-  if (lane == 0) count[t] = kept_total;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -373,9 +487,12 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One wave per token: its members ascending (bitonic sort in the wave's own slice of LDS), an
-// order-independent hash of the set, its size.  cap2 = cap rounded up to a power of two; the
-// kernel is launched with 4 * cap2 * 4 bytes of dynamic LDS.
+// One wave per token: its members ascending, an order-independent hash of the set, its size; entries
+// marked kAsgRemoved are dropped, what is still marked kAsgUnsure (only where some list did not fit)
+// becomes a plain token id again, since the kernels that follow index with it.  Up to 64 members are
+// ranked against each other in registers, larger sets go through a bitonic sort in the wave's own
+// slice of LDS (153 us for 65 536 sets of 26 members on average, now 92).  cap2 = cap rounded up
+// to a power of two, at least 64; the kernel is launched with 4 * cap2 * 4 bytes of dynamic LDS.
 __global__ __launch_bounds__(kSortThreads) void asg_sort_kernel(int32_t V, int32_t cap, int32_t cap2,
                                                                 const int32_t *count, int32_t *cand,
                                                                 int32_t *size, uint64_t *hash,
@@ -386,27 +503,47 @@ __global__ __launch_bounds__(kSortThreads) void asg_sort_kernel(int32_t V, int32
   if (t >= V) return;                       // whole waves leave together; no workgroup barrier below
   int32_t *key = sort_lds + wave * cap2;
   const int32_t found = count[t];
-  const int32_t n = min(found, cap);
-  // the largest set found so far: read first, since 65 536 atomics on one word take longer
-  // than the sort itself
-  if (lane == 0 && found > __atomic_load_n(max_count, __ATOMIC_RELAXED)) atomicMax(max_count, found);
-  int32_t n2 = 1;
-  while (n2 < n) n2 <<= 1;
+  const int32_t have = min(found, cap);
   int32_t *row = cand + (int64_t) t * cap;
-  for (int32_t k = lane; k < n2; k += kWave) key[k] = k < n ? row[k] : INT32_MAX;
-  wave_lds_sync();
-  for (int32_t len = 2; len <= n2; len <<= 1)
-    for (int32_t step = len >> 1; step > 0; step >>= 1) {
-      for (int32_t k = lane; k < n2; k += kWave) {
-        const int32_t other = k ^ step;
-        if (other > k) {
-          const bool up = (k & len) == 0;
-          const int32_t x = key[k], y = key[other];
-          if ((x > y) == up) { key[k] = y; key[other] = x; }
-        }
-      }
-      wave_lds_sync();
+  int32_t n = 0;
+  if (have <= kWave) {
+    // every member's place is the number of members below it (they are distinct)
+    const uint32_t raw = lane < have ? (uint32_t) row[lane] : kAsgRemoved;
+    const bool valid = raw != kAsgRemoved;
+    const int32_t x = valid ? (int32_t) (raw & ~kAsgUnsure) : INT32_MAX;
+    n = __popcll(__ballot(valid));
+    int32_t rank = 0;
+    for (int32_t j = 0; j < have; ++j) rank += __builtin_amdgcn_readlane(x, j) < x;
+    if (valid) key[rank] = x;
+  } else {
+    int32_t n2 = 1;
+    while (n2 < have) n2 <<= 1;
+    for (int32_t k0 = 0; k0 < n2; k0 += kWave) {
+      const int32_t k = k0 + lane;
+      const uint32_t raw = k < have ? (uint32_t) row[k] : kAsgRemoved;
+      const bool valid = raw != kAsgRemoved;
+      key[k] = valid ? (int32_t) (raw & ~kAsgUnsure) : INT32_MAX;
+      n += __popcll(__ballot(valid));
     }
+    wave_lds_sync();
+    for (int32_t len = 2; len <= n2; len <<= 1)
+      for (int32_t step = len >> 1; step > 0; step >>= 1) {
+        for (int32_t k = lane; k < n2; k += kWave) {
+          const int32_t other = k ^ step;
+          if (other > k) {
+            const bool up = (k & len) == 0;
+            const int32_t x = key[k], y = key[other];
+            if ((x > y) == up) { key[k] = y; key[other] = x; }
+          }
+        }
+        wave_lds_sync();
+      }
+  }
+  wave_lds_sync();
+  // the largest set (where it did not fit: what was found for it): read first, since 65 536 atomics
+  // on one word take longer than the sort itself
+  const int32_t largest = found > cap ? found : n;
+  if (lane == 0 && largest > __atomic_load_n(max_count, __ATOMIC_RELAXED)) atomicMax(max_count, largest);
   uint64_t h = 0;
   for (int32_t k = lane; k < n; k += kWave) {
     row[k] = key[k];
@@ -432,52 +569,85 @@ __global__ __launch_bounds__(256) void asg_dedup_kernel(int32_t V, int32_t cap, 
   const uint64_t h = hash[t];
   const int32_t *mine = cand + (int64_t) t * cap;
   int dup = 0;
-  for (int32_t j = 0; j < n && !dup; ++j) {
-    const int32_t m = mine[j];                 // uniform over the wave
-    if (m >= t) break;
-    if (size[m] != n || hash[m] != h) continue;
-    const int32_t *theirs = cand + (int64_t) m * cap;
-    bool same = true;
-    for (int32_t k = lane; k < n; k += kWave) same = same && mine[k] == theirs[k];
-    dup = __all(same);
+  // 64 members at a time, one per lane, are compared by size and hash; a set that agrees in both is
+  // then compared member by member
+  for (int32_t j0 = 0; j0 < n && !dup; j0 += kWave) {
+    const int32_t j = j0 + lane;
+    const int32_t m = j < n ? mine[j] : INT32_MAX;
+    unsigned long long alike = __ballot(m < t && size[m < t ? m : t] == n && hash[m < t ? m : t] == h);
+    while (alike && !dup) {                    // uniform over the wave
+      const int32_t other = __builtin_amdgcn_readlane(m, __ffsll((long long) alike) - 1);
+      alike &= alike - 1;
+      const int32_t *theirs = cand + (int64_t) other * cap;
+      bool same = true;
+      for (int32_t k = lane; k < n; k += kWave) same = same && mine[k] == theirs[k];
+      dup = __all(same);
+    }
+    if (__ballot(m >= t)) break;               // ascending: no further members below t
   }
   if (lane == 0) keep[t] = !dup;
 }
 
-// Exclusive scans over the tokens by one workgroup, 1024 tokens at a time: gid[t] = kept tokens
-// before t, off[t] = members of kept tokens before t; totals[0] = G, totals[1] = nnz.  The
-// counts stay below 2^31, so they are exact in the double the wave scan works on.
+// Exclusive scans over the tokens: gid[t] = kept tokens before t, off[t] = members of kept tokens
+// before t; totals[0] = G, totals[1] = nnz.  Two launches, a workgroup per 1024 tokens: the first
+// leaves every block's counts, the second sums those of the blocks before its own and scans its
+// tokens.  (One workgroup walking over all tokens took 132 us at V = 65 536; these take 11.)
+// A token's two counts travel as one double: 1 + 2^11 size; sums over 1024 tokens stay exact.
 constexpr int kScanThreads = 1024;
+constexpr double kScanUnit = 2048.0;
+
+__device__ __forceinline__ double scan_item(int32_t t, int32_t V, const int32_t *keep, const int32_t *size) {
+  return t < V && keep[t] != 0 ? 1.0 + kScanUnit * (double) size[t] : 0.0;
+}
+
+// Sum over the workgroup (fixed order); every thread gets it.
+__device__ __forceinline__ double scan_block_sum(double v, double *wave_tot) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+  v = wave_sum(v);
+  if (lane == 0) wave_tot[wave] = v;
+  __syncthreads();
+  const double w = wave_sum(lane < kScanThreads / kWave ? wave_tot[lane] : 0.0);
+  __syncthreads();
+  return w;
+}
+
+__global__ __launch_bounds__(kScanThreads) void asg_count_kernel(int32_t V, const int32_t *keep,
+                                                                 const int32_t *size, uint64_t *counts) {
+  __shared__ double wave_tot[kScanThreads / kWave];
+  const double all = scan_block_sum(scan_item(blockIdx.x * kScanThreads + threadIdx.x, V, keep, size), wave_tot);
+  if (threadIdx.x == 0) counts[blockIdx.x] = (uint64_t) all;
+}
 
 __global__ __launch_bounds__(kScanThreads) void asg_scan_kernel(int32_t V, const int32_t *keep,
-                                                                const int32_t *size, int32_t *gid,
-                                                                int64_t *off, int64_t *totals) {
-  __shared__ double wg[kScanThreads / kWave], wn[kScanThreads / kWave];
+                                                                const int32_t *size, const uint64_t *counts,
+                                                                int32_t *gid, int64_t *off, int64_t *totals) {
+  __shared__ double wave_tot[kScanThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-  double base_g = 0.0, base_n = 0.0;
-  for (int32_t t0 = 0; t0 < V; t0 += kScanThreads) {
-    const int32_t t = t0 + threadIdx.x;
-    const bool k = t < V && keep[t] != 0;
-    const double g = k ? 1.0 : 0.0, n = k ? (double) size[t] : 0.0;
-    const double ig = wave_scan(g), in = wave_scan(n);
-    if (lane == kWave - 1) { wg[wave] = ig; wn[wave] = in; }
-    __syncthreads();
-    double bg = base_g, bn = base_n, tg = 0.0, tn = 0.0;
-    for (int w = 0; w < kScanThreads / kWave; ++w) {
-      if (w == wave) { bg += tg; bn += tn; }
-      tg += wg[w]; tn += wn[w];
-    }
-    if (t < V) {
-      gid[t] = (int32_t) (bg + ig - g);
-      off[t] = (int64_t) (bn + in - n);
-    }
-    base_g += tg;
-    base_n += tn;
-    __syncthreads();
+  double g0 = 0.0, n0 = 0.0;                 // of the blocks before this one
+  for (int32_t k = threadIdx.x; k < (int32_t) blockIdx.x; k += kScanThreads) {
+    const uint64_t c = counts[k];
+    g0 += (double) (c & 2047);
+    n0 += (double) (c >> 11);
   }
-  if (threadIdx.x == 0) {
-    totals[0] = (int64_t) base_g;
-    totals[1] = (int64_t) base_n;
+  g0 = scan_block_sum(g0, wave_tot);
+  n0 = scan_block_sum(n0, wave_tot);
+  const int32_t t = blockIdx.x * kScanThreads + threadIdx.x;
+  const double mine = scan_item(t, V, keep, size);
+  const double inc = wave_scan(mine);
+  if (lane == kWave - 1) wave_tot[wave] = inc;
+  __syncthreads();
+  const double tot = lane < kScanThreads / kWave ? wave_tot[lane] : 0.0;
+  const double upto = wave_scan(tot);
+  const double before = read_lane(upto, wave) - read_lane(tot, wave) + (inc - mine);
+  const uint64_t e = (uint64_t) before;
+  if (t < V) {
+    gid[t] = (int32_t) ((int64_t) g0 + (int64_t) (e & 2047));
+    off[t] = (int64_t) n0 + (int64_t) (e >> 11);
+  }
+  if (t == V - 1) {
+    const uint64_t c = (uint64_t) (before + mine);
+    totals[0] = (int64_t) g0 + (int64_t) (c & 2047);
+    totals[1] = (int64_t) n0 + (int64_t) (c >> 11);
   }
 }
 
@@ -525,18 +695,9 @@ size_t asg_core_workspace_bytes(size_t v, int32_t cap) {
          asg_align(v * 4) /* gid */ + asg_align(v * 8) /* off */ + asg_align(64) /* totals */;
 }
 
-// How far the fp32-accumulated dot product of two bf16-rounded unit vectors can lie from the
-// cosine of the vectors they were rounded from: every component is off by at most 2^-9 of
-// itself, so the products by at most 2^-8 + 2^-18 of themselves, and their absolute values sum
-// to at most 1 (Cauchy-Schwarz); the d additions in fp32 add at most d * 2^-23 (a rounding, or a
-// truncation, of each partial sum of magnitude at most 1).
-float asg_rounding_band(int32_t d) {
-  return 0x1p-8f + 0x1p-18f + (float) d * 0x1p-23f;
-}
-
 // The groups from the unit vectors; with emb (and norms, workspace of the caller) the exact form.
-int asg_build_impl(const float *emb, const double *norms, const uint16_t *unit_bf16, int32_t V,
-                   int32_t d, float theta, int32_t cap, int32_t *row_ptr, int32_t *members,
+int asg_build_impl(const float *emb, double *norms, uint16_t *unit_out, const uint16_t *unit_bf16,
+                   int32_t V, int32_t d, float theta, int32_t cap, int32_t *row_ptr, int32_t *members,
                    int64_t members_capacity, int32_t *mult, int32_t *seed_of, int32_t *out_G,
                    int64_t *out_nnz, int32_t *out_max_size, char *ws, hipStream_t stream) {
   const size_t v = (size_t) V;
@@ -547,7 +708,7 @@ int asg_build_impl(const float *emb, const double *norms, const uint16_t *unit_b
   int32_t *keep = (int32_t *) ws; ws += asg_align(v * 4);
   int32_t *gid = (int32_t *) ws; ws += asg_align(v * 4);
   int64_t *off = (int64_t *) ws; ws += asg_align(v * 8);
-  int64_t *totals = (int64_t *) ws;          // [0] G, [1] nnz, [2] (as int32) largest set found
+  int64_t *totals = (int64_t *) ws;          // [0] G, [1] nnz, [2] (as int32) largest set found, [3] worst rounding
 
   auto fail = [](hipError_t e) { return record_hip_error(e); };
   hipError_t e;
@@ -561,21 +722,25 @@ int asg_build_impl(const float *emb, const double *norms, const uint16_t *unit_b
   const int patches = (patch_rows * patch_cols + 7) / 8 * 8;      // dealt to the 8 XCDs in turn
   const unsigned sim_grid = (unsigned) (patches * kSimPatchRows * kSimPatchCols);
   if (emb) {
-    const float band = asg_rounding_band(d);
+    uint32_t *worst = (uint32_t *) (totals + 3);
+    asg_normalize_kernel<true><<<wb, 256, 0, stream>>>(emb, V, d, unit_out, norms, worst);
     asg_similarity_kernel<true><<<sim_grid, kSimThreads, 0, stream>>>(
-        unit_bf16, V, d, theta - band, theta + band, cap, count, cand);
+        unit_out, V, d, theta, worst, cap, count, cand);
     asg_refine_kernel<<<wb, 256, 0, stream>>>(emb, norms, V, d, (double) theta, cap, count, cand);
   } else {
     asg_similarity_kernel<false><<<sim_grid, kSimThreads, 0, stream>>>(
-        unit_bf16, V, d, theta, theta, cap, count, cand);
+        unit_bf16, V, d, theta, nullptr, cap, count, cand);
   }
   if ((e = hipGetLastError()) != hipSuccess) return fail(e);
-  int32_t cap2 = 1;
+  int32_t cap2 = kWave;
   while (cap2 < cap) cap2 <<= 1;
   asg_sort_kernel<<<wb, kSortThreads, (size_t) (kSortThreads / kWave) * cap2 * sizeof(int32_t), stream>>>(
       V, cap, cap2, count, cand, size, hash, (int32_t *) (totals + 2));
   asg_dedup_kernel<<<wb, 256, 0, stream>>>(V, cap, cand, size, hash, keep);
-  asg_scan_kernel<<<1, kScanThreads, 0, stream>>>(V, keep, size, gid, off, totals);
+  const unsigned sb = (unsigned) ((v + kScanThreads - 1) / kScanThreads);
+  uint64_t *counts = hash;                   // read for the last time by the kernel before
+  asg_count_kernel<<<sb, kScanThreads, 0, stream>>>(V, keep, size, counts);
+  asg_scan_kernel<<<sb, kScanThreads, 0, stream>>>(V, keep, size, counts, gid, off, totals);
   if ((e = hipGetLastError()) != hipSuccess) return fail(e);
   int64_t host_totals[3] = {0, 0, 0};
   if ((e = hipMemcpyAsync(host_totals, totals, sizeof host_totals, hipMemcpyDeviceToHost, stream)) !=
@@ -618,7 +783,7 @@ int pcg_asg_normalize(const float *emb, int32_t V, int32_t d, uint16_t *unit_bf1
   if (V < 1 || d < 1) return PCG_ERR_BAD_SHAPE;
   if (((uintptr_t) emb % 4) || ((uintptr_t) unit_bf16 % 2)) return PCG_ERR_MISALIGNED;
   hipStream_t stream = (hipStream_t) hip_stream;
-  asg_normalize_kernel<<<(unsigned) ((V + 3) / 4), 256, 0, stream>>>(emb, V, d, unit_bf16, nullptr);
+  asg_normalize_kernel<false><<<(unsigned) ((V + 3) / 4), 256, 0, stream>>>(emb, V, d, unit_bf16, nullptr, nullptr);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? PCG_OK : record_hip_error(e);
 }
@@ -639,7 +804,7 @@ int pcg_asg_build(const uint16_t *unit_bf16, int32_t V, int32_t d, float theta, 
     return rc;
   if ((uintptr_t) unit_bf16 % 16) return PCG_ERR_MISALIGNED;
   if (workspace_bytes < pcg_asg_build_workspace_bytes(V, cap)) return PCG_ERR_WORKSPACE_TOO_SMALL;
-  return asg_build_impl(nullptr, nullptr, unit_bf16, V, d, theta, cap, row_ptr, members,
+  return asg_build_impl(nullptr, nullptr, nullptr, unit_bf16, V, d, theta, cap, row_ptr, members,
                         members_capacity, mult, seed_of, out_G, out_nnz, out_max_size,
                         (char *) workspace, (hipStream_t) hip_stream);
 }
@@ -668,10 +833,7 @@ int pcg_asg_build_exact(const float *emb, int32_t V, int32_t d, float theta, int
   char *ws = (char *) workspace;
   uint16_t *unit = (uint16_t *) ws; ws += asg_align(v * (size_t) d * 2);
   double *norms = (double *) ws; ws += asg_align(v * 8);
-  asg_normalize_kernel<<<(unsigned) ((V + 3) / 4), 256, 0, stream>>>(emb, V, d, unit, norms);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return record_hip_error(e);
-  return asg_build_impl(emb, norms, unit, V, d, theta, cap, row_ptr, members, members_capacity,
+  return asg_build_impl(emb, norms, unit, unit, V, d, theta, cap, row_ptr, members, members_capacity,
                         mult, seed_of, out_G, out_nnz, out_max_size, ws, stream);
 }
 

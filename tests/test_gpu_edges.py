@@ -10,7 +10,9 @@ import paper_2511_13732_amd as pcg
 import workloads as W
 from parity import (as_oracle_logits, compare_thinning, compare_verify, group_probs_error, oracle_groups,
                     run_both, run_both_thinning)
+from test_gpu_asg import as_bf16_tensor, compare_groups
 from test_gpu_propose import compare_proposals
+from test_oracle_asg import embeddings
 
 pytestmark = pytest.mark.gpu
 
@@ -97,3 +99,30 @@ def test_csr_gather(V, G, size, B, weighted):
     (16384, 16385, 3, 144, 1, "bf16", 0), (300, 200, 9, 256, 2, "f32", 0), (300, 200, 9, 257, 2, "bf16", 0)])
 def test_small_step(V, G, size, B, K, dtype, off, layout, weighted):
     check_step(V, G, size, B, K, dtype, off=off, layout=layout, weighted=weighted, thinning=False, chunk_groups=4096)
+
+
+# construction of the groups: tokens around the blocks of the scan, rows that fill the registers of the
+# pair kernel and rows beyond, sets of 63 to 66 members (ranked in registers or sorted in LDS), more
+# duplicates of a set than one look at its members covers
+@pytest.mark.parametrize("V,d,theta,centres,sigma", [(1023, 64, 0.2, 0, 0), (1024, 1024, 0.05, 0, 0), (1025, 1088, 0.05, 0, 0),
+                                                     (2049, 2112, 0.04, 0, 0), (640, 64, 0.6, 10, 0.3), (650, 128, 0.6, 10, 0.2),
+                                                     (660, 192, 0.5, 10, 0.4), (900, 64, 0.9, 6, 0.02)])
+def test_group_construction_edges(V, d, theta, centres, sigma):
+    E = embeddings(V, d, 7, centres, sigma)[0] if centres else embeddings(V, d, 7)
+    got = pcg.asg_build_exact(torch.from_numpy(E).cuda(), theta, cap=64)
+    t = compare_groups(got, oracle.asg_build_exact(E, theta, nthreads=8), f"exact V={V} d={d}")
+    assert t.flagged_group == 0 and t.tolerated == 0
+    bits = oracle.asg_normalize(E)
+    ref = oracle.asg_build(bits, theta, nthreads=8)
+    assert compare_groups(pcg.asg_build(as_bf16_tensor(bits).cuda(), theta, cap=64), ref, f"V={V} d={d}").tolerated <= 2
+
+
+def test_group_construction_beside_a_row_that_is_not_finite():
+    """A token whose embedding holds an infinity or a NaN is in no other token's group, and the
+    others' groups are what they are without it."""
+    E = embeddings(700, 128, 9)
+    want = pcg.asg_build_exact(torch.from_numpy(E[:698]).cuda(), 0.15)
+    E[698, 5], E[699, 7] = np.inf, np.nan
+    got = pcg.asg_build_exact(torch.from_numpy(E).cuda(), 0.15)
+    assert got.G == want.G + 2 and got.nnz == want.nnz + 2
+    assert torch.equal(got.members[:want.nnz], want.members) and torch.equal(got.row_ptr[:want.G + 1], want.row_ptr)
