@@ -529,13 +529,15 @@ int pcg_propose(const pcg_groups *groups, const void *draft_logits, pcg_dtype dt
   rs.inv_npos1 = 1.0;
   const Factors f = factors(temperature);
   hipStream_t stream = (hipStream_t) hip_stream;
-  StatPart *parts = (StatPart *) workspace;
+  StatPart *parts = propose_in_rows(V) ? nullptr : (StatPart *) workspace;
   StageTimer tm(stream);
   hipError_t e;
-  tm.begin(kStageStats);
-  // cached pass: the draw that follows is a chain of small reads into the same rows
-  if ((e = launch_row_stats(rs, bf16, V, rows, f.c, false, parts, stream)) != hipSuccess) return hip_fail(e);
-  tm.end(kStageStats);
+  if (parts) {
+    tm.begin(kStageStats);
+    // cached pass: the draw that follows is a chain of small reads into the same rows
+    if ((e = launch_row_stats(rs, bf16, V, rows, f.c, false, parts, stream)) != hipSuccess) return hip_fail(e);
+    tm.end(kStageStats);
+  }
   tm.begin(kStagePropose);
   if ((e = launch_propose(rs, bf16, V, K, pos0, f.c, parts, groups->tok_ptr, groups->tok_groups,
                           groups->weights ? groups->tok_weights : nullptr, seed, offset,

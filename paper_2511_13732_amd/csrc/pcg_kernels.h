@@ -28,6 +28,9 @@ hipError_t launch_accept_thin(const AcceptArgs &a, bool bf16, int32_t B, const i
                               int32_t max_trials, hipStream_t stream);
 int32_t thin_max_parts();
 
+// Whether a draft row goes through one workgroup, statistics and draw (launch_propose without parts).
+bool propose_in_rows(int32_t V);
+
 hipError_t launch_propose(const RowSet &rs, bool bf16, int32_t V, int32_t K, int32_t pos0, float c,
                           const StatPart *parts, const int32_t *tok_ptr, const int32_t *tok_groups,
                           const float *tok_weights, uint64_t seed, uint64_t offset,

@@ -126,3 +126,28 @@ def test_group_construction_beside_a_row_that_is_not_finite():
     got = pcg.asg_build_exact(torch.from_numpy(E).cuda(), 0.15)
     assert got.G == want.G + 2 and got.nnz == want.nnz + 2
     assert torch.equal(got.members[:want.nnz], want.members) and torch.equal(got.row_ptr[:want.G + 1], want.row_ptr)
+
+
+# proposals: a draft row in one workgroup up to 64 parts (V = 131 072), in two launches beyond; one row,
+# more rows than compute units; rows of less than one 16-byte piece
+@pytest.mark.parametrize("V,B,K,dtype,off", [(2, 3, 2, "f32", 0), (5, 300, 3, "bf16", 1), (2048, 1, 1, "bf16", 0),
+                                             (32769, 5, 3, "f32", 3), (131072, 2, 1, "bf16", 0), (131073, 2, 2, "bf16", 5)])
+def test_propose_rows(V, B, K, dtype, off):
+    rp, mem = W.random_groups(V, max(1, V // 2), 1, min(V, 5), seed=V) if V < 100000 else \
+        (np.arange(V + 1, dtype=np.int32), np.arange(V, dtype=np.int32)[::-1].copy())
+    og = oracle_groups(V, rp, mem)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=False, reverse=True)
+    rng = np.random.default_rng([V, B, K])
+    x = torch.from_numpy((3.0 * rng.standard_normal((B, K, V))).astype(np.float32))
+    if dtype == "bf16":
+        x = x.to(torch.bfloat16)
+    if B > 2 and V > 2:
+        x[1, 0, : V - 1] = -float("inf")          # all mass on the last token
+    x = rows_at(x, off)
+    diag = torch.zeros(8, dtype=torch.int32, device="cuda")
+    tok, grp = pcg.propose(dg, x, temperature=1.1, seed=4, offset=2, pos0=1, diag=diag)
+    ref = oracle.propose(og, oracle.reverse_index(og), as_oracle_logits(x), temperature=1.1, seed=4, offset=2, pos0=1, nthreads=8)
+    assert compare_proposals(tok, grp, ref, og).tolerated <= 1
+    assert diag[pcg.Diag.NAMES.index("sequences")] == B * K
+    if B > 2 and V > 2:
+        assert int(tok[1, 0]) == V - 1
