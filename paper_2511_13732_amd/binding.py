@@ -351,10 +351,9 @@ def _workspace(device: torch.device, nbytes: int) -> torch.Tensor:
     refers to it may be queued or recorded).  While the stream is being captured into a graph the
     caller must bring the workspace (or use ``static_scratch``): a tensor allocated here would
     be tied to the capture."""
-    stream = torch.cuda.current_stream(device)
     if torch.cuda.is_current_stream_capturing():
         raise RuntimeError("pass workspace= (or static_scratch=True) when calling under stream capture")
-    key = (device, stream.cuda_stream)
+    key = (device, _stream(device))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         if ws is not None:
@@ -373,7 +372,21 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    """The current stream of the device as the library takes it.  (The stream object that
+    torch.cuda.current_stream builds costs 1.8 us a call, as much as a kernel launch.)"""
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+def _call(device, what: str, fn, *args):
+    """fn(*args, stream) with `device` current; a non-zero status is raised.  The device guard (1.3 us)
+    is entered only where the caller is on another device."""
+    if torch.cuda.current_device() == device.index:
+        rc = fn(*args, _stream(device))
+    else:
+        with torch.cuda.device(device):
+            rc = fn(*args, _stream(device))
+    if rc:
+        raise PcgError(rc, what)
 
 
 def group_probs_workspace_bytes(V: int, rows: int) -> int:
@@ -394,14 +407,11 @@ def group_probs(groups: Groups, logits: torch.Tensor, temperature: float = 1.0,
     if out is None:
         out = torch.empty((rows, groups.G), dtype=torch.float32, device=logits.device)
     assert out.shape == (rows, groups.G) and out.is_contiguous() and out.dtype == torch.float32
-    need = group_probs_workspace_bytes(groups.V, rows)
-    ws = _workspace(logits.device, need) if workspace is None else workspace
-    gs = groups.struct()
-    with torch.cuda.device(logits.device):
-        _check(lib().pcg_group_probs(C.byref(gs), logits.data_ptr(), _dtype_code(logits), rows,
-                                     logits.stride(0) if rows > 1 else groups.V,
-                                     float(temperature), out.data_ptr(), ws.data_ptr(),
-                                     ws.numel(), _stream(logits.device)), "pcg_group_probs")
+    dev = logits.device
+    ws = _workspace(dev, group_probs_workspace_bytes(groups.V, rows)) if workspace is None else workspace
+    _call(dev, "pcg_group_probs", lib().pcg_group_probs, C.byref(groups.struct()), logits.data_ptr(),
+          _dtype_code(logits), rows, logits.stride(0) if rows > 1 else groups.V, float(temperature),
+          out.data_ptr(), ws.data_ptr(), ws.numel())
     return out
 
 
@@ -430,51 +440,51 @@ def verify(groups: Groups, target_logits: torch.Tensor, draft_logits: torch.Tens
     ``static_scratch`` calls pcg_verify_static: no workspace is passed or allocated, the
     library's own array is used (``out`` must then be given, so that nothing is allocated).
     """
-    assert target_logits.dim() == 3 and draft_logits.dim() == 3
-    K, V = target_logits.shape[1] - 1, target_logits.shape[2]
-    assert V == groups.V and draft_logits.shape[2] == V and draft_logits.shape[1] >= K
-    assert target_logits.stride(2) == 1 and draft_logits.stride(2) == 1
-    assert target_logits.dtype == draft_logits.dtype
-    dev = target_logits.device
-    assert dev == groups.device == draft_logits.device
-    if B is None:
-        B = target_logits.shape[0]
-    shared = B != target_logits.shape[0]
-    if shared:
-        assert target_logits.shape[0] == 1 and draft_logits.shape[0] == 1
-    tbs = 0 if shared else (target_logits.stride(0) if B > 1 else 0)
-    dbs = 0 if shared else (draft_logits.stride(0) if B > 1 else 0)
-    assert prop_tokens.dtype == torch.int32 and prop_groups.dtype == torch.int32
+    assert target_logits.device == groups.device == draft_logits.device
     assert prop_tokens.is_contiguous() and prop_groups.is_contiguous()
-    assert prop_tokens.numel() == B * K and prop_groups.numel() == B * K
+    B, K, V, dev, rows = _step_rows(groups, target_logits, draft_logits, prop_tokens, prop_groups, B)
     if out is None:
-        out = VerifyOutput(torch.empty(B, dtype=torch.int32, device=dev),
-                           torch.empty((B, K + 1), dtype=torch.int32, device=dev),
-                           torch.empty((B, K + 1), dtype=torch.int32, device=dev))
-    gs = groups.struct()
+        out = _step_outputs(B, K, dev)
+    args = (C.byref(groups.struct()), *rows, float(temperature), prop_tokens.data_ptr(), prop_groups.data_ptr(),
+            seed, offset, out.accept_len.data_ptr(), out.out_tokens.data_ptr(), out.out_groups.data_ptr(),
+            None if diag is None else diag.data_ptr())
     if static_scratch:
         assert workspace is None
-        with torch.cuda.device(dev):
-            _check(lib().pcg_verify_static(
-                C.byref(gs), target_logits.data_ptr(), draft_logits.data_ptr(),
-                _dtype_code(target_logits), B, K, tbs, target_logits.stride(1), dbs,
-                draft_logits.stride(1) if K > 1 else V, float(temperature), prop_tokens.data_ptr(),
-                prop_groups.data_ptr(), seed, offset, out.accept_len.data_ptr(),
-                out.out_tokens.data_ptr(), out.out_groups.data_ptr(),
-                None if diag is None else diag.data_ptr(), _stream(dev)), "pcg_verify_static")
+        _call(dev, "pcg_verify_static", lib().pcg_verify_static, *args)
         return out
-    need = verify_workspace_bytes(V, groups.G, B, K)
-    ws = _workspace(dev, need) if workspace is None else workspace
-    with torch.cuda.device(dev):
-        _check(lib().pcg_verify(C.byref(gs), target_logits.data_ptr(), draft_logits.data_ptr(),
-                                _dtype_code(target_logits), B, K, tbs, target_logits.stride(1),
-                                dbs, draft_logits.stride(1) if K > 1 else V, float(temperature),
-                                prop_tokens.data_ptr(), prop_groups.data_ptr(), seed, offset,
-                                out.accept_len.data_ptr(), out.out_tokens.data_ptr(),
-                                out.out_groups.data_ptr(),
-                                None if diag is None else diag.data_ptr(), ws.data_ptr(),
-                                ws.numel(), _stream(dev)), "pcg_verify")
+    ws = _workspace(dev, verify_workspace_bytes(V, groups.G, B, K)) if workspace is None else workspace
+    _call(dev, "pcg_verify", lib().pcg_verify, *args, ws.data_ptr(), ws.numel())
     return out
+
+
+def _step_rows(groups: Groups, target_logits, draft_logits, prop_tokens, prop_groups, B):
+    """Checks the tensors of a step; (B, K, V, device, the C arguments from target_logits to the last
+    stride)."""
+    tshape, dshape = target_logits.shape, draft_logits.shape
+    assert len(tshape) == 3 and len(dshape) == 3
+    Bt, K, V = tshape
+    K -= 1
+    assert V == groups.V and dshape[2] == V and dshape[1] >= K
+    ts, ds = target_logits.stride(), draft_logits.stride()
+    assert ts[2] == 1 and ds[2] == 1
+    assert target_logits.dtype == draft_logits.dtype
+    dev = target_logits.device
+    if B is None:
+        B = Bt
+    shared = B != Bt
+    if shared:
+        assert Bt == 1 and dshape[0] == 1
+    one = shared or B <= 1
+    assert prop_tokens.dtype == torch.int32 and prop_groups.dtype == torch.int32
+    assert prop_tokens.numel() == B * K and prop_groups.numel() == B * K
+    return B, K, V, dev, (target_logits.data_ptr(), draft_logits.data_ptr(), _dtype_code(target_logits), B, K,
+                          0 if one else ts[0], ts[1], 0 if one else ds[0], ds[1] if K > 1 else V)
+
+
+def _step_outputs(B: int, K: int, dev) -> VerifyOutput:
+    return VerifyOutput(torch.empty(B, dtype=torch.int32, device=dev),
+                        torch.empty((B, K + 1), dtype=torch.int32, device=dev),
+                        torch.empty((B, K + 1), dtype=torch.int32, device=dev))
 
 
 THIN_MAX_TRIALS = 65520      # PCG_THIN_MAX_TRIALS of pcg.h
@@ -494,39 +504,16 @@ def verify_thinning(groups: Groups, target_logits: torch.Tensor, draft_logits: t
     ``verify``; ``groups`` must have been built with ``reverse=True``.  Returns the outputs and
     the int32 [B] number of thinning trials per sequence."""
     assert groups.tok_ptr is not None, "build the groups with reverse=True"
-    assert target_logits.dim() == 3 and draft_logits.dim() == 3
-    K, V = target_logits.shape[1] - 1, target_logits.shape[2]
-    assert V == groups.V and draft_logits.shape[2] == V and draft_logits.shape[1] >= K
-    assert target_logits.stride(2) == 1 and draft_logits.stride(2) == 1
-    assert target_logits.dtype == draft_logits.dtype
-    dev = target_logits.device
-    if B is None:
-        B = target_logits.shape[0]
-    shared = B != target_logits.shape[0]
-    if shared:
-        assert target_logits.shape[0] == 1 and draft_logits.shape[0] == 1
-    tbs = 0 if shared else (target_logits.stride(0) if B > 1 else 0)
-    dbs = 0 if shared else (draft_logits.stride(0) if B > 1 else 0)
-    assert prop_tokens.dtype == torch.int32 and prop_groups.dtype == torch.int32
-    assert prop_tokens.numel() == B * K and prop_groups.numel() == B * K
+    B, K, V, dev, rows = _step_rows(groups, target_logits, draft_logits, prop_tokens, prop_groups, B)
     if out is None:
-        out = VerifyOutput(torch.empty(B, dtype=torch.int32, device=dev),
-                           torch.empty((B, K + 1), dtype=torch.int32, device=dev),
-                           torch.empty((B, K + 1), dtype=torch.int32, device=dev))
+        out = _step_outputs(B, K, dev)
     if trials is None:
         trials = torch.empty(B, dtype=torch.int32, device=dev)
-    need = verify_thinning_workspace_bytes(V, B, K)
-    ws = _workspace(dev, need) if workspace is None else workspace
-    gs = groups.struct()
-    with torch.cuda.device(dev):
-        _check(lib().pcg_verify_thinning(
-            C.byref(gs), target_logits.data_ptr(), draft_logits.data_ptr(),
-            _dtype_code(target_logits), B, K, tbs, target_logits.stride(1), dbs,
-            draft_logits.stride(1) if K > 1 else V, float(temperature), prop_tokens.data_ptr(),
-            prop_groups.data_ptr(), seed, offset, out.accept_len.data_ptr(),
-            out.out_tokens.data_ptr(), out.out_groups.data_ptr(), trials.data_ptr(),
-            None if diag is None else diag.data_ptr(), ws.data_ptr(), ws.numel(), _stream(dev)),
-            "pcg_verify_thinning")
+    ws = _workspace(dev, verify_thinning_workspace_bytes(V, B, K)) if workspace is None else workspace
+    _call(dev, "pcg_verify_thinning", lib().pcg_verify_thinning, C.byref(groups.struct()), *rows,
+          float(temperature), prop_tokens.data_ptr(), prop_groups.data_ptr(), seed, offset,
+          out.accept_len.data_ptr(), out.out_tokens.data_ptr(), out.out_groups.data_ptr(), trials.data_ptr(),
+          None if diag is None else diag.data_ptr(), ws.data_ptr(), ws.numel())
     return out, trials
 
 
@@ -544,32 +531,27 @@ def propose(groups: Groups, draft_logits: torch.Tensor, *, temperature: float = 
     leading dimension of 1, all B sequences share the rows.  Returns int32 [B, K] tokens and
     groups."""
     assert groups.tok_ptr is not None, "build the groups with reverse=True"
-    assert draft_logits.dim() == 3 and draft_logits.stride(2) == 1
-    K, V = draft_logits.shape[1], draft_logits.shape[2]
+    shape, strides = draft_logits.shape, draft_logits.stride()
+    assert len(shape) == 3 and strides[2] == 1
+    Bd, K, V = shape
     assert V == groups.V
     dev = draft_logits.device
     if B is None:
-        B = draft_logits.shape[0]
-    shared = B != draft_logits.shape[0]
+        B = Bd
+    shared = B != Bd
     if shared:
-        assert draft_logits.shape[0] == 1
-    dbs = 0 if shared else (draft_logits.stride(0) if B > 1 else 0)
+        assert Bd == 1
     if prop_tokens is None:
         prop_tokens = torch.empty((B, K), dtype=torch.int32, device=dev)
     if prop_groups is None:
         prop_groups = torch.empty((B, K), dtype=torch.int32, device=dev)
     assert prop_tokens.dtype == torch.int32 and prop_groups.dtype == torch.int32
     assert prop_tokens.numel() == B * K and prop_groups.numel() == B * K
-    need = propose_workspace_bytes(V, B, K)
-    ws = _workspace(dev, need) if workspace is None else workspace
-    gs = groups.struct()
-    with torch.cuda.device(dev):
-        _check(lib().pcg_propose(
-            C.byref(gs), draft_logits.data_ptr(), _dtype_code(draft_logits), B, K, pos0, dbs,
-            draft_logits.stride(1) if K > 1 else V, float(temperature), seed, offset,
-            prop_tokens.data_ptr(), prop_groups.data_ptr(),
-            None if diag is None else diag.data_ptr(), ws.data_ptr(), ws.numel(), _stream(dev)),
-            "pcg_propose")
+    ws = _workspace(dev, propose_workspace_bytes(V, B, K)) if workspace is None else workspace
+    _call(dev, "pcg_propose", lib().pcg_propose, C.byref(groups.struct()), draft_logits.data_ptr(),
+          _dtype_code(draft_logits), B, K, pos0, 0 if shared or B <= 1 else strides[0],
+          strides[1] if K > 1 else V, float(temperature), seed, offset, prop_tokens.data_ptr(),
+          prop_groups.data_ptr(), None if diag is None else diag.data_ptr(), ws.data_ptr(), ws.numel())
     return prop_tokens, prop_groups
 
 
