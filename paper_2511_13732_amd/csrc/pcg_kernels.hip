@@ -1989,7 +1989,6 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   __shared__ Probe probes[PCG_MAX_K];
   __shared__ __attribute__((aligned(16))) float tab[kSmallTokens + kBanks];
   __shared__ __attribute__((aligned(16))) float sums[kSmallGroups];
-  __shared__ int next_item;
   constexpr bool kWeighted = SUMS == kSumsPreparedWeighted || SUMS == kSumsCsrWeighted;
   const int b = blockIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
@@ -1997,45 +1996,39 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   const RowSet &rs = a.rs;
   const int32_t V = a.V, G = a.G, K = a.K;
 
-  // the first multiplicities and the first blocks of slots do not depend on any row
+  // Row parts, dealt to the waves in turn, and probes, one each for the first waves.  Everything starts
+  // with a trip to memory, so a wave asks for its first two parts before anything else and keeps two
+  // on their way: they come in behind the probes' chains of loads.  (Handed out one by one to
+  // whichever wave was free, a part at a time ahead, 34 parts and 8 probes took 7.4 us instead of 6.5, of which
+  // their arithmetic on one compute unit is 5.6.)
+  const int32_t nparts_all = (2 * K + 1) * a.nparts;
+  RowPart<BF16, true, false> raw[2];    // cached: the decision rows are read again
+  auto ask = [&](RowPart<BF16, true, false> &to, int32_t it) {
+    const int32_t r = it / a.nparts, part = it % a.nparts;
+    const int64_t row = r <= K ? (int64_t) b * (K + 1) + r : rs.nrows0 + (int64_t) b * K + (r - K - 1);
+    to.load(row_base(rs, row, BF16), part * kPartElems, V, lane);
+  };
+  if (wave < nparts_all) ask(raw[0], wave);
+  if (wave + kGatherWaves < nparts_all) ask(raw[1], wave + kGatherWaves);
+  // the first multiplicities do not depend on any row
   const int32_t first = threadIdx.x * kTokensPerThread;
   float m[8];
   if (first < V) load8_mult<true>(kWeighted ? nullptr : a.mult, slice_start<true>(first, V), V, m);
+  if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
+  for (int32_t i = wave; i < K; i += kGatherWaves) probe_row<BF16>(rs, pa, b, i, a.c, lane, probes + i);
+  auto reduce = [&](RowPart<BF16, true, false> &from, int32_t it) {
+    float x[32];
+    from.get(x, (it % a.nparts) * kPartElems, V, lane);
+    if (it + 2 * kGatherWaves < nparts_all) ask(from, it + 2 * kGatherWaves);
+    const StatPart sp = part_stats(x, a.c);
+    if (lane == kWave - 1) parts[it] = sp;
+  };
+  for (int32_t it = wave; it < nparts_all; it += 2 * kGatherWaves) {
+    reduce(raw[0], it);
+    if (it + kGatherWaves < nparts_all) reduce(raw[1], it + kGatherWaves);
+  }
   SlotStream<kWeighted> stream;
   if constexpr (SUMS <= kSumsPreparedWeighted) load_desc(p.desc, p.blocks_per_chunk, wave, stream.steps, stream.offs);
-
-  // Row parts and probes, handed to whichever wave is free: the probes, chains of dependent loads,
-  // first; a wave asks for its next part before it works on the one that has come.
-  if (threadIdx.x == 0) next_item = kGatherWaves;
-  lds_barrier();
-  if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
-  const int32_t nitems = K + (2 * K + 1) * a.nparts;
-  auto take = [&]() {
-    int32_t n = 0;
-    if (lane == 0) n = atomicAdd(&next_item, 1);
-    return (int32_t) __builtin_amdgcn_readfirstlane(n);
-  };
-  int32_t item = wave;
-  while (item < K) {
-    probe_row<BF16>(rs, pa, b, item, a.c, lane, probes + item);
-    item = take();
-  }
-  RowPart<BF16, true, false> raw;       // cached: the decision rows are read again
-  auto ask = [&](int32_t it) {
-    const int32_t r = (it - K) / a.nparts, part = (it - K) % a.nparts;
-    const int64_t row = r <= K ? (int64_t) b * (K + 1) + r : rs.nrows0 + (int64_t) b * K + (r - K - 1);
-    raw.load(row_base(rs, row, BF16), part * kPartElems, V, lane);
-  };
-  if (item < nitems) ask(item);
-  while (item < nitems) {
-    float x[32];
-    raw.get(x, ((item - K) % a.nparts) * kPartElems, V, lane);
-    const int32_t next = take();
-    if (next < nitems) ask(next);
-    const StatPart sp = part_stats(x, a.c);
-    if (lane == kWave - 1) parts[item - K] = sp;
-    item = next;
-  }
   // the first chunk's slots and the places of its sums: on their way through the accept scan
   uint32_t nsteps[kMaxBlocksPerWave], noffs[kMaxBlocksPerWave];
   uint16_t where[kMaxAcc];
