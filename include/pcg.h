@@ -474,7 +474,8 @@ int pcg_groups_prepare_weights_host(int32_t V, int32_t G, const int32_t *row_ptr
  * calls are recorded; later ones run unrecorded.  Stage names: pcg_stage_name(i).  The stage
  * "event_overhead" is an empty event pair recorded at the start of each call: the time an
  * event pair adds, which is included in every other stage's figure.  A step that is small enough
- * to run as one kernel is recorded under "gather"; its other stages then read as event_overhead.
+ * to run as one or two kernels has everything after row_stats (or with it) recorded under "gather";
+ * the stages so absorbed then read as event_overhead.
  * Not thread-safe; one profile at a time.
  */
 int pcg_profile_begin(int32_t max_calls);

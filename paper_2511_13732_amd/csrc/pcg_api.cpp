@@ -369,15 +369,23 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
 
   StageTimer tm(stream);
   hipError_t e;
-  if (small_step_fits(*groups, B, K)) {
+  const StepShape shape = step_shape(*groups, B, K);
+  if (shape != StepShape::kFour) {
+    // Everything after the statistics, or with them, is one kernel: recorded under gather; the
+    // stages that it has absorbed are empty event pairs.
     AcceptArgs small = aa;
-    small.parts = nullptr;              // everything between the phases stays in LDS
-    small.probes = nullptr;
-    small.rowstat = nullptr;
-    // one kernel: recorded under gather; the stages it has absorbed are empty event pairs
-    for (Stage st : {kStageStats, kStageAccept}) { tm.begin(st); tm.end(st); }
+    small.rowstat = nullptr;            // stays in LDS
+    tm.begin(kStageStats);
+    // cached pass: the rows are small, and a single compute unit reads the decision rows again
+    if (shape == StepShape::kTwo &&
+        (e = launch_row_stats(rs, bf16, V, rows, f.c, false, parts, stream, &pa)) != hipSuccess)
+      return hip_fail(e);
+    tm.end(kStageStats);
+    tm.begin(kStageAccept);
+    tm.end(kStageAccept);
     tm.begin(kStageGather);
-    if ((e = launch_small_step(small, fa, pa, *groups, bf16, B, stream)) != hipSuccess) return hip_fail(e);
+    if ((e = launch_small_step(small, fa, pa, *groups, bf16, shape == StepShape::kOne, B, stream)) != hipSuccess)
+      return hip_fail(e);
     tm.end(kStageGather);
     tm.begin(kStageFinalize);
     tm.end(kStageFinalize);
@@ -403,12 +411,12 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
     // sequence's row parts were, which nothing reads after the accept scan.
     const int64_t room = (groups->G + kChunkStep - 1) / kChunkStep;
     const int64_t parts_room = (2 * K + 1) * (int64_t) nparts * (sizeof(StatPart) / sizeof(double));
-    const CsrShape shape = csr_shape(V, groups->G, groups->nnz, B, std::max(room, parts_room));
-    nchunks = shape.nchunks;
-    chunk_groups = shape.chunk_groups;
+    const CsrShape cut = csr_shape(V, groups->G, groups->nnz, B, std::max(room, parts_room));
+    nchunks = cut.nchunks;
+    chunk_groups = cut.chunk_groups;
     csum_stride = nchunks <= room ? room : parts_room;
     if (nchunks > room) csum = (double *) parts;
-    e = launch_gather(*groups, shape, B, table, nullptr, csum, csum_stride, runs, stream);
+    e = launch_gather(*groups, cut, B, table, nullptr, csum, csum_stride, runs, stream);
   }
   if (e != hipSuccess) return hip_fail(e);
   tm.end(kStageGather);

@@ -56,11 +56,15 @@ hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, 
 hipError_t launch_gather_prepared(const pcg_groups &g, int32_t nrows, const float *table, float *out,
                                   double *csum, double *runs, hipStream_t stream);
 
-// A whole pcg_verify step as one launch of one workgroup per sequence, where the sequence fits a
-// compute unit's LDS and B workgroups are the better way to run it.
-bool small_step_fits(const pcg_groups &g, int32_t B, int32_t K);
+// How many launches a pcg_verify step takes: one (a workgroup per sequence does everything), two (the
+// statistics and probes spread over the chip, then a workgroup per sequence), or four.
+enum class StepShape { kOne, kTwo, kFour };
+StepShape step_shape(const pcg_groups &g, int32_t B, int32_t K);
+
+// The launch of a workgroup per sequence.  stats: it forms the row parts and probes itself, otherwise
+// a.parts and a.probes hold them.
 hipError_t launch_small_step(const AcceptArgs &a, const FinalizeArgs &fa, const ProbeArgs &pa,
-                             const pcg_groups &g, bool bf16, int32_t B, hipStream_t stream);
+                             const pcg_groups &g, bool bf16, bool stats, int32_t B, hipStream_t stream);
 
 hipError_t launch_finalize(const FinalizeArgs &fa, bool bf16, const pcg_groups &g, int32_t B,
                            const double *csum, int64_t csum_stride, const double *runs, int32_t nchunks,

@@ -15,8 +15,9 @@
 //                 written.
 //   finalize      per sequence: the chunk and the run that hold u * total, the run's 16 sums
 //                 formed again, the group by inverse CDF, then the token inside it (Eq. 10)
-// A step that is small, or has many sequences of moderate size, runs as one kernel instead
-// (small_step): one workgroup per sequence does all of the above with everything in LDS.
+// A step that is small, or has many sequences of moderate size, runs as one or two kernels instead
+// (small_step, after row_stats where the rows are many): one workgroup per sequence does all of the
+// above with everything in LDS.
 // pcg_group_probs runs row_stats, a weights kernel (q(t) / N(t)) and the same gather;
 // pcg_verify_thinning runs row_stats and accept_thin; pcg_propose runs row_stats and propose.
 #include "pcg_kernels.h"
@@ -1897,9 +1898,10 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
 // Four launches cost about 5 us each whatever the size (the launch, a trip to memory for what the
 // kernel before has written, a drain); here the parts, the probes, the table and the sums pass
 // through LDS, and what is left is the chain of loads proposal -> members -> logits and group ->
-// members -> logits.  Bound by latency: at V = 4096, K = 8 the rows and probes take 7.7 us (34 parts
-// and 8 probes on 16 waves), the accept scan 1.7, the table 1.3, the sums 2.8, the draws 3.2; the whole
-// call 23.8 -> 19.8 us at B = 8, and 22.8 -> 13.5 at V = 1024, K = 4, B = 1.
+// members -> logits.  Bound by latency, and by one compute unit's arithmetic in the statistics (34
+// parts and 8 probes of V = 4096, K = 8: 6.5 us), which a launch of their own spreads over the chip where
+// there are more than a few.  Accept scan 1.7 us, table 1.3, sums 2.8, draws 3.2.  The whole call: V = 1024,
+// K = 4, B = 1 22.8 -> 12.9 us (one launch); V = 4096, K = 8, B = 8 23.8 -> 17.4 (two).
 // =============================================================================================
 
 constexpr int kSmallTokens = 16384;    // table entries in LDS: 64 KB
@@ -1980,13 +1982,14 @@ __device__ CdfPick pick_group(const float *sums, int32_t n, double u) {
   return res;
 }
 
-template <bool BF16, int SUMS>
+// STATS: the row parts and probes are formed here; otherwise row_stats has left them in memory.
+template <bool BF16, int SUMS, bool STATS>
 __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a, FinalizeArgs fa, ProbeArgs pa,
                                                                     PreparedView p, int32_t nnz) {
   static_assert(kAcceptThreads == kGatherThreads, "one workgroup plays both parts");
   __shared__ AcceptShared sh;
-  __shared__ StatPart parts[kSmallParts];
-  __shared__ Probe probes[PCG_MAX_K];
+  __shared__ StatPart parts[STATS ? kSmallParts : 1];
+  __shared__ Probe probes[STATS ? PCG_MAX_K : 1];
   __shared__ __attribute__((aligned(16))) float tab[kSmallTokens + kBanks];
   __shared__ __attribute__((aligned(16))) float sums[kSmallGroups];
   constexpr bool kWeighted = SUMS == kSumsPreparedWeighted || SUMS == kSumsCsrWeighted;
@@ -1996,36 +1999,44 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   const RowSet &rs = a.rs;
   const int32_t V = a.V, G = a.G, K = a.K;
 
-  // Row parts, dealt to the waves in turn, and probes, one each for the first waves.  Everything starts
-  // with a trip to memory, so a wave asks for its first two parts before anything else and keeps two
-  // on their way: they come in behind the probes' chains of loads.  (Handed out one by one to
-  // whichever wave was free, a part at a time ahead, 34 parts and 8 probes took 7.4 us instead of 6.5, of which
-  // their arithmetic on one compute unit is 5.6.)
-  const int32_t nparts_all = (2 * K + 1) * a.nparts;
-  RowPart<BF16, true, false> raw[2];    // cached: the decision rows are read again
-  auto ask = [&](RowPart<BF16, true, false> &to, int32_t it) {
-    const int32_t r = it / a.nparts, part = it % a.nparts;
-    const int64_t row = r <= K ? (int64_t) b * (K + 1) + r : rs.nrows0 + (int64_t) b * K + (r - K - 1);
-    to.load(row_base(rs, row, BF16), part * kPartElems, V, lane);
-  };
-  if (wave < nparts_all) ask(raw[0], wave);
-  if (wave + kGatherWaves < nparts_all) ask(raw[1], wave + kGatherWaves);
   // the first multiplicities do not depend on any row
   const int32_t first = threadIdx.x * kTokensPerThread;
   float m[8];
-  if (first < V) load8_mult<true>(kWeighted ? nullptr : a.mult, slice_start<true>(first, V), V, m);
-  if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
-  for (int32_t i = wave; i < K; i += kGatherWaves) probe_row<BF16>(rs, pa, b, i, a.c, lane, probes + i);
-  auto reduce = [&](RowPart<BF16, true, false> &from, int32_t it) {
-    float x[32];
-    from.get(x, (it % a.nparts) * kPartElems, V, lane);
-    if (it + 2 * kGatherWaves < nparts_all) ask(from, it + 2 * kGatherWaves);
-    const StatPart sp = part_stats(x, a.c);
-    if (lane == kWave - 1) parts[it] = sp;
+  auto load_m = [&]() {
+    if (first < V) load8_mult<true>(kWeighted ? nullptr : a.mult, slice_start<true>(first, V), V, m);
   };
-  for (int32_t it = wave; it < nparts_all; it += 2 * kGatherWaves) {
-    reduce(raw[0], it);
-    if (it + kGatherWaves < nparts_all) reduce(raw[1], it + kGatherWaves);
+  if constexpr (STATS) {
+    // Row parts, dealt to the waves in turn, and probes, one each for the first waves.  Everything starts
+    // with a trip to memory, so a wave asks for its first two parts before anything else and keeps two
+    // on their way: they come in behind the probes' chains of loads.  (Handed out one by one to
+    // whichever wave was free, a part at a time ahead, 34 parts and 8 probes took 7.4 us instead of 6.5, of which
+    // their arithmetic on one compute unit is 5.6.)
+    const int32_t nparts_all = (2 * K + 1) * a.nparts;
+    RowPart<BF16, true, false> raw[2];    // cached: the decision rows are read again
+    auto ask = [&](RowPart<BF16, true, false> &to, int32_t it) {
+      const int32_t r = it / a.nparts, part = it % a.nparts;
+      const int64_t row = r <= K ? (int64_t) b * (K + 1) + r : rs.nrows0 + (int64_t) b * K + (r - K - 1);
+      to.load(row_base(rs, row, BF16), part * kPartElems, V, lane);
+    };
+    if (wave < nparts_all) ask(raw[0], wave);
+    if (wave + kGatherWaves < nparts_all) ask(raw[1], wave + kGatherWaves);
+    load_m();
+    if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
+    for (int32_t i = wave; i < K; i += kGatherWaves) probe_row<BF16>(rs, pa, b, i, a.c, lane, probes + i);
+    auto reduce = [&](RowPart<BF16, true, false> &from, int32_t it) {
+      float x[32];
+      from.get(x, (it % a.nparts) * kPartElems, V, lane);
+      if (it + 2 * kGatherWaves < nparts_all) ask(from, it + 2 * kGatherWaves);
+      const StatPart sp = part_stats(x, a.c);
+      if (lane == kWave - 1) parts[it] = sp;
+    };
+    for (int32_t it = wave; it < nparts_all; it += 2 * kGatherWaves) {
+      reduce(raw[0], it);
+      if (it + kGatherWaves < nparts_all) reduce(raw[1], it + kGatherWaves);
+    }
+  } else {
+    load_m();
+    if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
   }
   SlotStream<kWeighted> stream;
   if constexpr (SUMS <= kSumsPreparedWeighted) load_desc(p.desc, p.blocks_per_chunk, wave, stream.steps, stream.offs);
@@ -2046,7 +2057,9 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   };
   if constexpr (SUMS <= kSumsPreparedWeighted) ask_chunk(0);
   lds_barrier();
-  accept_phase<true>(sh, a, b, true, probes, parts, parts + (K + 1) * a.nparts);
+  if constexpr (STATS) accept_phase<true>(sh, a, b, true, probes, parts, parts + (K + 1) * a.nparts);
+  else accept_phase<true>(sh, a, b, true, a.probes + (int64_t) b * K, a.parts + (int64_t) b * (K + 1) * a.nparts,
+                          a.parts + (rs.nrows0 + (int64_t) b * K) * a.nparts);
 
   // the table on the decision row, straight into LDS
   const int32_t istar = sh.istar;
@@ -2299,36 +2312,45 @@ hipError_t launch_gather_prepared(const pcg_groups &g, int32_t nrows, const floa
   return hipGetLastError();
 }
 
-bool small_step_fits(const pcg_groups &g, int32_t B, int32_t K) {
-  // what the kernel's LDS and its row loads can take
+StepShape step_shape(const pcg_groups &g, int32_t B, int32_t K) {
+  // what the small step's LDS and its row loads can take
   const int64_t row_parts = (2 * (int64_t) K + 1) * stats_nparts(g.V);
-  if (g.V < 8 || g.V > kSmallTokens || g.G > kSmallGroups || row_parts > kSmallParts) return false;
-  if (g.prepared && (g.prepared_info->ntiles != 1 || g.prepared_info->tile_len > kSmallTokens)) return false;
-  if (B > 256) return false;                        // one workgroup per compute unit at a time
-  // Where one compute unit per sequence is the faster way.  From 144 sequences on it keeps the chip
-  // busy and always is (B = 256, K = 8: V = 1024 25.1 -> 16.8 us, 16 384 60.1 -> 47.1).  With few
-  // sequences the four kernels take 18 to 25 us whatever the size and spread one sequence over many
-  // compute units, so it has to be small: 8 items (probes and row parts) cost it about 1 us, as do 32 K
-  // entries and 2.5 K tokens.  B = 1, K = 8, members each: V = 4096, 16: 21.3 -> 19.0 us (load 71);
-  // V = 2048, 100: 26.0 -> 20.3 (82); V = 4096, 32, fp32: 22.8 -> 20.5 (88); V = 8192, 16: 21.5 -> 26.6
-  // (135).  From the CSR the crossing is earlier: V = 1024 19.3 -> 14.6 (32), V = 4096, K = 4
-  // 18.9 -> 19.0 (51).
-  const int64_t load = K + row_parts + g.nnz / 4096 + g.V / 320;
-  return B >= 144 || load <= (g.prepared ? 90 : 50);
+  if (g.V < 8 || g.V > kSmallTokens || g.G > kSmallGroups || B > 256) return StepShape::kFour;
+  if (g.prepared && (g.prepared_info->ntiles != 1 || g.prepared_info->tile_len > kSmallTokens))
+    return StepShape::kFour;
+  // One compute unit per sequence for all that follows the statistics, or four kernels that spread a
+  // sequence over the chip but pay for three more boundaries.  What the one unit has to do grows with the
+  // tokens (table) and the entries; from 128 sequences on the four kernels have no idle units left to
+  // spread to, and near 256 they lose at any size.  Kernels' time, four -> two launches, K = 8, members:
+  //   prepared, B = 1:   V = 4096, 16: 21.6 -> 16.7 us (load 28);  8192, 32: 22.9 -> 22.8 (89);
+  //                      12 000, 24: 22.8 -> 26.3 (107);  B = 128: 38.3 -> 33.4;
+  //                      16 384, 32 (179): B = 128 44.7 -> 43.8, B = 256 66.8 -> 56.3
+  //   CSR, B = 8:        4096, 16: 21.1 -> 19.6 (28);  2048, 100: 25.3 -> 31.3 (56), B = 128: 37.9 -> 34.0;
+  //                      16 384, 100 (451): B = 128 158 -> 214, B = 256 288 -> 231
+  const int64_t load = g.V / 320 + g.nnz / 4096;
+  const int64_t limit = g.prepared ? (B >= 176 ? INT64_MAX : B >= 128 ? 140 : 90)
+                                   : (B >= 208 ? INT64_MAX : B >= 128 ? 80 : 35);
+  if (load > limit) return StepShape::kFour;
+  // The statistics by the same workgroup, if that is at most two items a wave (V = 1024, K = 4: 13.0
+  // against 13.7 us; V = 4096, K = 8: 19.0 against 16.7) or there is a sequence for every compute unit
+  // (B = 256: V = 4096 22.1 against 25.3, 16 384 52.8 against 56.3).
+  const bool one = row_parts <= kSmallParts && (K + row_parts <= 2 * kGatherWaves || B > 128);
+  return one ? StepShape::kOne : StepShape::kTwo;
 }
 
 hipError_t launch_small_step(const AcceptArgs &a, const FinalizeArgs &fa, const ProbeArgs &pa,
-                             const pcg_groups &g, bool bf16, int32_t B, hipStream_t stream) {
+                             const pcg_groups &g, bool bf16, bool stats, int32_t B, hipStream_t stream) {
   const PreparedView p = g.prepared ? prepared_view(g) : PreparedView{};
   auto launch = [&](auto kernel) {
     kernel<<<B, kAcceptThreads, 0, stream>>>(a, fa, pa, p, (int32_t) g.nnz);
   };
-  auto pick = [&](auto is_bf16) {
-    constexpr bool BF = decltype(is_bf16)::value;
-    if (g.prepared) { if (g.weights) launch(small_step_kernel<BF, kSumsPreparedWeighted>); else launch(small_step_kernel<BF, kSumsPrepared>); }
-    else { if (g.weights) launch(small_step_kernel<BF, kSumsCsrWeighted>); else launch(small_step_kernel<BF, kSumsCsr>); }
+  auto pick = [&](auto is_bf16, auto with_stats) {
+    constexpr bool BF = decltype(is_bf16)::value, ST = decltype(with_stats)::value;
+    if (g.prepared) { if (g.weights) launch(small_step_kernel<BF, kSumsPreparedWeighted, ST>); else launch(small_step_kernel<BF, kSumsPrepared, ST>); }
+    else { if (g.weights) launch(small_step_kernel<BF, kSumsCsrWeighted, ST>); else launch(small_step_kernel<BF, kSumsCsr, ST>); }
   };
-  if (bf16) pick(std::true_type{}); else pick(std::false_type{});
+  if (bf16) { if (stats) pick(std::true_type{}, std::true_type{}); else pick(std::true_type{}, std::false_type{}); }
+  else { if (stats) pick(std::false_type{}, std::true_type{}); else pick(std::false_type{}, std::false_type{}); }
   return hipGetLastError();
 }
 

@@ -89,14 +89,15 @@ def test_csr_gather(V, G, size, B, weighted):
     check_step(V, G, size, B, 2, "bf16", layout="csr", weighted=weighted, thinning=False)
 
 
-# the step in one kernel, and the sizes right beside it: the smallest row, rows of one part and more, the
-# most positions, the most tokens and groups its LDS holds, several chunks, the batch from which
-# any size takes it, the batch beyond it
+# the step in one and in two kernels, and the sizes right beside them: the smallest row, rows of one part
+# and more, the most positions, the most tokens and groups the LDS holds, several chunks, batches on
+# either side of the rule's lines, the batch beyond it
 @pytest.mark.parametrize("layout,weighted", [("prepared", False), ("prepared", True), ("csr", False), ("csr", True)])
 @pytest.mark.parametrize("V,G,size,B,K,dtype,off", [
     (8, 5, 4, 2, 1, "bf16", 0), (9, 2, 5, 3, 64, "f32", 1), (1023, 1025, 8, 5, 4, "bf16", 3), (2049, 4101, 3, 2, 8, "f32", 0),
-    (4095, 2000, 20, 1, 8, "bf16", 5), (16384, 16384, 3, 144, 1, "bf16", 0), (16383, 16001, 4, 145, 1, "f32", 2),
-    (16384, 16385, 3, 144, 1, "bf16", 0), (300, 200, 9, 256, 2, "f32", 0), (300, 200, 9, 257, 2, "bf16", 0)])
+    (4095, 2000, 20, 1, 8, "bf16", 5), (16384, 16384, 3, 208, 1, "bf16", 0), (16383, 16001, 4, 209, 1, "f32", 2),
+    (16384, 16385, 3, 208, 1, "bf16", 0), (4097, 4097, 9, 3, 8, "bf16", 1), (8192, 8000, 30, 2, 7, "f32", 0),
+    (8193, 9001, 7, 128, 1, "bf16", 3), (12000, 9000, 12, 127, 1, "bf16", 0), (1500, 1500, 9, 2, 33, "f32", 1), (300, 200, 9, 256, 2, "f32", 0), (300, 200, 9, 257, 2, "bf16", 0)])
 def test_small_step(V, G, size, B, K, dtype, off, layout, weighted):
     check_step(V, G, size, B, K, dtype, off=off, layout=layout, weighted=weighted, thinning=False, chunk_groups=4096)
 
