@@ -1115,18 +1115,22 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
       if constexpr (WEIGHTED) e.w[u] = load4(weights, j);
     }
   };
-  // what the four entries loaded for position j add to a sum: those from j on, inside the group
+  // what the four entries loaded for position j add to a sum: those from j on, inside the group (added in
+  // pairs: a chain of four and then the tree over the lanes would round once or twice more)
   auto add4 = [&](const u32x4 m, const u32x4 w, int32_t j, int32_t end, float acc) {
     const int32_t at = min(j, nnz - 4);
+    float v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int32_t t = (int32_t) m[k] - t0;
       const bool mine = at + k >= j && at + k < end && (uint32_t) t < (uint32_t) tl;
-      const float v = tab[mine ? t : zero];
-      if constexpr (WEIGHTED) acc = fmaf(v, __uint_as_float(w[k]), acc);
-      else acc += v;
+      v[k] = tab[mine ? t : zero];
     }
-    return acc;
+    if constexpr (WEIGHTED)
+      return acc + (fmaf(v[0], __uint_as_float(w[0]), v[1] * __uint_as_float(w[1])) +
+                    fmaf(v[2], __uint_as_float(w[2]), v[3] * __uint_as_float(w[3])));
+    else
+      return acc + ((v[0] + v[1]) + (v[2] + v[3]));
   };
   Bounds now, after;
   Entries e;
