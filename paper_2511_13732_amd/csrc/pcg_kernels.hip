@@ -1538,6 +1538,7 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
             nruns, [&](int32_t k) { return rp[k]; }, 0.0, true, goal - base);
         if (pr.index >= 0) {
           __shared__ int32_t run_n[kRunGroups];
+          __shared__ bool run_has[kRunGroups];          // some entry of the group adds to it
           const bool rejected = istar < K;
           const void *drow = row_base(fa.rs, fa.rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0), BF16);
           const RowStat sd = fa.rowstat[fa.rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0)];
@@ -1550,6 +1551,7 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
           // everything the token draw needs in its half-wave
           int32_t n_g = 0, t_first = -1;
           float lt_first = -INFINITY, share_first = 1.f;
+          bool adds = false;
           if (g < g0 + ng) {
             const int32_t beg = row_ptr[g], end = row_ptr[g + 1];
             n_g = end - beg;
@@ -1566,10 +1568,12 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
               }
               acc = wts ? fmaf((float) diff, share, acc)
                         : acc + (float) diff * __builtin_amdgcn_rcpf(share);
+              adds = adds || (diff > 0.0 && share > 0.f);
             }
           }
           acc = subwave_sum<32>(acc);                   // total in the last lane of each 32
-          if (l == 31) { run_r[k] = fmaxf(acc, 0.f); run_n[k] = n_g; }
+          const bool has = (__ballot(adds) >> (threadIdx.x & 32) & 0xffffffffull) != 0;   // of this half-wave
+          if (l == 31) { run_r[k] = fmaxf(acc, 0.f); run_n[k] = n_g; run_has[k] = has; }
           __syncthreads();
           double cum = base + pr.lo, last_v = 0.0;
           int pick = -1, last = -1;
@@ -1582,13 +1586,16 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
             }
           }
           if (pick < 0) {
-            // rounding (the run's total was summed in another order): the last group of the run
-            // that has mass, or its first group if none has
-            pick = last < 0 ? 0 : last;
+            // rounding (the run's total was summed in another order): the last group of the run that has
+            // mass.  Where sums that cancel gave the run its total and none of them comes out positive
+            // here, a group that has entries with q > p: any group with a positive sum had one.
+            pick = last;
+            for (int k2 = kRunGroups - 1; k2 >= 0 && last < 0; --k2)
+              if (run_has[k2]) pick = k2;
             pg.hi = cum; pg.lo = cum - last_v;
           }
-          pg.index = gr0 + pick;
-          if (run_n[pick] <= 32) {                      // uniform over the workgroup
+          if (pick >= 0) pg.index = gr0 + pick;         // none (cannot happen): the fallback below
+          if (pick >= 0 && run_n[pick] <= 32) {         // uniform over the workgroup
             // The token inside the group (Eq. 10) by the half-wave that formed the group's sum.
             const int wv = __builtin_amdgcn_readfirstlane(pick >> 1);
             if ((int) (threadIdx.x >> 6) == wv) {

@@ -152,3 +152,30 @@ def test_propose_rows(V, B, K, dtype, off):
     assert diag[pcg.Diag.NAMES.index("sequences")] == B * K
     if B > 2 and V > 2:
         assert int(tok[1, 0]) == V - 1
+
+
+# a draw that lands where a run's only mass is the rounding of sums that cancel: the draft rows hold the
+# target's logits in another order inside every group, so each T[g] - D[g] is 0 but for rounding, and the
+# gather and finalize, which add a group's entries in different orders, need not agree on its sign
+@pytest.mark.parametrize("layout", ["prepared", "csr"])
+@pytest.mark.parametrize("n", [20, 40, 100])
+def test_a_group_without_mass_is_never_drawn(n, layout):
+    V, B, K = 20000, 64, 1
+    G = 16 * (V // n)                               # in every run of 16 groups the last holds n tokens, the others none
+    sizes = np.where(np.arange(G) % 16 == 15, n, 0)
+    rp = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    mem = np.random.default_rng(1).permutation(V).reshape(-1, n)
+    mem.sort(axis=1)
+    dg = pcg.Groups.from_csr(V, rp, mem.ravel().astype(np.int32), "cuda", prepare=layout == "prepared")
+    rng = np.random.default_rng(n)
+    tgt = (2.0 * rng.standard_normal((B, K + 1, V))).astype(np.float32)
+    dft = np.empty((B, K, V), np.float32)
+    dft[:, 0, mem] = tgt[:, 0][:, rng.permuted(mem, axis=1)]
+    ptok = torch.zeros((B, K), dtype=torch.int32, device="cuda")
+    pgrp = torch.full((B, K), dg.G + 5, dtype=torch.int32, device="cuda")        # no group: rejected
+    for step in range(4):
+        out = pcg.verify(dg, torch.from_numpy(tgt).cuda(), torch.from_numpy(dft).cuda(), ptok, pgrp, seed=2, offset=step)
+        g, t = out.out_groups[:, 0].cpu().numpy(), out.out_tokens[:, 0].cpu().numpy()
+        assert (out.accept_len == 0).all()
+        assert (sizes[g] > 0).all(), f"{int((sizes[g] == 0).sum())} of {B} draws of a group without members"
+        assert all(t[b] in mem[g[b] // 16] for b in range(B))
