@@ -49,15 +49,17 @@ __device__ __forceinline__ uint16_t quotient_to_bf16(double e, double norm, doub
 
 __device__ __forceinline__ double bf16_value(uint16_t b) { return (double) __uint_as_float((uint32_t) b << 16); }
 
-// EXACT: norms receives ||emb[v]|| in double, and *worst (a non-negative float as its bits) the
-// largest ||unit_bf16[v] - emb[v] / ||emb[v]|| ||, how far rounding has moved a unit vector.
+// EXACT: norms receives ||emb[v]|| in double, and moved[v] ||unit_bf16[v] - emb[v] / ||emb[v]|| ||, how
+// far rounding has moved the unit vector; *worst, the largest of them once asg_setup_kernel has run, is
+// cleared for it.  (An atomic maximum here, by every wave at once, took 3.4 of 7.2 us at 2048 tokens.)
 // One wave per token; its row (up to kRowRegs * 256 elements, d a multiple of 4) stays in registers
 // between the norm and the quotients.  Bound by memory: 268 MB of embeddings and 134 MB of unit
-// vectors at 65 536 x 1024 take 80 us (175 with 4-byte loads, the row read twice and a
+// vectors at 65 536 x 1024 take 72 us (175 with 4-byte loads, the row read twice and a
 // division in double per element).
 template <bool EXACT>
 __global__ __launch_bounds__(256) void asg_normalize_kernel(const float *emb, int32_t V, int32_t d,
-                                                            uint16_t *unit, double *norms, uint32_t *worst) {
+                                                            uint16_t *unit, double *norms, float *moved,
+                                                            float *worst) {
   constexpr int kRowRegs = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t v = (int64_t) blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
@@ -110,10 +112,13 @@ __global__ __launch_bounds__(256) void asg_normalize_kernel(const float *emb, in
     }
   }
   if constexpr (EXACT) {
-    // rounded up; read before the atomic, since 65 536 atomics on one word would take their time.  A row
-    // with a NaN or an infinity has no cosine above any threshold and must not widen the band.
-    const uint32_t mine = __float_as_uint(__double2float_ru(sqrt(wave_sum(err)) * (1.0 + 0x1p-40)));
-    if (lane == 0 && mine < 0x7f800000u && mine > __atomic_load_n(worst, __ATOMIC_RELAXED)) atomicMax(worst, mine);
+    // rounded up.  A row with a NaN or an infinity has no cosine above any threshold and must not widen
+    // the band.
+    const float mine = __double2float_ru(sqrt(wave_sum(err)) * (1.0 + 0x1p-40));
+    if (lane == 0) {
+      moved[v] = mine < INFINITY ? mine : 0.f;
+      if (v == 0) *worst = 0.f;
+    }
   }
 }
 
@@ -163,6 +168,36 @@ __device__ __forceinline__ void sim_queue_pair(int32_t t, int32_t v, uint32_t fl
   }
 }
 
+// Clears what the kernels that follow count in.  EXACT: the largest of moved[0 .. V) into *worst, which
+// holds 0: one atomic per workgroup (a non-negative float orders as its bits do).
+constexpr int kSetupThreads = 256, kSetupTokens = 4 * kSetupThreads;
+
+template <bool EXACT>
+__global__ __launch_bounds__(kSetupThreads) void asg_setup_kernel(int32_t V, const float *moved, float *worst,
+                                                                  int32_t *count, int32_t *mult, int64_t *totals) {
+  __shared__ float wave_worst[kSetupThreads / kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+  if (blockIdx.x == 0 && threadIdx.x < 3) totals[threadIdx.x] = 0;
+  float mine = 0.f;
+#pragma unroll
+  for (int i = 0; i < kSetupTokens / kSetupThreads; ++i) {
+    const int32_t t = blockIdx.x * kSetupTokens + i * kSetupThreads + threadIdx.x;
+    if (t >= V) continue;
+    count[t] = 0;
+    mult[t] = 0;
+    if constexpr (EXACT) mine = fmaxf(mine, moved[t]);
+  }
+  if constexpr (EXACT) {
+    mine = wave_max(mine);
+    if (lane == 0) wave_worst[wave] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < kSetupThreads / kWave; ++w) mine = fmaxf(mine, wave_worst[w]);
+      atomicMax(reinterpret_cast<uint32_t *>(worst), __float_as_uint(mine));
+    }
+  }
+}
+
 // Waits until at most N of this wave's vector-memory operations are still in flight.
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -190,11 +225,11 @@ __device__ __forceinline__ float asg_rounding_band(int32_t d, float e) {
 // the band are marked kAsgUnsure for asg_refine_kernel.
 template <bool EXACT>
 __global__ __launch_bounds__(kSimThreads) void asg_similarity_kernel(
-    const uint16_t *__restrict__ unit, int32_t V, int32_t d, float theta, const uint32_t *worst,
+    const uint16_t *__restrict__ unit, int32_t V, int32_t d, float theta, const float *worst,
     int32_t cap, int32_t *count, int32_t *cand) {
   float theta_hi = theta;
   if constexpr (EXACT) {
-    const float band = asg_rounding_band(d, __uint_as_float(*worst));
+    const float band = asg_rounding_band(d, *worst);
     theta_hi = theta + band;
     theta = theta - band;
   }
@@ -383,8 +418,11 @@ __global__ __launch_bounds__(kSimThreads) void asg_similarity_kernel(
 // id, or kAsgRemoved (asg_sort_kernel closes the gaps).  No two waves write the same entry, and a
 // wave's own pairs are those with a larger token, whatever has happened to the others it reads.
 // The wave's own row stays in registers (up to kRowRegs * 256 elements), the other's comes from
-// memory: bound by the gather of those rows, 4 d bytes a pair.  65 536 x 1024, 0.7 M undecided pairs:
-// 1711 us when both tokens' waves computed each pair and read both rows for it, now 476.
+// memory, with its norm and the first 64 entries of its list, while the pair before is summed.  Bound
+// by the gather of those rows, 4 d bytes a pair: 65 536 x 1024, 0.7 M undecided pairs, 471 us (1711
+// when both tokens' waves computed each pair and read both rows for it).  With few tokens, all of whose
+// waves run at once, it is the longest chain of pairs that counts: 2048 x 128 5.1 us (5.3 with the
+// list fetched after the sum).
 // Lists that did not fit into cap stay undecided: their count stays above cap and the call reports
 // PCG_ERR_CAPACITY.
 // ---------------------------------------------------------------------------------------------
@@ -393,7 +431,8 @@ constexpr uint32_t kAsgRemoved = 0xffffffffu;
 __global__ __launch_bounds__(256) void asg_refine_kernel(const float *__restrict__ emb,
                                                          const double *__restrict__ norms, int32_t V,
                                                          int32_t d, double theta, int32_t cap,
-                                                         const int32_t *count, int32_t *cand) {
+                                                         const int32_t *__restrict__ count,
+                                                         int32_t *cand) {
   constexpr int kRowRegs = 4;
   const int lane = threadIdx.x & (kWave - 1);
   const int32_t t = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
@@ -413,13 +452,24 @@ __global__ __launch_bounds__(256) void asg_refine_kernel(const float *__restrict
     return ((double) a.x * (double) b.x + (double) a.y * (double) b.y) +
            ((double) a.z * (double) b.z + (double) a.w * (double) b.w);
   };
-  auto fetch = [&](int32_t v, float4 (&o)[kRowRegs]) {
+  struct Other {
+    float4 row[kRowRegs];
+    double norm;
+    int32_t found;
+    uint32_t first;                         // entry `lane` of its list, if it has one there
+  };
+  // This wave alone writes the entry it looks for in the other's list, so that one fetched early is as
+  // good as one fetched late, whatever happens to its neighbours.
+  auto fetch = [&](int32_t v, Other &o) {
     const float *ev = emb + (int64_t) v * d;
 #pragma unroll
     for (int i = 0; i < kRowRegs; ++i) {
       const int32_t k = 4 * (lane + i * kWave);
-      o[i] = k < d ? *reinterpret_cast<const float4 *>(ev + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      o.row[i] = k < d ? *reinterpret_cast<const float4 *>(ev + k) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
+    o.norm = norms[v];
+    o.found = count[v];
+    o.first = lane < cap ? (uint32_t) cand[(int64_t) v * cap + lane] : 0u;
   };
   for (int32_t c0 = 0; c0 < found; c0 += kWave) {
     const int32_t k = c0 + lane;
@@ -429,15 +479,13 @@ __global__ __launch_bounds__(256) void asg_refine_kernel(const float *__restrict
     if (mine == 0) continue;                           // uniform over the wave, as everything below
     bool member = false;
     int l = __ffsll((long long) mine) - 1;
-    float4 o[kRowRegs];
+    Other o;
     fetch(__builtin_amdgcn_readlane(entry, l), o);
     const unsigned long long all = mine;
     while (true) {
       mine &= mine - 1;
       const int32_t v = __builtin_amdgcn_readlane(entry, l);
-      float4 cur[kRowRegs];
-#pragma unroll
-      for (int i = 0; i < kRowRegs; ++i) cur[i] = o[i];
+      const Other cur = o;
       int ln = 0;
       if (mine) {                                      // the next row is on its way behind this one
         ln = __ffsll((long long) mine) - 1;
@@ -445,20 +493,22 @@ __global__ __launch_bounds__(256) void asg_refine_kernel(const float *__restrict
       }
       double dot = 0.0;
 #pragma unroll
-      for (int i = 0; i < kRowRegs; ++i) dot += product(own[i], cur[i]);
+      for (int i = 0; i < kRowRegs; ++i) dot += product(own[i], cur.row[i]);
       for (int32_t j = 4 * (lane + kRowRegs * kWave); j < d; j += 4 * kWave)
         dot += product(*reinterpret_cast<const float4 *>(et + j),
                        *reinterpret_cast<const float4 *>(emb + (int64_t) v * d + j));
       dot = wave_sum(dot);
-      const double nv = norms[v];
-      const double cosine = (nt > 0.0 && nv > 0.0) ? dot / (nt * nv) : 0.0;
+      const double cosine = (nt > 0.0 && cur.norm > 0.0) ? dot / (nt * cur.norm) : 0.0;
       const bool is_member = cosine > theta;
       if (lane == l) member = is_member;
       // the same pair in the other token's list
-      const int32_t theirs = min(count[v], cap);
+      const int32_t theirs = min(cur.found, cap);
       int32_t *other = cand + (int64_t) v * cap;
-      for (int32_t j = lane; j < theirs; j += kWave)
-        if ((uint32_t) other[j] == ((uint32_t) t | kAsgUnsure)) other[j] = is_member ? t : (int32_t) kAsgRemoved;
+      const uint32_t mark = (uint32_t) t | kAsgUnsure;
+      const int32_t outcome = is_member ? t : (int32_t) kAsgRemoved;
+      if (lane < theirs && cur.first == mark) other[lane] = outcome;
+      for (int32_t j = lane + kWave; j < theirs; j += kWave)
+        if ((uint32_t) other[j] == mark) other[j] = outcome;
       if (!mine) break;
       l = ln;
     }
@@ -491,19 +541,17 @@ __device__ __forceinline__ void wave_lds_sync() {
 // marked kAsgRemoved are dropped, what is still marked kAsgUnsure (only where some list did not fit)
 // becomes a plain token id again, since the kernels that follow index with it.  Up to 64 members are
 // ranked against each other in registers, larger sets go through a bitonic sort in the wave's own
-// slice of LDS (153 us for 65 536 sets of 26 members on average, now 92).  cap2 = cap rounded up
+// slice of LDS (153 us for 65 536 sets of 26 members on average, now 41).  cap2 = cap rounded up
 // to a power of two, at least 64; the kernel is launched with 4 * cap2 * 4 bytes of dynamic LDS.
 __global__ __launch_bounds__(kSortThreads) void asg_sort_kernel(int32_t V, int32_t cap, int32_t cap2,
                                                                 const int32_t *count, int32_t *cand,
-                                                                int32_t *size, uint64_t *hash,
-                                                                int32_t *max_count) {
+                                                                int32_t *size, uint64_t *hash) {
   extern __shared__ int32_t sort_lds[];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   const int32_t t = blockIdx.x * (kSortThreads / kWave) + wave;
   if (t >= V) return;                       // whole waves leave together; no workgroup barrier below
   int32_t *key = sort_lds + wave * cap2;
-  const int32_t found = count[t];
-  const int32_t have = min(found, cap);
+  const int32_t have = min(count[t], cap);
   int32_t *row = cand + (int64_t) t * cap;
   int32_t n = 0;
   if (have <= kWave) {
@@ -540,10 +588,6 @@ __global__ __launch_bounds__(kSortThreads) void asg_sort_kernel(int32_t V, int32
       }
   }
   wave_lds_sync();
-  // the largest set (where it did not fit: what was found for it): read first, since 65 536 atomics
-  // on one word take longer than the sort itself
-  const int32_t largest = found > cap ? found : n;
-  if (lane == 0 && largest > __atomic_load_n(max_count, __ATOMIC_RELAXED)) atomicMax(max_count, largest);
   uint64_t h = 0;
   for (int32_t k = lane; k < n; k += kWave) {
     row[k] = key[k];
@@ -589,11 +633,13 @@ __global__ __launch_bounds__(256) void asg_dedup_kernel(int32_t V, int32_t cap, 
 }
 
 // Exclusive scans over the tokens: gid[t] = kept tokens before t, off[t] = members of kept tokens
-// before t; totals[0] = G, totals[1] = nnz.  Two launches, a workgroup per 1024 tokens: the first
-// leaves every block's counts, the second sums those of the blocks before its own and scans its
-// tokens.  (One workgroup walking over all tokens took 132 us at V = 65 536; these take 11.)
+// before t; totals[0] = G, totals[1] = nnz, totals[2] = the largest set.  A workgroup per 1024 tokens scans its
+// own and needs the sums of those before them: from asg_count_kernel, which leaves every block's, or,
+// where that are few tokens, by reading them all (a launch costs more).  (One workgroup walking over
+// all tokens took 132 us at V = 65 536; the two take 11.  2048 tokens: 5.4 us, 4.6 in one launch.)
 // A token's two counts travel as one double: 1 + 2^11 size; sums over 1024 tokens stay exact.
 constexpr int kScanThreads = 1024;
+constexpr unsigned kScanAloneBlocks = 8;    // without asg_count_kernel up to 8192 tokens
 constexpr double kScanUnit = 2048.0;
 
 __device__ __forceinline__ double scan_item(int32_t t, int32_t V, const int32_t *keep, const int32_t *size) {
@@ -620,14 +666,23 @@ __global__ __launch_bounds__(kScanThreads) void asg_count_kernel(int32_t V, cons
 
 __global__ __launch_bounds__(kScanThreads) void asg_scan_kernel(int32_t V, const int32_t *keep,
                                                                 const int32_t *size, const uint64_t *counts,
-                                                                int32_t *gid, int64_t *off, int64_t *totals) {
+                                                                const int32_t *count, int32_t cap, int32_t *gid,
+                                                                int64_t *off, int64_t *totals) {
+  __shared__ int32_t wave_largest[kScanThreads / kWave];
   __shared__ double wave_tot[kScanThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   double g0 = 0.0, n0 = 0.0;                 // of the blocks before this one
-  for (int32_t k = threadIdx.x; k < (int32_t) blockIdx.x; k += kScanThreads) {
-    const uint64_t c = counts[k];
-    g0 += (double) (c & 2047);
-    n0 += (double) (c >> 11);
+  if (counts) {                              // uniform
+    for (int32_t k = threadIdx.x; k < (int32_t) blockIdx.x; k += kScanThreads) {
+      const uint64_t c = counts[k];
+      g0 += (double) (c & 2047);
+      n0 += (double) (c >> 11);
+    }
+  } else {
+    for (int32_t k = threadIdx.x; k < (int32_t) blockIdx.x * kScanThreads; k += kScanThreads) {
+      g0 += keep[k] != 0 ? 1.0 : 0.0;
+      n0 += keep[k] != 0 ? (double) size[k] : 0.0;
+    }
   }
   g0 = scan_block_sum(g0, wave_tot);
   n0 = scan_block_sum(n0, wave_tot);
@@ -649,11 +704,21 @@ __global__ __launch_bounds__(kScanThreads) void asg_scan_kernel(int32_t V, const
     totals[0] = (int64_t) g0 + (int64_t) (c & 2047);
     totals[1] = (int64_t) n0 + (int64_t) (c >> 11);
   }
-}
-
-__global__ __launch_bounds__(256) void asg_fill_kernel(int32_t *p, int64_t n, int32_t value) {
-  const int64_t i = (int64_t) blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = value;
+  // The largest set; where one did not fit, what was found for it.  One atomic per workgroup: one per
+  // token, by the kernel that sorts, took 39 of its 42 us at 4096 tokens.
+  int32_t largest = 0;
+  if (t < V) {
+    const int32_t found = count[t];
+    largest = found > cap ? found : size[t];
+  }
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) largest = max(largest, __shfl_xor(largest, o, kWave));
+  if (lane == 0) wave_largest[wave] = largest;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kScanThreads / kWave; ++w) largest = max(largest, wave_largest[w]);
+    atomicMax(reinterpret_cast<int32_t *>(totals + 2), largest);
+  }
 }
 
 __global__ __launch_bounds__(256) void asg_compact_kernel(int32_t V, int32_t cap, const int32_t *cand,
@@ -712,22 +777,22 @@ int asg_build_impl(const float *emb, double *norms, uint16_t *unit_out, const ui
 
   auto fail = [](hipError_t e) { return record_hip_error(e); };
   hipError_t e;
-  const unsigned vb = (unsigned) ((v + 255) / 256), wb = (unsigned) ((v + 3) / 4);
-  asg_fill_kernel<<<vb, 256, 0, stream>>>(count, V, 0);
-  asg_fill_kernel<<<vb, 256, 0, stream>>>(mult, V, 0);
-  asg_fill_kernel<<<1, 256, 0, stream>>>((int32_t *) totals, 16, 0);
+  const unsigned wb = (unsigned) ((v + 3) / 4), ub = (unsigned) ((v + kSetupTokens - 1) / kSetupTokens);
   const int tiles = (V + kSimTile - 1) / kSimTile;
   const int patch_rows = (tiles + kSimPatchRows - 1) / kSimPatchRows;
   const int patch_cols = (tiles + kSimPatchCols - 1) / kSimPatchCols;
   const int patches = (patch_rows * patch_cols + 7) / 8 * 8;      // dealt to the 8 XCDs in turn
   const unsigned sim_grid = (unsigned) (patches * kSimPatchRows * kSimPatchCols);
   if (emb) {
-    uint32_t *worst = (uint32_t *) (totals + 3);
-    asg_normalize_kernel<true><<<wb, 256, 0, stream>>>(emb, V, d, unit_out, norms, worst);
+    float *worst = (float *) (totals + 3);
+    float *moved = (float *) gid;            // read before gid is written
+    asg_normalize_kernel<true><<<wb, 256, 0, stream>>>(emb, V, d, unit_out, norms, moved, worst);
+    asg_setup_kernel<true><<<ub, kSetupThreads, 0, stream>>>(V, moved, worst, count, mult, totals);
     asg_similarity_kernel<true><<<sim_grid, kSimThreads, 0, stream>>>(
         unit_out, V, d, theta, worst, cap, count, cand);
     asg_refine_kernel<<<wb, 256, 0, stream>>>(emb, norms, V, d, (double) theta, cap, count, cand);
   } else {
+    asg_setup_kernel<false><<<ub, kSetupThreads, 0, stream>>>(V, nullptr, nullptr, count, mult, totals);
     asg_similarity_kernel<false><<<sim_grid, kSimThreads, 0, stream>>>(
         unit_bf16, V, d, theta, nullptr, cap, count, cand);
   }
@@ -735,12 +800,12 @@ int asg_build_impl(const float *emb, double *norms, uint16_t *unit_out, const ui
   int32_t cap2 = kWave;
   while (cap2 < cap) cap2 <<= 1;
   asg_sort_kernel<<<wb, kSortThreads, (size_t) (kSortThreads / kWave) * cap2 * sizeof(int32_t), stream>>>(
-      V, cap, cap2, count, cand, size, hash, (int32_t *) (totals + 2));
+      V, cap, cap2, count, cand, size, hash);
   asg_dedup_kernel<<<wb, 256, 0, stream>>>(V, cap, cand, size, hash, keep);
   const unsigned sb = (unsigned) ((v + kScanThreads - 1) / kScanThreads);
-  uint64_t *counts = hash;                   // read for the last time by the kernel before
-  asg_count_kernel<<<sb, kScanThreads, 0, stream>>>(V, keep, size, counts);
-  asg_scan_kernel<<<sb, kScanThreads, 0, stream>>>(V, keep, size, counts, gid, off, totals);
+  uint64_t *counts = sb > kScanAloneBlocks ? hash : nullptr;      // hash: read for the last time by the kernel before
+  if (counts) asg_count_kernel<<<sb, kScanThreads, 0, stream>>>(V, keep, size, counts);
+  asg_scan_kernel<<<sb, kScanThreads, 0, stream>>>(V, keep, size, counts, count, cap, gid, off, totals);
   if ((e = hipGetLastError()) != hipSuccess) return fail(e);
   int64_t host_totals[3] = {0, 0, 0};
   if ((e = hipMemcpyAsync(host_totals, totals, sizeof host_totals, hipMemcpyDeviceToHost, stream)) !=
@@ -783,7 +848,8 @@ int pcg_asg_normalize(const float *emb, int32_t V, int32_t d, uint16_t *unit_bf1
   if (V < 1 || d < 1) return PCG_ERR_BAD_SHAPE;
   if (((uintptr_t) emb % 4) || ((uintptr_t) unit_bf16 % 2)) return PCG_ERR_MISALIGNED;
   hipStream_t stream = (hipStream_t) hip_stream;
-  asg_normalize_kernel<false><<<(unsigned) ((V + 3) / 4), 256, 0, stream>>>(emb, V, d, unit_bf16, nullptr, nullptr);
+  asg_normalize_kernel<false><<<(unsigned) ((V + 3) / 4), 256, 0, stream>>>(emb, V, d, unit_bf16, nullptr, nullptr,
+                                                                            nullptr);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? PCG_OK : record_hip_error(e);
 }

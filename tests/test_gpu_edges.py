@@ -118,6 +118,18 @@ def test_group_construction_edges(V, d, theta, centres, sigma):
     assert compare_groups(pcg.asg_build(as_bf16_tensor(bits).cuda(), theta, cap=64), ref, f"V={V} d={d}").tolerated <= 2
 
 
+# the scan over the tokens in one launch and in two, an unfinished block of it, and lists of more than 64
+# entries, undecided pairs among them
+@pytest.mark.parametrize("V,d,theta,centres,sigma", [(8192, 64, 0.45, 0, 0), (8193, 64, 0.45, 0, 0), (9217, 64, 0.45, 0, 0),
+                                                     (4000, 64, 0.8, 40, 0.3)])
+def test_group_construction_scan(V, d, theta, centres, sigma):
+    E = embeddings(V, d, 11, centres, sigma)[0] if centres else embeddings(V, d, 11)
+    got = pcg.asg_build_exact(torch.from_numpy(E).cuda(), theta, cap=64)
+    t = compare_groups(got, oracle.asg_build_exact(E, theta, nthreads=16), f"exact V={V}")
+    assert t.flagged_group == 0 and t.tolerated == 0
+    assert got.max_size >= int(np.diff(got.row_ptr.cpu().numpy()).max()) and (got.max_size > 64) == (centres > 0)
+
+
 def test_group_construction_beside_a_row_that_is_not_finite():
     """A token whose embedding holds an infinity or a NaN is in no other token's group, and the
     others' groups are what they are without it."""
