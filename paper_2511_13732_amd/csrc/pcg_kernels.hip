@@ -1073,19 +1073,67 @@ __device__ __forceinline__ void store_sums(float *dst, const float *sums, int32_
   }
 }
 
+// Four consecutive entries of a CSR array of nnz, from position j on where they lie inside it.
+__device__ __forceinline__ u32x4 csr_load4(const void *p, int32_t j, int32_t nnz) {
+  const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
+  if (nnz >= 4) return load16<false>(q + min(j, nnz - 4));
+  u32x4 r = {0, 0, 0, 0};                           // fewer than four entries in all
+  for (int k = 0; k < 4; ++k) {
+    const int32_t at = nnz - 4 + k;
+    if (at >= 0) r[k] = q[at];
+  }
+  return r;
+}
+
+// What the four entries loaded for position j add to a sum: those from j on, inside the group that ends
+// at `end`, and of the tile (added in pairs: a chain of four and then the tree over the lanes would
+// round once or twice more).
+template <bool WEIGHTED>
+__device__ __forceinline__ float csr_add4(const float *tab, int32_t zero, int32_t t0, int32_t tl, const u32x4 m,
+                                          const u32x4 w, int32_t j, int32_t end, int32_t nnz, float acc) {
+  const int32_t at = min(j, nnz - 4);
+  float v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int32_t t = (int32_t) m[k] - t0;
+    const bool mine = at + k >= j && at + k < end && (uint32_t) t < (uint32_t) tl;
+    v[k] = tab[mine ? t : zero];
+  }
+  if constexpr (WEIGHTED)
+    return acc + (fmaf(v[0], __uint_as_float(w[0]), v[1] * __uint_as_float(w[1])) +
+                  fmaf(v[2], __uint_as_float(w[2]), v[3] * __uint_as_float(w[3])));
+  else
+    return acc + ((v[0] + v[1]) + (v[2] + v[3]));
+}
+
+// Entries above which a group is left to csr_long_sums: 16 trips of its own W lanes, and far above the mean
+// size (where most groups are that large, a few lanes each is the better split).
+static int32_t csr_long_size(int64_t nnz, int32_t G, int W) {
+  return (int32_t) std::min<int64_t>(INT32_MAX, std::max<int64_t>(64 * W, 4 * (nnz / G)));
+}
+
 // Sums over the groups [g_begin, g_end) of the table tile tab[0 .. tl) = tokens [t0, t0 + tl), read
 // straight from the CSR by a workgroup of kGatherThreads; sink(g, sum) is called by one lane per
 // group.  tab[zero] must read 0.  W lanes share a group, each taking four consecutive entries with
 // one 16-byte load (kept inside the nnz entries of the array; what lies outside the group is sent to
 // the zero slot); a sub-wave works on kInFlight groups at a time, and while it sums them the
 // entries of its next ones and the bounds of those after them are on their way.
+// A group of more than long_size entries would keep its few lanes at it, one trip to the L2 after another,
+// long after all others are done (one group of 10 000 beside 20 000 of 8, 8 rows: the step took 222 us
+// with 8 lanes a group and one entry a lane, 288 with two and four, 137 with this).  Only its first trip
+// is added; *has_long (in LDS, false before) tells that csr_long_sums has something to do.
 template <int W, bool WEIGHTED, typename Sink>
 __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t t0, int32_t tl, int32_t g_begin,
                                          int32_t g_end, const int32_t *row_ptr, const int32_t *members,
-                                         int32_t nnz, const float *weights, Sink sink) {
+                                         int32_t nnz, const float *weights, int32_t long_size, bool *has_long,
+                                         Sink sink) {
   constexpr int kInFlight = 4;
   constexpr int nsub = kGatherThreads / W;
   constexpr int kPass = nsub * kInFlight;           // groups per turn of the workgroup
+  // At the most lanes a group, second trips are the rule: they are asked for together (5 % of the step at
+  // sizes of 1 to 128).  With fewer lanes the test alone costs more than it gives (2.5 % of the step at
+  // 32 members), and with weights there are no registers for it.
+  constexpr bool kAskSecond = W == 16 && !WEIGHTED;
   const int sub = threadIdx.x / W, sl = threadIdx.x % W;
   struct Bounds { int32_t beg[kInFlight], end[kInFlight]; };
   struct Entries { u32x4 m[kInFlight], w[kInFlight]; };
@@ -1097,16 +1145,7 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
       r.end[u] = row_ptr[g + 1];
     }
   };
-  auto load4 = [&](const void *p, int32_t j) -> u32x4 {
-    const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
-    if (nnz >= 4) return load16<false>(q + min(j, nnz - 4));
-    u32x4 r = {0, 0, 0, 0};                         // fewer than four entries in all
-    for (int k = 0; k < 4; ++k) {
-      const int32_t at = nnz - 4 + k;
-      if (at >= 0) r[k] = q[at];
-    }
-    return r;
-  };
+  auto load4 = [&](const void *p, int32_t j) { return csr_load4(p, j, nnz); };
   auto entries = [&](const Bounds &r, Entries &e) {
 #pragma unroll
     for (int u = 0; u < kInFlight; ++u) {
@@ -1115,22 +1154,8 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
       if constexpr (WEIGHTED) e.w[u] = load4(weights, j);
     }
   };
-  // what the four entries loaded for position j add to a sum: those from j on, inside the group (added in
-  // pairs: a chain of four and then the tree over the lanes would round once or twice more)
   auto add4 = [&](const u32x4 m, const u32x4 w, int32_t j, int32_t end, float acc) {
-    const int32_t at = min(j, nnz - 4);
-    float v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int32_t t = (int32_t) m[k] - t0;
-      const bool mine = at + k >= j && at + k < end && (uint32_t) t < (uint32_t) tl;
-      v[k] = tab[mine ? t : zero];
-    }
-    if constexpr (WEIGHTED)
-      return acc + (fmaf(v[0], __uint_as_float(w[0]), v[1] * __uint_as_float(w[1])) +
-                    fmaf(v[2], __uint_as_float(w[2]), v[3] * __uint_as_float(w[3])));
-    else
-      return acc + ((v[0] + v[1]) + (v[2] + v[3]));
+    return csr_add4<WEIGHTED>(tab, zero, t0, tl, m, w, j, end, nnz, acc);
   };
   Bounds now, after;
   Entries e;
@@ -1144,14 +1169,30 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
       entries(after, en);
       bounds(min(gb + 2 * kPass, g_end - 1), later);
     }
+    u32x4 second[kAskSecond ? kInFlight : 1];
+    if constexpr (kAskSecond) {
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u)
+        if (now.beg[u] + 4 * (sl + W) < now.end[u]) second[u] = load4(members, now.beg[u] + 4 * (sl + W));
+    }
 #pragma unroll
     for (int u = 0; u < kInFlight; ++u) {
       float acc = add4(e.m[u], e.w[u], now.beg[u] + 4 * sl, now.end[u], 0.f);
-      for (int32_t j = now.beg[u] + 4 * (sl + W); j < now.end[u]; j += 4 * W) {   // longer than one trip
-        const u32x4 m = load4(members, j);
-        u32x4 w = m;
-        if constexpr (WEIGHTED) w = load4(weights, j);
-        acc = add4(m, w, j, now.end[u], acc);
+      int32_t j = now.beg[u] + 4 * (sl + W);
+      if (j < now.end[u]) {                         // longer than one trip
+        if (now.end[u] - now.beg[u] > long_size) {
+          *has_long = true;
+          j = now.end[u];
+        } else if constexpr (kAskSecond) {
+          acc = add4(second[u], second[u], j, now.end[u], acc);
+          j += 4 * W;
+        }
+        for (; j < now.end[u]; j += 4 * W) {
+          const u32x4 m = load4(members, j);
+          u32x4 w = m;
+          if constexpr (WEIGHTED) w = load4(weights, j);
+          acc = add4(m, w, j, now.end[u], acc);
+        }
       }
       acc = subwave_sum<W>(acc);
       const int32_t g = gb + u * nsub + sub;
@@ -1160,6 +1201,42 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
     now = after;
     after = later;
     e = en;
+  }
+}
+
+// The groups that csr_sums left: a wave adds the entries of each beyond its first trip, four loads a lane on
+// their way, and hands their sum to more(g, sum).  A barrier lies between csr_sums and this.
+template <int W, bool WEIGHTED, typename More>
+__device__ void csr_long_sums(const float *tab, int32_t zero, int32_t t0, int32_t tl, int32_t g_begin,
+                              int32_t g_end, const int32_t *row_ptr, const int32_t *members, int32_t nnz,
+                              const float *weights, int32_t long_size, More more) {
+  constexpr int kAtOnce = 4;
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int32_t g0 = g_begin + (threadIdx.x - lane); g0 < g_end; g0 += kGatherThreads) {
+    const int32_t g = g0 + lane;
+    const int32_t begs = g < g_end ? row_ptr[g] : 0, ends = g < g_end ? row_ptr[g + 1] : 0;
+    unsigned long long longs = __ballot(ends - begs > long_size);
+    while (longs) {                                 // uniform over the wave, as everything in it
+      const int l = __ffsll((long long) longs) - 1;
+      longs &= longs - 1;
+      const int32_t end = __builtin_amdgcn_readlane(ends, l);
+      float sum = 0.f;
+      for (int32_t j0 = __builtin_amdgcn_readlane(begs, l) + 4 * W; j0 < end; j0 += kAtOnce * 4 * kWave) {
+        u32x4 m[kAtOnce], w[kAtOnce];
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q)
+          if (j0 + q * 4 * kWave < end) {
+            m[q] = csr_load4(members, j0 + 4 * (q * kWave + lane), nnz);
+            if constexpr (WEIGHTED) w[q] = csr_load4(weights, j0 + 4 * (q * kWave + lane), nnz);
+          }
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q)
+          if (j0 + q * 4 * kWave < end)
+            sum = csr_add4<WEIGHTED>(tab, zero, t0, tl, m[q], w[q], j0 + 4 * (q * kWave + lane), end, nnz, sum);
+      }
+      sum = subwave_sum<64>(sum);
+      if (lane == kWave - 1) more(g0 + l, sum);
+    }
   }
 }
 
@@ -1210,9 +1287,10 @@ __device__ __forceinline__ void run_totals(const float *sums, int32_t ng, double
 template <int W, bool CSUM, bool WEIGHTED>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t groups_per_chunk, int32_t ntiles,
-    int32_t tile_len, int32_t nnz, const int32_t *row_ptr, const int32_t *members, const float *weights,
-    const float *table, float *out, double *csum, int64_t csum_stride, double *runs) {
+    int32_t tile_len, int32_t nnz, int32_t long_size, const int32_t *row_ptr, const int32_t *members,
+    const float *weights, const float *table, float *out, double *csum, int64_t csum_stride, double *runs) {
   __shared__ __attribute__((aligned(16))) float lds[kTileMax];
+  __shared__ bool has_long;
   float *sums = lds, *tab = lds + groups_per_chunk;
   const int xcd = blockIdx.x & 7;
   const int y = blockIdx.x >> 3;
@@ -1226,18 +1304,25 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     const int32_t t0 = tile * tile_len;
     const int32_t tl = min(tile_len, V - t0);
     if (tl <= 0) break;                             // uniform: no tile starts past the row
-    if (tile > 0) __syncthreads();                  // everyone is done reading the old tile
     stage_tile(tab, src + t0, tl, threadIdx.x);
-    if (threadIdx.x == 0) tab[tile_len] = 0.f;
+    if (threadIdx.x == 0) {
+      tab[tile_len] = 0.f;
+      if (tile == 0) has_long = false;              // the same groups are long in every tile
+    }
     __builtin_amdgcn_s_waitcnt(0x0f70);             // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
     csr_sums<W, WEIGHTED>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
-                          [&](int32_t g, float a) {
-                            // the same lane in every tile: no other touches this sum
+                          long_size, &has_long, [&](int32_t g, float a) {
+                            // the same lane in every tile: no other touches this sum meanwhile
                             sums[g - g_begin] = tile > 0 ? sums[g - g_begin] + a : a;
                           });
+    __syncthreads();                                // everyone is done with the tile
+    if (has_long) {                                 // uniform
+      csr_long_sums<W, WEIGHTED>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
+                                 long_size, [&](int32_t g, float a) { sums[g - g_begin] += a; });
+      __syncthreads();
+    }
   }
-  __syncthreads();
   if constexpr (CSUM) {
     run_totals(sums, ng, runs + ((int64_t) r * nchunks + chunk) * (groups_per_chunk / kRunGroups),
                csum + r * csum_stride + chunk);
@@ -1919,6 +2004,8 @@ constexpr int kSmallTokens = 16384;    // table entries in LDS: 64 KB
 constexpr int kSmallGroups = 16384;    // sums in LDS: 64 KB
 constexpr int kSmallParts = 512;       // row parts (2048 logits each) of a sequence: 8 KB
 
+constexpr int kSmallCsrWidth = 4;      // lanes per group, from the CSR
+
 // Where the sums come from.
 constexpr int kSumsPrepared = 0, kSumsPreparedWeighted = 1, kSumsCsr = 2, kSumsCsrWeighted = 3;
 
@@ -1996,7 +2083,7 @@ __device__ CdfPick pick_group(const float *sums, int32_t n, double u) {
 // STATS: the row parts and probes are formed here; otherwise row_stats has left them in memory.
 template <bool BF16, int SUMS, bool STATS>
 __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a, FinalizeArgs fa, ProbeArgs pa,
-                                                                    PreparedView p, int32_t nnz) {
+                                                                    PreparedView p, int32_t nnz, int32_t long_size) {
   static_assert(kAcceptThreads == kGatherThreads, "one workgroup plays both parts");
   __shared__ AcceptShared sh;
   __shared__ StatPart parts[STATS ? kSmallParts : 1];
@@ -2115,10 +2202,15 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
         if (where[j] != 0xFFFFu) sums[chunk * p.chunk_groups + where[j]] = acc[j];
     }
   } else {
-    if (threadIdx.x == 0) tab[V] = 0.f;
+    __shared__ bool has_long;
+    if (threadIdx.x == 0) { tab[V] = 0.f; has_long = false; }
     lds_barrier();
-    csr_sums<4, kWeighted>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights,
+    csr_sums<kSmallCsrWidth, kWeighted>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size, &has_long,
                            [&](int32_t g, float s) { sums[g] = s; });
+    lds_barrier();
+    if (has_long)                                   // uniform
+      csr_long_sums<kSmallCsrWidth, kWeighted>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size,
+                                  [&](int32_t g, float s) { sums[g] += s; });
   }
   lds_barrier();
 
@@ -2270,8 +2362,8 @@ hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, 
   const dim3 grid((unsigned) (8 * rows8 * p.nchunks));
   auto launch = [&](auto kernel) {
     kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, p.nchunks, p.chunk_groups, p.ntiles, p.tile_len,
-                                                (int32_t) g.nnz, g.row_ptr, g.members, g.weights, table, out,
-                                                csum, csum_stride, runs);
+                                                (int32_t) g.nnz, csr_long_size(g.nnz, g.G, p.width), g.row_ptr,
+                                                g.members, g.weights, table, out, csum, csum_stride, runs);
   };
   auto pick = [&](auto width) {
     constexpr int W = decltype(width)::value;
@@ -2353,7 +2445,7 @@ hipError_t launch_small_step(const AcceptArgs &a, const FinalizeArgs &fa, const 
                              const pcg_groups &g, bool bf16, bool stats, int32_t B, hipStream_t stream) {
   const PreparedView p = g.prepared ? prepared_view(g) : PreparedView{};
   auto launch = [&](auto kernel) {
-    kernel<<<B, kAcceptThreads, 0, stream>>>(a, fa, pa, p, (int32_t) g.nnz);
+    kernel<<<B, kAcceptThreads, 0, stream>>>(a, fa, pa, p, (int32_t) g.nnz, csr_long_size(g.nnz, g.G, kSmallCsrWidth));
   };
   auto pick = [&](auto is_bf16, auto with_stats) {
     constexpr bool BF = decltype(is_bf16)::value, ST = decltype(with_stats)::value;

@@ -25,10 +25,21 @@ def rows_at(x: torch.Tensor, off: int) -> torch.Tensor:
     return big[:, :, off:]
 
 
+def with_long_groups(V, rp, mem, longs):
+    """The membership with groups of the given sizes put between its own, evenly, the first one ahead."""
+    rng = np.random.default_rng([V, *longs])
+    sets = np.split(mem, rp[1:-1])
+    for i, n in enumerate(longs):
+        sets.insert(i * len(sets) // len(longs), np.sort(rng.choice(V, n, replace=False)).astype(np.int32))
+    return np.concatenate([[0], np.cumsum([len(s) for s in sets])]).astype(np.int32), np.concatenate(sets)
+
+
 def check_step(V, G, size, B, K, dtype, off=0, layout="prepared", chunk_groups=0, weighted=False, seed=0,
-               thinning=True, sigma=4.0):
+               thinning=True, sigma=4.0, longs=()):
     print(f"V={V} G={G} size={size} B={B} K={K} {dtype} off={off} {layout} {chunk_groups} w={weighted}", flush=True)
     rp, mem = W.random_groups(V, G, 1, size, seed=seed + V)
+    if longs:
+        rp, mem = with_long_groups(V, rp, mem, longs)
     og = oracle_groups(V, rp, mem)
     w = W.random_weights(og.V, og.members, seed) if weighted else None
     if weighted:
@@ -87,6 +98,17 @@ def test_prepared_gather_blocks(V, G, size, chunk, weighted):
                                         (45003, 20001, 17, 1), (81000, 300, 700, 3), (100003, 3000, 60, 12)])
 def test_csr_gather(V, G, size, B, weighted):
     check_step(V, G, size, B, 2, "bf16", layout="csr", weighted=weighted, thinning=False)
+
+
+# groups far above the mean size, which a whole wave of the CSR gather sums: right at the size where that
+# begins (64 entries for every lane a group has), past one and several turns of the wave, all tokens; every
+# number of lanes, several tiles, the step in one kernel
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("V,G,size,B,longs", [(20000, 9000, 7, 3, (128, 129, 130, 1500, 20000)), (20000, 3000, 20, 2, (256, 257, 1281, 4000)),
+                                              (45003, 3000, 40, 2, (512, 513, 2049, 9000)), (81000, 2000, 90, 3, (1024, 1025, 1089, 5000)),
+                                              (4000, 3000, 9, 2, (256, 257, 1300, 4000)), (700, 500, 5, 300, (257, 700))])
+def test_csr_long_groups(V, G, size, B, longs, weighted):
+    check_step(V, G, size, B, 2, "bf16", layout="csr", weighted=weighted, thinning=False, longs=longs)
 
 
 # the step in one and in two kernels, and the sizes right beside them: the smallest row, rows of one part
