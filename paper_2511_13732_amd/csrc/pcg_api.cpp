@@ -400,6 +400,16 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
     return hip_fail(e);
   tm.end(kStageAccept);
   tm.begin(kStageGather);
+  if (!groups->prepared && finalize_scans(groups->G)) {
+    if ((e = launch_gather(*groups, csr_shape(V, groups->G, groups->nnz, B, 256), B, table, R, nullptr, 0, nullptr,
+                           stream)) != hipSuccess)
+      return hip_fail(e);
+    tm.end(kStageGather);
+    tm.begin(kStageFinalize);
+    if ((e = launch_finalize_sums(fa, bf16, *groups, B, stream)) != hipSuccess) return hip_fail(e);
+    tm.end(kStageFinalize);
+    return PCG_OK;
+  }
   int32_t nchunks, chunk_groups;
   int64_t csum_stride;
   if (groups->prepared) {

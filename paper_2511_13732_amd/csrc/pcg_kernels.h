@@ -66,6 +66,11 @@ StepShape step_shape(const pcg_groups &g, int32_t B, int32_t K);
 hipError_t launch_small_step(const AcceptArgs &a, const FinalizeArgs &fa, const ProbeArgs &pa,
                              const pcg_groups &g, bool bf16, bool stats, int32_t B, hipStream_t stream);
 
+// Whether the last kernel of a step from the CSR works on all of a row's sums (launch_gather without csum,
+// into fa.R) instead of on totals of them.
+bool finalize_scans(int32_t G);
+hipError_t launch_finalize_sums(const FinalizeArgs &fa, bool bf16, const pcg_groups &g, int32_t B, hipStream_t stream);
+
 hipError_t launch_finalize(const FinalizeArgs &fa, bool bf16, const pcg_groups &g, int32_t B,
                            const double *csum, int64_t csum_stride, const double *runs, int32_t nchunks,
                            int32_t chunk_groups, hipStream_t stream);

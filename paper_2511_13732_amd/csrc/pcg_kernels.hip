@@ -10,16 +10,19 @@
 //                 that T[g] - D[g] = sum of delta over G_g
 //   gather        the overlap-aware segmented gather-sum of that table over the membership
 //                 (Eq. 5, Eq. 8), table tiles staged in LDS, from the prepared layout or the CSR.
-//                 Inside pcg_verify no sum leaves the kernel: only fp64 totals of max(0, .) per
-//                 run of 16 consecutive groups and per chunk.  pcg_group_probs has every sum
-//                 written.
+//                 Inside pcg_verify no sum leaves the kernel (but see finalize): only fp64 totals of
+//                 max(0, .) per run of 16 consecutive groups and per chunk.  pcg_group_probs has every
+//                 sum written.
 //   finalize      per sequence: the chunk and the run that hold u * total, the run's 16 sums
-//                 formed again, the group by inverse CDF, then the token inside it (Eq. 10)
+//                 formed again, the group by inverse CDF, then the token inside it (Eq. 10).
+//                 From the CSR with up to 4096 groups the gather writes every sum and the group is
+//                 drawn from those (finalize_sums).
 // A step that is small, or has many sequences of moderate size, runs as one or two kernels instead
 // (small_step, after row_stats where the rows are many): one workgroup per sequence does all of the
 // above with everything in LDS.
 // pcg_group_probs runs row_stats, a weights kernel (q(t) / N(t)) and the same gather;
-// pcg_verify_thinning runs row_stats and accept_thin; pcg_propose runs row_stats and propose.
+// pcg_verify_thinning runs row_stats and accept_thin.  pcg_propose runs one kernel, a workgroup per draft row
+// (propose_row), for rows of up to 131 072 logits, row_stats and propose beyond.
 #include "pcg_kernels.h"
 #include "pcg_layout.h"
 
@@ -1336,6 +1339,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
 // =============================================================================================
 
 constexpr int kFinalThreads = 512;
+constexpr int32_t kScanGroups = 4096;    // sums of a row that finalize reads and scans whole
 
 struct CdfPick {
   int32_t index;    // first index whose running sum exceeds the threshold; -1 if nothing has mass
@@ -1796,6 +1800,21 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(FinalizeArgs fa
                                                                  int32_t nchunks,
                                                                  int32_t chunk_groups) {
   finalize_sequence<BF16, kFinalThreads, OWN>(fa, V, G, blockIdx.x, csum, csum_stride, runs, nchunks, chunk_groups);
+}
+
+// The last step from the sums themselves: few enough that all of them are read and scanned sooner than
+// totals of them, a run and its sums formed again.  V = 4096, CSR, 8 rows: 100 members 7.0 us here, 9.3 from
+// the totals; 48 members 6.6 and 8.5.
+template <bool BF16>
+__global__ __launch_bounds__(kFinalThreads) void finalize_sums_kernel(FinalizeArgs fa, int32_t G) {
+  const int b = blockIdx.x;
+  const int32_t istar = fa.accept_len[b];
+  const int64_t trow_id = (int64_t) b * (fa.K + 1) + istar;
+  const Uniforms u = philox_uniforms(fa.seed, fa.offset, (uint32_t) b, (uint32_t) istar);
+  const float *sums = fa.R + (int64_t) b * G;
+  const CdfPick pg = block_inverse_cdf<kFinalThreads, kScanGroups / kFinalThreads>(
+      G, [&](int32_t g) { return (double) sums[g]; }, (double) u.grp);
+  finish_sequence<BF16, kFinalThreads>(fa, G, b, istar, row_base(fa.rs, trow_id, BF16), fa.rowstat[trow_id], u, pg);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2402,6 +2421,11 @@ CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max
   const double mean = (double) nnz / (double) G;
   p.width = 2;
   while (p.width < 16 && 4 * p.width < mean) p.width *= 2;
+  // More lanes for long groups only where every workgroup then has one pass and they all run at once (a
+  // row's workgroups share the 32 compute units of an XCD): V = 4096, 100 members, 8 rows 6.0 us with 32, 8.1
+  // with 16.  Elsewhere it loses: 32 rows 31.4 and 30.6, V = 20 000, 1 row 54.7 and 49.6.
+  const int64_t rows_per_xcd = (nrows + 7) / 8;
+  if (mean > 32 && (int64_t) G * rows_per_xcd <= 32 * 4 * (kGatherThreads / 32)) p.width = 32;
   // Chunks per row: a workgroup for every compute unit, each with at least one pass of groups, at most
   // kMaxChunkGroups and, where that allows it, at most max_chunks.
   const int64_t pass = 4 * (kGatherThreads / p.width);
@@ -2437,7 +2461,8 @@ hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, 
     case 2: pick(std::integral_constant<int, 2>{}); break;
     case 4: pick(std::integral_constant<int, 4>{}); break;
     case 8: pick(std::integral_constant<int, 8>{}); break;
-    default: pick(std::integral_constant<int, 16>{}); break;
+    case 16: pick(std::integral_constant<int, 16>{}); break;
+    default: pick(std::integral_constant<int, 32>{}); break;
   }
   return hipGetLastError();
 }
@@ -2517,6 +2542,14 @@ hipError_t launch_small_step(const AcceptArgs &a, const FinalizeArgs &fa, const 
   };
   if (bf16) { if (stats) pick(std::true_type{}, std::true_type{}); else pick(std::true_type{}, std::false_type{}); }
   else { if (stats) pick(std::false_type{}, std::true_type{}); else pick(std::false_type{}, std::false_type{}); }
+  return hipGetLastError();
+}
+
+bool finalize_scans(int32_t G) { return G <= kScanGroups; }
+
+hipError_t launch_finalize_sums(const FinalizeArgs &fa, bool bf16, const pcg_groups &g, int32_t B, hipStream_t stream) {
+  if (bf16) finalize_sums_kernel<true><<<B, kFinalThreads, 0, stream>>>(fa, g.G);
+  else finalize_sums_kernel<false><<<B, kFinalThreads, 0, stream>>>(fa, g.G);
   return hipGetLastError();
 }
 

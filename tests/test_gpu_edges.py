@@ -102,6 +102,15 @@ def test_csr_gather(V, G, size, B, weighted):
     check_step(V, G, size, B, 2, "bf16", layout="csr", weighted=weighted, thinning=False)
 
 
+# the last kernel reads all sums up to 4096 groups and totals beyond; 32 lanes a group up to 4096 groups of more
+# than 32 entries and 8 rows, 2048 and 16 rows
+@pytest.mark.parametrize("V,G,size,B", [(17000, 4096, 70, 2), (17000, 4097, 70, 2), (17000, 4096, 70, 9), (17000, 2048, 90, 9),
+                                        (17000, 4096, 9, 3), (17000, 1, 40, 2), (17000, 511, 66, 2)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_csr_few_groups(V, G, size, B, weighted):
+    check_step(V, G, size, B, 2, "f32", layout="csr", weighted=weighted, thinning=False)
+
+
 # groups far above the mean size, which a whole wave of the CSR gather sums: right at the size where that
 # begins (64 entries for every lane a group has), past one and several turns of the wave, all tokens; every
 # number of lanes, several tiles, the step in one kernel
