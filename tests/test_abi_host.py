@@ -395,3 +395,38 @@ def test_asg_argument_checks():
     assert need >= L.pcg_asg_build_workspace_bytes(256, 64) + 256 * 128 * 2 + 256 * 8      # unit vectors, norms
     assert exact(wsb=need - 1) == WS_SMALL
     assert L.pcg_asg_build_exact_workspace_bytes(1 << 22, 1024, 64) == 0
+
+
+FOUR, SMALL = False, True
+
+
+@pytest.mark.parametrize("V,size,B,layout,weighted,longs,small", [
+    # one chunk of groups: always in a workgroup per sequence
+    (1000, 8, 1, "prepared", False, 0, SMALL), (4096, 128, 64, "prepared", True, 0, SMALL), (4000, 8, 8, "prepared", False, 1, SMALL),
+    # several chunks: up to a number of tokens and slots, fewer of them with weights
+    (8192, 32, 1, "prepared", False, 0, SMALL), (8192, 32, 1, "prepared", True, 0, FOUR), (12000, 8, 64, "prepared", False, 0, SMALL),
+    (16384, 4, 1, "prepared", False, 0, FOUR), (16384, 4, 64, "prepared", False, 0, FOUR), (16384, 8, 128, "prepared", True, 0, SMALL),
+    (16384, 64, 192, "prepared", True, 0, SMALL), (16384, 4, 257, "prepared", False, 0, FOUR), (16385, 4, 192, "prepared", False, 0, FOUR),
+    # a few long groups pad their blocks: the slots count, not the entries
+    (8192, 8, 8, "prepared", False, 0, SMALL), (8192, 8, 8, "prepared", False, 8, FOUR),
+    # from the CSR
+    (4096, 16, 8, "csr", False, 0, SMALL), (1024, 32, 1, "csr", True, 0, SMALL), (8192, 4, 1, "csr", False, 0, FOUR),
+    (2048, 64, 8, "csr", False, 0, FOUR), (8192, 4, 128, "csr", False, 0, FOUR), (4096, 64, 128, "csr", True, 0, FOUR),
+    (2048, 64, 128, "csr", False, 0, SMALL), (8192, 16, 192, "csr", True, 0, SMALL), (16384, 128, 224, "csr", True, 0, SMALL)])
+def test_which_steps_run_in_a_workgroup_per_sequence(V, size, B, layout, weighted, longs, small):
+    """The rule that sends a step to one or two launches or to four, at sizes of which both sides were
+    timed.  It reads sizes only, no device memory."""
+    rng = np.random.default_rng(V)
+    sets = [np.sort((g + np.arange(size) * (V // size)) % V) for g in range(V)]
+    for k in rng.permutation(V)[:longs]:
+        sets[k] = np.arange(V // 2)
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in sets])]).astype(np.int32)
+    mem = np.concatenate(sets).astype(np.int32)
+    w = W.random_weights(V, mem, seed=1) if weighted else None
+    gs = _GroupsStruct(V, V, len(mem), P, P, P, None, None, None, None, P if weighted else None, None)
+    if layout == "prepared":
+        info = pcg.groups_prepare_host(V, rp, mem, pcg.suggest_chunk_groups(V, B), w)[1]
+        gs.prepared, gs.prepared_info = P, C.pointer(info)
+    shape = getattr(pcg.lib(), "_ZN3pcg10step_shapeERK10pcg_groupsii")      # pcg::step_shape(groups, B, K)
+    shape.restype, shape.argtypes = C.c_int, [C.c_void_p, C.c_int32, C.c_int32]
+    assert (shape(C.addressof(gs), B, 8) < 2) == small
