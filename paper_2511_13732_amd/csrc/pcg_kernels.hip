@@ -2509,49 +2509,47 @@ StepShape step_shape(const pcg_groups &g, int32_t B, int32_t K) {
   if (g.V < 8 || g.V > kSmallTokens || g.G > kSmallGroups || B > 256) return StepShape::kFour;
   if (g.prepared && (g.prepared_info->ntiles != 1 || g.prepared_info->tile_len > kSmallTokens))
     return StepShape::kFour;
-  // One compute unit per sequence for all that follows the statistics, or four kernels that spread a
-  // sequence over the chip but pay for three more boundaries and, from 128 sequences on, have few units
-  // left to spread to.  Whole calls in us, four launches and this, bf16, K = 8 (V, members, B):
-  if (g.prepared) {
-    // With one chunk of groups a sequence's gather is one workgroup in any case: this wins throughout:
-    // 4096, 64, 1: 27.2 and 20.8, 4096, 128 with weights, 128: 61 and 50, chunks of 16 384 groups 16 384, 4, 1: 23.6
-    // and 21.2, 16 384, 100 with weights, 130: 138 and 125.  Several are walked one after the other here, and side
-    // by side there: what counts is the table (tokens) and the slots, padding and all, that one unit reads,
-    // three times as many bytes each with weights.  From 176 sequences on at any size (16 384, 128 with
-    // weights, 192: 240 and 150).
-    //   B < 128:  load 128: 8192, 32, 1: 24.1 and 23.2, 64: 27.6 and 25.2;  116: 12 000, 8, 1: 23.1 and 23.8, 64:
-    //             29.1 and 28.0;  141: 12 000, 16, 1: 23.4 and 25.2;  143: 16 384, 4, 1: 22.7 and 26.8;  192: 8192, 32
-    //             with weights, 1: 26.0 and 26.1;  320: 8192, 64 with weights, 64: 43.7 and 49.1
-    //   from 128: load 256: 16 384, 16 with weights: 44.2 and 43.3, 8192, 48 with weights: 43.3 and 43.7;  192:
-    //             8192, 64: 37.0 and 35.0;  320: 8192, 64 with weights: 48.3 and 51.0
-    const pcg_prepared &p = *g.prepared_info;
-    const int64_t slots = ((p.off_weights ? p.off_weights : p.bytes) - p.off_data) / 2;
-    const int64_t load = g.V / 128 + slots / (g.weights ? 2048 : 4096);
-    if (p.nchunks > 1 && B < 176 && load > (B >= 128 ? 256 : 130)) return StepShape::kFour;
-  } else {
-    // The CSR is read by 256 sub-waves of four lanes: trips are the turns of 1024 groups times those of 16
-    // entries that the mean group needs.  The four kernels spread them.
-    //   B < 128:  2 trips: 1024, 32, 16: 18.3 and 16.0, 2048, 16, 16: 18.5 and 16.2, 4: 4096, 16, 16: 20.4 and 19.4 (one
-    //             of 16 entries a turn), but 2048, 32, 16: 18.5 and 19.2, 1024, 64, 1: 17.0 and 17.7;  8: 8192, 4, 16:
-    //             23.0 and 26.3, 4096, 24, 16: 20.4 and 24.8
-    //   from 128: 8 trips, up to 4096 groups: 4096, 24: 29.5 and 27.0, 1024, 128: 25.4 and 23.9, 2048, 64: 26.3 and 23.9;
-    //             beyond: 8192, 4: 30.2 and 31.3, 12 000, 8 with weights: 39.6 and 45.3;  16: 4096, 64 with weights:
-    //             42.2 and 46.7
-    //   from 160: 8192, 16 with weights, 192: 50.8 and 37.1, 16 384, 4, 160: 59.7 and 56.5
-    //   from 208: 16 384, 128 with weights, 224: 316 and 295
-    const int64_t turns = (g.G + 1023) / 1024, per_turn = (g.nnz + 16 * (int64_t) g.G - 1) / (16 * (int64_t) g.G);
-    bool small;
-    if (B >= 208) small = true;
-    else if (B >= 160) small = g.V / 320 + g.nnz / 4096 <= 80;
-    else if (B >= 128) small = g.G <= 4096 && turns * per_turn <= 8;
-    else small = turns * per_turn <= (per_turn <= 1 ? 4 : 3);
-    if (!small) return StepShape::kFour;
-  }
   // The statistics by the same workgroup, if that is at most two items a wave (V = 1024, K = 4: 13.0
   // against 13.7 us; V = 4096, K = 8: 19.0 against 16.7) or there is a sequence for every compute unit
   // (B = 256: V = 4096 22.1 against 25.3, 16 384 52.8 against 56.3).
   const bool one = row_parts <= kSmallParts && (K + row_parts <= 2 * kGatherWaves || B > 128);
-  return one ? StepShape::kOne : StepShape::kTwo;
+  const StepShape small = one ? StepShape::kOne : StepShape::kTwo;
+  // One compute unit per sequence for all that follows the statistics, or four kernels that spread a
+  // sequence over the chip but pay for three more boundaries.  Whole calls in us, four launches and this,
+  // bf16, K = 8 unless stated (V, members, B).
+  // From 129 sequences on not even two workgroups each of the four kernels run at once, and this wins at
+  // any size: 16 384, 32, 130, K = 3: 55 and 37, from the CSR 8192, 4, 130, K = 3: 33 and 27, 16 384, 40, 130, K = 3:
+  // 157 and 90, 16 384, 4, 160: 60 and 57, 16 384, 128 with weights, 224: 316 and 295.
+  if (B > 128) return small;
+  if (g.prepared) {
+    // With one chunk of groups a sequence's gather is one workgroup in any case, and this wins throughout:
+    // 4096, 64, 1: 27.2 and 20.8, 4096, 128 with weights, 128: 61 and 50, chunks of 16 384 groups 16 384, 4, 1: 23.6
+    // and 21.2, 16 384, 100, 1: 56.9 and 51.4.  Several are walked one after the other here, and side by side
+    // there: what counts is the table (tokens) and the slots, padding and all, that one unit reads, three
+    // times as many bytes each with weights.
+    //   B < 128:  load 128: 8192, 32, 1: 24.1 and 23.2, 64: 27.6 and 25.2;  117: 12 000, 8, 1: 23.1 and 23.8, 64:
+    //             29.1 and 28.0;  140: 12 000, 16, 1: 23.4 and 25.2;  144: 16 384, 4, 1: 22.7 and 26.8;  192: 8192, 32
+    //             with weights, 1: 26.0 and 26.1;  320: 8192, 64 with weights, 64: 43.7 and 49.1
+    //   B = 128:  load 256: 16 384, 16 with weights: 44.2 and 43.3, 8192, 48 with weights: 43.3 and 43.7;  192:
+    //             8192, 64: 37.0 and 35.0;  320: 8192, 64 with weights: 48.3 and 51.0
+    const pcg_prepared &p = *g.prepared_info;
+    const int64_t slots = ((p.off_weights ? p.off_weights : p.bytes) - p.off_data) / 2;
+    const int64_t load = g.V / 128 + slots / (g.weights ? 2048 : 4096);
+    return p.nchunks == 1 || load <= (B == 128 ? 256 : 130) ? small : StepShape::kFour;
+  }
+  // The CSR is read by 256 sub-waves of four lanes: trips are the turns of 1024 groups times those of 16
+  // entries that the mean group needs.  The four kernels spread them.
+  //   B < 128:  2 trips: 1024, 32, 16: 18.3 and 16.0, 2048, 16, 16: 18.5 and 16.2;  4 and 5, one a turn: 4096, 16, 16:
+  //             20.4 and 19.4, 5000, 4, 32, K = 1: 23.2 and 20.2, K = 3: 22.8 and 21.6;  4, two a turn and more: 2048,
+  //             32, 16: 18.5 and 19.2, 1024, 64, 1: 17.0 and 17.7;  8: 8192, 4, 16: 23.0 and 26.3, K = 1: 23.0 and
+  //             25.2, 4096, 24, 16: 20.4 and 24.8
+  //   B = 128:  8 trips, up to 4096 groups: 4096, 24: 29.5 and 27.0, 1024, 128: 25.4 and 23.9, 2048, 64: 26.3 and 23.9;
+  //             beyond: 8192, 4: 30.2 and 31.3, 12 000, 8 with weights: 39.6 and 45.3;  16: 4096, 64 with weights:
+  //             42.2 and 46.7
+  const int64_t turns = (g.G + 1023) / 1024, per_turn = (g.nnz + 16 * (int64_t) g.G - 1) / (16 * (int64_t) g.G);
+  const bool few = B == 128 ? g.G <= 4096 && turns * per_turn <= 8
+                            : turns * per_turn <= (per_turn > 1 ? 3 : one ? 5 : 4);
+  return few ? small : StepShape::kFour;
 }
 
 hipError_t launch_small_step(const AcceptArgs &a, const FinalizeArgs &fa, const ProbeArgs &pa,

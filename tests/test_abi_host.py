@@ -412,7 +412,7 @@ FOUR, SMALL = False, True
     # from the CSR
     (4096, 16, 8, "csr", False, 0, SMALL), (1024, 32, 1, "csr", True, 0, SMALL), (8192, 4, 1, "csr", False, 0, FOUR),
     (2048, 64, 8, "csr", False, 0, FOUR), (8192, 4, 128, "csr", False, 0, FOUR), (4096, 64, 128, "csr", True, 0, FOUR),
-    (2048, 64, 128, "csr", False, 0, SMALL), (8192, 16, 192, "csr", True, 0, SMALL), (16384, 128, 224, "csr", True, 0, SMALL)])
+    (2048, 64, 128, "csr", False, 0, SMALL), (8192, 4, 129, "csr", False, 0, SMALL), (16384, 16, 129, "prepared", False, 0, SMALL), (8192, 16, 192, "csr", True, 0, SMALL), (16384, 128, 224, "csr", True, 0, SMALL)])
 def test_which_steps_run_in_a_workgroup_per_sequence(V, size, B, layout, weighted, longs, small):
     """The rule that sends a step to one or two launches or to four, at sizes of which both sides were
     timed.  It reads sizes only, no device memory."""
