@@ -12,7 +12,7 @@ from parity import (as_oracle_logits, compare_thinning, compare_verify, group_pr
                     run_both, run_both_thinning)
 from test_gpu_asg import as_bf16_tensor, compare_groups
 from test_gpu_propose import compare_proposals
-from test_oracle_asg import embeddings
+from test_oracle_asg import bf16_to_f64, embeddings, stepped_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -93,11 +93,13 @@ def test_prepared_gather_blocks(V, G, size, chunk, weighted):
 
 
 # the CSR gather: fewer than four entries, every number of lanes per group, groups longer than one trip
-# and empty ones, one to four tiles, more chunks than the chunk totals have room for, few and many rows
+# and empty ones, one to four tiles, more chunks than the chunk totals have room for (129 in the last: the last
+# kernel takes their totals 64 at a time), few and many rows
 @pytest.mark.parametrize("weighted", [False, True])
 @pytest.mark.parametrize("V,G,size,B", [(3, 1, 3, 1), (5, 1, 5, 3), (700, 900, 6, 1), (700, 900, 14, 300),
                                         (3000, 2500, 29, 5), (9000, 400, 90, 2), (20000, 40000, 8, 2),
-                                        (45003, 20001, 17, 1), (81000, 300, 700, 3), (100003, 3000, 60, 12)])
+                                        (45003, 20001, 17, 1), (81000, 300, 700, 3), (100003, 3000, 60, 12),
+                                        (30011, 66000, 40, 1)])
 def test_csr_gather(V, G, size, B, weighted):
     check_step(V, G, size, B, 2, "bf16", layout="csr", weighted=weighted, thinning=False)
 
@@ -171,6 +173,19 @@ def test_group_construction_scan(V, d, theta, centres, sigma):
     t = compare_groups(got, oracle.asg_build_exact(E, theta, nthreads=16), f"exact V={V}")
     assert t.flagged_group == 0 and t.tolerated == 0
     assert got.max_size >= int(np.diff(got.row_ptr.cpu().numpy()).max()) and (got.max_size > 64) == (centres > 0)
+
+
+def test_group_construction_where_rounding_moves_most():
+    """Rows whose components all round the same way: similarities off by up to 7e-3, where a band of
+    2^-8 + 2^-18 + d 2^-23 around the threshold would leave pairs on the wrong side of it."""
+    E, m = stepped_rows(400, 3712, 2900)
+    theta = float(np.float32(0.98))
+    U = bf16_to_f64(oracle.asg_normalize(E))
+    rounded, cos = U @ U.T, np.sqrt(np.minimum.outer(m, m) / np.maximum.outer(m, m))
+    outside = np.abs(rounded - theta) > 2.0 ** -8 + 2.0 ** -18 + 3712 * 2.0 ** -23
+    assert (outside & ((rounded > theta) != (cos > theta))).sum() > 100
+    t = compare_groups(pcg.asg_build_exact(torch.from_numpy(E).cuda(), theta), oracle.asg_build_exact(E, theta, nthreads=8), "stepped")
+    assert t.flagged_group == 0 and t.tolerated == 0
 
 
 def test_group_construction_beside_a_row_that_is_not_finite():

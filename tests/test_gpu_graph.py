@@ -18,10 +18,13 @@ def same(a: pcg.VerifyOutput, b: pcg.VerifyOutput):
         np.testing.assert_array_equal(x.cpu().numpy(), y.cpu().numpy())
 
 
-def test_a_recorded_step_replays_to_the_eager_result():
-    V, G, B, K, tau = 6000, 4000, 24, 4, 0.9
+# steps of one, two and four launches, the last from the prepared layout and from the CSR with few groups and with many
+@pytest.mark.parametrize("V,G,B,layout", [(6000, 4000, 24, "prepared"), (1000, 900, 3, "csr"), (20011, 9000, 12, "prepared"),
+                                          (20011, 3000, 12, "csr"), (20011, 9000, 2, "csr")])
+def test_a_recorded_step_replays_to_the_eager_result(V, G, B, layout):
+    K, tau = 4, 0.9
     rp, mem = W.random_groups(V, G, 4, 24, seed=5, cover=False)
-    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", reverse=True)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=layout == "prepared", reverse=True)
     dev = torch.device("cuda")
     tgt = torch.empty((B, K + 1, V), dtype=torch.bfloat16, device=dev)
     dft = torch.empty((B, K, V), dtype=torch.bfloat16, device=dev)

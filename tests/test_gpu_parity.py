@@ -219,10 +219,16 @@ def test_singleton_groups_and_one_big_group():
     assert (gpu.accept_len == K).all()
 
 
-def test_zero_mass_proposals_identical_rows_and_masked_tokens():
-    V, K = 64, 2
-    rp, mem = W.random_groups(V, 30, 2, 6, seed=4, cover=True)
-    og, dg = oracle_groups(V, rp, mem), device_groups(V, rp, mem)
+# steps of one launch and of four: every sum scanned (CSR, up to 4096 groups), or the totals of more chunks than
+# their own region holds (CSR) or of those of the prepared layout
+STEP_FORMS = [(64, 30, "prepared"), (64, 30, "csr"), (20011, 9000, "prepared"), (20011, 3000, "csr"), (20011, 9000, "csr")]
+
+
+@pytest.mark.parametrize("V,G,layout", STEP_FORMS)
+def test_zero_mass_proposals_identical_rows_and_masked_tokens(V, G, layout):
+    K = 2
+    rp, mem = W.random_groups(V, G, 2, 6, seed=4, cover=True)
+    og, dg = oracle_groups(V, rp, mem), device_groups(V, rp, mem, prepare=layout == "prepared")
     g0 = 0
     seg = og.members[og.row_ptr[g0]:og.row_ptr[g0 + 1]]
     rng = np.random.default_rng(1)
@@ -250,10 +256,11 @@ def test_zero_mass_proposals_identical_rows_and_masked_tokens():
     assert z2[int(gpu.accept_len[2])] % 2 == 1          # a masked token is never emitted
 
 
-def test_out_of_range_proposal_is_rejected_not_dereferenced():
-    V, B, K = 500, 8, 3
-    rp, mem = W.random_groups(V, 300, 2, 8, seed=6, cover=True)
-    og, dg = oracle_groups(V, rp, mem), device_groups(V, rp, mem)
+@pytest.mark.parametrize("V,G,layout", [(500, 300, "prepared"), *STEP_FORMS[1:]])
+def test_out_of_range_proposal_is_rejected_not_dereferenced(V, G, layout):
+    B, K = 8, 3
+    rp, mem = W.random_groups(V, G, 2, 8, seed=6, cover=True)
+    og, dg = oracle_groups(V, rp, mem), device_groups(V, rp, mem, prepare=layout == "prepared")
     tgt, dft = logits_pair(B, K, V, "f32", seed=2)
     ptok, pgrp = coupled_proposals(dft, 1.0, og, seed=0)
     pgrp[0, 0] = dg.G + 5
@@ -361,12 +368,15 @@ def test_recipe_full_size(name, steps):
     assert total.tolerated <= max(1, total.sequences // 100)
 
 
-def test_profile_reports_every_kernel_of_a_step():
-    cfg = W.CONFIGS["C2"]
-    rp, mem = W.groups(cfg)
-    og = oracle_groups(cfg.V, rp, mem)
-    dg = device_groups(cfg.V, rp, mem, chunk_groups=pcg.suggest_chunk_groups(og.G, cfg.B))
-    tgt, dft, ptok, pgrp = W.step_inputs(cfg, og.row_ptr, og.members, 0)
+# what each launch of the step is recorded under; the rest are event pairs with nothing between them
+@pytest.mark.parametrize("V,G,B,launched", [(20011, 9000, 64, ("row_stats", "accept_delta", "gather", "finalize")),
+                                            (4096, 3000, 8, ("row_stats", "gather")), (900, 700, 2, ("gather",))])
+def test_profile_reports_every_kernel_of_a_step(V, G, B, launched):
+    K = 8 if V > 1000 else 2
+    rp, mem = W.random_groups(V, G, 8, 24, seed=6, cover=True)
+    og, dg = oracle_groups(V, rp, mem), device_groups(V, rp, mem)
+    tgt, dft = logits_pair(B, K, V, "bf16", seed=2)
+    ptok, pgrp = coupled_proposals(dft, 1.0, og, seed=0)
     args = (dg, tgt.cuda(), dft.cuda(), torch.from_numpy(ptok).cuda(), torch.from_numpy(pgrp).cuda())
     plain = pcg.verify(*args, seed=1, offset=2)
     pcg.profile_begin(4)
@@ -375,8 +385,12 @@ def test_profile_reports_every_kernel_of_a_step():
     torch.cuda.synchronize()
     ms, calls = pcg.profile_end()
     assert calls == 4
+    print({k: round(1e3 * v, 2) for k, v in ms.items()}, flush=True)
     for k in ("row_stats", "accept_delta", "gather", "finalize", "event_overhead"):
         assert 0.0 < ms[k] < 5.0, (k, ms)
+        # an empty pair reads as event_overhead within 0.2 us, the shortest kernel 1.4 us above it
+        if k != "event_overhead":
+            assert (ms[k] - ms["event_overhead"] > 0.7e-3) == (k in launched), (k, ms)
     assert ms["weights"] == 0.0
     assert torch.equal(plain.out_tokens, timed.out_tokens)      # timing does not change results
     with pytest.raises(pcg.PcgError):

@@ -215,12 +215,27 @@ def test_exact_groups_are_the_distinct_sets_of_eq1_in_order_of_first_appearance(
 
 
 # The similarity the kernels threshold is the dot product of unit vectors rounded to bfloat16
-# (8 significant bits: every component off by at most 2^-9 of itself).  With unit vectors x, y
-# and their roundings x(1+e), y(1+f), |e|, |f| <= 2^-9:
-#   |sum x_k y_k ((1+e_k)(1+f_k) - 1)| <= (2^-8 + 2^-18) sum |x_k y_k| <= 2^-8 + 2^-18
+# (8 significant bits: every component off by at most 2^-8 of itself, half a unit in the last place
+# where a binade begins).  With unit vectors x, y and their roundings x(1+e), y(1+f), |e|, |f| <= 2^-8:
+#   |sum x_k y_k ((1+e_k)(1+f_k) - 1)| <= (2^-7 + 2^-16) sum |x_k y_k| <= 2^-7 + 2^-16
 # (Cauchy-Schwarz).  A membership can therefore differ from Eq. (1) only for a pair whose cosine
 # lies within BF16_BAND of theta; the tie band of the bf16 form (1e-5) adds nothing visible.
-BF16_BAND = 2.0 ** -8 + 2.0 ** -18
+BF16_BAND = 2.0 ** -7 + 2.0 ** -16
+
+
+def stepped_rows(V, d, lowest):
+    """Rows of ones up to a length of its own each, zeros beyond: all components of a row round the same
+    way, which moves its products with others further than components that round at random do."""
+    m = np.random.default_rng(3).permutation(np.arange(lowest, d + 1))[:V]
+    return (np.arange(d)[None] < m[:, None]).astype(np.float32), m
+
+
+def test_rounding_moves_a_similarity_by_more_than_2_to_the_minus_8():
+    E, m = stepped_rows(400, 3712, 2900)
+    U = bf16_to_f64(oracle.asg_normalize(E))
+    off = np.abs(U @ U.T - np.sqrt(np.minimum.outer(m, m) / np.maximum.outer(m, m)))
+    print(f"largest |bf16 similarity - cosine| {off.max():.2e}, band {BF16_BAND:.2e}")
+    assert 2.0 ** -8 + 2.0 ** -18 < off.max() <= BF16_BAND
 
 
 @pytest.mark.parametrize("name,V,d,theta,centres,sigma", [
