@@ -373,8 +373,14 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 def _stream(device) -> int:
     """The current stream of the device as the library takes it.  (The stream object that
-    torch.cuda.current_stream builds costs 1.8 us a call, as much as a kernel launch.)"""
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    torch.cuda.current_stream builds costs 1.8 us a call, as much as a kernel launch; a torch
+    without the plain form gets that.)"""
+    if _raw_stream is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _call(device, what: str, fn, *args):
