@@ -475,7 +475,8 @@ int pcg_groups_prepare_weights_host(int32_t V, int32_t G, const int32_t *row_ptr
  * "event_overhead" is an empty event pair recorded at the start of each call: the time an
  * event pair adds, which is included in every other stage's figure.  A step that is small enough
  * to run as one or two kernels has everything after row_stats (or with it) recorded under "gather";
- * the stages so absorbed then read as event_overhead.
+ * the stages so absorbed then read as event_overhead.  pcg_propose on rows of up to 131 072 logits is
+ * one kernel, recorded under "propose": row_stats then reads 0.
  * Not thread-safe; one profile at a time.
  */
 int pcg_profile_begin(int32_t max_calls);

@@ -76,7 +76,7 @@ def test_random_shape(case):
             dft[:, :, mask] = -float("inf")
         if case % 2 == 1:
             # the rows as views into larger buffers: row strides above V, starts that are not
-            # 16-byte aligned (the kernels then take their element-wise loads), and the draft
+            # 16-byte aligned (the kernels load 16 bytes at any element), and the draft
             # inside a [B, K + 1, V] buffer whose last row is never read
             pad, off = int(rng.integers(1, 40)), int(rng.integers(0, 9))
             big_t = torch.zeros((B, K + 1, V + pad + off), dtype=tgt.dtype, device="cuda")
