@@ -357,10 +357,12 @@ constexpr int kAcceptTokens = kAcceptThreads * kTokensPerThread;   // delta toke
 struct AcceptShared {
   RowStat st_t[PCG_MAX_K + 1];                 // statistics of the target rows 0..K
   RowStat st_d[PCG_MAX_K];                     // ... and of the draft rows 0..K-1
+  double iz_t[PCG_MAX_K + 1], iz_d[PCG_MAX_K]; // 1 / Z of those rows
   double Tp[PCG_MAX_K], Dp[PCG_MAX_K];         // probe sums relative to the group's own maxima
   double Tn[PCG_MAX_K], Dn[PCG_MAX_K];         // T_i[g], D_i[g] of the proposed groups
   float Tref[PCG_MAX_K], Dref[PCG_MAX_K];      // those maxima
   float uacc[PCG_MAX_K];                       // accept uniforms
+  float ugrp[PCG_MAX_K + 1], utok[PCG_MAX_K + 1];   // group and token uniforms (accept_fetch)
   int bad[PCG_MAX_K], ptok[PCG_MAX_K], pgrp[PCG_MAX_K];
   int istar;                                   // accept_len of the sequence
 };
@@ -402,22 +404,30 @@ __device__ __forceinline__ RowStat merge_row16(const StatPart *rp, int32_t npart
 }
 
 // The accept scan of sequence b (Algorithm 1 up to the first rejection) by one workgroup of
-// kAcceptThreads.  On return sh.istar, sh.st_t and sh.st_d are valid for every thread; with
-// `writer` the sequence's outputs and counters are written, and its row statistics if a.rowstat is
-// given.  probes: the sequence's K probes; parts_t, parts_d: the parts of its target and draft rows.
-// FETCHED: the proposals and their accept uniforms are in sh already (accept_fetch).
+// kAcceptThreads, in two halves with a barrier between them.  In the end sh.istar, the statistics and their
+// reciprocals are valid for every thread; with `writer` the sequence's outputs and counters are written,
+// and its row statistics if a.rowstat is given.  probes: the sequence's K probes; parts_t, parts_d: the
+// parts of its target and draft rows.
+// Before the barrier one wave also fetches the proposals and draws the uniforms of every position, a
+// position per lane: at the decision's own position alone, once that is known, the generator's chain of
+// multiplications would stand in every wave's way (16 waves on four SIMDs: 0.7 of the 12.6 us of the small
+// step at V = 1024, B = 1, 1.4 of 14.3 at V = 4096, B = 8).
 __device__ __forceinline__ void accept_fetch(AcceptShared &sh, const AcceptArgs &a, int b, int lane) {
   for (int i = lane; i < a.K; i += kWave) {
     sh.pgrp[i] = a.prop_groups[(int64_t) b * a.K + i];
     sh.ptok[i] = a.prop_tokens[(int64_t) b * a.K + i];
-    sh.uacc[i] = philox_uniforms(a.seed, a.offset, (uint32_t) b, (uint32_t) i).acc;
+  }
+  for (int i = lane; i <= a.K; i += kWave) {
+    const Uniforms u = philox_uniforms(a.seed, a.offset, (uint32_t) b, (uint32_t) i);
+    if (i < a.K) sh.uacc[i] = u.acc;
+    sh.ugrp[i] = u.grp;
+    sh.utok[i] = u.tok;
   }
 }
 
-template <bool FETCHED>
-__device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs &a, int b, bool writer,
-                                             const Probe *probes, const StatPart *parts_t,
-                                             const StatPart *parts_d) {
+// First half: the probes fetched, the row statistics merged, all to sh.
+__device__ __forceinline__ void accept_merge(AcceptShared &sh, const AcceptArgs &a, int b, bool writer,
+                                             const Probe *probes, const StatPart *parts_t, const StatPart *parts_d) {
   const int K = a.K;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   constexpr int nw = kAcceptThreads / kWave;
@@ -430,7 +440,6 @@ __device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs 
       sh.Tp[i] = p.Tp; sh.Dp[i] = p.Dp; sh.Tref[i] = p.Tref; sh.Dref[i] = p.Dref;
       sh.bad[i] = p.bad;
     }
-    if constexpr (!FETCHED) accept_fetch(sh, a, b, lane);
   } else {
     // row statistics of this sequence's 2K+1 rows, four rows per wave at a time
     const int sub = lane & 15;
@@ -438,15 +447,20 @@ __device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs 
       const bool is_t = r <= K;
       const int i = is_t ? r : r - K - 1;
       const RowStat s = merge_row16((is_t ? parts_t : parts_d) + (int64_t) i * a.nparts, a.nparts, a.c, sub);
+      const double iz = 1.0 / s.Z;                  // here once, not by every wave that needs it
       if (sub == 0) {
         if (writer && a.rowstat)
           a.rowstat[is_t ? (int64_t) b * (K + 1) + i : a.rs.nrows0 + (int64_t) b * K + i] = s;
-        if (is_t) sh.st_t[i] = s; else sh.st_d[i] = s;
+        if (is_t) { sh.st_t[i] = s; sh.iz_t[i] = iz; } else { sh.st_d[i] = s; sh.iz_d[i] = iz; }
       }
     }
   }
-  lds_barrier();
+}
 
+// Second half, after a barrier; ends with one.
+__device__ __forceinline__ void accept_decide(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
+  const int K = a.K;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   // Both chains have met.  One wave, one position per lane (K <= 64): normalise the probe,
   // take the accept test, and find the first rejection with a ballot; the draft token stands
   // for its group on accept.
@@ -492,11 +506,19 @@ __device__ __forceinline__ void accept_phase(AcceptShared &sh, const AcceptArgs 
   lds_barrier();
 }
 
-// The same on the probes and parts that the statistics pass left in memory.
-__device__ __forceinline__ void accept_phase_stored(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
-  accept_phase<false>(sh, a, b, writer, a.probes + (int64_t) b * a.K,
-               a.parts + (int64_t) b * (a.K + 1) * a.nparts,
+// The first half on the probes and parts that the statistics pass left in memory.
+__device__ __forceinline__ void accept_merge_stored(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
+  accept_merge(sh, a, b, writer, a.probes + (int64_t) b * a.K, a.parts + (int64_t) b * (a.K + 1) * a.nparts,
                a.parts + (a.rs.nrows0 + (int64_t) b * a.K) * a.nparts);
+}
+
+// The whole scan on those, fetch and all.
+__device__ __forceinline__ void accept_phase_stored(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
+  accept_merge_stored(sh, a, b, writer);
+  // the last wave has the fewest rows to merge
+  if (threadIdx.x >= kAcceptThreads - kWave) accept_fetch(sh, a, b, threadIdx.x & (kWave - 1));
+  lds_barrier();
+  accept_decide(sh, a, b, writer);
 }
 
 // The table entries of eight tokens on a decision row (statistics st; draft sd if it was rejected).
@@ -549,7 +571,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs
   const void *drow = row_base(rs, rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0), BF16);
   const RowStat st = sh.st_t[istar];
   const RowStat sd = sh.st_d[rejected ? istar : 0];
-  const double izt = 1.0 / st.Z, izd = rejected ? 1.0 / sd.Z : 0.0;
+  const double izt = sh.iz_t[istar], izd = rejected ? sh.iz_d[istar] : 0.0;
   auto delta = [&](const float *xt, const float *xd, const float *m, float *v) {
     delta8(xt, xd, m, rejected, st, sd, izt, izd, c, c_lo, v);
   };
@@ -913,18 +935,22 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_thin_kernel(
 // of the membership entries of x.
 // =============================================================================================
 
-// The draw of one row by one wave, from the masses of its parts.
-template <bool BF16, int N>
-__device__ __forceinline__ void propose_draw(const PartMasses<N> &pm, uint32_t *redo, const RowSet &rs, int64_t row,
-                                             int32_t V, int32_t K, int32_t pos0, int32_t nparts, float c,
-                                             const int32_t *tok_ptr, const int32_t *tok_groups,
-                                             const float *tok_weights, uint64_t seed, uint64_t offset,
-                                             int32_t *prop_tokens, int32_t *prop_groups, pcg_diag *diag,
-                                             int lane) {
+// The uniforms of one row's draw; formed while its first loads are on their way.
+__device__ __forceinline__ ProposalDraws propose_uniforms(const RowSet &rs, int64_t row, int32_t K, int32_t pos0,
+                                                          uint64_t seed, uint64_t offset) {
   int64_t b;
   int32_t i;
   split_row(row, K, rs.inv_npos0, b, i);
-  const ProposalDraws d = philox_proposal(seed, offset, (uint32_t) b, (uint32_t) (pos0 + i));
+  return philox_proposal(seed, offset, (uint32_t) b, (uint32_t) (pos0 + i));
+}
+
+// The draw of one row by one wave, from the masses of its parts.
+template <bool BF16, int N>
+__device__ __forceinline__ void propose_draw(const PartMasses<N> &pm, uint32_t *redo, const RowSet &rs, int64_t row,
+                                             int32_t V, int32_t nparts, float c, const ProposalDraws &d,
+                                             const int32_t *tok_ptr, const int32_t *tok_groups,
+                                             const float *tok_weights, int32_t *prop_tokens,
+                                             int32_t *prop_groups, pcg_diag *diag, int lane) {
   bool near = false;
   const int32_t x = draw_token<BF16>(pm, redo, row_base(rs, row, BF16), V, nparts, c,
                                           (double) d.u_x, lane, &near);
@@ -951,13 +977,14 @@ __global__ __launch_bounds__(kWave) void propose_kernel(
   const int lane = threadIdx.x;
   const int64_t row = blockIdx.x;
   const StatPart *rp = parts + row * nparts;
+  const ProposalDraws d = propose_uniforms(rs, row, K, pos0, seed, offset);
   float M = -INFINITY;
   for (int32_t p = lane; p < nparts; p += kWave) M = fmaxf(M, rp[p].m);
   M = wave_max(M);
   fill_part_masses(pm, rp, nparts, M, c, lane, kWave);
   __syncthreads();
-  propose_draw<BF16>(pm, redo, rs, row, V, K, pos0, nparts, c, tok_ptr, tok_groups, tok_weights, seed,
-                     offset, prop_tokens, prop_groups, diag, lane);
+  propose_draw<BF16>(pm, redo, rs, row, V, nparts, c, d, tok_ptr, tok_groups, tok_weights, prop_tokens, prop_groups,
+                     diag, lane);
 }
 
 // The same in one launch, by one workgroup per row: the row's parts stay in LDS between its statistics
@@ -983,6 +1010,8 @@ __global__ __launch_bounds__(kProposeThreads) void propose_row_kernel(
   // cached loads: the draw reads a part again; a wave's next part is on its way behind the present one
   RowPart<BF16, WIDE, false> raw;
   if (wave < nparts) raw.load(rowp, wave * kPartElems, V, lane);
+  ProposalDraws d = {0.f, 0u};
+  if (wave == 0) d = propose_uniforms(rs, row, K, pos0, seed, offset);
   for (int32_t p = wave; p < nparts; p += kWaves) {
     float x[32];
     raw.get(x, p * kPartElems, V, lane);
@@ -998,8 +1027,8 @@ __global__ __launch_bounds__(kProposeThreads) void propose_row_kernel(
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  propose_draw<BF16>(pm, redo, rs, row, V, K, pos0, nparts, c, tok_ptr, tok_groups, tok_weights, seed,
-                     offset, prop_tokens, prop_groups, diag, lane);
+  propose_draw<BF16>(pm, redo, rs, row, V, nparts, c, d, tok_ptr, tok_groups, tok_weights, prop_tokens, prop_groups,
+                     diag, lane);
 }
 
 // =============================================================================================
@@ -1524,7 +1553,8 @@ __device__ void finish_sequence(const FinalizeArgs &fa, int32_t G, int b, int32_
       }
       double total = 0.0;
 #pragma unroll
-      for (int c = 0; c < kTokRounds; ++c) total += wave_sum(w[c]);      // ascending, 64 at a time
+      for (int c = 0; c < kTokRounds; ++c)
+        if (c * kWave < n) total += wave_sum(w[c]);                      // ascending, 64 at a time
       pt.index = -1; pt.total = total; pt.lo = pt.hi = 0.0;
       const double goal = (double) u.tok * total;
       double base = 0.0, last_v = 0.0;
@@ -2215,6 +2245,7 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
       if (it + kGatherWaves < nparts_all) reduce(raw[1], it + kGatherWaves);
     }
   } else {
+    accept_merge_stored(sh, a, b, true);
     load_m();
     if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
   }
@@ -2237,9 +2268,11 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   };
   if constexpr (SUMS <= kSumsPreparedWeighted) ask_chunk(0);
   lds_barrier();
-  if constexpr (STATS) accept_phase<true>(sh, a, b, true, probes, parts, parts + (K + 1) * a.nparts);
-  else accept_phase<true>(sh, a, b, true, a.probes + (int64_t) b * K, a.parts + (int64_t) b * (K + 1) * a.nparts,
-                          a.parts + (rs.nrows0 + (int64_t) b * K) * a.nparts);
+  if constexpr (STATS) {
+    accept_merge(sh, a, b, true, probes, parts, parts + (K + 1) * a.nparts);
+    lds_barrier();
+  }
+  accept_decide(sh, a, b, true);
 
   // the table on the decision row, straight into LDS
   const int32_t istar = sh.istar;
@@ -2248,7 +2281,7 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   const void *drow = row_base(rs, rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0), BF16);
   const RowStat st = sh.st_t[istar];
   const RowStat sd = sh.st_d[rejected ? istar : 0];
-  const double izt = 1.0 / st.Z, izd = rejected ? 1.0 / sd.Z : 0.0;
+  const double izt = sh.iz_t[istar], izd = rejected ? sh.iz_d[istar] : 0.0;
   for (int32_t at = first; at < V; at += kAcceptTokens) {
     const int32_t t = slice_start<true>(at, V);
     float xt[8], xd[8], v[8];
@@ -2296,7 +2329,10 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   }
   lds_barrier();
 
-  const Uniforms u = philox_uniforms(fa.seed, fa.offset, (uint32_t) b, (uint32_t) istar);
+  Uniforms u;
+  u.acc = 0.f;
+  u.grp = sh.ugrp[istar];
+  u.tok = sh.utok[istar];
   const CdfPick pg = pick_group(sums, G, (double) u.grp);
   finish_sequence<BF16, kAcceptThreads>(fa, G, b, istar, trow, st, u, pg);
 }
