@@ -81,6 +81,9 @@ struct StageTimer {
   }
 };
 
+// See RowSet.
+uint32_t row_magic(int32_t npos) { return npos > 1 ? (uint32_t) (((uint64_t) 1 << 32) / (uint32_t) npos) : 0u; }
+
 bool good_temperature(float t) { return std::isfinite(t) && t > 0.0f; }
 
 int check_groups(const pcg_groups *g) {
@@ -187,7 +190,7 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
   rs.npos0 = 1;
   rs.npos1 = 1;
   rs.nrows0 = rows;
-  rs.inv_npos0 = rs.inv_npos1 = 1.0;
+  rs.magic0 = rs.magic1 = row_magic(1);
   const Factors f = factors(temperature);
 
   StageTimer tm(stream);
@@ -254,8 +257,8 @@ int check_verify_args(const pcg_groups *groups, const void *target_logits, const
   rs.npos0 = K + 1;
   rs.npos1 = K;
   rs.nrows0 = (int64_t) B * (K + 1);
-  rs.inv_npos0 = 1.0 / (K + 1);
-  rs.inv_npos1 = 1.0 / K;
+  rs.magic0 = row_magic(K + 1);
+  rs.magic1 = row_magic(K);
   return PCG_OK;
 }
 
@@ -543,8 +546,8 @@ int pcg_propose(const pcg_groups *groups, const void *draft_logits, pcg_dtype dt
   rs.npos0 = K;
   rs.npos1 = 1;
   rs.nrows0 = rows;
-  rs.inv_npos0 = 1.0 / K;
-  rs.inv_npos1 = 1.0;
+  rs.magic0 = row_magic(K);
+  rs.magic1 = row_magic(1);
   const Factors f = factors(temperature);
   hipStream_t stream = (hipStream_t) hip_stream;
   StatPart *parts = propose_in_rows(V) ? nullptr : (StatPart *) workspace;

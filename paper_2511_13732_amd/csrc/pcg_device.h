@@ -36,30 +36,43 @@ struct RowSet {
   int64_t bs0, ps0, bs1, ps1;   // strides in elements
   int32_t npos0, npos1;
   int64_t nrows0;               // B * npos0
-  double inv_npos0, inv_npos1;  // 1 / npos, so that kernels split a row id without dividing
+  uint32_t magic0, magic1;      // floor(2^32 / npos) for npos > 1, so that kernels split a row id without dividing
 };
 
-// row / npos and row % npos for 0 <= row < 2^40, 1 <= npos <= 65: a multiplication by the
-// reciprocal and one correction step instead of a 64-bit integer division.
-__device__ __forceinline__ void split_row(int64_t row, int32_t npos, double inv_npos, int64_t &b,
-                                          int32_t &i) {
-  int64_t q = (int64_t) ((double) row * inv_npos);
-  int64_t r = row - q * npos;
-  if (r < 0) { --q; r += npos; }
-  if (r >= npos) { ++q; r -= npos; }
-  b = q;
+// row / npos and row % npos; row < 2^32 where npos > 1.  The product of row and the magic number falls short of
+// row / npos by less than one: one correction step.  Integers, so that it stays on the scalar unit where the
+// row is the same for the whole wave (in double it took some 60 vector instructions a row, in every wave
+// and, where a decision has just been taken, in its way).
+__device__ __forceinline__ void split_row(int64_t row, int32_t npos, uint32_t magic, int64_t &b, int32_t &i) {
+  if (npos == 1) {
+    b = row;
+    i = 0;
+    return;
+  }
+  uint32_t q = __umulhi((uint32_t) row, magic);
+  uint32_t r = (uint32_t) row - q * (uint32_t) npos;
+  if (r >= (uint32_t) npos) { ++q; r -= (uint32_t) npos; }
+  b = (int64_t) q;
   i = (int32_t) r;
+}
+
+// Position i of sequence b in set 0 (target rows) and set 1 (draft rows).
+__device__ __forceinline__ const void *target_row(const RowSet &rs, int64_t b, int32_t i, bool bf16) {
+  return elem_ptr(rs.base0, b * rs.bs0 + i * rs.ps0, bf16);
+}
+__device__ __forceinline__ const void *draft_row(const RowSet &rs, int64_t b, int32_t i, bool bf16) {
+  return elem_ptr(rs.base1, b * rs.bs1 + i * rs.ps1, bf16);
 }
 
 __device__ __forceinline__ const void *row_base(const RowSet &rs, int64_t row, bool bf16) {
   int64_t b;
   int32_t i;
   if (row < rs.nrows0) {
-    split_row(row, rs.npos0, rs.inv_npos0, b, i);
-    return elem_ptr(rs.base0, b * rs.bs0 + i * rs.ps0, bf16);
+    split_row(row, rs.npos0, rs.magic0, b, i);
+    return target_row(rs, b, i, bf16);
   }
-  split_row(row - rs.nrows0, rs.npos1, rs.inv_npos1, b, i);
-  return elem_ptr(rs.base1, b * rs.bs1 + i * rs.ps1, bf16);
+  split_row(row - rs.nrows0, rs.npos1, rs.magic1, b, i);
+  return draft_row(rs, b, i, bf16);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -96,8 +96,8 @@ __device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t b, int3
   double at = 0.0, ad = 0.0;
   float mt = -INFINITY, md = -INFINITY;
   if (ok) {
-    const void *trow = row_base(rs, b * (K + 1) + i, BF16);
-    const void *drow = row_base(rs, rs.nrows0 + b * K + i, BF16);
+    const void *trow = target_row(rs, b, i, BF16);
+    const void *drow = draft_row(rs, b, i, BF16);
     const int32_t beg = pa.row_ptr[g], end = pa.row_ptr[g + 1];
     // the first 64 members stay in registers; longer groups take a second trip
     const bool has = beg + lane < end;
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kStatsWaves *kWave) void row_stats_kernel(RowSet rs
     if (prow >= rs.nrows0) return;
     int64_t b;
     int32_t i;
-    split_row(prow, rs.npos0, rs.inv_npos0, b, i);
+    split_row(prow, rs.npos0, rs.magic0, b, i);
     if (i < pa.K) probe_row<BF16>(rs, pa, b, i, c, lane, pa.out + b * pa.K + i);   // the bonus row has none
     return;
   }
@@ -565,10 +565,10 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs
   accept_phase_stored(sh, a, b, split == 0);
 
   // 4. this workgroup's share of the table on the decision row: slices split, split + nsplit, ...
-  const int32_t istar = sh.istar;
+  const int32_t istar = __builtin_amdgcn_readfirstlane(sh.istar);
   const bool rejected = istar < K;
-  const void *trow = row_base(rs, (int64_t) b * (K + 1) + istar, BF16);
-  const void *drow = row_base(rs, rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0), BF16);
+  const void *trow = target_row(rs, b, istar, BF16);
+  const void *drow = draft_row(rs, b, rejected ? istar : 0, BF16);
   const RowStat st = sh.st_t[istar];
   const RowStat sd = sh.st_d[rejected ? istar : 0];
   const double izt = sh.iz_t[istar], izd = rejected ? sh.iz_d[istar] : 0.0;
@@ -832,11 +832,12 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_thin_kernel(
   accept_phase_stored(sh, a, b, true);
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int32_t K = a.K, V = a.V, istar = sh.istar;
+  const int32_t K = a.K, V = a.V, istar = __builtin_amdgcn_readfirstlane(sh.istar);
+  const int32_t pos = sh.istar;          // the same, for the generator: on the vector unit it is the faster chain
   const bool bonus = istar == K;
   const int64_t trow_id = (int64_t) b * (K + 1) + istar;
-  const void *trow = row_base(a.rs, trow_id, BF16);
-  const void *drow = row_base(a.rs, a.rs.nrows0 + (int64_t) b * K + (bonus ? 0 : istar), BF16);
+  const void *trow = target_row(a.rs, b, istar, BF16);
+  const void *drow = draft_row(a.rs, b, bonus ? 0 : istar, BF16);
   const RowStat st = sh.st_t[istar];
   const RowStat sd = sh.st_d[bonus ? 0 : istar];
   const float c_lo = (float) (a.cd - (double) a.c);
@@ -862,7 +863,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_thin_kernel(
     const int32_t trial = round * kThinTrialWaves + wave;
     const bool active = wave < kThinTrialWaves && (bonus ? trial == 0 : trial < max_trials);
     if (active) {   // uniform over the wave
-      const TrialDraws d = philox_trial(a.seed, a.offset, (uint32_t) b, (uint32_t) istar,
+      const TrialDraws d = philox_trial(a.seed, a.offset, (uint32_t) b, (uint32_t) pos,
                                         (uint32_t) trial);
       bool near_y = false;
       const int32_t y = draw_token<BF16>(th.pm, th.redo[wave], trow, V, a.nparts, a.c,
@@ -940,7 +941,7 @@ __device__ __forceinline__ ProposalDraws propose_uniforms(const RowSet &rs, int6
                                                           uint64_t seed, uint64_t offset) {
   int64_t b;
   int32_t i;
-  split_row(row, K, rs.inv_npos0, b, i);
+  split_row(row, K, rs.magic0, b, i);
   return philox_proposal(seed, offset, (uint32_t) b, (uint32_t) (pos0 + i));
 }
 
@@ -1613,7 +1614,7 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
   const int32_t K = fa.K;
   const int32_t istar = fa.accept_len[b];
   const int64_t trow_id = (int64_t) b * (K + 1) + istar;
-  const void *trow = row_base(fa.rs, trow_id, BF16);
+  const void *trow = target_row(fa.rs, b, istar, BF16);
   const RowStat st = fa.rowstat[trow_id];
   const Uniforms u = philox_uniforms(fa.seed, fa.offset, (uint32_t) b, (uint32_t) istar);
   const int32_t *row_ptr = fa.row_ptr, *members = fa.members, *mult = fa.mult;
@@ -1666,7 +1667,7 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
           __shared__ int32_t run_n[kRunGroups], run_beg[kRunGroups];
           __shared__ bool run_has[kRunGroups];          // some entry of the group adds to it
           const bool rejected = istar < K;
-          const void *drow = row_base(fa.rs, fa.rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0), BF16);
+          const void *drow = draft_row(fa.rs, b, rejected ? istar : 0, BF16);
           const RowStat sd = fa.rowstat[fa.rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0)];
           const double izt = 1.0 / st.Z, izd = rejected ? 1.0 / sd.Z : 0.0;
           const int32_t gr0 = g0 + pr.index * kRunGroups;
@@ -1844,7 +1845,7 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_sums_kernel(FinalizeAr
   const float *sums = fa.R + (int64_t) b * G;
   const CdfPick pg = block_inverse_cdf<kFinalThreads, kScanGroups / kFinalThreads>(
       G, [&](int32_t g) { return (double) sums[g]; }, (double) u.grp);
-  finish_sequence<BF16, kFinalThreads>(fa, G, b, istar, row_base(fa.rs, trow_id, BF16), fa.rowstat[trow_id], u, pg);
+  finish_sequence<BF16, kFinalThreads>(fa, G, b, istar, target_row(fa.rs, b, istar, BF16), fa.rowstat[trow_id], u, pg);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2225,8 +2226,7 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
     RowPart<BF16, true, false> raw[2];    // cached: the decision rows are read again
     auto ask = [&](RowPart<BF16, true, false> &to, int32_t it) {
       const int32_t r = it / a.nparts, part = it % a.nparts;
-      const int64_t row = r <= K ? (int64_t) b * (K + 1) + r : rs.nrows0 + (int64_t) b * K + (r - K - 1);
-      to.load(row_base(rs, row, BF16), part * kPartElems, V, lane);
+      to.load(r <= K ? target_row(rs, b, r, BF16) : draft_row(rs, b, r - K - 1, BF16), part * kPartElems, V, lane);
     };
     if (wave < nparts_all) ask(raw[0], wave);
     if (wave + kGatherWaves < nparts_all) ask(raw[1], wave + kGatherWaves);
@@ -2275,10 +2275,10 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   accept_decide(sh, a, b, true);
 
   // the table on the decision row, straight into LDS
-  const int32_t istar = sh.istar;
+  const int32_t istar = __builtin_amdgcn_readfirstlane(sh.istar);
   const bool rejected = istar < K;
-  const void *trow = row_base(rs, (int64_t) b * (K + 1) + istar, BF16);
-  const void *drow = row_base(rs, rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0), BF16);
+  const void *trow = target_row(rs, b, istar, BF16);
+  const void *drow = draft_row(rs, b, rejected ? istar : 0, BF16);
   const RowStat st = sh.st_t[istar];
   const RowStat sd = sh.st_d[rejected ? istar : 0];
   const double izt = sh.iz_t[istar], izd = rejected ? sh.iz_d[istar] : 0.0;
