@@ -43,6 +43,18 @@ constexpr int kStatsWaves = 4;        // waves per workgroup
 // Row id of a workgroup: grid.y carries the low part, grid.z the rest (grid.y <= 65535).
 constexpr int kRowsPerGridY = 32768;
 
+// Asks for all of the kernel's arguments (BYTES of them) at once: one word of every 64-byte line.
+template <size_t BYTES>
+__device__ __forceinline__ void warm_arguments() {
+  const __attribute__((address_space(4))) uint32_t *ka =
+      (const __attribute__((address_space(4))) uint32_t *) __builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t w[(BYTES + 63) / 64];
+#pragma unroll
+  for (size_t i = 0; i < (BYTES + 63) / 64; ++i) w[i] = ka[16 * i];
+#pragma unroll
+  for (size_t i = 0; i < (BYTES + 63) / 64; ++i) asm volatile("" ::"s"(w[i]));
+}
+
 // A 16-byte load at any element address (the type says so to the compiler, which then relies on
 // the unaligned access that the amdhsa target guarantees for global memory: the same instruction
 // as an aligned load, at most one cache line more per wave).  Optionally marked as streaming
@@ -358,14 +370,21 @@ struct AcceptShared {
   RowStat st_t[PCG_MAX_K + 1];                 // statistics of the target rows 0..K
   RowStat st_d[PCG_MAX_K];                     // ... and of the draft rows 0..K-1
   double iz_t[PCG_MAX_K + 1], iz_d[PCG_MAX_K]; // 1 / Z of those rows
-  double Tp[PCG_MAX_K], Dp[PCG_MAX_K];         // probe sums relative to the group's own maxima
-  double Tn[PCG_MAX_K], Dn[PCG_MAX_K];         // T_i[g], D_i[g] of the proposed groups
-  float Tref[PCG_MAX_K], Dref[PCG_MAX_K];      // those maxima
+  Probe probe[PCG_MAX_K];                      // of the proposed groups
   float uacc[PCG_MAX_K];                       // accept uniforms
   float ugrp[PCG_MAX_K + 1], utok[PCG_MAX_K + 1];   // group and token uniforms (accept_fetch)
-  int bad[PCG_MAX_K], ptok[PCG_MAX_K], pgrp[PCG_MAX_K];
+  int ptok[PCG_MAX_K], pgrp[PCG_MAX_K];
   int istar;                                   // accept_len of the sequence
 };
+
+// Statistics of a row of one part.
+__device__ __forceinline__ RowStat one_part(const StatPart &sp, float c) {
+  RowStat r;
+  r.Z = sp.z > 0.0 ? sp.z * exp2((double) sp.t - (double) sp.m * (double) c) : 0.0;
+  r.M = sp.m;
+  r.pad = 0.f;
+  return r;
+}
 
 // Statistics of one row from its parts, by the 16 lanes of one DPP row (sub = lane & 15); four
 // rows are merged per wave at once.  Every lane of the 16 returns the result.
@@ -425,7 +444,7 @@ __device__ __forceinline__ void accept_fetch(AcceptShared &sh, const AcceptArgs 
   }
 }
 
-// First half: the probes fetched, the row statistics merged, all to sh.
+// First half: the probes fetched (NULL: they are in sh), the row statistics merged, all to sh.
 __device__ __forceinline__ void accept_merge(AcceptShared &sh, const AcceptArgs &a, int b, bool writer,
                                              const Probe *probes, const StatPart *parts_t, const StatPart *parts_d) {
   const int K = a.K;
@@ -435,11 +454,8 @@ __device__ __forceinline__ void accept_merge(AcceptShared &sh, const AcceptArgs 
   // them (one position per lane), the others merge the row statistics.
   const int nprobe = 1;
   if (wave == 0) {
-    for (int i = lane; i < K; i += kWave) {
-      const Probe p = probes[i];
-      sh.Tp[i] = p.Tp; sh.Dp[i] = p.Dp; sh.Tref[i] = p.Tref; sh.Dref[i] = p.Dref;
-      sh.bad[i] = p.bad;
-    }
+    if (probes)
+      for (int i = lane; i < K; i += kWave) sh.probe[i] = probes[i];
   } else {
     // row statistics of this sequence's 2K+1 rows, four rows per wave at a time
     const int sub = lane & 15;
@@ -457,53 +473,57 @@ __device__ __forceinline__ void accept_merge(AcceptShared &sh, const AcceptArgs 
   }
 }
 
-// Second half, after a barrier; ends with one.
+// Second half, after a barrier.
 __device__ __forceinline__ void accept_decide(AcceptShared &sh, const AcceptArgs &a, int b, bool writer) {
   const int K = a.K;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   // Both chains have met.  One wave, one position per lane (K <= 64): normalise the probe,
   // take the accept test, and find the first rejection with a ballot; the draft token stands
-  // for its group on accept.
+  // for its group on accept.  The others wait for nothing but the position: outputs and counters come
+  // after the barrier.
+  const int i = lane;
+  const bool in = i < K;
+  double T = 0.0, D = 0.0, u = 0.0;
+  bool bad = false;
+  unsigned long long rejects = 0;
   if (wave == 0) {
-    const int i = lane;
-    const bool in = i < K;
-    double T = 0.0, D = 0.0, u = 0.0;
-    bool bad = false;
     if (in) {
-      if (sh.Tp[i] > 0.0) T = sh.Tp[i] * exp2((double) (sh.Tref[i] - sh.st_t[i].M) * a.cd) / sh.st_t[i].Z;
-      if (sh.Dp[i] > 0.0) D = sh.Dp[i] * exp2((double) (sh.Dref[i] - sh.st_d[i].M) * a.cd) / sh.st_d[i].Z;
+      const Probe p = sh.probe[i];
+      if (p.Tp > 0.0) T = p.Tp * exp2((double) (p.Tref - sh.st_t[i].M) * a.cd) * sh.iz_t[i];
+      if (p.Dp > 0.0) D = p.Dp * exp2((double) (p.Dref - sh.st_d[i].M) * a.cd) * sh.iz_d[i];
       u = (double) sh.uacc[i];
-      bad = sh.bad[i] != 0;
-      sh.Tn[i] = T;
-      sh.Dn[i] = D;
+      bad = p.bad != 0;
     }
-    const unsigned long long rejects = __ballot(in && !(u * D < T));
-    const int istar = rejects ? __ffsll((long long) rejects) - 1 : K;
+    rejects = __ballot(in && !(u * D < T));
+    if (lane == 0) sh.istar = rejects ? __ffsll((long long) rejects) - 1 : K;
+  }
+  lds_barrier();
+  const int istar = sh.istar;
+  if (writer && wave == kAcceptThreads / kWave - 1) {
+    int32_t *otok = a.out_tokens + (int64_t) b * (K + 1);
+    int32_t *ogrp = a.out_groups + (int64_t) b * (K + 1);
+    for (int k = lane; k <= K; k += kWave) {
+      // the entry at istar itself is written once the group has been drawn, by another wave
+      if (k != istar) {
+        otok[k] = k < istar ? sh.ptok[k] : -1;
+        ogrp[k] = k < istar ? sh.pgrp[k] : -1;
+      }
+    }
+    if (lane == 0) a.accept_len[b] = istar;
+  }
+  if (writer && wave == 0 && a.diag) {
     const bool evaluated = in && i <= istar;
     const uint32_t near = __popcll(__ballot(evaluated && fabs(u * D - T) < 1e-6 * D));
     const uint32_t zero_d = __popcll(__ballot(evaluated && !bad && D == 0.0));
     const uint32_t nbad = __popcll(__ballot(evaluated && bad));
-    if (lane == 0) sh.istar = istar;
-    if (writer) {
-      int32_t *otok = a.out_tokens + (int64_t) b * (K + 1);
-      int32_t *ogrp = a.out_groups + (int64_t) b * (K + 1);
-      for (int k = lane; k <= K; k += kWave) {
-        otok[k] = k < istar ? sh.ptok[k] : -1;
-        ogrp[k] = k < istar ? sh.pgrp[k] : -1;
-      }
-      if (lane == 0) {
-        a.accept_len[b] = istar;
-        if (a.diag) {
-          if (near) atomicAdd(&a.diag->near_accept, near);
-          if (zero_d) atomicAdd(&a.diag->zero_draft_mass, zero_d);
-          if (nbad) atomicAdd(&a.diag->bad_proposal, nbad);
-          atomicAdd(&a.diag->accepted_total, (uint32_t) istar);
-          atomicAdd(&a.diag->sequences, 1u);
-        }
-      }
+    if (lane == 0) {
+      if (near) atomicAdd(&a.diag->near_accept, near);
+      if (zero_d) atomicAdd(&a.diag->zero_draft_mass, zero_d);
+      if (nbad) atomicAdd(&a.diag->bad_proposal, nbad);
+      atomicAdd(&a.diag->accepted_total, (uint32_t) istar);
+      atomicAdd(&a.diag->sequences, 1u);
     }
   }
-  lds_barrier();
 }
 
 // The first half on the probes and parts that the statistics pass left in memory.
@@ -549,6 +569,7 @@ template <bool BF16, bool WIDE>
 __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs a, int32_t nsplit,
                                                                       float c_lo, float *table) {
   __shared__ AcceptShared sh;
+  warm_arguments<sizeof(AcceptArgs) + 16>();
   const int b = blockIdx.x / nsplit;
   const int split = blockIdx.x % nsplit;
   const RowSet &rs = a.rs;
@@ -1830,6 +1851,7 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(FinalizeArgs fa
                                                                  const double *runs,
                                                                  int32_t nchunks,
                                                                  int32_t chunk_groups) {
+  warm_arguments<sizeof(FinalizeArgs) + 48>();
   finalize_sequence<BF16, kFinalThreads, OWN>(fa, V, G, blockIdx.x, csum, csum_stride, runs, nchunks, chunk_groups);
 }
 
@@ -2029,6 +2051,7 @@ template <bool CSUM, bool WEIGHTED>
 __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     int32_t V, int32_t G, int32_t nrows, PreparedView p, const float *__restrict__ table,
     float *__restrict__ out, double *__restrict__ csum, double *__restrict__ runs) {
+  warm_arguments<16 + sizeof(PreparedView) + 32>();
   const int32_t nchunks = p.nchunks, chunk_groups = p.chunk_groups, ntiles = p.ntiles, tile_len = p.tile_len;
   const int32_t bpc = p.blocks_per_chunk;
   const uint4 *__restrict__ data = p.data;
@@ -2198,9 +2221,9 @@ template <bool BF16, int SUMS, bool STATS>
 __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a, FinalizeArgs fa, ProbeArgs pa,
                                                                     PreparedView p, int32_t nnz, int32_t long_size) {
   static_assert(kAcceptThreads == kGatherThreads, "one workgroup plays both parts");
+  warm_arguments<sizeof(AcceptArgs) + sizeof(FinalizeArgs) + sizeof(ProbeArgs) + sizeof(PreparedView) + 8>();
   __shared__ AcceptShared sh;
   __shared__ StatPart parts[STATS ? kSmallParts : 1];
-  __shared__ Probe probes[STATS ? PCG_MAX_K : 1];
   __shared__ __attribute__((aligned(16))) float tab[kSmallTokens + kBanks];
   __shared__ __attribute__((aligned(16))) float sums[kSmallGroups];
   constexpr bool kWeighted = SUMS == kSumsPreparedWeighted || SUMS == kSumsCsrWeighted;
@@ -2216,6 +2239,7 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   auto load_m = [&]() {
     if (first < V) load8_mult<true>(kWeighted ? nullptr : a.mult, slice_start<true>(first, V), V, m);
   };
+  const bool whole_rows = a.nparts == 1;              // a part is a row: nothing to merge
   if constexpr (STATS) {
     // Row parts, dealt to the waves in turn, and probes, one each for the first waves.  Everything starts
     // with a trip to memory, so a wave asks for its first two parts before anything else and keeps two
@@ -2225,17 +2249,17 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
     const int32_t nparts_all = (2 * K + 1) * a.nparts;
     RowPart<BF16, true, false> raw[2];    // cached: the decision rows are read again
     auto ask = [&](RowPart<BF16, true, false> &to, int32_t it) {
-      const int32_t r = it / a.nparts, part = it % a.nparts;
+      const int32_t r = whole_rows ? it : it / a.nparts, part = whole_rows ? 0 : it % a.nparts;
       to.load(r <= K ? target_row(rs, b, r, BF16) : draft_row(rs, b, r - K - 1, BF16), part * kPartElems, V, lane);
     };
     if (wave < nparts_all) ask(raw[0], wave);
     if (wave + kGatherWaves < nparts_all) ask(raw[1], wave + kGatherWaves);
     load_m();
     if (wave == kGatherWaves - 1) accept_fetch(sh, a, b, lane);
-    for (int32_t i = wave; i < K; i += kGatherWaves) probe_row<BF16>(rs, pa, b, i, a.c, lane, probes + i);
+    for (int32_t i = wave; i < K; i += kGatherWaves) probe_row<BF16>(rs, pa, b, i, a.c, lane, sh.probe + i);
     auto reduce = [&](RowPart<BF16, true, false> &from, int32_t it) {
       float x[32];
-      from.get(x, (it % a.nparts) * kPartElems, V, lane);
+      from.get(x, whole_rows ? 0 : (it % a.nparts) * kPartElems, V, lane);
       if (it + 2 * kGatherWaves < nparts_all) ask(from, it + 2 * kGatherWaves);
       const StatPart sp = part_stats(x, a.c);
       if (lane == kWave - 1) parts[it] = sp;
@@ -2243,6 +2267,12 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
     for (int32_t it = wave; it < nparts_all; it += 2 * kGatherWaves) {
       reduce(raw[0], it);
       if (it + kGatherWaves < nparts_all) reduce(raw[1], it + kGatherWaves);
+    }
+    const int32_t r = wave + kGatherWaves * lane;     // the wave's own rows, one per lane
+    if (whole_rows && r < nparts_all) {
+      const RowStat s = one_part(parts[r], a.c);
+      const double iz = 1.0 / s.Z;
+      if (r <= K) { sh.st_t[r] = s; sh.iz_t[r] = iz; } else { sh.st_d[r - K - 1] = s; sh.iz_d[r - K - 1] = iz; }
     }
   } else {
     accept_merge_stored(sh, a, b, true);
@@ -2269,8 +2299,10 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
   if constexpr (SUMS <= kSumsPreparedWeighted) ask_chunk(0);
   lds_barrier();
   if constexpr (STATS) {
-    accept_merge(sh, a, b, true, probes, parts, parts + (K + 1) * a.nparts);
-    lds_barrier();
+    if (!whole_rows) {
+      accept_merge(sh, a, b, true, nullptr, parts, parts + (K + 1) * a.nparts);
+      lds_barrier();
+    }
   }
   accept_decide(sh, a, b, true);
 
