@@ -1621,6 +1621,44 @@ __device__ void finish_sequence(const FinalizeArgs &fa, int32_t G, int b, int32_
   }
 }
 
+// Inverse CDF over the run totals rp[0 .. n) >= 0, n <= 2 NT, by a workgroup of NT threads, two neighbouring
+// runs each: the first whose running sum exceeds `goal`; index -1 if nothing has mass.  All threads get
+// the result.  (Two barriers; block_inverse_cdf, which takes any function and any number, has four.)
+template <int NT>
+__device__ __forceinline__ CdfPick pick_run(const double *rp, int32_t n, double goal) {
+  constexpr int kWaves = NT / kWave;
+  __shared__ double wave_tot[kWaves];
+  __shared__ CdfPick res;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t k = 2 * tid;
+  double r0 = 0.0, r1 = 0.0;
+  if (k < n) r0 = fmax(rp[k], 0.0);
+  if (k + 1 < n) r1 = fmax(rp[k + 1], 0.0);
+  const double mine = r0 + r1, inc = wave_scan(mine);
+  if (lane == kWave - 1) wave_tot[wave] = inc;
+  lds_barrier();
+  const double tot = lane < kWaves ? wave_tot[lane] : 0.0, upto = wave_scan(tot);
+  const unsigned long long pos = __ballot(tot > 0.0), hit = __ballot(tot > 0.0 && upto > goal);
+  // the wave that holds the crossing; rounding at the top end may leave none: the last that has mass
+  const int at = !pos ? 0 : hit ? __ffsll((long long) hit) - 1 : 63 - __clzll((long long) pos);
+  if (wave == at) {                                   // uniform over the wave
+    const double before = read_lane(upto, at) - read_lane(tot, at), total = read_lane(upto, kWave - 1);
+    const unsigned long long has = __ballot(mine > 0.0);
+    const unsigned long long over = hit ? __ballot(mine > 0.0 && before + inc > goal) : 0;
+    const int l = !has ? 0 : over ? __ffsll((long long) over) - 1 : 63 - __clzll((long long) has);
+    if (lane == l) {
+      const double lo = before + (inc - mine);
+      const bool second = r0 <= 0.0 || (r1 > 0.0 && lo + r0 <= goal);
+      res.index = !pos ? -1 : k + (second ? 1 : 0);
+      res.total = total;
+      res.lo = second ? lo + r0 : lo;
+      res.hi = second ? lo + mine : lo + r0;
+    }
+  }
+  lds_barrier();
+  return res;
+}
+
 // The last step of a sequence, by one whole workgroup of NT threads.  The gather left no sums, only
 // the totals of max(0, T[g] - D[g]) (T[g] on a bonus row) over chunks of chunk_groups consecutive
 // groups and over runs of kRunGroups: the chunk and the run that hold the draw are located from
@@ -1633,10 +1671,17 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
                                   const double *csum, int64_t csum_stride, const double *runs,
                                   int32_t nchunks, int32_t chunk_groups) {
   const int32_t K = fa.K;
+  // asked for before anything waits for the accept length
+  const double *cs = csum + b * csum_stride;
+  const int ln = threadIdx.x & (kWave - 1);
+  const double cs_any = cs[min(ln, nchunks - 1)];
   const int32_t istar = fa.accept_len[b];
+  const bool rejected = istar < K;
   const int64_t trow_id = (int64_t) b * (K + 1) + istar;
   const void *trow = target_row(fa.rs, b, istar, BF16);
+  const void *drow = draft_row(fa.rs, b, rejected ? istar : 0, BF16);
   const RowStat st = fa.rowstat[trow_id];
+  const RowStat sd = fa.rowstat[fa.rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0)];
   const Uniforms u = philox_uniforms(fa.seed, fa.offset, (uint32_t) b, (uint32_t) istar);
   const int32_t *row_ptr = fa.row_ptr, *members = fa.members, *mult = fa.mult;
   const float *wts = fa.weights;
@@ -1646,9 +1691,7 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
   // side; every wave does the same
   CdfPick pg;
   {
-    const double *cs = csum + b * csum_stride;
-    const int ln = threadIdx.x & (kWave - 1);
-    const double cs0 = ln < nchunks ? cs[ln] : 0.0;
+    const double cs0 = ln < nchunks ? cs_any : 0.0;
     double S = wave_sum(cs0);
     for (int32_t c0 = kWave; c0 < nchunks; c0 += kWave) S += wave_sum(c0 + ln < nchunks ? cs[c0 + ln] : 0.0);
     const double goal = (double) u.grp * S;
@@ -1682,14 +1725,10 @@ __device__ void finalize_sequence(const FinalizeArgs &fa, int32_t V, int32_t G, 
         const int32_t nruns = (ng + kRunGroups - 1) / kRunGroups;
         const double *rp = runs + ((int64_t) b * nchunks + cstar) * (chunk_groups / kRunGroups);
         static_assert(kMaxChunkGroups / kRunGroups <= 2 * NT, "two runs per thread at most");
-        const CdfPick pr = block_inverse_cdf<NT, 2>(
-            nruns, [&](int32_t k) { return rp[k]; }, 0.0, true, goal - base);
+        const CdfPick pr = pick_run<NT>(rp, nruns, goal - base);
         if (pr.index >= 0) {
           __shared__ int32_t run_n[kRunGroups], run_beg[kRunGroups];
           __shared__ bool run_has[kRunGroups];          // some entry of the group adds to it
-          const bool rejected = istar < K;
-          const void *drow = draft_row(fa.rs, b, rejected ? istar : 0, BF16);
-          const RowStat sd = fa.rowstat[fa.rs.nrows0 + (int64_t) b * K + (rejected ? istar : 0)];
           const double izt = 1.0 / st.Z, izd = rejected ? 1.0 / sd.Z : 0.0;
           const int32_t gr0 = g0 + pr.index * kRunGroups;
           const int k = threadIdx.x >> 5, l = threadIdx.x & 31;
