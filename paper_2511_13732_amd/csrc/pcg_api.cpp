@@ -272,6 +272,7 @@ ProbeArgs probe_args(const pcg_groups *groups, int32_t K, const Factors &f,
   pa.weights = groups->weights;
   pa.K = K;
   pa.G = groups->G;
+  pa.even = even_size(*groups);
   pa.c_lo = f.c_lo;
   pa.out = out;
   return pa;

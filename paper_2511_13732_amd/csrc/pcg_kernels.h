@@ -12,6 +12,11 @@ namespace pcg {
 
 int32_t stats_nparts(int32_t V);
 
+// The size of every group if they may all be of one size (nnz divides by G), else 0.  Where a kernel is about
+// to look one group up, its entries are then asked for where they lie if it is so, together with the bounds
+// that tell whether it is: a trip to memory fewer for the k nearest neighbours of every token.
+int32_t even_size(const pcg_groups &g);
+
 // streaming: read the logits with nontemporal loads (faster pass, nothing left in the caches)
 // probes: also form the probe of every target row that has a proposal (NULL: none)
 hipError_t launch_row_stats(const RowSet &rs, bool bf16, int32_t V, int64_t nrows, float c,

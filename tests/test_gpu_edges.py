@@ -147,6 +147,40 @@ def test_small_step(V, G, size, B, K, dtype, off, layout, weighted):
     check_step(V, G, size, B, K, dtype, off=off, layout=layout, weighted=weighted, thinning=False, chunk_groups=4096)
 
 
+# groups of one size, which are looked up before their bounds are known, around the 64 entries of a wave; and
+# of one size on average only: an entry moved from one group to a later one, so that those between start
+# elsewhere, or two groups emptied into a third; with the rows of a step streamed or cached, its probes in
+# two launches and in four
+@pytest.mark.parametrize("V,B,K,dtype,size,moved", [
+    (V, B, K, dtype, size, moved) for V, B, K, dtype in [(17003, 3, 6, "bf16"), (4100, 2, 9, "f32")]
+    for size in (1, 8, 64, 65, 130) for moved in ("none", "one", "emptied")] + [(65536, 16, 17, "bf16", 8, "one")])
+def test_groups_of_one_size(V, B, K, dtype, size, moved):
+    print(f"V={V} B={B} K={K} {dtype} size={size} {moved}", flush=True)
+    sets = [(g + np.arange(size)) % V for g in range(V)]
+    sets = [np.sort(x).astype(np.int32) for x in sets]
+    if moved == "one":
+        sets[9] = np.sort(np.append(sets[9], np.int32((9 + size) % V)))
+        sets[5] = sets[5][:-1] if size > 1 else sets[5][:0]
+    if moved == "emptied":
+        sets[7] = np.sort(np.concatenate([(7 + np.arange(3 * size)) % V])).astype(np.int32)
+        sets[6] = sets[8] = np.zeros(0, np.int32)
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in sets])]).astype(np.int32)
+    mem = np.concatenate(sets)
+    rng = np.random.default_rng([V, size])
+    ptok = rng.integers(0, V, (B, K)).astype(np.int32)
+    pgrp = np.where(rng.random((B, K)) < 0.7, rng.integers(0, 14, (B, K)), rng.integers(0, V, (B, K))).astype(np.int32)
+    tgt = torch.from_numpy((3 * rng.standard_normal((B, K + 1, V))).astype(np.float32))
+    dft = tgt[:, :K] + torch.from_numpy((0.3 * rng.standard_normal((B, K, V))).astype(np.float32))
+    if dtype == "bf16":
+        tgt, dft = tgt.to(torch.bfloat16), dft.to(torch.bfloat16)
+    og = oracle_groups(V, rp, mem)
+    for prepare in (True, False):
+        dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=prepare)
+        gpu, ref, _, diag = run_both(V, rp, mem, tgt, dft, ptok, pgrp, seed=11, offset=2, dg=dg, og=og, nthreads=8)
+        assert compare_verify(gpu, ref, og, ptok, pgrp).tolerated <= 1
+        assert diag["bad_proposal"] == 0 and diag["sequences"] == B
+
+
 # construction of the groups: tokens around the blocks of the scan, rows that fill the registers of the
 # pair kernel and rows beyond, sets of 63 to 66 members (ranked in registers or sorted in LDS), more
 # duplicates of a set than one look at its members covers
