@@ -81,6 +81,8 @@ struct StageTimer {
   }
 };
 
+constexpr int64_t kStreamBytes = (int64_t) 64 << 20;      // logits of a step above which they are streamed
+
 // See RowSet.
 uint32_t row_magic(int32_t npos) { return npos > 1 ? (uint32_t) (((uint64_t) 1 << 32) / (uint32_t) npos) : 0u; }
 
@@ -396,8 +398,12 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
     return PCG_OK;
   }
   tm.begin(kStageStats);
-  // streaming pass: only the rejected position's two rows (2 of 2K+1) are read again
-  if ((e = launch_row_stats(rs, bf16, V, rows, f.c, true, parts, stream, &pa)) != hipSuccess) return hip_fail(e);
+  // Streaming pass where the rows are large: only the rejected position's two (2 of 2K+1) are read again.
+  // Rows that the Infinity Cache holds with room to spare are better left there for that: V = 65 536, bf16,
+  // K = 8, row_stats and finalize 6.8 + 8.9 us streamed and 5.9 + 7.9 cached for 8 sequences (18 MB), 9.1 + 8.8
+  // and 8.0 + 8.0 for 16, 13.8 + 9.0 and 13.6 + 8.7 for 32 (71 MB); for 64 (143 MB) 23.1 and 24.6 alone.
+  const bool streaming = rows * V * (bf16 ? 2 : 4) > kStreamBytes;
+  if ((e = launch_row_stats(rs, bf16, V, rows, f.c, streaming, parts, stream, &pa)) != hipSuccess) return hip_fail(e);
   tm.end(kStageStats);
   tm.begin(kStageAccept);
   if ((e = launch_accept_delta(aa, bf16, B, f.c_lo, table, stream)) != hipSuccess)
