@@ -43,18 +43,6 @@ constexpr int kStatsWaves = 4;        // waves per workgroup
 // Row id of a workgroup: grid.y carries the low part, grid.z the rest (grid.y <= 65535).
 constexpr int kRowsPerGridY = 32768;
 
-// Asks for all of the kernel's arguments (BYTES of them) at once: one word of every 64-byte line.
-template <size_t BYTES>
-__device__ __forceinline__ void warm_arguments() {
-  const __attribute__((address_space(4))) uint32_t *ka =
-      (const __attribute__((address_space(4))) uint32_t *) __builtin_amdgcn_kernarg_segment_ptr();
-  uint32_t w[(BYTES + 63) / 64];
-#pragma unroll
-  for (size_t i = 0; i < (BYTES + 63) / 64; ++i) w[i] = ka[16 * i];
-#pragma unroll
-  for (size_t i = 0; i < (BYTES + 63) / 64; ++i) asm volatile("" ::"s"(w[i]));
-}
-
 // A 16-byte load at any element address (the type says so to the compiler, which then relies on
 // the unaligned access that the amdhsa target guarantees for global memory: the same instruction
 // as an aligned load, at most one cache line more per wave).  Optionally marked as streaming
@@ -579,7 +567,6 @@ template <bool BF16, bool WIDE>
 __global__ __launch_bounds__(kAcceptThreads) void accept_delta_kernel(AcceptArgs a, int32_t nsplit,
                                                                       float c_lo, float *table) {
   __shared__ AcceptShared sh;
-  warm_arguments<sizeof(AcceptArgs) + 16>();
   const int b = blockIdx.x / nsplit;
   const int split = blockIdx.x % nsplit;
   const RowSet &rs = a.rs;
@@ -1900,7 +1887,6 @@ __global__ __launch_bounds__(kFinalThreads) void finalize_kernel(FinalizeArgs fa
                                                                  const double *runs,
                                                                  int32_t nchunks,
                                                                  int32_t chunk_groups) {
-  warm_arguments<sizeof(FinalizeArgs) + 48>();
   finalize_sequence<BF16, kFinalThreads, OWN>(fa, V, G, blockIdx.x, csum, csum_stride, runs, nchunks, chunk_groups);
 }
 
@@ -2100,7 +2086,6 @@ template <bool CSUM, bool WEIGHTED>
 __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
     int32_t V, int32_t G, int32_t nrows, PreparedView p, const float *__restrict__ table,
     float *__restrict__ out, double *__restrict__ csum, double *__restrict__ runs) {
-  warm_arguments<16 + sizeof(PreparedView) + 32>();
   const int32_t nchunks = p.nchunks, chunk_groups = p.chunk_groups, ntiles = p.ntiles, tile_len = p.tile_len;
   const int32_t bpc = p.blocks_per_chunk;
   const uint4 *__restrict__ data = p.data;
@@ -2270,7 +2255,6 @@ template <bool BF16, int SUMS, bool STATS>
 __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a, FinalizeArgs fa, ProbeArgs pa,
                                                                     PreparedView p, int32_t nnz, int32_t long_size) {
   static_assert(kAcceptThreads == kGatherThreads, "one workgroup plays both parts");
-  warm_arguments<sizeof(AcceptArgs) + sizeof(FinalizeArgs) + sizeof(ProbeArgs) + sizeof(PreparedView) + 8>();
   __shared__ AcceptShared sh;
   __shared__ StatPart parts[STATS ? kSmallParts : 1];
   __shared__ __attribute__((aligned(16))) float tab[kSmallTokens + kBanks];
