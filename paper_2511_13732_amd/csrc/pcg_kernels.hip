@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(kWave) void propose_kernel(
 
 // The same in one launch, by one workgroup per row: the row's parts stay in LDS between its statistics
 // and the draw, and the rows' draws, chains of dependent loads, run behind other rows' streaming.
-// V = 65 536, bf16: 64 rows 8.6 us against 3.6 + 4.5 in two launches, 512 rows 17.5 against 12.4 + 5.2; the
+// V = 65 536, bf16: 64 rows 8.2 us against 3.6 + 4.5 in two launches, 512 rows 17.5 against 12.4 + 5.2; the
 // call, whose launches cost its caller more than that, 14.3 -> 11.3 us for 64 rows.
 constexpr int kProposeThreads = 1024;
 constexpr int kProposeParts = 64;        // V <= 131 072: beyond, a row is too long for one compute unit
@@ -1138,16 +1138,18 @@ __device__ __forceinline__ u32x4 csr_load4(const void *p, int32_t j, int32_t nnz
 
 // What the four entries loaded for position j add to a sum: those from j on, inside the group that ends
 // at `end`, and of the tile (added in pairs: a chain of four and then the tree over the lanes would
-// round once or twice more).
-template <bool WEIGHTED>
+// round once or twice more).  WHOLE: the tile is the whole row, which every member lies in.
+template <bool WEIGHTED, bool WHOLE>
 __device__ __forceinline__ float csr_add4(const float *tab, int32_t zero, int32_t t0, int32_t tl, const u32x4 m,
                                           const u32x4 w, int32_t j, int32_t end, int32_t nnz, float acc) {
-  const int32_t at = min(j, nnz - 4);
+  const int32_t skip = min(j, nnz - 4) - j;            // below 0 where the load was moved back into the array
+  const uint32_t count = (uint32_t) max(end - j, 0);
   float v[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const int32_t t = (int32_t) m[k] - t0;
-    const bool mine = at + k >= j && at + k < end && (uint32_t) t < (uint32_t) tl;
+    const int32_t t = WHOLE ? (int32_t) m[k] : (int32_t) m[k] - t0;
+    // from j on and inside the group, in one comparison
+    const bool mine = (uint32_t) (skip + k) < count && (WHOLE || (uint32_t) t < (uint32_t) tl);
     v[k] = tab[mine ? t : zero];
   }
   if constexpr (WEIGHTED)
@@ -1173,7 +1175,7 @@ static int32_t csr_long_size(int64_t nnz, int32_t G, int W) {
 // long after all others are done (one group of 10 000 beside 20 000 of 8, 8 rows: the step took 222 us
 // with 8 lanes a group and one entry a lane, 288 with two and four, 137 with this).  Only its first trip
 // is added; *has_long (in LDS, false before) tells that csr_long_sums has something to do.
-template <int W, bool WEIGHTED, typename Sink>
+template <int W, bool WEIGHTED, bool WHOLE, typename Sink>
 __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t t0, int32_t tl, int32_t g_begin,
                                          int32_t g_end, const int32_t *row_ptr, const int32_t *members,
                                          int32_t nnz, const float *weights, int32_t long_size, bool *has_long,
@@ -1206,7 +1208,7 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
     }
   };
   auto add4 = [&](const u32x4 m, const u32x4 w, int32_t j, int32_t end, float acc) {
-    return csr_add4<WEIGHTED>(tab, zero, t0, tl, m, w, j, end, nnz, acc);
+    return csr_add4<WEIGHTED, WHOLE>(tab, zero, t0, tl, m, w, j, end, nnz, acc);
   };
   Bounds now, after;
   Entries e;
@@ -1257,7 +1259,7 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
 
 // The groups that csr_sums left: a wave adds the entries of each beyond its first trip, four loads a lane on
 // their way, and hands their sum to more(g, sum).  A barrier lies between csr_sums and this.
-template <int W, bool WEIGHTED, typename More>
+template <int W, bool WEIGHTED, bool WHOLE, typename More>
 __device__ void csr_long_sums(const float *tab, int32_t zero, int32_t t0, int32_t tl, int32_t g_begin,
                               int32_t g_end, const int32_t *row_ptr, const int32_t *members, int32_t nnz,
                               const float *weights, int32_t long_size, More more) {
@@ -1283,7 +1285,7 @@ __device__ void csr_long_sums(const float *tab, int32_t zero, int32_t t0, int32_
 #pragma unroll
         for (int q = 0; q < kAtOnce; ++q)
           if (j0 + q * 4 * kWave < end)
-            sum = csr_add4<WEIGHTED>(tab, zero, t0, tl, m[q], w[q], j0 + 4 * (q * kWave + lane), end, nnz, sum);
+            sum = csr_add4<WEIGHTED, WHOLE>(tab, zero, t0, tl, m[q], w[q], j0 + 4 * (q * kWave + lane), end, nnz, sum);
       }
       sum = subwave_sum<64>(sum);
       if (lane == kWave - 1) more(g0 + l, sum);
@@ -1333,9 +1335,11 @@ __device__ __forceinline__ void run_totals(const float *sums, int32_t ng, double
 // gather; otherwise every sum.
 // Bound by the L2, which hands every row its own copy of the members (4 bytes an entry, once per
 // tile).  One entry per lane and load, with every pass waiting for its bounds, then its entries, took
-// 28.3 us at V = 16 384, 32 members, 32 rows, and 13.2 us to scan the sums; this takes 14.6, and 7.6 to
-// locate the draw (V = 65 536, 64 rows: 450 us and 51 us before, 197 and 9 now).
-template <int W, bool CSUM, bool WEIGHTED>
+// 28.3 us at V = 16 384, 32 members, 32 rows, and 13.2 us to scan the sums; this takes 12.9, and 6.4 to
+// locate the draw (V = 65 536, 64 rows: 450 us and 51 us before, 190 and 9 now).  Behind the L2 it is the vector
+// instructions of an entry that count: without the test for the tile where there is one only (WHOLE) and
+// with one comparison for both ends of a group 14.6 -> 12.9 us, V = 32 768, 64 rows 70.7 -> 66.8.
+template <int W, bool CSUM, bool WEIGHTED, bool WHOLE>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t groups_per_chunk, int32_t ntiles,
     int32_t tile_len, int32_t nnz, int32_t long_size, const int32_t *row_ptr, const int32_t *members,
@@ -1362,14 +1366,14 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);             // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
-    csr_sums<W, WEIGHTED>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
+    csr_sums<W, WEIGHTED, WHOLE>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
                           long_size, &has_long, [&](int32_t g, float a) {
                             // the same lane in every tile: no other touches this sum meanwhile
                             sums[g - g_begin] = tile > 0 ? sums[g - g_begin] + a : a;
                           });
     __syncthreads();                                // everyone is done with the tile
     if (has_long) {                                 // uniform
-      csr_long_sums<W, WEIGHTED>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
+      csr_long_sums<W, WEIGHTED, WHOLE>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
                                  long_size, [&](int32_t g, float a) { sums[g - g_begin] += a; });
       __syncthreads();
     }
@@ -2166,8 +2170,11 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
 // through LDS, and what is left is the chain of loads proposal -> members -> logits and group ->
 // members -> logits.  Bound by latency, and by one compute unit's arithmetic in the statistics (34
 // parts and 8 probes of V = 4096, K = 8: 6.5 us), which a launch of their own spreads over the chip where
-// there are more than a few.  Accept scan 1.7 us, table 1.3, sums 2.8, draws 3.2.  The whole call: V = 1024,
-// K = 4, B = 1 22.8 -> 12.9 us (one launch); V = 4096, K = 8, B = 8 23.8 -> 17.4 (two).
+// there are more than a few.  At V = 1024, K = 4: statistics and probes 4.4 us, accept scan 0.9, table 1.2, sums
+// 1.6, group 1.4, token 1.3.  The whole call: V = 1024, K = 4, B = 1 10.7 us (one launch; four take 22.8);
+// V = 4096, K = 8, B = 8 14.2 (two; four 23.8).  With 16 waves on four SIMDs an instruction that every wave
+// repeats costs four: what is the same for all of them is computed once, ahead of the decision where it can
+// be, or on the scalar unit (12.9 -> 10.7 and 17.4 -> 14.2 us).
 // =============================================================================================
 
 constexpr int kSmallTokens = 16384;    // table entries in LDS: 64 KB
@@ -2385,11 +2392,11 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
     __shared__ bool has_long;
     if (threadIdx.x == 0) { tab[V] = 0.f; has_long = false; }
     lds_barrier();
-    csr_sums<kSmallCsrWidth, kWeighted>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size, &has_long,
+    csr_sums<kSmallCsrWidth, kWeighted, true>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size, &has_long,
                            [&](int32_t g, float s) { sums[g] = s; });
     lds_barrier();
     if (has_long)                                   // uniform
-      csr_long_sums<kSmallCsrWidth, kWeighted>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size,
+      csr_long_sums<kSmallCsrWidth, kWeighted, true>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size,
                                   [&](int32_t g, float s) { sums[g] += s; });
   }
   lds_barrier();
@@ -2557,8 +2564,12 @@ hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, 
   };
   auto pick = [&](auto width) {
     constexpr int W = decltype(width)::value;
-    if (g.weights) { if (csum) launch(gather_kernel<W, true, true>); else launch(gather_kernel<W, false, true>); }
-    else { if (csum) launch(gather_kernel<W, true, false>); else launch(gather_kernel<W, false, false>); }
+    auto form = [&](auto whole) {
+      constexpr bool O = decltype(whole)::value;
+      if (g.weights) { if (csum) launch(gather_kernel<W, true, true, O>); else launch(gather_kernel<W, false, true, O>); }
+      else { if (csum) launch(gather_kernel<W, true, false, O>); else launch(gather_kernel<W, false, false, O>); }
+    };
+    if (p.ntiles == 1) form(std::true_type{}); else form(std::false_type{});
   };
   switch (p.width) {
     case 2: pick(std::integral_constant<int, 2>{}); break;
