@@ -277,6 +277,13 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// What lanes of this wave have written to LDS may be read by its other lanes behind this.
+__device__ __forceinline__ void wave_handoff() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Merge the parts of one row inside a wave: every lane returns the row's (M, Z).
 // c must be the same fp32 factor row_stats used, so that 2^(xc-t) * 2^(t-Mc) = 2^((x-M)c).
 __device__ __forceinline__ RowStat merge_row(const StatPart *parts, int64_t row, int32_t nparts,
@@ -817,9 +824,7 @@ __device__ int32_t draw_token(const PartMasses<N> &pm, uint32_t *redo, const voi
 #pragma unroll
     for (int k = 0; k < Logits32<BF16>::kWords; ++k) redo[k] = raw.w[k];
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  wave_handoff();
   float x = -INFINITY;
   if (lane < 32) {
     if constexpr (BF16) x = __uint_as_float((uint32_t) reinterpret_cast<const uint16_t *>(redo)[lane] << 16);
@@ -1043,9 +1048,7 @@ __global__ __launch_bounds__(kProposeThreads) void propose_row_kernel(
   float M = lane < nparts ? parts[lane].m : -INFINITY;
   M = wave_max(M);
   fill_part_masses(pm, parts, nparts, M, c, lane, kWave);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  wave_handoff();
   propose_draw<BF16>(pm, redo, rs, row, V, nparts, c, d, tok_ptr, tok_groups, tok_weights, prop_tokens, prop_groups,
                      diag, lane);
 }
@@ -2308,6 +2311,7 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
       reduce(raw[0], it);
       if (it + kGatherWaves < nparts_all) reduce(raw[1], it + kGatherWaves);
     }
+    wave_handoff();                                   // parts, from the lane that has a sum to the lane of its row
     const int32_t r = wave + kGatherWaves * lane;     // the wave's own rows, one per lane
     if (whole_rows && r < nparts_all) {
       const RowStat s = one_part(parts[r], a.c);

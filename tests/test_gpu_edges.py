@@ -147,6 +147,36 @@ def test_small_step(V, G, size, B, K, dtype, off, layout, weighted):
     check_step(V, G, size, B, K, dtype, off=off, layout=layout, weighted=weighted, thinning=False, chunk_groups=4096)
 
 
+# rows of one part in one launch, whose statistics the wave that reduced them finishes, a row per lane: one row
+# a wave, two and three, up to the nine of the most positions, few sequences and one per compute unit; the
+# longest such row and the first that has two parts
+@pytest.mark.parametrize("V,B,K,dtype", [(1024, 3, 7, "bf16"), (1024, 3, 8, "f32"), (2048, 2, 10, "bf16"), (1500, 129, 8, "bf16"),
+                                         (2048, 130, 15, "f32"), (2048, 129, 16, "bf16"), (2049, 129, 16, "bf16"),
+                                         (700, 131, 24, "bf16"), (300, 256, 64, "f32")])
+@pytest.mark.parametrize("layout", ["prepared", "csr"])
+def test_small_step_rows_of_one_part(V, B, K, dtype, layout):
+    # the draft's rows are the target's up to a position, where every proposal is accepted: the decision falls
+    # on rows of every lane
+    print(f"V={V} B={B} K={K} {dtype} {layout}", flush=True)
+    rp, mem = W.random_groups(V, V, 1, 8, seed=V + K)
+    og = oracle_groups(V, rp, mem)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=layout == "prepared", reverse=True)
+    rng = np.random.default_rng([V, B, K])
+    tgt = torch.from_numpy((3.0 * rng.standard_normal((B, K + 1, V))).astype(np.float32))
+    moved = torch.from_numpy(rng.integers(0, K + 1, B))                 # the first position where the rows differ
+    noise = torch.from_numpy(rng.standard_normal((B, K, V)).astype(np.float32))
+    dft = tgt[:, :K] + torch.where((torch.arange(K)[None] >= moved[:, None])[..., None], noise, torch.zeros(()))
+    if dtype == "bf16":
+        tgt, dft = tgt.to(torch.bfloat16), dft.to(torch.bfloat16)
+    pref = oracle.propose(og, oracle.reverse_index(og), as_oracle_logits(dft), temperature=0.9, seed=3, offset=1, nthreads=8)
+    gpu, ref, _, diag = run_both(V, rp, mem, tgt, dft, pref.tokens, pref.groups, temperature=0.9, seed=3, offset=4,
+                                 dg=dg, og=og, nthreads=8)
+    assert compare_verify(gpu, ref, og, pref.tokens, pref.groups).tolerated <= 1
+    assert diag["sequences"] == B and diag["accepted_total"] == int(gpu.accept_len.sum())
+    if B > 2 * K:
+        assert len(np.unique(gpu.accept_len.cpu().numpy())) > K // 2
+
+
 # groups of one size, which are looked up before their bounds are known, around the 64 entries of a wave; and
 # of one size on average only: an entry moved from one group to a later one, so that those between start
 # elsewhere, or two groups emptied into a third; with the rows of a step streamed or cached, its probes in
