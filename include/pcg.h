@@ -85,7 +85,11 @@ typedef enum {
  *   mult    [V]    mult[v] = number of CSR entries equal to v, >= 1 for all v
  * A token listed twice in one group carries weight 2/mult there.  The arrays
  * must describe a membership that pcg_groups_validate_host accepts; the
- * kernels do not re-check them.
+ * kernels do not re-check them.  nnz is the number of entries, not room for
+ * more: any of the nnz is read, 16 bytes at a time and, where nnz / G says that
+ * all groups might be of one size, before a group's bounds are known.  (Where
+ * nnz is larger than row_ptr[G] all the same, what lies behind has no effect as
+ * long as weights there are finite.)
  */
 typedef struct pcg_prepared pcg_prepared;
 

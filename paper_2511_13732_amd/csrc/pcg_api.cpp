@@ -272,6 +272,7 @@ ProbeArgs probe_args(const pcg_groups *groups, int32_t K, const Factors &f,
   pa.mult = groups->mult;
   pa.prop_groups = prop_groups;
   pa.weights = groups->weights;
+  pa.V = groups->V;
   pa.K = K;
   pa.G = groups->G;
   pa.even = even_size(*groups);

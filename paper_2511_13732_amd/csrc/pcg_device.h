@@ -288,7 +288,7 @@ struct Probe {
 struct ProbeArgs {
   const int32_t *row_ptr, *members, *mult, *prop_groups;
   const float *weights;    // general weights per CSR entry, or NULL for the equal split
-  int32_t K, G, even;      // even: see even_size
+  int32_t V, K, G, even;   // even: see even_size
   float c_lo;              // low part of log2(e) / temperature (the high part is row_stats' c)
   Probe *out;              // [B * K]; NULL: no probes in this launch
 };

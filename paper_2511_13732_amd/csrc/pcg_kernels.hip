@@ -106,9 +106,9 @@ __device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t b, int3
     // one size they are asked for before their bounds are known, and again if those are others.
     const float *wts = pa.weights;
     float lt0, ld0, m0, w0;
-    auto first_members = [&](int32_t from, int32_t to) {
+    auto first_members = [&](int32_t from, int32_t to, uint32_t largest) {
       const bool has = from + lane < to;
-      const int32_t t0 = has ? pa.members[from + lane] : 0;
+      const uint32_t t0 = has ? min((uint32_t) pa.members[from + lane], largest) : 0u;
       lt0 = has ? logit_at<BF16>(trow, t0) : -INFINITY;
       ld0 = has ? logit_at<BF16>(drow, t0) : -INFINITY;
       // the entry's share of its token: 1 / N(t) (Eq. 3), or the caller's weight (Eq. 2)
@@ -116,8 +116,10 @@ __device__ void probe_row(const RowSet &rs, const ProbeArgs &pa, int64_t b, int3
       w0 = has && wts ? wts[from + lane] : 1.f;
     };
     const int32_t even = GUESS ? pa.even : 0, guess = g * even;
-    if (even > 0) first_members(guess, guess + even);
-    if (even == 0 || beg != guess || end != guess + even) first_members(beg, end);    // uniform over the wave
+    // A wrong guess may meet entries that no group holds (nnz above row_ptr[G]): the token ids it finds are
+    // kept inside the row, and nothing of it is used.
+    if (even > 0) first_members(guess, guess + even, (uint32_t) pa.V - 1);
+    if (even == 0 || beg != guess || end != guess + even) first_members(beg, end, UINT32_MAX);   // uniform over the wave
     mt = lt0;
     md = ld0;
     for (int32_t j = beg + lane + kWave; j < end; j += kWave) {

@@ -211,6 +211,38 @@ def test_groups_of_one_size(V, B, K, dtype, size, moved):
         assert diag["bad_proposal"] == 0 and diag["sequences"] == B
 
 
+# more entries in the arrays than the groups have, as many as make them divide evenly among the groups: the
+# proposed groups are looked up where they are not, among token ids that are none
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("layout", ["prepared", "csr"])
+@pytest.mark.parametrize("V,G,size,B,K,dtype", [(17003, 900, 40, 3, 6, "bf16"), (17003, 300, 130, 2, 5, "f32"), (4100, 4090, 9, 2, 9, "f32")])
+def test_entries_behind_the_last_group(V, G, size, B, K, dtype, layout, weighted):
+    print(f"V={V} G={G} size={size} {layout} w={weighted}", flush=True)
+    rp, mem = W.random_groups(V, G, 1, size, seed=V + G)
+    og = oracle_groups(V, rp, mem)
+    w = W.random_weights(og.V, og.members, 1) if weighted else None
+    if weighted:
+        og = oracle.with_weights(og, w)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=layout == "prepared", weights=w)
+    nnz = (dg.nnz // dg.G + 3) * dg.G
+    none = torch.tensor([2 ** 31 - 1, -2 ** 31, V, -1], dtype=torch.int32, device="cuda").repeat(nnz // 4 + 1)
+    members = torch.cat([dg.members[:dg.nnz], none[:nnz - dg.nnz]])
+    weights = None if w is None else torch.cat([dg.weights, torch.full((nnz - dg.nnz,), 3.0, device="cuda")])
+    dg = pcg.Groups(V, dg.row_ptr, members, dg.mult, nnz, dg.prepared, dg.prepared_info, weights=weights)
+    rng = np.random.default_rng([V, G])
+    ptok = rng.integers(0, V, (B, K)).astype(np.int32)
+    pgrp = rng.integers(0, og.G, (B, K)).astype(np.int32)
+    pgrp[:, -2:] = og.G - 1 - rng.integers(0, 4, (B, 2))
+    tgt = torch.from_numpy((3 * rng.standard_normal((B, K + 1, V))).astype(np.float32))
+    dft = tgt[:, :K] + torch.from_numpy((0.05 * rng.standard_normal((B, K, V))).astype(np.float32))
+    if dtype == "bf16":
+        tgt, dft = tgt.to(torch.bfloat16), dft.to(torch.bfloat16)
+    for step in range(3):
+        gpu, ref, _, diag = run_both(V, rp, mem, tgt, dft, ptok, pgrp, seed=11, offset=step, dg=dg, og=og, nthreads=8)
+        assert compare_verify(gpu, ref, og, ptok, pgrp).tolerated <= 1
+        assert diag["bad_proposal"] == 0 and diag["sequences"] == B
+
+
 # construction of the groups: tokens around the blocks of the scan, rows that fill the registers of the
 # pair kernel and rows beyond, sets of 63 to 66 members (ranked in registers or sorted in LDS), more
 # duplicates of a set than one look at its members covers
