@@ -1340,10 +1340,11 @@ __device__ __forceinline__ void run_totals(const float *sums, int32_t ng, double
 // gather; otherwise every sum.
 // Bound by the L2, which hands every row its own copy of the members (4 bytes an entry, once per
 // tile).  One entry per lane and load, with every pass waiting for its bounds, then its entries, took
-// 28.3 us at V = 16 384, 32 members, 32 rows, and 13.2 us to scan the sums; this takes 12.9, and 6.4 to
-// locate the draw (V = 65 536, 64 rows: 450 us and 51 us before, 190 and 9 now).  Behind the L2 it is the vector
+// 28.3 us at V = 16 384, 32 members, 32 rows, and 13.2 us to scan the sums; this takes 12.6, and 6.4 to
+// locate the draw (V = 65 536, 64 rows: 450 us and 51 us before, 189 and 9 now).  Behind the L2 it is the vector
 // instructions of an entry that count: without the test for the tile where there is one only (WHOLE) and
-// with one comparison for both ends of a group 14.6 -> 12.9 us, V = 32 768, 64 rows 70.7 -> 66.8.
+// with one comparison for both ends of a group 14.0 -> 12.6 us, V = 32 768, 64 rows 71.8 -> 67.4; with weights
+// 16.0 -> 14.8, V = 65 536, 64 rows 234 -> 223.
 template <int W, bool CSUM, bool WEIGHTED, bool WHOLE>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t groups_per_chunk, int32_t ntiles,
@@ -1360,10 +1361,15 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
   const float *src = table + (int64_t) r * V;
   const int32_t g_begin = chunk * groups_per_chunk;
   const int32_t ng = min(groups_per_chunk, G - g_begin);
-  for (int tile = 0; tile < ntiles; ++tile) {
+  for (int tile = 0; tile < (WHOLE ? 1 : ntiles); ++tile) {
     const int32_t t0 = tile * tile_len;
     const int32_t tl = min(tile_len, V - t0);
     if (tl <= 0) break;                             // uniform: no tile starts past the row
+    // With weights the compiler must not know that the groups are the same in every tile: it would keep the
+    // addresses of the first ones' bounds from one tile to the next, 16 registers that this form does not
+    // have (3 went to scratch: V = 65 536, 32 members, one sequence 74.5 us instead of 65.8).
+    int32_t first = g_begin;
+    if constexpr (WEIGHTED && !WHOLE) asm volatile("" : "+s"(first));
     stage_tile(tab, src + t0, tl, threadIdx.x);
     if (threadIdx.x == 0) {
       tab[tile_len] = 0.f;
@@ -1371,7 +1377,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);             // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
-    csr_sums<W, WEIGHTED, WHOLE>(tab, tile_len, t0, tl, g_begin, g_begin + ng, row_ptr, members, nnz, weights,
+    csr_sums<W, WEIGHTED, WHOLE>(tab, tile_len, t0, tl, first, first + ng, row_ptr, members, nnz, weights,
                           long_size, &has_long, [&](int32_t g, float a) {
                             // the same lane in every tile: no other touches this sum meanwhile
                             sums[g - g_begin] = tile > 0 ? sums[g - g_begin] + a : a;
