@@ -1411,10 +1411,9 @@ struct CdfPick {
 
 // Inverse CDF over f(0..n-1) >= 0 by a whole workgroup of NT threads.  Each thread owns a
 // contiguous run, so the running sum is the ascending one up to fp64 rounding.  All threads get
-// the result.  The threshold is u * total, or `goal_in` (relative to this range) with have_goal.
+// the result.  The threshold is u * total.
 template <int NT, int kRegRun = 32, typename F>   // kRegRun: runs up to this length are held in registers
-__device__ CdfPick block_inverse_cdf(int32_t n, F f, double u, bool have_goal = false,
-                                     double goal_in = 0.0) {
+__device__ CdfPick block_inverse_cdf(int32_t n, F f, double u) {
   __shared__ double wave_tot[NT / kWave];
   __shared__ int first_thread, last_pos;
   __shared__ CdfPick res;
@@ -1448,31 +1447,14 @@ __device__ CdfPick block_inverse_cdf(int32_t n, F f, double u, bool have_goal = 
     total += wave_tot[w];
   }
   const double excl = before + (inc - mine);
-  const double goal = have_goal ? goal_in : u * total;
+  const double goal = u * total;
   // the first thread whose run carries the running sum past the threshold: first lane of each
   // wave by ballot, then one LDS atomic per wave
   const unsigned long long hit = __ballot(mine > 0.0 && excl + mine > goal);
   if (hit != 0 && lane == __ffsll((long long) hit) - 1) atomicMin(&first_thread, tid);
   __syncthreads();
   const int ft = __builtin_amdgcn_readfirstlane(first_thread);   // the same in every lane
-  if (kRegRun <= 4 && in_regs) {
-    // a run of a few bins: thread ft walks its own registers
-    if (ft == tid) {
-      double cum = excl, last_v = 0.0;
-      int32_t last = lo_i;
-      bool done = false;
-#pragma unroll
-      for (int j = 0; j < kRegRun; ++j) {
-        if (!done && vals[j] > 0.0) {
-          const double nxt = cum + vals[j];
-          if (nxt > goal) { res.index = lo_i + j; res.lo = cum; res.hi = nxt; done = true; }
-          else { last = lo_i + j; last_v = vals[j]; cum = nxt; }
-        }
-      }
-      if (!done) { res.index = last; res.lo = cum - last_v; res.hi = cum; }
-      res.total = total;
-    }
-  } else if (in_regs && ft != INT_MAX) {
+  if (in_regs && ft != INT_MAX) {
     // The crossing lies inside thread ft's run: its wave looks at the run's bins side by side, one
     // per lane (a run held in registers is at most 32 long), instead of thread ft walking them
     // one after the other.
