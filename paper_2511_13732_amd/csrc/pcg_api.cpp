@@ -81,7 +81,7 @@ struct StageTimer {
   }
 };
 
-constexpr int64_t kStreamBytes = (int64_t) 64 << 20;      // logits of a step above which they are streamed
+constexpr int64_t kStreamBytes = (int64_t) 96 << 20;      // logits of a step above which they are streamed
 
 // See RowSet.
 uint32_t row_magic(int32_t npos) { return npos > 1 ? (uint32_t) (((uint64_t) 1 << 32) / (uint32_t) npos) : 0u; }
@@ -399,10 +399,19 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
     return PCG_OK;
   }
   tm.begin(kStageStats);
-  // Streaming pass where the rows are large: only the rejected position's two (2 of 2K+1) are read again.
-  // Rows that the Infinity Cache holds with room to spare are better left there for that: V = 65 536, bf16,
-  // K = 8, row_stats and finalize 6.8 + 8.9 us streamed and 5.9 + 7.9 cached for 8 sequences (18 MB), 9.1 + 8.8
-  // and 8.0 + 8.0 for 16, 13.8 + 9.0 and 13.6 + 8.7 for 32 (71 MB); for 64 (143 MB) 23.1 and 24.6 alone.
+  // Streaming pass where the rows are large: only the rejected position's two (2 of 2K+1) are read again.  Rows
+  // that the Infinity Cache holds with room to spare are better left there for that, by accept_delta and
+  // finalize.  The four kernels in us, streamed and cached, on logits that a copy has just written, and on
+  // logits last touched 800 MB ago (one that is repeated on the same logits finds them in the caches, which no
+  // new step does):
+  //   bf16, V = 65 536, K = 8:  18 MB 35.7 and 34.5, 35.8 and 35.0;  36 MB 39.2 and 37.7, 39.6 and 37.7;
+  //             71 MB 46.1 and 45.6, 47.5 and 46.5;  98 MB 77.7 and 76.2, 78.5 and 78.2;  107 MB 78.4 and 77.6,
+  //             78.7 and 79.6;  143 MB 68.0 and 72.0, 68.2 and 69.7
+  //   fp32, V = 32 768, K = 6:  27 MB 32.6 and 30.7, 33.0 and 31.1;  55 MB 37.6 and 35.7, 37.7 and 36.9;
+  //             82 MB 43.1 and 41.7, 43.7 and 43.2;  99 MB 46.0 and 45.6, 47.3 and 47.4;  109 MB 47.7 and 47.5, 48.8 and 49.1;
+  //             218 MB 81.4 and 89.0, 77.9 and 80.5
+  // At 71 MB row_stats itself takes 13.0 and 13.4, 14.2 and 14.2, at 143 MB 23.0 and 24.3, 23.2 and 25.3; the two
+  // behind it 16.0 and 15.0, 15.9 and 14.8 at 71 MB.
   const bool streaming = rows * V * (bf16 ? 2 : 4) > kStreamBytes;
   if ((e = launch_row_stats(rs, bf16, V, rows, f.c, streaming, parts, stream, &pa)) != hipSuccess) return hip_fail(e);
   tm.end(kStageStats);

@@ -183,7 +183,8 @@ def test_small_step_rows_of_one_part(V, B, K, dtype, layout):
 # two launches and in four
 @pytest.mark.parametrize("V,B,K,dtype,size,moved", [
     (V, B, K, dtype, size, moved) for V, B, K, dtype in [(17003, 3, 6, "bf16"), (4100, 2, 9, "f32")]
-    for size in (1, 8, 64, 65, 130) for moved in ("none", "one", "emptied")] + [(65536, 16, 17, "bf16", 8, "one")])
+    for size in (1, 8, 64, 65, 130) for moved in ("none", "one", "emptied")] +
+    [(65536, 16, 17, "bf16", 8, "one"), (65536, 21, 17, "bf16", 8, "one"), (65536, 22, 17, "bf16", 8, "one")])
 def test_groups_of_one_size(V, B, K, dtype, size, moved):
     print(f"V={V} B={B} K={K} {dtype} size={size} {moved}", flush=True)
     sets = [(g + np.arange(size)) % V for g in range(V)]
