@@ -177,6 +177,19 @@ def test_small_step_rows_of_one_part(V, B, K, dtype, layout):
         assert len(np.unique(gpu.accept_len.cpu().numpy())) > K // 2
 
 
+def groups_of_one_size(V, size, moved):
+    sets = [(g + np.arange(size)) % V for g in range(V)]
+    sets = [np.sort(x).astype(np.int32) for x in sets]
+    if moved == "one":
+        sets[9] = np.sort(np.append(sets[9], np.int32((9 + size) % V)))
+        sets[5] = sets[5][:-1] if size > 1 else sets[5][:0]
+    if moved == "emptied":
+        sets[7] = np.sort(np.concatenate([(7 + np.arange(3 * size)) % V])).astype(np.int32)
+        sets[6] = sets[8] = np.zeros(0, np.int32)
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in sets])]).astype(np.int32)
+    return rp, np.concatenate(sets)
+
+
 # groups of one size, which are looked up before their bounds are known, around the 64 entries of a wave; and
 # of one size on average only: an entry moved from one group to a later one, so that those between start
 # elsewhere, or two groups emptied into a third; with the rows of a step streamed or cached, its probes in
@@ -187,16 +200,7 @@ def test_small_step_rows_of_one_part(V, B, K, dtype, layout):
     [(65536, 16, 17, "bf16", 8, "one"), (65536, 21, 17, "bf16", 8, "one"), (65536, 22, 17, "bf16", 8, "one")])
 def test_groups_of_one_size(V, B, K, dtype, size, moved):
     print(f"V={V} B={B} K={K} {dtype} size={size} {moved}", flush=True)
-    sets = [(g + np.arange(size)) % V for g in range(V)]
-    sets = [np.sort(x).astype(np.int32) for x in sets]
-    if moved == "one":
-        sets[9] = np.sort(np.append(sets[9], np.int32((9 + size) % V)))
-        sets[5] = sets[5][:-1] if size > 1 else sets[5][:0]
-    if moved == "emptied":
-        sets[7] = np.sort(np.concatenate([(7 + np.arange(3 * size)) % V])).astype(np.int32)
-        sets[6] = sets[8] = np.zeros(0, np.int32)
-    rp = np.concatenate([[0], np.cumsum([len(x) for x in sets])]).astype(np.int32)
-    mem = np.concatenate(sets)
+    rp, mem = groups_of_one_size(V, size, moved)
     rng = np.random.default_rng([V, size])
     ptok = rng.integers(0, V, (B, K)).astype(np.int32)
     pgrp = np.where(rng.random((B, K)) < 0.7, rng.integers(0, 14, (B, K)), rng.integers(0, V, (B, K))).astype(np.int32)
@@ -207,6 +211,31 @@ def test_groups_of_one_size(V, B, K, dtype, size, moved):
     og = oracle_groups(V, rp, mem)
     for prepare in (True, False):
         dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=prepare)
+        gpu, ref, _, diag = run_both(V, rp, mem, tgt, dft, ptok, pgrp, seed=11, offset=2, dg=dg, og=og, nthreads=8)
+        assert compare_verify(gpu, ref, og, ptok, pgrp).tolerated <= 1
+        assert diag["bad_proposal"] == 0 and diag["sequences"] == B
+
+
+# the same with weights, which are looked up with the members: proposals of the groups that are not where they
+# are looked for (their entries' weights taken from there instead would change 7 to 38 of the sequences)
+@pytest.mark.parametrize("V,B,dtype", [(4100, 100, "f32"), (17003, 60, "bf16")])
+@pytest.mark.parametrize("size", [8, 64, 65])
+@pytest.mark.parametrize("moved", ["none", "one", "emptied"])
+def test_weights_of_groups_of_one_size(V, B, dtype, size, moved, K=8):
+    print(f"V={V} B={B} {dtype} size={size} {moved}", flush=True)
+    rp, mem = groups_of_one_size(V, size, moved)
+    og = oracle_groups(V, rp, mem)
+    w = W.random_weights(og.V, og.members, 1)
+    og = oracle.with_weights(og, w)
+    rng = np.random.default_rng([V, size])
+    ptok = rng.integers(0, V, (B, K)).astype(np.int32)
+    pgrp = rng.choice([5, 7, 7, 9] if moved == "emptied" else [5, 6, 7, 8, 9], (B, K)).astype(np.int32)
+    tgt = torch.from_numpy((3 * rng.standard_normal((B, K + 1, V))).astype(np.float32))
+    dft = tgt[:, :K] + torch.from_numpy(rng.standard_normal((B, K, V)).astype(np.float32))
+    if dtype == "bf16":
+        tgt, dft = tgt.to(torch.bfloat16), dft.to(torch.bfloat16)
+    for prepare in (True, False):
+        dg = pcg.Groups.from_csr(V, rp, mem, "cuda", prepare=prepare, weights=w)
         gpu, ref, _, diag = run_both(V, rp, mem, tgt, dft, ptok, pgrp, seed=11, offset=2, dg=dg, og=og, nthreads=8)
         assert compare_verify(gpu, ref, og, ptok, pgrp).tolerated <= 1
         assert diag["bad_proposal"] == 0 and diag["sequences"] == B
