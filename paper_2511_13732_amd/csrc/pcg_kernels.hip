@@ -496,8 +496,8 @@ __device__ __forceinline__ void accept_decide(AcceptShared &sh, const AcceptArgs
   if (wave == 0) {
     if (in) {
       const Probe p = sh.probe[i];
-      if (p.Tp > 0.0) T = p.Tp * exp2((double) (p.Tref - sh.st_t[i].M) * a.cd) * sh.iz_t[i];
-      if (p.Dp > 0.0) D = p.Dp * exp2((double) (p.Dref - sh.st_d[i].M) * a.cd) * sh.iz_d[i];
+      if (p.Tp > 0.0) T = p.Tp * exp2((double) (p.Tref - sh.st_t[i].M) * a.cd) / sh.st_t[i].Z;
+      if (p.Dp > 0.0) D = p.Dp * exp2((double) (p.Dref - sh.st_d[i].M) * a.cd) / sh.st_d[i].Z;
       u = (double) sh.uacc[i];
       bad = p.bad != 0;
     }
