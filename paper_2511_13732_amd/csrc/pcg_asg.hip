@@ -1,5 +1,5 @@
 // Construction of the Acoustic Similarity Groups (Sec. 2.1, Eq. 1) on gfx950: unit vectors in
-// bfloat16, the V x V cosine similarity as a bf16 MFMA contraction with fp32 accumulation that
+// bfloat16 (the exact form: fp16), the V x V cosine similarity as an MFMA contraction with fp32 accumulation that
 // is thresholded on the fly (the similarity matrix is never stored), per-token member lists
 // sorted ascending, identical sets dropped, and the CSR the verification kernels read.  The
 // exact form (pcg_asg_build_exact) uses the same contraction as a filter: pairs whose rounded
@@ -7,8 +7,10 @@
 // embeddings themselves in double, so its groups are those of Eq. (1) as written.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "pcg_device.h"
 #include "pcg_kernels.h"
@@ -47,10 +49,28 @@ __device__ __forceinline__ uint16_t quotient_to_bf16(double e, double norm, doub
   return (uint16_t) ((u + 0x8000u) >> 16);
 }
 
-__device__ __forceinline__ double bf16_value(uint16_t b) { return (double) __uint_as_float((uint32_t) b << 16); }
+// The exact form's filter works on the unit vectors in fp16, times 2^8: components up to 256, and what would be
+// subnormal (below 2^-22 of the unit) is 0.  Three bits more than bf16 at the same MFMA rate narrow the band of
+// pairs that have to be settled in double from 3.4e-3 to 5.5e-4 at 65 536 x 1024 (0.7 M pairs to 0.12 M:
+// asg_refine_kernel 472 us to 119); the products take 4 % longer for it (the wider multipliers draw
+// more power, which is what sets the clock there).
+constexpr float kHalfScale = 256.f;
 
-// EXACT: norms receives ||emb[v]|| in double, and moved[v] ||unit_bf16[v] - emb[v] / ||emb[v]|| ||, how
-// far rounding has moved the unit vector; *worst, the largest of them once asg_setup_kernel has run, is
+// An element of a unit vector as the products read it, and back.
+template <bool EXACT>
+__device__ __forceinline__ uint16_t unit_element(double e, double norm, double inv) {
+  if constexpr (!EXACT) return quotient_to_bf16(e, norm, inv);
+  const float f = (float) (e * inv) * kHalfScale;
+  return fabsf(f) < 0x1p-14f ? (uint16_t) 0 : __builtin_bit_cast(uint16_t, (_Float16) f);
+}
+template <bool EXACT>
+__device__ __forceinline__ double unit_value(uint16_t b) {
+  if constexpr (!EXACT) return (double) __uint_as_float((uint32_t) b << 16);
+  return (double) ((float) __builtin_bit_cast(_Float16, b) * (1.f / kHalfScale));
+}
+
+// EXACT: unit vectors in scaled fp16; norms receives ||emb[v]|| in double, and moved[v] how far
+// rounding has moved the unit vector; *worst, the largest of them once asg_setup_kernel has run, is
 // cleared for it.  (An atomic maximum here, by every wave at once, took 3.4 of 7.2 us at 2048 tokens.)
 // One wave per token; its row (up to kRowRegs * 256 elements, d a multiple of 4) stays in registers
 // between the norm and the quotients.  Bound by memory: 268 MB of embeddings and 134 MB of unit
@@ -89,9 +109,9 @@ __global__ __launch_bounds__(256) void asg_normalize_kernel(const float *emb, in
       uint16_t q[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        q[j] = norm > 0.0 ? quotient_to_bf16((double) xs[j], norm, inv) : (uint16_t) 0;
+        q[j] = norm > 0.0 ? unit_element<EXACT>((double) xs[j], norm, inv) : (uint16_t) 0;
         if constexpr (EXACT) {
-          const double off = bf16_value(q[j]) - (double) xs[j] * inv;
+          const double off = unit_value<EXACT>(q[j]) - (double) xs[j] * inv;
           err += off * off;
         }
       }
@@ -103,10 +123,10 @@ __global__ __launch_bounds__(256) void asg_normalize_kernel(const float *emb, in
     const double norm = sqrt(wave_sum(ss)), inv = norm > 0.0 ? 1.0 / norm : 0.0;
     if (EXACT && lane == 0) norms[v] = norm;
     for (int32_t k = lane; k < d; k += kWave) {
-      const uint16_t q = norm > 0.0 ? quotient_to_bf16((double) e[k], norm, inv) : (uint16_t) 0;
+      const uint16_t q = norm > 0.0 ? unit_element<EXACT>((double) e[k], norm, inv) : (uint16_t) 0;
       out[k] = q;
       if constexpr (EXACT) {
-        const double off = bf16_value(q) - (double) e[k] * inv;
+        const double off = unit_value<EXACT>(q) - (double) e[k] * inv;
         err += off * off;
       }
     }
@@ -130,42 +150,112 @@ __global__ __launch_bounds__(256) void asg_normalize_kernel(const float *emb, in
 // k per stage, four stages resident: while one is used the loads of the next three are in flight,
 // and no register is spent on staging.  The matrix is symmetric: only tiles on or above the
 // diagonal are computed, and a pair found off the diagonal is recorded for both of its tokens.
+//
+// A workgroup stays for its share of the tiles, one after the other, and its loads run on into the next
+// tile: with one wave a SIMD nothing hides the first loads of a tile, the threshold pass, or the
+// atomics that hand out places in the lists (2 to 4 us a round trip between eight XCDs), unless the same
+// wave overlaps them.  65 536 x 1024, a workgroup per tile -> this, with fp16 operands: 4.91 -> 4.24 ms; matrix
+// cores busy 48 -> 64 % of the cycles, at a clock that falls from 1.7 to 1.6 GHz as they do (2.3 without
+// them: the card's power limit).  Of a tile's 51 thousand cycles the products are 33, the threshold pass 6 and
+// waits for barriers, loads and LDS 10.  What each part gave, in cycles of the same case (one workgroup a tile:
+// 8.5 million): tiles one after the other in one workgroup, places of a tile's pairs used a tile later 8.0;
+// threshold pass of 28 instructions a block and loads from scalar bases 7.2; a stage's operands read a
+// whole stage ahead 6.6.  Taken out again: 128 x 256 tiles, two workgroups a compute unit (they
+// overlap each other, but read half as much again from the L2: 5.1 ms for 4.9).
 // ---------------------------------------------------------------------------------------------
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));      // or eight fp16 values, see mfma
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kSimTile = 256;                 // rows and columns of a workgroup's tile
 constexpr int kSimK = 32;                     // k columns per LDS stage: rows of 64 bytes
 constexpr int kSimBufs = 4;                   // stages resident in LDS
 constexpr int kSimThreads = 256;
+
+template <bool EXACT>
+__device__ __forceinline__ floatx16 mfma(bf16x8 a, bf16x8 b, floatx16 c) {
+  if constexpr (EXACT)
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
 constexpr int kSimStageBytes = kSimTile * kSimK * 2;      // one operand of one stage: 16 KiB
 constexpr int kSimLoads = 2 * kSimTile / 16 / 4;          // direct-to-LDS loads per wave and stage: 8
-constexpr int kSimQueue = 8192;               // pairs a workgroup can hold back in LDS
-constexpr int kSimPatchRows = 16, kSimPatchCols = 2;       // tiles that one XCD works on together
+constexpr int kSimQueue = 2048;               // pairs a wave can hold back in LDS
+constexpr int kSimPatchRows = 16;             // rows of tiles walked column by column (sim_tile)
 
-// Record v as a member of G(t).
-__device__ __forceinline__ void asg_emit(int32_t t, int32_t v, int32_t cap, int32_t *count,
-                                         int32_t *cand) {
-  const int32_t pos = atomicAdd(&count[t], 1);
-  if (pos < cap) cand[(int64_t) t * cap + pos] = v;
+// Makes a wave's LDS writes visible to its own later reads (no other wave shares the data).
+__device__ __forceinline__ void wave_handoff() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // A member that the rounded similarity could not decide carries this bit until the exact form
 // has settled it (token ids stay below 2^31).
 constexpr uint32_t kAsgUnsure = 0x80000000u;
 
-// Appends the pair (t, v) to the workgroup's queue in LDS; pairs beyond its capacity are
-// recorded at once.  flag: 0 or kAsgUnsure.
-__device__ __forceinline__ void sim_queue_pair(int32_t t, int32_t v, uint32_t flag, int32_t cap,
-                                               int32_t *count, int32_t *cand, uint32_t *qn, uint2 *q) {
-  const uint32_t k = atomicAdd(qn, 1u);
-  if (k < (uint32_t) kSimQueue) {
-    q[k] = make_uint2((uint32_t) t, (uint32_t) v | flag);
-  } else {
-    asg_emit(t, (int32_t) ((uint32_t) v | flag), cap, count, cand);
-    if (t != v) asg_emit(v, (int32_t) ((uint32_t) t | flag), cap, count, cand);
+// A wave's pairs on their way to the lists: collected in its own slice of LDS (no other wave touches it), so
+// that the round trips of the atomics that hand out the places overlap instead of following one another.
+// An entry is the pair's row and column inside the wave's part of the tile, kSimUnsure where marked.
+constexpr uint32_t kSimUnsure = 0x80000000u;
+
+// The pair of an entry of the part of a tile that begins at (row0, col0).
+__device__ __forceinline__ void sim_pair(uint32_t e, int32_t row0, int32_t col0, int32_t &t, int32_t &v) {
+  t = row0 + (int32_t) ((e >> 16) & 0x7fffu);
+  v = col0 + (int32_t) (e & 0xffffu);
+}
+
+// Places for a pair in the lists of both of its tokens, and the pair into them.
+struct SimPlaces { int32_t p0, p1; };
+__device__ __forceinline__ SimPlaces sim_ask(int32_t t, int32_t v, int32_t cap, int32_t *count) {
+  SimPlaces p;
+  p.p0 = atomicAdd(&count[t], 1);
+  p.p1 = t != v ? atomicAdd(&count[v], 1) : cap;
+  return p;
+}
+__device__ __forceinline__ void sim_put(const SimPlaces &p, int32_t t, int32_t v, uint32_t e, int32_t cap, int32_t *cand) {
+  const uint32_t flag = e & kSimUnsure;
+  if (p.p0 < cap) cand[(int64_t) t * cap + p.p0] = (int32_t) ((uint32_t) v | flag);
+  if (p.p1 < cap) cand[(int64_t) v * cap + p.p1] = (int32_t) ((uint32_t) t | flag);
+}
+
+// Entries [from, n) of a wave's queue, all the way.
+__device__ __forceinline__ void sim_flush(const uint32_t *q, uint32_t from, uint32_t n, int32_t row0, int32_t col0,
+                                          int32_t cap, int32_t *count, int32_t *cand, int lane) {
+  wave_handoff();
+  for (uint32_t k = from + lane; k < n; k += kWave) {
+    int32_t t, v;
+    sim_pair(q[k], row0, col0, t, v);
+    sim_put(sim_ask(t, v, cap, count), t, v, q[k], cap, cand);
   }
+  wave_handoff();
+}
+
+// Tile n of those on or above the diagonal of an nt x nt grid: kSimPatchRows rows of tiles at a time,
+// column by column from the diagonal on, so that 32 tiles in a row are a patch of 16 x 2 (8 x 4: 5.2 ms for
+// 5.0, 4 x 8: 5.7): the 32 workgroups of an XCD find each other's rows in their L2.
+__device__ __forceinline__ int sim_tiles(int nt, int first_row) {      // of the rows of tiles from first_row on
+  const int h = nt - first_row < kSimPatchRows ? nt - first_row : kSimPatchRows;
+  return h * (h + 1) / 2 + (nt - first_row - h) * h;
+}
+__device__ __forceinline__ void sim_tile(int n, int nt, int &ti, int &tj) {
+  int first = 0;
+  for (int k = sim_tiles(nt, 0); n >= k; k = sim_tiles(nt, first)) {
+    n -= k;
+    first += kSimPatchRows;
+  }
+  const int h = min(kSimPatchRows, nt - first);
+  int c = 0;
+  while (c < h && n > c) n -= ++c;             // columns of 1, 2 .. h tiles
+  if (c == h) {                                // and of h
+    c += n / h;
+    n %= h;
+  }
+  ti = first + n;
+  tj = first + c;
 }
 
 // Clears what the kernels that follow count in.  EXACT: the largest of moved[0 .. V) into *worst, which
@@ -212,7 +302,7 @@ __device__ __forceinline__ void bare_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// How far the fp32-accumulated dot product of two bf16-rounded unit vectors can lie from the cosine of
+// How far the fp32-accumulated dot product of two rounded unit vectors can lie from the cosine of
 // the vectors they were rounded from, if rounding moved neither by more than e: the exact dot product
 // of the rounded ones lies within 2 e + e^2 (Cauchy-Schwarz), and the d additions in fp32 add at most
 // d 2^-23 of the vectors' lengths (a rounding, or a truncation, of each partial sum).  2^-20 covers
@@ -224,191 +314,213 @@ __device__ __forceinline__ float asg_rounding_band(int32_t d, float e) {
 // EXACT: pairs above theta minus the rounding band are candidates, and those not above theta plus
 // the band are marked kAsgUnsure for asg_refine_kernel.
 template <bool EXACT>
-__global__ __launch_bounds__(kSimThreads) void asg_similarity_kernel(
+__global__ __launch_bounds__(kSimThreads, 1) void asg_similarity_kernel(
     const uint16_t *__restrict__ unit, int32_t V, int32_t d, float theta, const float *worst,
-    int32_t cap, int32_t *count, int32_t *cand) {
+    int32_t cap, int32_t ntiles, int32_t run, int32_t *count, int32_t *cand) {
   float theta_hi = theta;
   if constexpr (EXACT) {
     const float band = asg_rounding_band(d, *worst);
-    theta_hi = theta + band;
-    theta = theta - band;
+    theta_hi = (theta + band) * (kHalfScale * kHalfScale);
+    theta = (theta - band) * (kHalfScale * kHalfScale);
   }
-  // Workgroups go to the 8 XCDs round-robin; the 32 that run together on one XCD take a patch of
-  // 16 x 2 tiles (measured: 5.0 ms against 5.2 for 8 x 4 and 5.7 for 4 x 8), so that they find each
-  // other's rows in their L2.
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  constexpr int kPatch = kSimPatchRows * kSimPatchCols;
-  const int patch = (local / kPatch) * 8 + xcd;
-  const int within = local % kPatch;
-  const int ntl = (V + kSimTile - 1) / kSimTile;
-  const int super_cols = (ntl + kSimPatchCols - 1) / kSimPatchCols;
-  const int ti = (patch / super_cols) * kSimPatchRows + within / kSimPatchCols;
-  const int tj = (patch % super_cols) * kSimPatchCols + within % kSimPatchCols;
-  if (ti >= ntl || tj >= ntl || tj < ti) return;      // the whole workgroup leaves
+  const int nt = (V + kSimTile - 1) / kSimTile;
   // [buffer][operand][row][64 bytes].  A 16-byte LDS read is served 16 lanes at a time, free of
   // conflicts when their addresses differ modulo 256 bytes; the four 16-byte chunks of a row are
   // therefore stored at position chunk ^ ((row >> 2) & 3), which spreads the same chunk of 16
   // consecutive rows over all 16 slots.
   __shared__ __attribute__((aligned(1024))) unsigned char lds[kSimBufs * 2 * kSimStageBytes];
+  __shared__ uint32_t queue[kSimThreads / kWave][kSimQueue];
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int32_t row0 = ti * kSimTile, col0 = tj * kSimTile;
+  uint32_t *q = queue[wave];
+
+  // Workgroups go to the 8 XCDs round-robin; the `run` of one XCD take `run` tiles in a row at a time.
+  const int step_tiles = 8 * run;
+  int n = (blockIdx.x & 7) * run + (int) (blockIdx.x >> 3);
+  if (n >= ntiles) return;
 
   // Direct-to-LDS loads: one instruction of a wave fills 1 KiB = 16 rows, lane i the 16 bytes at
-  // row i / 4, position i % 4.  Wave w brings rows 64 w .. 64 w + 63 of both operands.
-  int32_t src[kSimLoads];
-  {
+  // row i / 4, position i % 4.  Wave w brings rows 64 w .. 64 w + 63 of both operands.  The loads run ahead
+  // of the products by kSimBufs stages, across the tiles: they have a place of their own.
+  int ld_n = n, ld_k = 0;
+  uint32_t src[kSimLoads];              // byte offsets of this lane's rows and chunk (V d < 2^31 elements)
+  auto aim = [&]() {
+    int ti, tj;
+    sim_tile(ld_n, nt, ti, tj);
     const int r = lane >> 2, p = lane & 3;
     const int c = p ^ ((r >> 2) & 3);                  // the chunk of the row that belongs there
 #pragma unroll
     for (int j = 0; j < kSimLoads / 2; ++j) {
       const int row = wave * 64 + j * 16 + r;
       // rows past the end of the matrix re-read the last row; their results are never recorded
-      src[j] = min(row0 + row, V - 1) * d + c * 8;
-      src[kSimLoads / 2 + j] = min(col0 + row, V - 1) * d + c * 8;
+      src[j] = 2u * (uint32_t) (min(ti * kSimTile + row, V - 1) * d + c * 8);
+      src[kSimLoads / 2 + j] = 2u * (uint32_t) (min(tj * kSimTile + row, V - 1) * d + c * 8);
     }
-  }
-  const int nstages = d / kSimK;        // even: d is a multiple of 64
-  auto load_a = [&](int j, unsigned char *dst, int k0) {
-    __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void *) (unit + src[j] + k0),
-        (__attribute__((address_space(3))) void *) (dst + j * 1024), 16, 0, 0);
   };
-  auto load_b = [&](int j, unsigned char *dst, int k0) {
+  aim();
+  auto load = [&](int j, unsigned char *stage) {
+    unsigned char *dst = stage + (j & 1) * kSimStageBytes + wave * 64 * 64 + (j >> 1) * 1024;
     __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void *) (unit + src[kSimLoads / 2 + j] + k0),
-        (__attribute__((address_space(3))) void *) (dst + kSimStageBytes + j * 1024), 16, 0, 0);
+        (const __attribute__((address_space(1))) void *) (reinterpret_cast<const char *>(unit + ld_k) +
+                                                          src[(j & 1) * (kSimLoads / 2) + (j >> 1)]),
+        (__attribute__((address_space(3))) void *) dst, 16, 0, 0);
+  };
+  // On to the next stage; past the last tile its stages are repeated: nobody reads what they bring.
+  auto advance = [&]() {
+    ld_k += kSimK;
+    if (ld_k == d) {
+      ld_k = 0;
+      if (ld_n + step_tiles < ntiles) {
+        ld_n += step_tiles;
+        aim();
+      }
+    }
   };
 
   floatx16 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
   // operand reads of this lane: row lane % 32 of a block, k half lane / 32 of a 16-column step
   const int fr = lane & 31, fh = lane >> 5;
   const int sw = (fr >> 2) & 3;                        // block rows start at multiples of 32
-  const int a_row = (wm * 128 + fr) * 64, b_row = (wn * 128 + fr) * 64;
+  const int a_row = (wm * 128 + fr) * 64, b_row = (wn * 128 + fr) * 64 + kSimStageBytes;
   const int pos0 = ((0 + fh) ^ sw) * 16, pos1 = ((2 + fh) ^ sw) * 16;
 
-  bf16x8 f0a[4], f0b[4], f1a[4], f1b[4];      // operands of the two 16-column steps of a stage
-  // One 16-column step: 16 MFMAs on (ca, cb).  Behind the first eight of them, one at a time,
-  // the next step's operands (na, nb) are read from LDS at ta / tb and, with FETCH, the eight
-  // loads of a later stage are started.  The LDS and memory queues are short: instructions
-  // issued in a burst would hold the MFMAs behind them back, and reads issued late would make
-  // the next step wait.  The order is pinned.
-  auto step = [&](const bf16x8 (&ca)[4], const bf16x8 (&cb)[4], bf16x8 (&na)[4], bf16x8 (&nb)[4],
-                  const unsigned char *ta, const unsigned char *tb, bool with_fetch,
-                  unsigned char *dst, int k0) {
+  // Operands of two stages, each of two 16-column steps: one in use, the next on its way from LDS.
+  bf16x8 fa[2][2][4], fb[2][2][4];
+  auto read = [&](bf16x8 (&a)[2][4], bf16x8 (&b)[2][4], const unsigned char *buf, int k) {      // k: 0 .. 15
+    const int pos = k < 8 ? pos0 : pos1, i = k & 3;
+    if ((k & 7) < 4) a[k >> 3][i] = *reinterpret_cast<const bf16x8 *>(buf + a_row + pos + i * 32 * 64);
+    else b[k >> 3][i] = *reinterpret_cast<const bf16x8 *>(buf + b_row + pos + i * 32 * 64);
+  };
+  unsigned char *cur = lds, *const end = lds + kSimBufs * 2 * kSimStageBytes;
+  // One stage: 32 MFMAs on operand set P.  Behind the first 24 of them, one at a time, the next stage's operands
+  // are read from LDS into the other set and the loads of the stage after those on their way are
+  // started.  The LDS and memory queues are short: instructions issued in a burst would hold the
+  // MFMAs behind them back, and with one wave a SIMD nothing else runs while one waits: the last
+  // read has eight MFMAs to come in.  The order is pinned.  FIRST: the sums begin with these products.
+  auto stage = [&](auto set, auto first) {
+    constexpr int P = decltype(set)::value;
+    constexpr bool kFirst = decltype(first)::value;
+    unsigned char *nxt = cur + 2 * kSimStageBytes;
+    if (nxt == end) nxt = lds;
+    // This wave's loads of the next stage have landed once only those of the two stages behind it
+    // are out; past the barrier everyone's have, and nobody reads buffer `cur` any more (this stage's
+    // operands are in registers).
+    wait_vm<(kSimBufs - 2) * kSimLoads>();
+    bare_barrier();
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int i = m >> 2, j = m & 3;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca[i], cb[j], acc[i][j], 0, 0, 0);
-      if (m < 8) {
+    for (int m = 0; m < 32; ++m) {
+      const int i = (m >> 2) & 3, j = m & 3;
+      if (kFirst && m < 16) acc[i][j] = mfma<EXACT>(fa[P][0][i], fb[P][0][j], floatx16{});
+      else acc[i][j] = mfma<EXACT>(fa[P][m >> 4][i], fb[P][m >> 4][j], acc[i][j]);
+      if (m < 24) {
         __builtin_amdgcn_sched_barrier(0);
-        if (with_fetch) {
-          if ((m & 1) == 0) load_a(m >> 1, dst, k0); else load_b(m >> 1, dst, k0);
-        }
-        if (m < 4) na[m] = *reinterpret_cast<const bf16x8 *>(ta + m * 32 * 64);
-        else nb[m - 4] = *reinterpret_cast<const bf16x8 *>(tb + (m - 4) * 32 * 64);
+        if (m % 3 == 2) load(m / 3, cur);
+        else read(fa[1 - P], fb[1 - P], nxt, m / 3 * 2 + m % 3);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     __builtin_amdgcn_sched_barrier(0);
+    advance();
+    cur = nxt;
   };
+  constexpr std::integral_constant<int, 0> kEven{};
+  constexpr std::integral_constant<int, 1> kOdd{};
 
-  // Loads that would reach past the last stage repeat it instead: nobody reads what they bring,
-  // and the number of loads in flight stays the same on every turn, which the waits rely on.
 #pragma unroll
   for (int s = 0; s < kSimBufs; ++s) {
-    unsigned char *dst = lds + s * 2 * kSimStageBytes + wave * 64 * 64;
-    const int k0 = min(s, nstages - 1) * kSimK;
 #pragma unroll
-    for (int j = 0; j < kSimLoads / 2; ++j) { load_a(j, dst, k0); load_b(j, dst, k0); }
+    for (int j = 0; j < kSimLoads; ++j) load(j, lds + s * 2 * kSimStageBytes);
+    advance();
   }
   wait_vm<(kSimBufs - 1) * kSimLoads>();    // stage 0 is in; the ones behind it may be on their way
   bare_barrier();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f0a[i] = *reinterpret_cast<const bf16x8 *>(lds + a_row + pos0 + i * 32 * 64);
-    f0b[i] = *reinterpret_cast<const bf16x8 *>(lds + kSimStageBytes + b_row + pos0 + i * 32 * 64);
-  }
-  for (int s = 0; s < nstages; ++s) {
-    unsigned char *cur = lds + (s % kSimBufs) * 2 * kSimStageBytes;
-    const unsigned char *nxt = lds + ((s + 1) % kSimBufs) * 2 * kSimStageBytes;
-    // first half of the stage; the operands of its second half arrive behind it
-    step(f0a, f0b, f1a, f1b, cur + a_row + pos1, cur + kSimStageBytes + b_row + pos1, false, nullptr, 0);
-    // This wave's loads of stage s + 1 have landed once only those of the two stages behind it
-    // are out; past the barrier everyone's have, and nobody reads buffer `cur` any more (the
-    // operands of this stage's second half are in registers).
-    wait_vm<(kSimBufs - 2) * kSimLoads>();
-    bare_barrier();
-    // second half; behind it the loads of stage s + 4 start, into the buffer just freed, and the
-    // next stage's first operands are read
-    step(f1a, f1b, f0a, f0b, nxt + a_row + pos0, nxt + kSimStageBytes + b_row + pos0, true,
-         cur + wave * 64 * 64, min(s + kSimBufs, nstages - 1) * kSimK);
-  }
+  for (int k = 0; k < 16; ++k) read(fa[0], fb[0], lds, k);
 
-  // Threshold (Eq. 1).  The stage buffers are free once the loads past the end have landed: pairs
-  // that pass are collected there, then every thread records its share of them, so that the
-  // round trips of the atomics overlap instead of following one another.
-  wait_vm<0>();
-  __syncthreads();
-  uint32_t *qn = reinterpret_cast<uint32_t *>(lds);
-  uint2 *q = reinterpret_cast<uint2 *>(lds + 16);
-  if (tid == 0) *qn = 0;
-  __syncthreads();
+  // the last pairs of a tile: their places are asked for at its end and used at the end of the next
+  SimPlaces late = {cap, cap};
+  int32_t late_t = 0, late_v = 0;
+  uint32_t late_e = 0;
+  const int nstages = d / kSimK;        // even: d is a multiple of 64
+  for (;; n += step_tiles) {
+    stage(kEven, std::true_type{});
+    stage(kOdd, std::false_type{});
+#pragma unroll 1
+    for (int s = 2; s < nstages; s += 2) {
+      stage(kEven, std::false_type{});
+      stage(kOdd, std::false_type{});
+    }
+
+    // Threshold (Eq. 1)
+    int ti, tj;
+    sim_tile(n, nt, ti, tj);
+    const int32_t row0 = ti * kSimTile + wm * 128, col0 = tj * kSimTile + wn * 128;
+    uint32_t nq = 0;                                   // uniform over the wave
+    auto push = [&](bool mine, uint32_t entry) {
+      const unsigned long long who = __builtin_amdgcn_ballot_w64(mine);
+      if (mine)
+        q[nq + __builtin_amdgcn_mbcnt_hi((uint32_t) (who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t) who, 0))] = entry;
+      nq += (uint32_t) __popcll(who);
+    };
+    // Accumulator r of a lane is row 8 (r / 4) + 4 (lane / 32) + r % 4 and column lane % 32 of its 32 x 32
+    // block.  Most blocks hold nothing above the threshold: one maximum per lane and a ballot tell.  A queue
+    // that cannot take what a block may hold is emptied, and the blocks go on from there.
+    int done = 0;
+    while (true) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+      for (int b = 0; b < 16; ++b) {
+        __builtin_amdgcn_sched_barrier(0);             // one block's sums at a time in registers
+        if (done != b || nq > (uint32_t) (kSimQueue - 32 * 32)) continue;
+        ++done;
+        asm volatile("" : "+a"(acc[b >> 2][b & 3]));   // stays where the products left it until here
+        const floatx16 a = acc[b >> 2][b & 3];
+        float m = fmaxf(a[0], a[1]);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      // Accumulator r of a lane is row 8 (r / 4) + 4 (lane / 32) + r % 4 and column lane % 32 of
-      // the 32 x 32 block.  Most blocks hold nothing above the threshold: one maximum per lane
-      // and a ballot settle those.
-      const int32_t t0 = row0 + wm * 128 + i * 32, v0 = col0 + wn * 128 + j * 32;
-      if (v0 + 31 < t0) continue;                      // wholly below the diagonal
-      const floatx16 a = acc[i][j];
-      const float m = fmaxf(fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])),
-                                  fmaxf(fmaxf(a[4], a[5]), fmaxf(a[6], a[7]))),
-                            fmaxf(fmaxf(fmaxf(a[8], a[9]), fmaxf(a[10], a[11])),
-                                  fmaxf(fmaxf(a[12], a[13]), fmaxf(a[14], a[15]))));
-      const int32_t v = v0 + (lane & 31), tl = t0 + 4 * (lane >> 5);
-      if (__builtin_amdgcn_ballot_w64(m > theta) != 0) {
-        uint32_t hits = 0, sure = 0xffffu;
+        for (int r = 2; r < 16; r += 2) m = fmaxf(fmaxf(m, a[r]), a[r + 1]);
+        if (__builtin_amdgcn_ballot_w64(m > theta) == 0) continue;
+        const int32_t lt = (b >> 2) * 32 + 4 * (lane >> 5), lv = (b & 3) * 32 + (lane & 31);
+        const int32_t room = col0 + lv < V ? min(V, col0 + lv) - (row0 + lt) : 0;    // rows below V and the diagonal
+        uint32_t hits = 0, sure = 0;                   // bit 15 - r
 #pragma unroll
-        for (int r = 0; r < 16; ++r) hits |= (a[r] > theta ? 1u : 0u) << r;
+        for (int r = 0; r < 16; ++r) hits = (hits + (a[r] > theta ? 1u : 0u)) + hits;
         if constexpr (EXACT) {
-          sure = 0;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sure |= (a[r] > theta_hi ? 1u : 0u) << r;
+          for (int r = 0; r < 16; ++r) sure = (sure + (a[r] > theta_hi ? 1u : 0u)) + sure;
+        } else {
+          sure = hits;
         }
-        while (hits) {                                 // only the lanes that hold a pair
-          const int r = __builtin_ctz(hits);
+        while (__builtin_amdgcn_ballot_w64(hits != 0) != 0) {      // every lane its own next one
+          const int k = __builtin_ctz(hits | 0x10000u), r = 15 - k, at = 8 * (r >> 2) + (r & 3);
+          push(hits != 0 && at < room, (uint32_t) (lt + at) << 16 | (uint32_t) lv | (((sure >> k) & 1u) ? 0u : kSimUnsure));
           hits &= hits - 1;
-          const int32_t t = tl + 8 * (r >> 2) + (r & 3);
-          if (t < V && v < V && v > t)
-            sim_queue_pair(t, v, ((sure >> r) & 1u) ? 0u : kAsgUnsure, cap, count, cand, qn, q);
         }
       }
-      // a token is always a member of its own group, whatever the rounded product says
-      if (t0 == v0 && lane < 32 && t0 + lane < V)
-        sim_queue_pair(t0 + lane, t0 + lane, 0u, cap, count, cand, qn, q);
+      if (done == 16) break;
+      sim_flush(q, 0, nq, row0, col0, cap, count, cand, lane);
+      nq = 0;
     }
-  __syncthreads();
-  const uint32_t nq = min(*qn, (uint32_t) kSimQueue);
-  for (uint32_t k = tid; k < nq; k += kSimThreads) {
-    const uint2 pr = q[k];
-    const uint32_t flag = pr.y & kAsgUnsure;
-    const int32_t t = (int32_t) pr.x, v = (int32_t) (pr.y & ~kAsgUnsure);
-    const int32_t p0 = atomicAdd(&count[t], 1);
-    const int32_t p1 = t != v ? atomicAdd(&count[v], 1) : cap;
-    if (p0 < cap) cand[(int64_t) t * cap + p0] = (int32_t) ((uint32_t) v | flag);
-    if (p1 < cap) cand[(int64_t) v * cap + p1] = (int32_t) ((uint32_t) t | flag);
+    // a token is always a member of its own group, whatever the rounded product says
+    if (row0 == col0) {
+      if (nq > (uint32_t) (kSimQueue - 128)) {
+        sim_flush(q, 0, nq, row0, col0, cap, count, cand, lane);
+        nq = 0;
+      }
+      for (int k = 0; k < 128; k += kWave)
+        push(row0 + k + lane < V, (uint32_t) (k + lane) << 16 | (uint32_t) (k + lane));
+    }
+    sim_flush(q, kWave, nq, row0, col0, cap, count, cand, lane);
+    sim_put(late, late_t, late_v, late_e, cap, cand);
+    late.p0 = late.p1 = cap;
+    if ((uint32_t) lane < nq) {
+      late_e = q[lane];
+      sim_pair(late_e, row0, col0, late_t, late_v);
+      late = sim_ask(late_t, late_v, cap, count);
+    }
+    if (n + step_tiles >= ntiles) break;
   }
+  wait_vm<0>();                         // the loads past the end land while the LDS is still this workgroup's
+  sim_put(late, late_t, late_v, late_e, cap, cand);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -530,13 +642,6 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {   // splitmix64 finalise
   return x ^ (x >> 31);
 }
 
-// Makes a wave's LDS writes visible to its own later reads (no other wave shares the data).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // One wave per token: its members ascending, an order-independent hash of the set, its size; entries
 // marked kAsgRemoved are dropped, what is still marked kAsgUnsure (only where some list did not fit)
 // becomes a plain token id again, since the kernels that follow index with it.  Up to 64 members are
@@ -573,7 +678,7 @@ __global__ __launch_bounds__(kSortThreads) void asg_sort_kernel(int32_t V, int32
       key[k] = valid ? (int32_t) (raw & ~kAsgUnsure) : INT32_MAX;
       n += __popcll(__ballot(valid));
     }
-    wave_lds_sync();
+    wave_handoff();
     for (int32_t len = 2; len <= n2; len <<= 1)
       for (int32_t step = len >> 1; step > 0; step >>= 1) {
         for (int32_t k = lane; k < n2; k += kWave) {
@@ -584,10 +689,10 @@ __global__ __launch_bounds__(kSortThreads) void asg_sort_kernel(int32_t V, int32
             if ((x > y) == up) { key[k] = y; key[other] = x; }
           }
         }
-        wave_lds_sync();
+        wave_handoff();
       }
   }
-  wave_lds_sync();
+  wave_handoff();
   uint64_t h = 0;
   for (int32_t k = lane; k < n; k += kWave) {
     row[k] = key[k];
@@ -778,23 +883,24 @@ int asg_build_impl(const float *emb, double *norms, uint16_t *unit_out, const ui
   auto fail = [](hipError_t e) { return record_hip_error(e); };
   hipError_t e;
   const unsigned wb = (unsigned) ((v + 3) / 4), ub = (unsigned) ((v + kSetupTokens - 1) / kSetupTokens);
-  const int tiles = (V + kSimTile - 1) / kSimTile;
-  const int patch_rows = (tiles + kSimPatchRows - 1) / kSimPatchRows;
-  const int patch_cols = (tiles + kSimPatchCols - 1) / kSimPatchCols;
-  const int patches = (patch_rows * patch_cols + 7) / 8 * 8;      // dealt to the 8 XCDs in turn
-  const unsigned sim_grid = (unsigned) (patches * kSimPatchRows * kSimPatchCols);
+  const int nt = (V + kSimTile - 1) / kSimTile;
+  if (nt > 65535) return PCG_ERR_BAD_SHAPE;            // their tiles no longer count in 31 bits
+  const int tiles = (int) ((int64_t) nt * (nt + 1) / 2);
+  // a workgroup for every compute unit, 32 of an XCD on tiles in a row
+  const int run = std::min(32, (tiles + 7) / 8);
+  const unsigned sim_grid = (unsigned) (8 * run);
   if (emb) {
     float *worst = (float *) (totals + 3);
     float *moved = (float *) gid;            // read before gid is written
     asg_normalize_kernel<true><<<wb, 256, 0, stream>>>(emb, V, d, unit_out, norms, moved, worst);
     asg_setup_kernel<true><<<ub, kSetupThreads, 0, stream>>>(V, moved, worst, count, mult, totals);
     asg_similarity_kernel<true><<<sim_grid, kSimThreads, 0, stream>>>(
-        unit_out, V, d, theta, worst, cap, count, cand);
+        unit_out, V, d, theta, worst, cap, tiles, run, count, cand);
     asg_refine_kernel<<<wb, 256, 0, stream>>>(emb, norms, V, d, (double) theta, cap, count, cand);
   } else {
     asg_setup_kernel<false><<<ub, kSetupThreads, 0, stream>>>(V, nullptr, nullptr, count, mult, totals);
     asg_similarity_kernel<false><<<sim_grid, kSimThreads, 0, stream>>>(
-        unit_bf16, V, d, theta, nullptr, cap, count, cand);
+        unit_bf16, V, d, theta, nullptr, cap, tiles, run, count, cand);
   }
   if ((e = hipGetLastError()) != hipSuccess) return fail(e);
   int32_t cap2 = kWave;

@@ -255,6 +255,30 @@ def test_exact_rows_of_a_clustered_recipe_at_full_size():
     assert closest > 1e-12 and n_band > 0
 
 
+@pytest.mark.parametrize("V,d,theta,centres,sigma", [
+    (1, 64, 0.5, 0, 0),            # one token
+    (5889, 64, 0.38, 0, 0),        # 24 x 24 tiles, the last of one row: more than the workgroups that share them
+    (5700, 128, 0.25, 0, 0),       # 23 x 23
+    (8200, 192, 0.2, 0, 0),       # 33 x 33: three rows of patches, the last of one tile
+    (6000, 64, 0.55, 60, 0.6),     # clusters of about 100: more than 64 pairs in a wave's part of a tile
+    (6100, 320, 0.4, 3, 0.9),      # three clusters: tiles whose pairs overflow their queue
+])
+def test_tiles_that_follow_one_another(V, d, theta, centres, sigma):
+    """A workgroup that goes through several tiles, with the loads of one behind the products of the one
+    before and the places of a tile's pairs used a tile later: both forms, whole CSR."""
+    E = embeddings(V, d, V + d) if centres == 0 else embeddings(V, d, V + d, centres, sigma)[0]
+    th = float(np.float32(theta))
+    name = f"asg tiles V={V} d={d}"
+    print(name, flush=True)
+    dev = torch.from_numpy(E).cuda()
+    t = compare_groups(pcg.asg_build_exact(dev, theta), oracle.asg_build_exact(E, th, nthreads=16), name + " exact")
+    assert t.flagged_group == 0 and t.tolerated == 0
+    bits = oracle.asg_normalize(E)
+    t = compare_groups(pcg.asg_build(as_bf16_tensor(bits).cuda(), theta), oracle.asg_build(bits, theta, nthreads=16), name)
+    t.report(name)
+    assert t.tolerated <= max(2, t.flagged_group)
+
+
 @pytest.mark.parametrize("case", range(int(os.environ.get("PCG_RANDOM_CASES", "16"))))
 def test_random_construction_shapes(case):
     """Seeded random shapes of the construction: vocabulary, embedding width, threshold, iid or
