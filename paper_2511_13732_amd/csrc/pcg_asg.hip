@@ -264,7 +264,7 @@ constexpr int kSetupThreads = 256, kSetupTokens = 4 * kSetupThreads;
 
 template <bool EXACT>
 __global__ __launch_bounds__(kSetupThreads) void asg_setup_kernel(int32_t V, const float *moved, float *worst,
-                                                                  int32_t *count, int32_t *mult, int64_t *totals) {
+                                                                  int32_t *count, int64_t *totals) {
   __shared__ float wave_worst[kSetupThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   if (blockIdx.x == 0 && threadIdx.x < 3) totals[threadIdx.x] = 0;
@@ -274,7 +274,6 @@ __global__ __launch_bounds__(kSetupThreads) void asg_setup_kernel(int32_t V, con
     const int32_t t = blockIdx.x * kSetupTokens + i * kSetupThreads + threadIdx.x;
     if (t >= V) continue;
     count[t] = 0;
-    mult[t] = 0;
     if constexpr (EXACT) mine = fmaxf(mine, moved[t]);
   }
   if constexpr (EXACT) {
@@ -826,6 +825,9 @@ __global__ __launch_bounds__(kScanThreads) void asg_scan_kernel(int32_t V, const
   }
 }
 
+// The CSR, and N(t): similarity is symmetric, so the groups that hold t are those of its own members, less the
+// dropped ones.  Every wave counts those of its token (an atomic per member on mult[] took 73 us at
+// 65 536 tokens of 26 members; this 22).
 __global__ __launch_bounds__(256) void asg_compact_kernel(int32_t V, int32_t cap, const int32_t *cand,
                                                           const int32_t *size, const int32_t *keep,
                                                           const int32_t *gid, const int64_t *off,
@@ -836,15 +838,19 @@ __global__ __launch_bounds__(256) void asg_compact_kernel(int32_t V, int32_t cap
   const int32_t t = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
   if (t >= V) return;
   if (t == 0 && lane == 0) row_ptr[totals[0]] = (int32_t) totals[1];
-  if (!keep[t]) return;
+  const bool kept = keep[t] != 0;
   const int32_t n = size[t], g = gid[t];
   const int64_t o = off[t];
   const int32_t *mine = cand + (int64_t) t * cap;
-  for (int32_t k = lane; k < n; k += kWave) {
-    const int32_t m = mine[k];
-    members[o + k] = m;
-    atomicAdd(&mult[m], 1);
+  int32_t holders = 0;                       // uniform
+  for (int32_t k0 = 0; k0 < n; k0 += kWave) {
+    const int32_t k = k0 + lane;
+    const int32_t m = k < n ? mine[k] : 0;
+    if (k < n && kept) members[o + k] = m;
+    holders += (int32_t) __popcll(__ballot(k < n && keep[m] != 0));
   }
+  if (lane == 0) mult[t] = holders;
+  if (!kept) return;
   if (lane == 0) {
     row_ptr[g] = (int32_t) o;
     if (seed_of) seed_of[g] = t;
@@ -893,12 +899,12 @@ int asg_build_impl(const float *emb, double *norms, uint16_t *unit_out, const ui
     float *worst = (float *) (totals + 3);
     float *moved = (float *) gid;            // read before gid is written
     asg_normalize_kernel<true><<<wb, 256, 0, stream>>>(emb, V, d, unit_out, norms, moved, worst);
-    asg_setup_kernel<true><<<ub, kSetupThreads, 0, stream>>>(V, moved, worst, count, mult, totals);
+    asg_setup_kernel<true><<<ub, kSetupThreads, 0, stream>>>(V, moved, worst, count, totals);
     asg_similarity_kernel<true><<<sim_grid, kSimThreads, 0, stream>>>(
         unit_out, V, d, theta, worst, cap, tiles, run, count, cand);
     asg_refine_kernel<<<wb, 256, 0, stream>>>(emb, norms, V, d, (double) theta, cap, count, cand);
   } else {
-    asg_setup_kernel<false><<<ub, kSetupThreads, 0, stream>>>(V, nullptr, nullptr, count, mult, totals);
+    asg_setup_kernel<false><<<ub, kSetupThreads, 0, stream>>>(V, nullptr, nullptr, count, totals);
     asg_similarity_kernel<false><<<sim_grid, kSimThreads, 0, stream>>>(
         unit_bf16, V, d, theta, nullptr, cap, tiles, run, count, cand);
   }
