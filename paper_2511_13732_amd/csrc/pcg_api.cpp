@@ -197,17 +197,21 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
 
   StageTimer tm(stream);
   hipError_t e;
-  tm.begin(kStageStats);
-  if ((e = launch_row_stats(rs, bf16, groups->V, rows, f.c, true, parts, stream)) != hipSuccess)
-    return hip_fail(e);
-  tm.end(kStageStats);
   const int64_t batch = group_probs_batch(groups->V, rows);
   for (int64_t r0 = 0; r0 < rows; r0 += batch) {
     const int32_t n = (int32_t) std::min(batch, rows - r0);
-    if (r0 == 0) tm.begin(kStageTable);
-    if ((e = launch_weights(rs, bf16, *groups, r0, n, f.c, f.c, f.c_lo, parts, table, stream)) !=
-        hipSuccess)
+    const bool by_rows = weights_by_rows(groups->V, n);      // statistics and table in one launch
+    if (r0 == 0) tm.begin(kStageStats);
+    RowSet some = rs;
+    some.base0 = static_cast<const char *>(logits) + r0 * row_stride * (bf16 ? 2 : 4);
+    some.nrows0 = n;
+    if (!by_rows &&
+        (e = launch_row_stats(some, bf16, groups->V, n, f.c, true, parts, stream)) != hipSuccess)
       return hip_fail(e);
+    if (r0 == 0) { tm.end(kStageStats); tm.begin(kStageTable); }
+    e = by_rows ? launch_row_weights(some, bf16, *groups, 0, n, f.c, f.c_lo, f.cd, table, stream)
+                : launch_weights(some, bf16, *groups, 0, n, f.c, f.c, f.c_lo, parts, table, stream);
+    if (e != hipSuccess) return hip_fail(e);
     if (r0 == 0) { tm.end(kStageTable); tm.begin(kStageGather); }
     e = groups->prepared
             ? launch_gather_prepared(*groups, n, table, out + r0 * groups->G, nullptr, nullptr, stream)

@@ -20,12 +20,14 @@
 // A step that is small, or has many sequences of moderate size, runs as one or two kernels instead
 // (small_step, after row_stats where the rows are many): one workgroup per sequence does all of the
 // above with everything in LDS.
-// pcg_group_probs runs row_stats, a weights kernel (q(t) / N(t)) and the same gather;
+// pcg_group_probs runs row_weights, statistics and the table q(t) / N(t) by one workgroup a row, or, for few long
+// rows, row_stats and weights, and then the same gather;
 // pcg_verify_thinning runs row_stats and accept_thin.  pcg_propose runs one kernel, a workgroup per draft row
 // (propose_row), for rows of up to 131 072 logits, row_stats and propose beyond.
 #include "pcg_kernels.h"
 #include "pcg_layout.h"
 
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
@@ -1088,6 +1090,127 @@ __global__ __launch_bounds__(kTableThreads) void weights_kernel(
   for (int k = 0; k < 8; ++k)
     v[k] = (float) ((double) exp_rel(x[k], s.M, c_hi, c_lo) * iz) * __builtin_amdgcn_rcpf(m[k]);
   store8<WIDE>(table + (int64_t) local * V, t, V, v);
+}
+
+// The same from the logits in one launch, a row by one workgroup: what the statistics need of a row, its
+// exponentials, stays in registers until its total is known, and is then scaled and written.  NP: row parts a
+// wave holds (64 exponentials a lane with two; longer rows take row_stats and weights).  A row is read once and its
+// exponentials are formed once, where the two kernels read it twice and form them twice.  256 rows of 65 536
+// bf16 logits 26.0 us against 6.3 + 27.4, fp32 29.4 against 11.7 + 29.5; what is written (67 MB) and read takes 20 at
+// the rate of a copy, and one row, by one compute unit, 17: 20 issue slots an element, of which the
+// exponential and the reciprocal of N(t) take four each.
+constexpr int kRowTableThreads = 1024;
+constexpr int kRowTableParts = 2 * kRowTableThreads / kWave;      // V <= 65 536
+
+// Four consecutive logits, at any element address.
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+template <bool BF16>
+__device__ __forceinline__ void load4_once(const void *row, int32_t t, uint32_t *w) {
+  const char *p = reinterpret_cast<const char *>(row) + (int64_t) t * (BF16 ? 2 : 4);
+  if constexpr (BF16) {
+    const u32x2_any q = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any *>(p));
+    w[0] = q.x; w[1] = q.y;
+  } else {
+    const u32x4 q = load16<true>(p);
+    w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+  }
+}
+
+template <bool BF16, int NP>
+__global__ __launch_bounds__(kRowTableThreads) void row_weights_kernel(RowSet rs, int32_t V, int32_t nparts, int64_t row0,
+                                                                       float c, float c_lo, double cd,
+                                                                       const int32_t *mult, float *table) {
+  constexpr int kPieces = kPartElems / (4 * kWave);      // of four tokens a lane, in a part
+  constexpr int kWords = BF16 ? 2 : 4;
+  __shared__ double part_z[kRowTableParts];
+  __shared__ float part_m[kRowTableParts];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const void *rowp = row_base(rs, row0 + blockIdx.x, BF16);
+  float *out = table + (int64_t) blockIdx.x * V;
+  // Token of piece j of part p in this lane; in the row's last part, pieces that would cross its end are read
+  // where its last four tokens lie, and the `over` first of those belong to the piece before.
+  auto token = [&](int32_t p, int j) { return p * kPartElems + (j * kWave + lane) * 4; };
+  uint32_t w[NP][kPieces][kWords];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int32_t p = wave * NP + q;
+    if (p >= nparts) continue;                           // uniform over the wave
+#pragma unroll
+    for (int j = 0; j < kPieces; ++j) load4_once<BF16>(rowp, min(token(p, j), V - 4), w[q][j]);
+  }
+  float e[NP][kPieces * 4], m[NP];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int32_t p = wave * NP + q;
+    m[q] = -INFINITY;
+    if (p >= nparts) continue;
+    const bool whole = (p + 1) * kPartElems <= V;        // uniform
+#pragma unroll
+    for (int j = 0; j < kPieces; ++j) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float x;
+        if constexpr (BF16) x = __uint_as_float((k & 1) ? (w[q][j][k >> 1] & 0xffff0000u) : (w[q][j][k >> 1] << 16));
+        else x = __uint_as_float(w[q][j][k]);
+        if (!whole && k < token(p, j) - (V - 4)) x = -INFINITY;
+        e[q][4 * j + k] = x;
+      }
+    }
+    float top = e[q][0];
+#pragma unroll
+    for (int k = 1; k < 4 * kPieces; ++k) top = fmaxf(top, e[q][k]);
+    m[q] = wave_max(top);
+    // relative to the part's own maximum; a part without mass has none (its -inf - (-inf) would be NaN)
+    const float ref = m[q] == -INFINITY ? 0.f : m[q];
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 4 * kPieces; ++k) {
+      // exp_rel; of its test for -inf only the low product is left, which for it is an infinity of either sign
+      // or, with c_lo = 0, a NaN
+      const float d = e[q][k] - ref;
+      e[q][k] = __builtin_amdgcn_exp2f(fmaf(d, c, fminf(d * c_lo, FLT_MAX)));
+      s[k & 3] += e[q][k];
+    }
+    const double z = subwave_sum<64>((double) ((s[0] + s[1]) + (s[2] + s[3])));
+    if (lane == kWave - 1) { part_z[p] = z; part_m[p] = m[q]; }
+  }
+  __syncthreads();
+  // every wave: the row's maximum and total, a part per lane
+  const float pm = lane < nparts ? part_m[lane] : -INFINITY;
+  const double pz = lane < nparts ? part_z[lane] : 0.0;
+  const float M = wave_max(pm);
+  const double up = exp2((double) (pm - M) * cd);        // from the part's maximum to the row's
+  const double iz = 1.0 / wave_sum(pz > 0.0 ? pz * up : 0.0);
+  const double scale = up * iz;
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int32_t p = wave * NP + q;
+    if (p >= nparts) continue;
+    // the product with a double, rounded once: two floats hold enough of it
+    const double f = read_lane(scale, p);
+    const float f_hi = (float) f, f_lo = (float) (f - (double) f_hi);
+    const bool whole = (p + 1) * kPartElems <= V;
+#pragma unroll
+    for (int j = 0; j < kPieces; ++j) {
+      const int32_t at = token(p, j), t = min(at, V - 4);
+      f32x4_any v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = fmaf(e[q][4 * j + k], f_hi, e[q][4 * j + k] * f_lo);
+      if (mult) {                                        // uniform
+        const u32x4 n = load16<false>(mult + t);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] *= __builtin_amdgcn_rcpf((float) (int32_t) n[k]);
+      }
+      if (whole || at <= V - 4) {
+        *reinterpret_cast<f32x4_any *>(out + t) = v;
+      } else {
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+          if (k >= at - t) out[t + k] = v[k];
+      }
+    }
+  }
 }
 
 // =============================================================================================
@@ -2515,6 +2638,32 @@ hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int6
   if (bf16) { if (vec) PCG_LAUNCH_WEIGHTS(true, true); else PCG_LAUNCH_WEIGHTS(true, false); }
   else { if (vec) PCG_LAUNCH_WEIGHTS(false, true); else PCG_LAUNCH_WEIGHTS(false, false); }
 #undef PCG_LAUNCH_WEIGHTS
+  return hipGetLastError();
+}
+
+// One compute unit a row, and a launch less, or the row's parts spread over the chip twice.  The call by
+// row_stats and weights, and by rows, in us (V, members, rows; bf16 unless stated):
+//   up to 8 parts:   1000, 8, 18: 14.1 and 10.8;  4096, 8, 32: 14.1 and 11.3, 1152: 44.8 and 37.0;  12 000, 8, 2: 14.0 and
+//                    11.6;  16 384, 8, 128: 19.0 and 16.1, 1152: 93.9 and 78.3
+//   up to 16 parts:  32 768, 32, 2: 14.5 and 16.0, 16: 15.7 and 16.7, fp32 8: 14.8 and 16.4;  30 000, 32, 64: 23.0 and 21.7,
+//                    128: 32.5 and 30.4;  32 768, 32, 128, fp32: 34.6 and 30.9
+//   beyond:          40 000, 32, 64: 26.6 and 30.9, 96: 40.8 and 43.5, 128: 49.9 and 49.9;  65 536, 32, 64: 36.3 and 40.8, 96:
+//                    58.8 and 59.6, 128: 65.8 and 63.8;  fp32, 96: 57.7 and 57.6 at 50 000
+bool weights_by_rows(int32_t V, int32_t nrows) {
+  const int32_t nparts = stats_nparts(V);
+  return V >= 4 && nparts <= kRowTableParts && nrows >= (nparts <= 8 ? 1 : nparts <= 16 ? 64 : 128);
+}
+
+hipError_t launch_row_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int64_t row0, int32_t nrows, float c,
+                              float c_lo, double cd, float *table, hipStream_t stream) {
+  const int32_t nparts = stats_nparts(g.V);
+  const int32_t *mult = g.weights ? nullptr : g.mult;
+  auto launch = [&](auto kernel, int np) {
+    const unsigned waves = (unsigned) ((nparts + np - 1) / np);
+    kernel<<<(unsigned) nrows, waves * kWave, 0, stream>>>(rs, g.V, nparts, row0, c, c_lo, cd, mult, table);
+  };
+  if (nparts * 2 <= kRowTableParts) { if (bf16) launch(row_weights_kernel<true, 1>, 1); else launch(row_weights_kernel<false, 1>, 1); }
+  else { if (bf16) launch(row_weights_kernel<true, 2>, 2); else launch(row_weights_kernel<false, 2>, 2); }
   return hipGetLastError();
 }
 

@@ -375,3 +375,56 @@ def test_a_group_without_mass_is_never_drawn(n, layout):
         assert (out.accept_len == 0).all()
         assert (sizes[g] > 0).all(), f"{int((sizes[g] == 0).sum())} of {B} draws of a group without members"
         assert all(t[b] in mem[g[b] // 16] for b in range(B))
+
+
+# rows shorter than a piece, of one piece, around a part of 2048, and on both sides of the lines between a
+# workgroup per row and two kernels (8 and 16 parts; 64 and 128 rows)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V,n,off,weighted", [
+    (3, 2, 0, False), (4, 1, 1, False), (5, 3, 0, True), (7, 9, 2, False), (2047, 2, 3, False), (2050, 5, 1, True),
+    (6145, 4, 0, False), (16384, 3, 0, False), (16385, 64, 0, False), (20011, 64, 7, True), (32768, 65, 0, False),
+    (32769, 128, 1, False), (36865, 128, 0, False), (65533, 130, 3, False), (65536, 128, 0, True), (65537, 128, 0, False)])
+def test_group_probs_table(V, n, off, weighted, dtype):
+    """Every row against the oracle, and, where few rows take the two kernels, against the same rows a few at a
+    time: masked logits, a row whose second part has no mass, one with a single finite logit."""
+    G = min(V, 700)
+    rp, mem = W.random_groups(V, G, 1, min(V, 12), seed=V)
+    og = oracle_groups(V, rp, mem)
+    w = W.random_weights(og.V, og.members, V) if weighted else None
+    if weighted:
+        og = oracle.with_weights(og, w)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", weights=w)
+    rng = np.random.default_rng([V, n])
+    x = (4.0 * rng.standard_normal((1, n, V))).astype(np.float32)
+    x[0, n // 2][rng.random(V) < 0.2] = -np.inf
+    if V > 2048:
+        x[0, 0, 2048:4096] = -np.inf
+    if n > 2:
+        x[0, 1] = -np.inf
+        x[0, 1, V // 3] = 2.5
+    x = torch.from_numpy(x).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    x = rows_at(x, off)[0]
+    print(f"V={V} n={n} off={off} w={weighted} {dtype}", flush=True)
+    for temperature in (0.9, 0.07):
+        out = pcg.group_probs(dg, x, temperature)
+        assert group_probs_error(out, oracle.group_probs(og, as_oracle_logits(x), temperature)) <= 1e-5
+    few = torch.cat([pcg.group_probs(dg, x[i:i + 20], 0.9) for i in range(0, n, 20)])
+    out = pcg.group_probs(dg, x, 0.9)
+    # a term's argument is at most some 50 in size: 50 ln 2 2^-24 on either side
+    torch.testing.assert_close(out, few, rtol=4.2e-6, atol=1e-30)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_group_probs_table_beside_values_that_are_not_finite(value, dtype):
+    """A row with a NaN or an infinity: the same groups are NaN by rows and by two kernels, the rest equal, and
+    other rows do not notice."""
+    V, n = 20000, 64
+    rp, mem = W.random_groups(V, V, 1, 12, seed=5)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda")
+    x = 4.0 * torch.randn((n, V), device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    x[3, 5000] = value
+    x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    out, few = pcg.group_probs(dg, x, 1.0), pcg.group_probs(dg, x[:20], 1.0)
+    assert torch.isnan(few[3]).any() and not torch.isnan(out[4:]).any()
+    torch.testing.assert_close(out[:20], few, rtol=4.2e-6, atol=1e-30, equal_nan=True)
