@@ -1218,6 +1218,22 @@ __global__ __launch_bounds__(kRowTableThreads) void row_weights_kernel(RowSet rs
 // =============================================================================================
 
 
+// Workgroup id -> (row, chunk).  Workgroups are dealt to the 8 XCDs round-robin by id, and each XCD has to bring
+// the table rows and the membership of its own workgroups into its own L2.  XCD x takes the rows that are
+// x % row_parts modulo row_parts and the chunks that are x / row_parts modulo 8 / row_parts.
+struct GatherMap {
+  int32_t row_parts, chunk_parts;       // their product is 8
+  int32_t chunks_each;                  // of an XCD, at most
+};
+
+// False: the workgroup has none.
+__device__ __forceinline__ bool gather_place(const GatherMap &m, int32_t nrows, int32_t nchunks, int32_t &row, int32_t &chunk) {
+  const int32_t xcd = blockIdx.x & 7, y = blockIdx.x >> 3;
+  row = xcd % m.row_parts + m.row_parts * (y / m.chunks_each);
+  chunk = xcd / m.row_parts + m.chunk_parts * (y % m.chunks_each);
+  return row < nrows && chunk < nchunks;
+}
+
 // One tile of a table row, global memory -> LDS directly: every load of the tile is in flight at once
 // and none passes through a register (a wave's instruction fills 64 pieces in lane order, which is
 // the table's own order).  16 bytes per lane, or 4 where the row or the tile does not start on 16
@@ -1303,12 +1319,46 @@ static int32_t csr_long_size(int64_t nnz, int32_t G, int W) {
 // long after all others are done (one group of 10 000 beside 20 000 of 8, 8 rows: the step took 222 us
 // with 8 lanes a group and one entry a lane, 288 with two and four, 137 with this).  Only its first trip
 // is added; *has_long (in LDS, false before) tells that csr_long_sums has something to do.
+// csr_start asks for the first groups' bounds and entries: ahead of the tile, so that their two trips to memory
+// are over when it has come.
+constexpr int kCsrInFlight = 4;
+template <bool WEIGHTED>
+struct CsrGroups {
+  int32_t beg[kCsrInFlight], end[kCsrInFlight];     // of the groups that are summed next
+  int32_t beg2[kCsrInFlight], end2[kCsrInFlight];   // of those after them
+  u32x4 m[kCsrInFlight], w[WEIGHTED ? kCsrInFlight : 1];      // entries of the next ones
+};
+
+template <int W>
+__device__ __forceinline__ void csr_bounds(int32_t gb, int32_t g_end, const int32_t *row_ptr,
+                                           int32_t (&beg)[kCsrInFlight], int32_t (&end)[kCsrInFlight]) {
+#pragma unroll
+  for (int u = 0; u < kCsrInFlight; ++u) {
+    const int32_t g = min(gb + u * (kGatherThreads / W) + (int32_t) threadIdx.x / W, g_end - 1);
+    beg[u] = row_ptr[g];
+    end[u] = row_ptr[g + 1];
+  }
+}
+
+template <int W, bool WEIGHTED>
+__device__ __forceinline__ void csr_start(CsrGroups<WEIGHTED> &c, int32_t g_begin, int32_t g_end, const int32_t *row_ptr,
+                                          const int32_t *members, int32_t nnz, const float *weights) {
+  csr_bounds<W>(g_begin, g_end, row_ptr, c.beg, c.end);
+  csr_bounds<W>(min(g_begin + kCsrInFlight * (kGatherThreads / W), g_end - 1), g_end, row_ptr, c.beg2, c.end2);
+#pragma unroll
+  for (int u = 0; u < kCsrInFlight; ++u) {
+    const int32_t j = c.beg[u] + 4 * ((int32_t) threadIdx.x % W);
+    c.m[u] = csr_load4(members, j, nnz);
+    if constexpr (WEIGHTED) c.w[u] = csr_load4(weights, j, nnz);
+  }
+}
+
 template <int W, bool WEIGHTED, bool WHOLE, typename Sink>
-__device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t t0, int32_t tl, int32_t g_begin,
-                                         int32_t g_end, const int32_t *row_ptr, const int32_t *members,
-                                         int32_t nnz, const float *weights, int32_t long_size, bool *has_long,
-                                         Sink sink) {
-  constexpr int kInFlight = 4;
+__device__ __forceinline__ void csr_sums(const CsrGroups<WEIGHTED> &start, const float *tab, int32_t zero, int32_t t0,
+                                         int32_t tl, int32_t g_begin, int32_t g_end, const int32_t *row_ptr,
+                                         const int32_t *members, int32_t nnz, const float *weights, int32_t long_size,
+                                         bool *has_long, Sink sink) {
+  constexpr int kInFlight = kCsrInFlight;
   constexpr int nsub = kGatherThreads / W;
   constexpr int kPass = nsub * kInFlight;           // groups per turn of the workgroup
   // At the most lanes a group, second trips are the rule: they are asked for together (5 % of the step at
@@ -1318,14 +1368,7 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
   const int sub = threadIdx.x / W, sl = threadIdx.x % W;
   struct Bounds { int32_t beg[kInFlight], end[kInFlight]; };
   struct Entries { u32x4 m[kInFlight], w[kInFlight]; };
-  auto bounds = [&](int32_t gb, Bounds &r) {
-#pragma unroll
-    for (int u = 0; u < kInFlight; ++u) {
-      const int32_t g = min(gb + u * nsub + sub, g_end - 1);
-      r.beg[u] = row_ptr[g];
-      r.end[u] = row_ptr[g + 1];
-    }
-  };
+  auto bounds = [&](int32_t gb, Bounds &r) { csr_bounds<W>(gb, g_end, row_ptr, r.beg, r.end); };
   auto load4 = [&](const void *p, int32_t j) { return csr_load4(p, j, nnz); };
   auto entries = [&](const Bounds &r, Entries &e) {
 #pragma unroll
@@ -1340,9 +1383,13 @@ __device__ __forceinline__ void csr_sums(const float *tab, int32_t zero, int32_t
   };
   Bounds now, after;
   Entries e;
-  bounds(g_begin, now);
-  entries(now, e);
-  bounds(min(g_begin + kPass, g_end - 1), after);
+#pragma unroll
+  for (int u = 0; u < kInFlight; ++u) {
+    now.beg[u] = start.beg[u]; now.end[u] = start.end[u];
+    after.beg[u] = start.beg2[u]; after.end[u] = start.end2[u];
+    e.m[u] = start.m[u];
+    if constexpr (WEIGHTED) e.w[u] = start.w[u];
+  }
   for (int32_t gb = g_begin; gb < g_end; gb += kPass) {
     Entries en;
     Bounds later;
@@ -1455,9 +1502,7 @@ __device__ __forceinline__ void run_totals(const float *sums, int32_t ng, double
   }
 }
 
-// Workgroup id -> (row, chunk).  Workgroups are dealt to the 8 XCDs round-robin by id, so all
-// chunks of one row are given ids that are equal mod 8: they then share that XCD's L2 for the
-// table row and none other holds it.
+// A workgroup sums a chunk of consecutive groups of one row (gather_place).
 // LDS holds a tile of the table (tile_len tokens, the zero slot behind it) and the chunk's sums
 // (groups_per_chunk, a multiple of 4).  CSUM: only run and chunk totals leave, as from the prepared
 // gather; otherwise every sum.
@@ -1467,23 +1512,23 @@ __device__ __forceinline__ void run_totals(const float *sums, int32_t ng, double
 // locate the draw (V = 65 536, 64 rows: 450 us and 51 us before, 189 and 9 now).  Behind the L2 it is the vector
 // instructions of an entry that count: without the test for the tile where there is one only (WHOLE) and
 // with one comparison for both ends of a group 14.0 -> 12.6 us, V = 32 768, 64 rows 71.8 -> 67.4; with weights
-// 16.0 -> 14.8, V = 65 536, 64 rows 234 -> 223.
+// 16.0 -> 14.8, V = 65 536, 64 rows 234 -> 223.  The first groups' bounds and entries asked for ahead of the tile: 12.2 -> 11.9
+// there; whole calls V = 65 536, 64 rows 218 -> 212, fp32, V = 32 768, 1 to 128 members, 128 rows 450 -> 440, one sequence of
+// V = 1024 (small step) 10.7 -> 10.2, eight of V = 4096 17.1 -> 16.3.
 template <int W, bool CSUM, bool WEIGHTED, bool WHOLE>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
-    int32_t V, int32_t G, int32_t nrows, int32_t nchunks, int32_t groups_per_chunk, int32_t ntiles,
+    int32_t V, int32_t G, int32_t nrows, GatherMap map, int32_t nchunks, int32_t groups_per_chunk, int32_t ntiles,
     int32_t tile_len, int32_t nnz, int32_t long_size, const int32_t *row_ptr, const int32_t *members,
     const float *weights, const float *table, float *out, double *csum, int64_t csum_stride, double *runs) {
   __shared__ __attribute__((aligned(16))) float lds[kTileMax];
   __shared__ bool has_long;
   float *sums = lds, *tab = lds + groups_per_chunk;
-  const int xcd = blockIdx.x & 7;
-  const int y = blockIdx.x >> 3;
-  const int r = xcd + 8 * (y / nchunks);
-  const int chunk = y % nchunks;
-  if (r >= nrows) return;   // whole workgroup leaves together, before any barrier
+  int32_t r, chunk;
+  if (!gather_place(map, nrows, nchunks, r, chunk)) return;   // whole workgroup leaves together, before any barrier
   const float *src = table + (int64_t) r * V;
   const int32_t g_begin = chunk * groups_per_chunk;
   const int32_t ng = min(groups_per_chunk, G - g_begin);
+  CsrGroups<WEIGHTED> groups;
   for (int tile = 0; tile < (WHOLE ? 1 : ntiles); ++tile) {
     const int32_t t0 = tile * tile_len;
     const int32_t tl = min(tile_len, V - t0);
@@ -1493,6 +1538,11 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     // have (3 went to scratch: V = 65 536, 32 members, one sequence 74.5 us instead of 65.8).
     int32_t first = g_begin;
     if constexpr (WEIGHTED && !WHOLE) asm volatile("" : "+s"(first));
+    // Where there is one turn of the workgroup and registers to spare, the entries of its groups are kept for the
+    // next tile (V = 65 536, 32 members, one row: the call 27.0 -> 26.4 us).
+    constexpr bool kKeep = W <= 8 && !WEIGHTED;
+    if (WHOLE || !kKeep || tile == 0 || ng > kCsrInFlight * (kGatherThreads / W))
+      csr_start<W>(groups, first, first + ng, row_ptr, members, nnz, weights);
     stage_tile(tab, src + t0, tl, threadIdx.x);
     if (threadIdx.x == 0) {
       tab[tile_len] = 0.f;
@@ -1500,7 +1550,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);             // vmcnt(0): this wave's part of the tile has landed
     __syncthreads();
-    csr_sums<W, WEIGHTED, WHOLE>(tab, tile_len, t0, tl, first, first + ng, row_ptr, members, nnz, weights,
+    csr_sums<W, WEIGHTED, WHOLE>(groups, tab, tile_len, t0, tl, first, first + ng, row_ptr, members, nnz, weights,
                           long_size, &has_long, [&](int32_t g, float a) {
                             // the same lane in every tile: no other touches this sum meanwhile
                             sums[g - g_begin] = tile > 0 ? sums[g - g_begin] + a : a;
@@ -2204,7 +2254,7 @@ struct SlotStream {
 
 template <bool CSUM, bool WEIGHTED>
 __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
-    int32_t V, int32_t G, int32_t nrows, PreparedView p, const float *__restrict__ table,
+    int32_t V, int32_t G, int32_t nrows, GatherMap map, PreparedView p, const float *__restrict__ table,
     float *__restrict__ out, double *__restrict__ csum, double *__restrict__ runs) {
   const int32_t nchunks = p.nchunks, chunk_groups = p.chunk_groups, ntiles = p.ntiles, tile_len = p.tile_len;
   const int32_t bpc = p.blocks_per_chunk;
@@ -2212,11 +2262,8 @@ __global__ __launch_bounds__(kGatherThreads) void gather_prepared_kernel(
   const float4 *__restrict__ wdata = p.wdata;
   const uint16_t *__restrict__ perm = p.perm;
   __shared__ __attribute__((aligned(16))) float tab[kTileMax];
-  const int xcd = blockIdx.x & 7;
-  const int y = blockIdx.x >> 3;
-  const int r = xcd + 8 * (y / nchunks);
-  const int chunk = y % nchunks;
-  if (r >= nrows) return;   // whole workgroup leaves together, before any barrier
+  int32_t r, chunk;
+  if (!gather_place(map, nrows, nchunks, r, chunk)) return;   // whole workgroup leaves together, before any barrier
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t g0 = chunk * chunk_groups;
@@ -2453,7 +2500,9 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
                      : (uint16_t) 0xFFFFu;
     }
   };
+  CsrGroups<SUMS == kSumsCsrWeighted> groups;
   if constexpr (SUMS <= kSumsPreparedWeighted) ask_chunk(0);
+  else csr_start<kSmallCsrWidth>(groups, 0, G, a.row_ptr, a.members, nnz, a.weights);
   lds_barrier();
   if constexpr (STATS) {
     if (!whole_rows) {
@@ -2509,7 +2558,7 @@ __global__ __launch_bounds__(kAcceptThreads) void small_step_kernel(AcceptArgs a
     __shared__ bool has_long;
     if (threadIdx.x == 0) { tab[V] = 0.f; has_long = false; }
     lds_barrier();
-    csr_sums<kSmallCsrWidth, kWeighted, true>(tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size, &has_long,
+    csr_sums<kSmallCsrWidth, kWeighted, true>(groups, tab, V, 0, V, 0, G, a.row_ptr, a.members, nnz, a.weights, long_size, &has_long,
                            [&](int32_t g, float s) { sums[g] = s; });
     lds_barrier();
     if (has_long)                                   // uniform
@@ -2667,6 +2716,15 @@ hipError_t launch_row_weights(const RowSet &rs, bool bf16, const pcg_groups &g, 
   return hipGetLastError();
 }
 
+// The most chunks of nrows rows that all run at once, on the 32 compute units of each XCD, by some split of rows
+// and chunks over the XCDs (as many as there are compute units in all, rounded up, left the last few for
+// a second turn: the call at V = 20 000, 32 members, 12 rows 30.8 us, now 24.8; 24 rows with weights 41.7, now 31.5).
+static int64_t csr_chunks_at_once(int64_t nrows) {
+  int64_t most = 1;
+  for (int64_t rp = 8; rp >= 1; rp /= 2) most = std::max(most, 8 / rp * (32 / ((nrows + rp - 1) / rp)));
+  return most;
+}
+
 CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max_chunks) {
   CsrShape p;
   // Lanes per group: enough for a group of mean size in one trip of four entries a lane, 2 to 16
@@ -2682,7 +2740,7 @@ CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max
   // Chunks per row: a workgroup for every compute unit, each with at least one pass of groups, at most
   // kMaxChunkGroups and, where that allows it, at most max_chunks.
   const int64_t pass = 4 * (kGatherThreads / p.width);
-  int64_t nchunks = std::min<int64_t>({(256 + nrows - 1) / nrows, max_chunks, (G + pass - 1) / pass});
+  int64_t nchunks = std::min<int64_t>({csr_chunks_at_once(nrows), max_chunks, (G + pass - 1) / pass});
   nchunks = std::max<int64_t>(nchunks, ((int64_t) G + kMaxChunkGroups - 1) / kMaxChunkGroups);
   int64_t gpc = (G + nchunks - 1) / nchunks;
   gpc = (gpc + kRunGroups - 1) / kRunGroups * kRunGroups;
@@ -2695,13 +2753,39 @@ CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max
   return p;
 }
 
+// How the XCDs share rows and chunks.  All chunks of a row on one XCD, unless another split saves each of them 1 MiB
+// to bring in (the rows, which everything waits for, counted twice).  Whole calls, or the gather alone, in us, all
+// on one and split (V, members, rows):
+//   prepared:  65 536, 32, 8: gather 15.8 and 14.3;  16: 15.8 and 14.7;  weights, 16: 26.2 and 20.6, 64: 50.7 and 46.6;
+//              64 (no saving): 25.4 and 27.0;  32 768, 1 to 128, 128 (none): 47.6 and 51.9
+//   CSR:       65 536, 32, 1: call 58.8 and 25.9;  30 000, 100, 8: 49.7 and 38.7;  16 384, 32, 32 (0.5 MiB): gather 12.6 and
+//              12.2, but finalize, which finds a row's totals in its own XCD's L2 if they were formed there, 6.2 and 6.5
+static GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes) {
+  GatherMap best{8, 1, nchunks};
+  int64_t least = INT64_MAX, fewest = INT64_MAX;
+  for (int32_t rp = 8; rp >= 1; rp /= 2) {
+    const int32_t cp = 8 / rp, rows = (nrows + rp - 1) / rp, chunks = (nchunks + cp - 1) / cp;
+    const int64_t bytes = 2 * rows * row_bytes + chunks * chunk_bytes + (rp < 8 ? (int64_t) 1 << 20 : 0);
+    const int64_t turns = ((int64_t) rows * chunks + 31) / 32;         // of the XCD's compute units
+    if (turns < fewest || (turns == fewest && bytes < least)) {
+      fewest = turns;
+      least = bytes;
+      best = GatherMap{rp, cp, chunks};
+    }
+  }
+  return best;
+}
+static unsigned gather_grid(const GatherMap &m, int32_t nrows) {
+  return (unsigned) (8 * ((nrows + m.row_parts - 1) / m.row_parts) * m.chunks_each);
+}
+
 hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, const float *table, float *out,
                          double *csum, int64_t csum_stride, double *runs, hipStream_t stream) {
   if (nrows == 0) return hipSuccess;
-  const int32_t rows8 = (nrows + 7) / 8;
-  const dim3 grid((unsigned) (8 * rows8 * p.nchunks));
+  const GatherMap map = gather_map(nrows, p.nchunks, (int64_t) g.V * 4, g.nnz * (g.weights ? 8 : 4) / p.nchunks);
+  const dim3 grid(gather_grid(map, nrows));
   auto launch = [&](auto kernel) {
-    kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, p.nchunks, p.chunk_groups, p.ntiles, p.tile_len,
+    kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, map, p.nchunks, p.chunk_groups, p.ntiles, p.tile_len,
                                                 (int32_t) g.nnz, csr_long_size(g.nnz, g.G, p.width), g.row_ptr,
                                                 g.members, g.weights, table, out, csum, csum_stride, runs);
   };
@@ -2722,6 +2806,13 @@ hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, 
     default: pick(std::integral_constant<int, 32>{}); break;
   }
   return hipGetLastError();
+}
+
+// Bytes of slots (and weights) that a gather over the prepared layout reads for a row.
+static int64_t prepared_slot_bytes(const pcg_groups &g) {
+  const pcg_prepared &p = *g.prepared_info;
+  const int64_t slots = (p.off_weights ? p.off_weights : p.bytes) - p.off_data;
+  return g.weights ? 3 * slots : slots;
 }
 
 static PreparedView prepared_view(const pcg_groups &g) {
@@ -2745,10 +2836,10 @@ hipError_t launch_gather_prepared(const pcg_groups &g, int32_t nrows, const floa
                                   double *csum, double *runs, hipStream_t stream) {
   if (nrows == 0) return hipSuccess;
   const PreparedView p = prepared_view(g);
-  const int32_t rows8 = (nrows + 7) / 8;
-  const dim3 grid((unsigned) (8 * rows8 * p.nchunks));
+  const GatherMap map = gather_map(nrows, p.nchunks, (int64_t) g.V * 4, prepared_slot_bytes(g) / p.nchunks);
+  const dim3 grid(gather_grid(map, nrows));
   auto launch = [&](auto kernel) {
-    kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, p, table, out, csum, runs);
+    kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, map, p, table, out, csum, runs);
   };
   if (g.weights) {
     if (csum) launch(gather_prepared_kernel<true, true>);

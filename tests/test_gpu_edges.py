@@ -428,3 +428,12 @@ def test_group_probs_table_beside_values_that_are_not_finite(value, dtype):
     out, few = pcg.group_probs(dg, x, 1.0), pcg.group_probs(dg, x[:20], 1.0)
     assert torch.isnan(few[3]).any() and not torch.isnan(out[4:]).any()
     torch.testing.assert_close(out[:20], few, rtol=4.2e-6, atol=1e-30, equal_nan=True)
+
+
+# rows and chunks in every split over the XCDs, numbers of them that divide by nothing
+@pytest.mark.parametrize("V,G,size,B,K,layout,weighted", [
+    (50001, 50001, 40, 1, 1, "csr", False), (41000, 41000, 12, 9, 1, "csr", True), (33000, 33000, 70, 12, 1, "csr", False),
+    (20000, 20000, 30, 33, 1, "csr", False), (9000, 9000, 100, 24, 1, "csr", True), (50000, 50000, 40, 2, 1, "csr", False),
+    (70000, 70000, 20, 9, 1, "prepared", False), (70000, 66000, 20, 17, 1, "prepared", True)])
+def test_rows_and_chunks_over_the_chip(V, G, size, B, K, layout, weighted):
+    check_step(V, G, size, B, K, "bf16", layout=layout, weighted=weighted, chunk_groups=4096, thinning=False)
