@@ -103,8 +103,9 @@ typedef struct {
   /* Optional fast form of the same membership (see pcg_groups_prepare_host): the blob
    * uploaded to the DEVICE and its HOST descriptor.  Both NULL = use the CSR directly, which
    * gives the same results but re-reads the 4-byte member ids from L2 for every row: at
-   * V = G = 65 536 with 32-member groups and 64 sequences a step takes about 0.25 ms from the
-   * CSR against about 0.07 ms from the prepared form. */
+   * V = G = 65 536 with 32-member groups and 64 sequences a step takes about 0.21 ms from the
+   * CSR against about 0.07 ms from the prepared form.  (For a few rows the library may read the CSR
+   * although the prepared form is there, where that is faster.) */
   const void *prepared;
   const pcg_prepared *prepared_info;
   /* Optional reverse index token -> groups (the paper's S(t); see pcg_groups_reverse_host),

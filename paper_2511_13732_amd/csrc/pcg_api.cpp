@@ -213,10 +213,10 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
                 : launch_weights(some, bf16, *groups, 0, n, f.c, f.c, f.c_lo, parts, table, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (r0 == 0) { tm.end(kStageTable); tm.begin(kStageGather); }
-    e = groups->prepared
+    const CsrShape cut = csr_shape(groups->V, groups->G, groups->nnz, n, 256);
+    e = groups->prepared && !csr_is_faster(*groups, cut)
             ? launch_gather_prepared(*groups, n, table, out + r0 * groups->G, nullptr, nullptr, stream)
-            : launch_gather(*groups, csr_shape(groups->V, groups->G, groups->nnz, n, 256), n, table,
-                            out + r0 * groups->G, nullptr, 0, nullptr, stream);
+            : launch_gather(*groups, cut, n, table, out + r0 * groups->G, nullptr, 0, nullptr, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (r0 == 0) tm.end(kStageGather);
   }
@@ -436,16 +436,16 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
   }
   int32_t nchunks, chunk_groups;
   int64_t csum_stride;
-  if (groups->prepared) {
+  // The CSR gather may cut a row finer than csum has room for; its chunk totals then go where the
+  // sequence's row parts were, which nothing reads after the accept scan.
+  const int64_t room = (groups->G + kChunkStep - 1) / kChunkStep;
+  const int64_t parts_room = (2 * K + 1) * (int64_t) nparts * (sizeof(StatPart) / sizeof(double));
+  const CsrShape cut = csr_shape(V, groups->G, groups->nnz, B, std::max(room, parts_room));
+  if (groups->prepared && !csr_is_faster(*groups, cut)) {
     csum_stride = nchunks = groups->prepared_info->nchunks;
     chunk_groups = groups->prepared_info->chunk_groups;
     e = launch_gather_prepared(*groups, B, table, R, csum, runs, stream);
   } else {
-    // The CSR gather may cut a row finer than csum has room for; its chunk totals then go where the
-    // sequence's row parts were, which nothing reads after the accept scan.
-    const int64_t room = (groups->G + kChunkStep - 1) / kChunkStep;
-    const int64_t parts_room = (2 * K + 1) * (int64_t) nparts * (sizeof(StatPart) / sizeof(double));
-    const CsrShape cut = csr_shape(V, groups->G, groups->nnz, B, std::max(room, parts_room));
     nchunks = cut.nchunks;
     chunk_groups = cut.chunk_groups;
     csum_stride = nchunks <= room ? room : parts_room;

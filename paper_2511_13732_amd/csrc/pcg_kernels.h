@@ -57,6 +57,8 @@ struct CsrShape {
   int32_t width, nchunks, chunk_groups, ntiles, tile_len;
 };
 CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max_chunks);
+// Whether a gather so cut is ahead of one from the prepared layout of the same groups.
+bool csr_is_faster(const pcg_groups &g, const CsrShape &p);
 
 // With csum (and runs): no sums, only the clamped totals per chunk (row r's at csum + r * csum_stride)
 // and per run of kRunGroups groups; otherwise every sum to out.

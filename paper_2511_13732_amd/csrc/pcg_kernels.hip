@@ -2779,6 +2779,28 @@ static unsigned gather_grid(const GatherMap &m, int32_t nrows) {
   return (unsigned) (8 * ((nrows + m.row_parts - 1) / m.row_parts) * m.chunks_each);
 }
 
+// Few rows leave most of the chip to chunks of at least 4096 groups, and those who have one wait for their slots from
+// memory; from the CSR a row is cut as fine as there are compute units.  Whole calls, prepared and CSR, in us
+// (V, members, sequences; turns: of the CSR's workgroups):
+//   one tile, one turn:   20 000, 8, 1: 21.5 and 20.7, 24: 25.2 and 24.4;  32, 1: 23.4 and 21.3, 6: 25.0 and 22.5;
+//                         100, 1: 31.8 and 26.2;  40 000, 32, 2: 25.0 and 22.7;  30 000, 1 to 128, 1: 31.6 and 25.3
+//   two:                  20 000, 32, 7: 25.0 and 23.8, 12: 26.1 and 24.8;  100, 6: 33.2 and 29.4;  30 000, 1 to 128, 3: 32.6 and
+//                         30.6;  but with fewer lanes a group and sizes that differ, 1 to 40, 5: 26.1 and 27.0;  20 000, 8,
+//                         32: 25.8 and 26.0
+//   more:                 20 000, 32, 16: 26.7 and 27.2;  100, 12: 34.7 and 36.6
+//   weights:              20 000, 12, 8 (one): 24.0 and 22.4, 16 (two): 25.7 and 25.5;  32, 24 (four): 33.1 and 31.5;  33 000, 32,
+//                         20 (six): 35.0 and 37.0;  80, 8 (five): 47.3 and 44.4, 16 (nine): 49.3 and 59.0
+//   two tiles, one turn:  65 536, 32, 1: 27.9 and 26.4, 2: 28.4 and 27.4;  50 000, 32, 2: 27.5 and 26.1;  8, 2: 25.9 and 26.3;  100, 1:
+//                         37.1 and 38.9;  weights, 32, 4: 34.3 and 35.7
+bool csr_is_faster(const pcg_groups &g, const CsrShape &p) {
+  const int32_t turn = kCsrInFlight * (kGatherThreads / p.width), turns = (p.chunk_groups + turn - 1) / turn;
+  if (g.G <= kScanGroups) return false;                // one chunk, whose totals finalize reads at once
+  if (p.ntiles == 2) return p.width == 8 && !g.weights && turns == 1;
+  const int32_t most = g.weights ? (p.width >= 16 ? 5 : p.width == 8 ? 4 : 1)
+                                 : (p.width >= 16 || (p.width == 8 && even_size(g) > 0) ? 2 : 1);
+  return p.ntiles == 1 && turns <= most;
+}
+
 hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, const float *table, float *out,
                          double *csum, int64_t csum_stride, double *runs, hipStream_t stream) {
   if (nrows == 0) return hipSuccess;

@@ -437,3 +437,30 @@ def test_group_probs_table_beside_values_that_are_not_finite(value, dtype):
     (70000, 70000, 20, 9, 1, "prepared", False), (70000, 66000, 20, 17, 1, "prepared", True)])
 def test_rows_and_chunks_over_the_chip(V, G, size, B, K, layout, weighted):
     check_step(V, G, size, B, K, "bf16", layout=layout, weighted=weighted, chunk_groups=4096, thinning=False)
+
+
+# few rows of a prepared membership: from the CSR, one turn and two of its workgroups, one tile and two, and on the
+# other side of those lines
+@pytest.mark.parametrize("V,G,size,B,K,layout,weighted", [
+    (17000, 17000, 8, 1, 2, "prepared", False), (17001, 17003, 30, 3, 2, "prepared", False),
+    (20000, 20000, 30, 12, 2, "prepared", False), (20011, 20011, 90, 6, 1, "prepared", False),
+    (20011, 20011, 90, 7, 1, "prepared", False), (33000, 33000, 20, 5, 2, "prepared", True),
+    (33001, 33001, 50, 20, 1, "prepared", True), (17000, 17000, 10, 17, 1, "prepared", True),
+    (50001, 50001, 40, 1, 1, "prepared", False), (50000, 50000, 40, 2, 1, "prepared", False),
+    (41000, 41000, 12, 3, 1, "prepared", False), (45000, 45000, 34, 1, 2, "prepared", True),
+    (30000, 4096, 9, 2, 2, "prepared", False), (30000, 33, 40, 2, 2, "prepared", False)])
+def test_few_rows(V, G, size, B, K, layout, weighted):
+    check_step(V, G, size, B, K, "bf16", layout=layout, weighted=weighted, chunk_groups=4096, thinning=False)
+
+
+@pytest.mark.parametrize("V,size,n", [(17000, 32, 12), (20000, 32, 16), (45000, 20, 2), (45000, 20, 3), (20000, 60, 5)])
+def test_few_rows_of_groups_of_one_size(V, size, n):
+    """The same lines where all groups are of one size: every sum by the prepared layout's handle and by the CSR's."""
+    rp, mem = W.random_groups(V, V, size, size, seed=V)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", chunk_groups=4096)
+    og = oracle_groups(V, rp, mem)
+    x = 4.0 * torch.randn((n, V), device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    print(f"V={V} size={size} n={n}", flush=True)
+    ref = oracle.group_probs(og, as_oracle_logits(x.cpu()), 0.9)
+    for g in (dg, dg.without_prepared()):
+        assert group_probs_error(pcg.group_probs(g, x, 0.9), ref) <= 1e-5
