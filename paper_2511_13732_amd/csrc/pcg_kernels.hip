@@ -807,10 +807,9 @@ __device__ int32_t draw_token(const PartMasses<N> &pm, uint32_t *redo, const voi
   const int32_t e0 = p * kPartElems + lane * 32;
   Logits32<BF16> raw;
   load32<BF16>(trow, e0, V, raw);
-  // the same expression row_stats summed
-  auto mass = [&](float x) -> float {
-    return x > -INFINITY ? __builtin_amdgcn_exp2f(fmaf(x, c, -t)) : 0.f;
-  };
+  // the same expression row_stats summed; the part has mass, so t is finite and no logit a NaN, and -inf gives 0 without
+  // a test (two of its instructions an element: thinning, V = 65 536, 64 sequences 35.8 -> 35.5 us the call)
+  auto mass = [&](float x) -> float { return __builtin_amdgcn_exp2f(fmaf(x, c, -t)); };
   double s = 0.0;
 #pragma unroll
   for (int k = 0; k < 32; k += 2) s += (double) mass(raw.get(k)) + (double) mass(raw.get(k + 1));
