@@ -633,8 +633,15 @@ int pcg_verify_thinning(const pcg_groups *groups, const void *target_logits,
   StageTimer tm(stream);
   hipError_t e;
   tm.begin(kStageStats);
-  // cached pass: every trial is a chain of small reads into the same rows
-  if ((e = launch_row_stats(rs, bf16, V, rows, f.c, false, parts, stream, &pa)) != hipSuccess) return hip_fail(e);
+  // Cached pass: every trial is a chain of small reads into the same rows.  Streamed for large batches of bf16 logits,
+  // of which a trial reads half the bytes again.  Whole calls in us, cached and streamed, on logits last touched
+  // 430 MB or more ago, and repeated on the same:
+  //   bf16, V = 65 536, K = 8:  111 MB 33.8 and 33.5, 31.4 and 29.7;  143 MB 39.3 and 38.3, 35.5 and 34.8;  178 MB 45.1 and
+  //             43.2, 40.5 and 40.5
+  //   fp32, V = 32 768, K = 6:  109 MB 34.1 and 34.9, 31.0 and 30.4;  179 MB 50.1 and 49.7, 41.4 and 42.7;  218 MB 56.5 and
+  //             55.0, 54.2 and 56.0;  V = 65 536, K = 8:  160 MB 47.6 and 48.2, 39.6 and 38.4
+  const bool streaming = bf16 && rows * V * 2 > kStreamBytes;
+  if ((e = launch_row_stats(rs, bf16, V, rows, f.c, streaming, parts, stream, &pa)) != hipSuccess) return hip_fail(e);
   tm.end(kStageStats);
   tm.begin(kStageThin);
   if ((e = launch_accept_thin(aa, bf16, B, groups->tok_ptr, groups->tok_groups,
