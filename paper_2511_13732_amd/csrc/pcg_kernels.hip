@@ -1218,18 +1218,19 @@ __global__ __launch_bounds__(kRowTableThreads) void row_weights_kernel(RowSet rs
 
 
 // Workgroup id -> (row, chunk).  Workgroups are dealt to the 8 XCDs round-robin by id, and each XCD has to bring
-// the table rows and the membership of its own workgroups into its own L2.  XCD x takes the rows that are
-// x % row_parts modulo row_parts and the chunks that are x / row_parts modulo 8 / row_parts.
+// the table rows and the membership of its own workgroups into its own L2.  With row_parts = 2^row_shift, XCD x
+// takes the rows that are x % row_parts modulo row_parts and the chunks that are x / row_parts modulo 8 / row_parts.
+// (A shift: a division is some 30 dependent instructions ahead of a workgroup's first load, and one is left.)
 struct GatherMap {
-  int32_t row_parts, chunk_parts;       // their product is 8
+  int32_t row_shift;
   int32_t chunks_each;                  // of an XCD, at most
 };
 
 // False: the workgroup has none.
 __device__ __forceinline__ bool gather_place(const GatherMap &m, int32_t nrows, int32_t nchunks, int32_t &row, int32_t &chunk) {
-  const int32_t xcd = blockIdx.x & 7, y = blockIdx.x >> 3;
-  row = xcd % m.row_parts + m.row_parts * (y / m.chunks_each);
-  chunk = xcd / m.row_parts + m.chunk_parts * (y % m.chunks_each);
+  const uint32_t xcd = blockIdx.x & 7, y = blockIdx.x >> 3, turn = y / (uint32_t) m.chunks_each;
+  row = (int32_t) ((xcd & ((1u << m.row_shift) - 1)) + (turn << m.row_shift));
+  chunk = (int32_t) ((xcd >> m.row_shift) + ((y - turn * (uint32_t) m.chunks_each) << (3 - m.row_shift)));
   return row < nrows && chunk < nchunks;
 }
 
@@ -2760,22 +2761,22 @@ CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max
 //   CSR:       65 536, 32, 1: call 58.8 and 25.9;  30 000, 100, 8: 49.7 and 38.7;  16 384, 32, 32 (0.5 MiB): gather 12.6 and
 //              12.2, but finalize, which finds a row's totals in its own XCD's L2 if they were formed there, 6.2 and 6.5
 static GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes) {
-  GatherMap best{8, 1, nchunks};
+  GatherMap best{3, nchunks};
   int64_t least = INT64_MAX, fewest = INT64_MAX;
-  for (int32_t rp = 8; rp >= 1; rp /= 2) {
-    const int32_t cp = 8 / rp, rows = (nrows + rp - 1) / rp, chunks = (nchunks + cp - 1) / cp;
+  for (int32_t shift = 3; shift >= 0; --shift) {
+    const int32_t rp = 1 << shift, cp = 8 / rp, rows = (nrows + rp - 1) / rp, chunks = (nchunks + cp - 1) / cp;
     const int64_t bytes = 2 * rows * row_bytes + chunks * chunk_bytes + (rp < 8 ? (int64_t) 1 << 20 : 0);
     const int64_t turns = ((int64_t) rows * chunks + 31) / 32;         // of the XCD's compute units
     if (turns < fewest || (turns == fewest && bytes < least)) {
       fewest = turns;
       least = bytes;
-      best = GatherMap{rp, cp, chunks};
+      best = GatherMap{shift, chunks};
     }
   }
   return best;
 }
 static unsigned gather_grid(const GatherMap &m, int32_t nrows) {
-  return (unsigned) (8 * ((nrows + m.row_parts - 1) / m.row_parts) * m.chunks_each);
+  return 8u * (((unsigned) nrows + (1u << m.row_shift) - 1) >> m.row_shift) * (unsigned) m.chunks_each;
 }
 
 // Few rows leave most of the chip to chunks of at least 4096 groups, and those who have one wait for their slots from
