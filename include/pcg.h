@@ -375,10 +375,10 @@ size_t pcg_asg_build_workspace_bytes(int32_t V, int32_t cap);
 /*
  * The same groups by Eq. (1) exactly as written: G(t) = every v with cos(emb[t], emb[v]) > theta,
  * the cosine of the float32 embeddings themselves in double (dot product and both norms, one
- * division), and t itself.  The bf16 contraction of pcg_asg_build serves as a filter: a pair
- * whose rounded similarity lies within 2 e + e^2 + d 2^-23 (1 + e)^2 + 2^-20 of theta, e the farthest
- * that rounding to bfloat16 has moved any of the unit vectors (measured; 2^-8 at most, typically
- * 1.6e-3: the band is how far rounding and summing in fp32 can move it), is decided by the double-precision
+ * division), and t itself.  The contraction of pcg_asg_build, on unit vectors rounded to fp16, serves as a
+ * filter: a pair whose rounded similarity lies within 2 e + e^2 + d 2^-23 (1 + e)^2 + 2^-20 of theta, e the
+ * farthest that rounding has moved any of the unit vectors (measured; typically 2.1e-4: the band is how
+ * far rounding and summing in fp32 can move it), is decided by the double-precision
  * cosine, every other pair by the rounded one.  Outputs, order of the groups, waiting for the
  * stream and PCG_ERR_CAPACITY as for pcg_asg_build, except that cap must hold every candidate
  * of a group (the pairs above theta minus that band) while it is collected; *out_max_size is

@@ -627,7 +627,7 @@ def asg_build(unit: torch.Tensor, theta: float, cap: int = 256,
 def asg_build_exact(emb: torch.Tensor, theta: float, cap: int = 256,
                     members_capacity: Optional[int] = None) -> AsgGroups:
     """The distinct similarity groups of Eq. (1) from the float32 embeddings [V, d] themselves:
-    the cosine is decided in double wherever the bfloat16 contraction cannot.  Same outputs and
+    the cosine is decided in double wherever the contraction of rounded unit vectors cannot.  Same outputs and
     retries as asg_build."""
     assert emb.dim() == 2 and emb.dtype == torch.float32 and emb.is_contiguous()
     V, d = emb.shape
