@@ -198,6 +198,10 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
   StageTimer tm(stream);
   hipError_t e;
   const int64_t batch = group_probs_batch(groups->V, rows);
+  // One order of summation for every row of the call, that of its first batch (the table's entries do not depend on it):
+  // equal rows give equal sums, to the bit.
+  const CsrShape first = csr_shape(groups->V, groups->G, groups->nnz, batch, 256);
+  const bool from_csr = !groups->prepared || csr_is_faster(*groups, first);
   for (int64_t r0 = 0; r0 < rows; r0 += batch) {
     const int32_t n = (int32_t) std::min(batch, rows - r0);
     const bool by_rows = weights_by_rows(groups->V, n);      // statistics and table in one launch
@@ -206,17 +210,19 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
     some.base0 = static_cast<const char *>(logits) + r0 * row_stride * (bf16 ? 2 : 4);
     some.nrows0 = n;
     if (!by_rows &&
-        (e = launch_row_stats(some, bf16, groups->V, n, f.c, true, parts, stream)) != hipSuccess)
+        (e = launch_weights_parts(some, bf16, groups->V, n, f.c, f.c_lo, parts, stream)) != hipSuccess)
       return hip_fail(e);
     if (r0 == 0) { tm.end(kStageStats); tm.begin(kStageTable); }
-    e = by_rows ? launch_row_weights(some, bf16, *groups, 0, n, f.c, f.c_lo, f.cd, table, stream)
-                : launch_weights(some, bf16, *groups, 0, n, f.c, f.c, f.c_lo, parts, table, stream);
+    e = by_rows ? launch_row_weights(some, bf16, *groups, n, f.c, f.c_lo, f.cd, table, stream)
+                : launch_weights(some, bf16, *groups, n, f.c, f.c_lo, f.cd, parts, table, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (r0 == 0) { tm.end(kStageTable); tm.begin(kStageGather); }
-    const CsrShape cut = csr_shape(groups->V, groups->G, groups->nnz, n, 256);
-    e = groups->prepared && !csr_is_faster(*groups, cut)
-            ? launch_gather_prepared(*groups, n, table, out + r0 * groups->G, nullptr, nullptr, stream)
-            : launch_gather(*groups, cut, n, table, out + r0 * groups->G, nullptr, 0, nullptr, stream);
+    CsrShape cut = csr_shape(groups->V, groups->G, groups->nnz, n, 256);      // no larger chunks than `first`
+    cut.width = first.width;
+    cut.ntiles = first.ntiles;
+    cut.tile_len = first.tile_len;
+    e = from_csr ? launch_gather(*groups, cut, n, table, out + r0 * groups->G, nullptr, 0, nullptr, stream)
+                 : launch_gather_prepared(*groups, n, table, out + r0 * groups->G, nullptr, nullptr, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (r0 == 0) tm.end(kStageGather);
   }

@@ -42,14 +42,15 @@ hipError_t launch_propose(const RowSet &rs, bool bf16, int32_t V, int32_t K, int
                           int32_t *prop_tokens, int32_t *prop_groups, pcg_diag *diag,
                           hipStream_t stream);
 
-hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int64_t row0,
-                          int32_t nrows, float c, float c_hi, float c_lo, const StatPart *parts,
-                          float *table, hipStream_t stream);
-
-// The table of pcg_group_probs from the logits in one launch, where weights_by_rows says so.
+// The table of pcg_group_probs in two launches, the statistics of every part ahead of it, or, where weights_by_rows says
+// so, from the logits in one.  The same bits.
+hipError_t launch_weights_parts(const RowSet &rs, bool bf16, int32_t V, int32_t nrows, float c, float c_lo, StatPart *parts,
+                                hipStream_t stream);
+hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int32_t nrows, float c, float c_lo, double cd,
+                          const StatPart *parts, float *table, hipStream_t stream);
 bool weights_by_rows(int32_t V, int32_t nrows);
-hipError_t launch_row_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int64_t row0, int32_t nrows, float c,
-                              float c_lo, double cd, float *table, hipStream_t stream);
+hipError_t launch_row_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int32_t nrows, float c, float c_lo, double cd,
+                              float *table, hipStream_t stream);
 
 // How the CSR gather cuts `nrows` rows: lanes per group, chunks of consecutive groups (a multiple of
 // kRunGroups; no more of them than max_chunks or ceil(G / kMaxChunkGroups)), tiles of the vocabulary.

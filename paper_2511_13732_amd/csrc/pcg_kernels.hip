@@ -21,7 +21,7 @@
 // (small_step, after row_stats where the rows are many): one workgroup per sequence does all of the
 // above with everything in LDS.
 // pcg_group_probs runs row_weights, statistics and the table q(t) / N(t) by one workgroup a row, or, for few long
-// rows, row_stats and weights, and then the same gather;
+// rows, weights_parts and weights, and then the same gather;
 // pcg_verify_thinning runs row_stats and accept_thin.  pcg_propose runs one kernel, a workgroup per draft row
 // (propose_row), for rows of up to 131 072 logits, row_stats and propose beyond.
 #include "pcg_kernels.h"
@@ -286,27 +286,6 @@ __device__ __forceinline__ void wave_handoff() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Merge the parts of one row inside a wave: every lane returns the row's (M, Z).
-// c must be the same fp32 factor row_stats used, so that 2^(xc-t) * 2^(t-Mc) = 2^((x-M)c).
-__device__ __forceinline__ RowStat merge_row(const StatPart *parts, int64_t row, int32_t nparts,
-                                             float c, int lane) {
-  const StatPart *rp = parts + row * nparts;
-  float M = -INFINITY;
-  for (int32_t k = lane; k < nparts; k += kWave) M = fmaxf(M, rp[k].m);
-  M = wave_max(M);
-  double Z = 0.0;
-  for (int32_t k = lane; k < nparts; k += kWave) {
-    StatPart sp = rp[k];
-    if (sp.z > 0.0) Z += sp.z * exp2((double) sp.t - (double) M * (double) c);
-  }
-  Z = wave_sum(Z);
-  RowStat r;
-  r.Z = Z;
-  r.M = M;
-  r.pad = 0.f;
-  return r;
 }
 
 // =============================================================================================
@@ -1057,43 +1036,143 @@ __global__ __launch_bounds__(kProposeThreads) void propose_row_kernel(
 }
 
 // =============================================================================================
-// weights: the per-token table of pcg_group_probs.
+// weights: the per-token table of pcg_group_probs, q(t) / N(t), or q(t) with general weights.
 // =============================================================================================
 
-constexpr int kTableThreads = 256;
-constexpr int kTableTokens = kTableThreads * kTokensPerThread;    // tokens per workgroup
+// A row goes in parts of kPartElems tokens, a wave's each: exponentials relative to the part's own maximum, their sum, and
+// once the row's total is known the exponentials times the part's scale.  Either a workgroup holds a whole row
+// (row_weights_kernel), or a row's parts are spread over the chip twice (weights_parts_kernel, weights_kernel).  Both take every
+// step by the functions here, element by element and sum by sum on the same lanes: a row's table is the same to
+// the bit whichever kernels form it, so that how many rows come with it does not matter.
+constexpr int kTablePieces = kPartElems / (4 * kWave);      // of four tokens a lane, in a part
 
-// group_probs: w[r][t] = softmax(row r)[t] / N(t) for a batch of rows starting at row0.
-template <bool BF16, bool WIDE>
-__global__ __launch_bounds__(kTableThreads) void weights_kernel(
-    RowSet rs, int32_t V, int32_t nparts, int32_t nct, int64_t row0, float c, float c_hi,
-    float c_lo, const StatPart *parts, const int32_t *mult, float *table) {
-  __shared__ RowStat sh;
-  const int32_t local = blockIdx.x / nct;
-  const int64_t row = row0 + local;
-  if (threadIdx.x < kWave) {
-    RowStat s = merge_row(parts, row, nparts, c, threadIdx.x);
-    if (threadIdx.x == 0) sh = s;
-  }
-  __syncthreads();
-  const int32_t at = (blockIdx.x % nct) * kTableTokens + threadIdx.x * kTokensPerThread;
-  if (at >= V) return;
-  const int32_t t = slice_start<WIDE>(at, V);
-  const RowStat s = sh;
-  const double iz = 1.0 / s.Z;
-  const void *rowp = row_base(rs, row, BF16);
-  float x[8], m[8], v[8];
-  load8<BF16, WIDE>(rowp, t, V, x);
-  load8_mult<WIDE>(mult, t, V, m);
+// First token of piece j of part p in this lane; in the row's last part, pieces that would cross its end are read
+// where its last four tokens lie, and the first of those belong to the piece before.
+__device__ __forceinline__ int32_t piece_token(int32_t p, int j, int lane) { return p * kPartElems + (j * kWave + lane) * 4; }
+
+// Four consecutive logits as they lie in memory, at any element address.  WIDE: V >= 4.
+template <bool BF16>
+struct Piece { uint32_t w[BF16 ? 2 : 4]; };
+
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+template <bool BF16, bool WIDE, bool STREAM>
+__device__ __forceinline__ Piece<BF16> load_piece(const void *row, int32_t t) {
+  Piece<BF16> r;
+  if constexpr (!WIDE) {                                   // t + k < 0: no token, not read
 #pragma unroll
-  for (int k = 0; k < 8; ++k)
-    v[k] = (float) ((double) exp_rel(x[k], s.M, c_hi, c_lo) * iz) * __builtin_amdgcn_rcpf(m[k]);
-  store8<WIDE>(table + (int64_t) local * V, t, V, v);
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (BF16) {
+        const uint32_t b = t + k >= 0 ? reinterpret_cast<const uint16_t *>(row)[t + k] : 0u;
+        if (k & 1) r.w[k >> 1] |= b << 16; else r.w[k >> 1] = b;
+      } else {
+        r.w[k] = t + k >= 0 ? reinterpret_cast<const uint32_t *>(row)[t + k] : 0u;
+      }
+    }
+  } else if constexpr (BF16) {
+    const u32x2_any *src = reinterpret_cast<const u32x2_any *>(reinterpret_cast<const uint16_t *>(row) + t);
+    const u32x2_any q = STREAM ? __builtin_nontemporal_load(src) : *src;
+    r.w[0] = q.x; r.w[1] = q.y;
+  } else {
+    const u32x4 q = load16<STREAM>(reinterpret_cast<const float *>(row) + t);
+    r.w[0] = q.x; r.w[1] = q.y; r.w[2] = q.z; r.w[3] = q.w;
+  }
+  return r;
 }
 
-// The same from the logits in one launch, a row by one workgroup: what the statistics need of a row, its
-// exponentials, stays in registers until its total is known, and is then scaled and written.  NP: row parts a
-// wave holds (64 exponentials a lane with two; longer rows take row_stats and weights).  A row is read once and its
+// N pieces of part p from piece j0 on, all asked for at once.  V >= 4.
+template <bool BF16, bool STREAM, int N>
+__device__ __forceinline__ void load_pieces(Piece<BF16> (&w)[N], const void *row, int32_t p, int j0, int32_t V, int lane) {
+  if ((p + 1) * kPartElems <= V) {                         // uniform
+    const void *src = elem_ptr(row, piece_token(p, j0, lane), BF16);
+#pragma unroll
+    for (int j = 0; j < N; ++j) w[j] = load_piece<BF16, true, STREAM>(src, 4 * kWave * j);
+  } else {
+#pragma unroll
+    for (int j = 0; j < N; ++j) w[j] = load_piece<BF16, true, STREAM>(row, min(piece_token(p, j0 + j, lane), V - 4));
+  }
+}
+
+// The logits of N pieces of part p from piece j0 on; -inf for what belongs to the piece before.
+template <bool BF16, int N>
+__device__ __forceinline__ void piece_logits(const Piece<BF16> (&w)[N], int32_t p, int j0, int32_t V, int lane, float (&x)[4 * N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (BF16) x[4 * j + k] = __uint_as_float((k & 1) ? (w[j].w[k >> 1] & 0xffff0000u) : (w[j].w[k >> 1] << 16));
+      else x[4 * j + k] = __uint_as_float(w[j].w[k]);
+    }
+  if ((p + 1) * kPartElems > V) {                          // uniform
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int32_t over = piece_token(p, j0 + j, lane) - (V - 4);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < over) x[4 * j + k] = -INFINITY;
+    }
+  }
+}
+
+// The exponential of a logit relative to the maximum of its part: exp_rel; of its test for -inf only the low product is
+// left, which for it is an infinity of either sign or, with c_lo = 0, a NaN.  A part without mass has no maximum (its
+// -inf - (-inf) would be NaN).
+__device__ __forceinline__ float part_exp(float x, float m, float c, float c_lo) {
+  const float d = x - (m == -INFINITY ? 0.f : m);
+  return __builtin_amdgcn_exp2f(fmaf(d, c, fminf(d * c_lo, FLT_MAX)));
+}
+
+// Statistics of a part and, in e, its exponentials.  The maximum is every lane's, the sum the last lane's.
+template <bool BF16>
+__device__ __forceinline__ double part_exponentials(const Piece<BF16> (&w)[kTablePieces], int32_t p, int32_t V, int lane, float c,
+                                                    float c_lo, float (&e)[4 * kTablePieces], float &m) {
+  piece_logits<BF16>(w, p, 0, V, lane, e);
+  float top = e[0];
+#pragma unroll
+  for (int k = 1; k < 4 * kTablePieces; ++k) top = fmaxf(top, e[k]);
+  m = wave_max(top);
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 4 * kTablePieces; ++k) {
+    e[k] = part_exp(e[k], m, c, c_lo);
+    s[k & 3] += e[k];
+  }
+  return subwave_sum<64>((double) ((s[0] + s[1]) + (s[2] + s[3])));
+}
+
+// N(t) of a piece.
+template <bool WIDE>
+__device__ __forceinline__ u32x4 load_mult(const int32_t *mult, int32_t at, int32_t V) {
+  const int32_t t = min(at, V - 4);
+  if constexpr (WIDE) return load16<false>(mult + t);
+  u32x4 n;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) n[k] = t + k >= 0 ? (uint32_t) mult[t + k] : 1u;
+  return n;
+}
+
+// Four entries of the table from their exponentials: the product with the scale, a double, rounded once (two floats hold
+// enough of it), and, if divide, with 1 / N(t).
+__device__ __forceinline__ void store_piece(float *out, const float *e, double scale, bool divide, const u32x4 n, int32_t at,
+                                            int32_t V, bool whole) {
+  const float f_hi = (float) scale, f_lo = (float) (scale - (double) f_hi);
+  const int32_t t = min(at, V - 4);
+  f32x4_any v;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    v[k] = fmaf(e[k], f_hi, e[k] * f_lo);
+    if (divide) v[k] *= __builtin_amdgcn_rcpf((float) (int32_t) n[k]);      // uniform
+  }
+  if (whole || at <= V - 4) {
+    *reinterpret_cast<f32x4_any *>(out + t) = v;
+  } else {
+#pragma unroll
+    for (int k = 1; k < 4; ++k)
+      if (k >= at - t) out[t + k] = v[k];
+  }
+}
+
+// A row by one workgroup: its exponentials stay in registers until its total is known.  NP: row parts a wave holds (64
+// exponentials a lane with two; longer rows take the two kernels below).  A row is read once and its
 // exponentials are formed once, where the two kernels read it twice and form them twice.  256 rows of 65 536
 // bf16 logits 26.0 us against 6.3 + 27.4, fp32 29.4 against 11.7 + 29.5; what is written (67 MB) and read takes 20 at
 // the rate of a copy, and one row, by one compute unit, 17: 20 issue slots an element, of which the
@@ -1101,78 +1180,31 @@ __global__ __launch_bounds__(kTableThreads) void weights_kernel(
 constexpr int kRowTableThreads = 1024;
 constexpr int kRowTableParts = 2 * kRowTableThreads / kWave;      // V <= 65 536
 
-// Four consecutive logits, at any element address.
-typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
-template <bool BF16>
-__device__ __forceinline__ void load4_once(const void *row, int32_t t, uint32_t *w) {
-  const char *p = reinterpret_cast<const char *>(row) + (int64_t) t * (BF16 ? 2 : 4);
-  if constexpr (BF16) {
-    const u32x2_any q = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any *>(p));
-    w[0] = q.x; w[1] = q.y;
-  } else {
-    const u32x4 q = load16<true>(p);
-    w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-  }
-}
-
-template <bool BF16, int NP>
-__global__ __launch_bounds__(kRowTableThreads) void row_weights_kernel(RowSet rs, int32_t V, int32_t nparts, int64_t row0,
-                                                                       float c, float c_lo, double cd,
-                                                                       const int32_t *mult, float *table) {
-  constexpr int kPieces = kPartElems / (4 * kWave);      // of four tokens a lane, in a part
-  constexpr int kWords = BF16 ? 2 : 4;
+template <bool BF16, bool WIDE, int NP>
+__global__ __launch_bounds__(kRowTableThreads) void row_weights_kernel(RowSet rs, int32_t V, int32_t nparts, float c, float c_lo,
+                                                                       double cd, const int32_t *mult, float *table) {
   __shared__ double part_z[kRowTableParts];
   __shared__ float part_m[kRowTableParts];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const void *rowp = row_base(rs, row0 + blockIdx.x, BF16);
+  const void *rowp = row_base(rs, blockIdx.x, BF16);
   float *out = table + (int64_t) blockIdx.x * V;
-  // Token of piece j of part p in this lane; in the row's last part, pieces that would cross its end are read
-  // where its last four tokens lie, and the `over` first of those belong to the piece before.
-  auto token = [&](int32_t p, int j) { return p * kPartElems + (j * kWave + lane) * 4; };
-  uint32_t w[NP][kPieces][kWords];
+  Piece<BF16> w[NP][kTablePieces];
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     const int32_t p = wave * NP + q;
     if (p >= nparts) continue;                           // uniform over the wave
 #pragma unroll
-    for (int j = 0; j < kPieces; ++j) load4_once<BF16>(rowp, min(token(p, j), V - 4), w[q][j]);
+    for (int j = 0; j < kTablePieces; ++j) w[q][j] = load_piece<BF16, WIDE, true>(rowp, min(piece_token(p, j, lane), V - 4));
   }
-  float e[NP][kPieces * 4], m[NP];
+  float e[NP][4 * kTablePieces];
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     const int32_t p = wave * NP + q;
-    m[q] = -INFINITY;
     if (p >= nparts) continue;
-    const bool whole = (p + 1) * kPartElems <= V;        // uniform
-#pragma unroll
-    for (int j = 0; j < kPieces; ++j) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float x;
-        if constexpr (BF16) x = __uint_as_float((k & 1) ? (w[q][j][k >> 1] & 0xffff0000u) : (w[q][j][k >> 1] << 16));
-        else x = __uint_as_float(w[q][j][k]);
-        if (!whole && k < token(p, j) - (V - 4)) x = -INFINITY;
-        e[q][4 * j + k] = x;
-      }
-    }
-    float top = e[q][0];
-#pragma unroll
-    for (int k = 1; k < 4 * kPieces; ++k) top = fmaxf(top, e[q][k]);
-    m[q] = wave_max(top);
-    // relative to the part's own maximum; a part without mass has none (its -inf - (-inf) would be NaN)
-    const float ref = m[q] == -INFINITY ? 0.f : m[q];
-    float s[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < 4 * kPieces; ++k) {
-      // exp_rel; of its test for -inf only the low product is left, which for it is an infinity of either sign
-      // or, with c_lo = 0, a NaN
-      const float d = e[q][k] - ref;
-      e[q][k] = __builtin_amdgcn_exp2f(fmaf(d, c, fminf(d * c_lo, FLT_MAX)));
-      s[k & 3] += e[q][k];
-    }
-    const double z = subwave_sum<64>((double) ((s[0] + s[1]) + (s[2] + s[3])));
-    if (lane == kWave - 1) { part_z[p] = z; part_m[p] = m[q]; }
+    float m;
+    const double z = part_exponentials<BF16>(w[q], p, V, lane, c, c_lo, e[q], m);
+    if (lane == kWave - 1) { part_z[p] = z; part_m[p] = m; }
   }
   __syncthreads();
   // every wave: the row's maximum and total, a part per lane
@@ -1186,30 +1218,76 @@ __global__ __launch_bounds__(kRowTableThreads) void row_weights_kernel(RowSet rs
   for (int q = 0; q < NP; ++q) {
     const int32_t p = wave * NP + q;
     if (p >= nparts) continue;
-    // the product with a double, rounded once: two floats hold enough of it
     const double f = read_lane(scale, p);
-    const float f_hi = (float) f, f_lo = (float) (f - (double) f_hi);
     const bool whole = (p + 1) * kPartElems <= V;
 #pragma unroll
-    for (int j = 0; j < kPieces; ++j) {
-      const int32_t at = token(p, j), t = min(at, V - 4);
-      f32x4_any v;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = fmaf(e[q][4 * j + k], f_hi, e[q][4 * j + k] * f_lo);
-      if (mult) {                                        // uniform
-        const u32x4 n = load16<false>(mult + t);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] *= __builtin_amdgcn_rcpf((float) (int32_t) n[k]);
-      }
-      if (whole || at <= V - 4) {
-        *reinterpret_cast<f32x4_any *>(out + t) = v;
-      } else {
-#pragma unroll
-        for (int k = 1; k < 4; ++k)
-          if (k >= at - t) out[t + k] = v[k];
-      }
+    for (int j = 0; j < kTablePieces; ++j) {
+      const int32_t at = piece_token(p, j, lane);
+      u32x4 n = {1, 1, 1, 1};
+      if (mult) n = load_mult<WIDE>(mult, at, V);
+      store_piece(out, e[q] + 4 * j, f, mult, n, at, V, whole);
     }
   }
+}
+
+// The statistics of every part of every row, a wave each.  V >= 4.
+template <bool BF16>
+__global__ __launch_bounds__(kStatsWaves *kWave) void weights_parts_kernel(RowSet rs, int32_t V, int32_t nparts, float c,
+                                                                           float c_lo, StatPart *parts) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int32_t p = blockIdx.x * kStatsWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (p >= nparts) return;                               // whole wave leaves together
+  const void *rowp = row_base(rs, blockIdx.y, BF16);
+  Piece<BF16> w[kTablePieces];
+  load_pieces<BF16, true>(w, rowp, p, 0, V, lane);
+  float e[4 * kTablePieces];
+  StatPart sp;
+  sp.z = part_exponentials<BF16>(w, p, V, lane, c, c_lo, e, sp.m);
+  sp.t = 0.f;
+  if (lane == kWave - 1) parts[(int64_t) blockIdx.y * nparts + p] = sp;
+}
+
+// The table from those, a part by one workgroup.
+constexpr int kTableThreads = 256;
+
+template <bool BF16>
+__global__ __launch_bounds__(kTableThreads) void weights_kernel(RowSet rs, int32_t V, int32_t nparts, float c, float c_lo,
+                                                                double cd, const StatPart *parts, const int32_t *mult,
+                                                                float *table) {
+  constexpr int kMine = kTablePieces / (kTableThreads / kWave);      // pieces of a wave
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t row = blockIdx.y, p = blockIdx.x;
+  const void *rowp = row_base(rs, row, BF16);
+  Piece<BF16> w[kMine];
+  load_pieces<BF16, false>(w, rowp, p, wave * kMine, V, lane);
+  u32x4 n[kMine] = {};
+  if (mult)
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) n[j] = load_mult<true>(mult, piece_token(p, wave * kMine + j, lane), V);
+  // the row's maximum and total as above; a lane's first part stays in registers (V <= 131 072: all of them)
+  const StatPart *rp = parts + (int64_t) row * nparts;
+  const float pm = lane < nparts ? rp[lane].m : -INFINITY;
+  const double pz = lane < nparts ? rp[lane].z : 0.0;
+  float top = pm;
+  for (int32_t k = lane + kWave; k < nparts; k += kWave) top = fmaxf(top, rp[k].m);
+  const float M = wave_max(top);
+  const double up = exp2((double) (pm - M) * cd);
+  double z = pz > 0.0 ? pz * up : 0.0;
+  for (int32_t k = lane + kWave; k < nparts; k += kWave)
+    if (rp[k].z > 0.0) z += rp[k].z * exp2((double) (rp[k].m - M) * cd);
+  const double iz = 1.0 / wave_sum(z);
+  const bool kept = p < kWave;                           // uniform
+  const float m = kept ? __int_as_float(read_lane(__float_as_int(pm), p)) : rp[p].m;
+  const double scale = (kept ? read_lane(up, p) : exp2((double) (m - M) * cd)) * iz;
+  float *out = table + (int64_t) row * V;
+  const bool whole = (p + 1) * kPartElems <= V;
+  float e[4 * kMine];
+  piece_logits<BF16>(w, p, wave * kMine, V, lane, e);
+#pragma unroll
+  for (int k = 0; k < 4 * kMine; ++k) e[k] = part_exp(e[k], m, c, c_lo);
+#pragma unroll
+  for (int j = 0; j < kMine; ++j) store_piece(out, e + 4 * j, scale, mult, n[j], piece_token(p, wave * kMine + j, lane), V, whole);
 }
 
 // =============================================================================================
@@ -2672,47 +2750,51 @@ hipError_t launch_propose(const RowSet &rs, bool bf16, int32_t V, int32_t K, int
   return hipGetLastError();
 }
 
-hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int64_t row0,
-                          int32_t nrows, float c, float c_hi, float c_lo, const StatPart *parts,
-                          float *table, hipStream_t stream) {
-  const int32_t nct = (g.V + kTableTokens - 1) / kTableTokens;
-  const dim3 grid((unsigned) ((int64_t) nct * nrows));
+hipError_t launch_weights_parts(const RowSet &rs, bool bf16, int32_t V, int32_t nrows, float c, float c_lo, StatPart *parts,
+                                hipStream_t stream) {
+  const int32_t nparts = stats_nparts(V);
+  const dim3 grid((unsigned) ((nparts + kStatsWaves - 1) / kStatsWaves), (unsigned) nrows);
+  auto launch = [&](auto kernel) { kernel<<<grid, kStatsWaves * kWave, 0, stream>>>(rs, V, nparts, c, c_lo, parts); };
+  if (bf16) launch(weights_parts_kernel<true>); else launch(weights_parts_kernel<false>);
+  return hipGetLastError();
+}
+
+hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int32_t nrows, float c, float c_lo, double cd,
+                          const StatPart *parts, float *table, hipStream_t stream) {
   const int32_t nparts = stats_nparts(g.V);
-  const bool vec = g.V >= 8;
   // with general weights the table is the plain probability: the gather applies the weights
   const int32_t *mult = g.weights ? nullptr : g.mult;
-#define PCG_LAUNCH_WEIGHTS(BF, VE)                                                             \
-  weights_kernel<BF, VE><<<grid, kTableThreads, 0, stream>>>(rs, g.V, nparts, nct, row0, c, c_hi, \
-                                                             c_lo, parts, mult, table)
-  if (bf16) { if (vec) PCG_LAUNCH_WEIGHTS(true, true); else PCG_LAUNCH_WEIGHTS(true, false); }
-  else { if (vec) PCG_LAUNCH_WEIGHTS(false, true); else PCG_LAUNCH_WEIGHTS(false, false); }
-#undef PCG_LAUNCH_WEIGHTS
+  auto launch = [&](auto kernel) {
+    kernel<<<dim3((unsigned) nparts, (unsigned) nrows), kTableThreads, 0, stream>>>(rs, g.V, nparts, c, c_lo, cd, parts, mult, table);
+  };
+  if (bf16) launch(weights_kernel<true>); else launch(weights_kernel<false>);
   return hipGetLastError();
 }
 
 // One compute unit a row, and a launch less, or the row's parts spread over the chip twice.  The call by
-// row_stats and weights, and by rows, in us (V, members, rows; bf16 unless stated):
-//   up to 8 parts:   1000, 8, 18: 14.1 and 10.8;  4096, 8, 32: 14.1 and 11.3, 1152: 44.8 and 37.0;  12 000, 8, 2: 14.0 and
-//                    11.6;  16 384, 8, 128: 19.0 and 16.1, 1152: 93.9 and 78.3
-//   up to 16 parts:  32 768, 32, 2: 14.5 and 16.0, 16: 15.7 and 16.7, fp32 8: 14.8 and 16.4;  30 000, 32, 64: 23.0 and 21.7,
-//                    128: 32.5 and 30.4;  32 768, 32, 128, fp32: 34.6 and 30.9
-//   beyond:          40 000, 32, 64: 26.6 and 30.9, 96: 40.8 and 43.5, 128: 49.9 and 49.9;  65 536, 32, 64: 36.3 and 40.8, 96:
-//                    58.8 and 59.6, 128: 65.8 and 63.8;  fp32, 96: 57.7 and 57.6 at 50 000
+// weights_parts and weights, and by rows, in us (V, members, rows; bf16 unless stated):
+//   up to 8 parts:   1000, 8, 18: 11.9 and 10.1;  4096, 8, 32: 12.5 and 11.2, 1152: 45.4 and 37.9;  12 000, 8, 2: 12.9 and
+//                    10.5;  16 384, 8, 128: 19.7 and 16.4, 1152: 89.0 and 79.0
+//   up to 16 parts:  32 768, 32, 2: 12.8 and 13.8, 16: 15.8 and 16.9, fp32 8: 14.7 and 16.3;  30 000, 32, 64: 24.7 and 22.8,
+//                    128: 33.8 and 31.9;  32 768, 32, 128, fp32: 35.6 and 32.7
+//   beyond:          40 000, 32, 64: 28.3 and 31.3, 96: 41.8 and 44.1, 128: 50.2 and 50.2;  65 536, 32, 64: 37.9 and 41.5, 96:
+//                    59.4 and 59.7, 128: 65.4 and 64.4;  fp32, 96: 57.2 and 57.7 at 50 000
 bool weights_by_rows(int32_t V, int32_t nrows) {
   const int32_t nparts = stats_nparts(V);
-  return V >= 4 && nparts <= kRowTableParts && nrows >= (nparts <= 8 ? 1 : nparts <= 16 ? 64 : 128);
+  return nparts <= kRowTableParts && nrows >= (nparts <= 8 ? 1 : nparts <= 16 ? 64 : 128);
 }
 
-hipError_t launch_row_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int64_t row0, int32_t nrows, float c,
-                              float c_lo, double cd, float *table, hipStream_t stream) {
+hipError_t launch_row_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int32_t nrows, float c, float c_lo, double cd,
+                              float *table, hipStream_t stream) {
   const int32_t nparts = stats_nparts(g.V);
   const int32_t *mult = g.weights ? nullptr : g.mult;
   auto launch = [&](auto kernel, int np) {
     const unsigned waves = (unsigned) ((nparts + np - 1) / np);
-    kernel<<<(unsigned) nrows, waves * kWave, 0, stream>>>(rs, g.V, nparts, row0, c, c_lo, cd, mult, table);
+    kernel<<<(unsigned) nrows, waves * kWave, 0, stream>>>(rs, g.V, nparts, c, c_lo, cd, mult, table);
   };
-  if (nparts * 2 <= kRowTableParts) { if (bf16) launch(row_weights_kernel<true, 1>, 1); else launch(row_weights_kernel<false, 1>, 1); }
-  else { if (bf16) launch(row_weights_kernel<true, 2>, 2); else launch(row_weights_kernel<false, 2>, 2); }
+  if (g.V < 4) { if (bf16) launch(row_weights_kernel<true, false, 1>, 1); else launch(row_weights_kernel<false, false, 1>, 1); }
+  else if (nparts * 2 <= kRowTableParts) { if (bf16) launch(row_weights_kernel<true, true, 1>, 1); else launch(row_weights_kernel<false, true, 1>, 1); }
+  else { if (bf16) launch(row_weights_kernel<true, true, 2>, 2); else launch(row_weights_kernel<false, true, 2>, 2); }
   return hipGetLastError();
 }
 

@@ -464,3 +464,42 @@ def test_few_rows_of_groups_of_one_size(V, size, n):
     ref = oracle.group_probs(og, as_oracle_logits(x.cpu()), 0.9)
     for g in (dg, dg.without_prepared()):
         assert group_probs_error(pcg.group_probs(g, x, 0.9), ref) <= 1e-5
+
+
+# one row or two more than a batch of the table holds: from the prepared layout by rows and by two kernels, few rows of
+# which would be gathered from the CSR, with the CSR alone, with weights
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V,size,n,layout,weighted", [
+    (65536, 32, 258, "prepared", False), (65536, 12, 513, "prepared", True), (20000, 32, 839, "prepared", False),
+    (12000, 60, 1399, "prepared", False), (20000, 32, 840, "csr", False), (70001, 20, 240, "prepared", False)])
+def test_equal_rows_of_a_call(V, size, n, layout, weighted, dtype):
+    """Rows of one call that hold the same logits have the same group probabilities, to the bit, wherever they stand."""
+    rp, mem = W.random_groups(V, V, size, size, seed=V)
+    w = W.random_weights(V, mem, V) if weighted else None
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", chunk_groups=4096, weights=w, prepare=layout == "prepared")
+    x = 4.0 * torch.randn((n, V), device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    x[n // 2] = x[0]
+    x[n - 1] = x[0]
+    x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    print(f"V={V} size={size} n={n} {layout} w={weighted} {dtype}", flush=True)
+    out = pcg.group_probs(dg, x, 0.9)
+    assert torch.equal(out[n // 2], out[0]) and torch.equal(out[n - 1], out[0])
+
+
+# the table by a workgroup a row for all rows, by two kernels for some of them
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("V,n,some,weighted", [
+    (65536, 130, 20, False), (65533, 128, 40, True), (32768, 65, 40, False), (30001, 64, 63, False), (36865, 129, 50, False)])
+def test_rows_of_calls_of_different_sizes(V, n, some, weighted, dtype):
+    """A row's group probabilities by the prepared layout are the same to the bit whatever number of rows comes with it
+    (of so many that none is gathered from the CSR)."""
+    rp, mem = W.random_groups(V, V, 1, 12, seed=V)
+    w = W.random_weights(V, mem, V) if weighted else None
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda", weights=w)
+    x = 4.0 * torch.randn((n, V), device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    x[1, :3000] = -float("inf")
+    x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    print(f"V={V} n={n} some={some} w={weighted} {dtype}", flush=True)
+    out = pcg.group_probs(dg, x, 0.9)
+    assert torch.equal(pcg.group_probs(dg, x[:some], 0.9), out[:some])
+    assert torch.equal(pcg.group_probs(dg, x[n - some:], 0.9), out[n - some:])
