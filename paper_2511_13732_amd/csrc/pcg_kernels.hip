@@ -2863,23 +2863,31 @@ static unsigned gather_grid(const GatherMap &m, int32_t nrows) {
 
 // Few rows leave most of the chip to chunks of at least 4096 groups, and those who have one wait for their slots from
 // memory; from the CSR a row is cut as fine as there are compute units.  Whole calls, prepared and CSR, in us
-// (V, members, sequences; turns: of the CSR's workgroups):
-//   one tile, one turn:   20 000, 8, 1: 21.5 and 20.7, 24: 25.2 and 24.4;  32, 1: 23.4 and 21.3, 6: 25.0 and 22.5;
-//                         100, 1: 31.8 and 26.2;  40 000, 32, 2: 25.0 and 22.7;  30 000, 1 to 128, 1: 31.6 and 25.3
-//   two:                  20 000, 32, 7: 25.0 and 23.8, 12: 26.1 and 24.8;  100, 6: 33.2 and 29.4;  30 000, 1 to 128, 3: 32.6 and
-//                         30.6;  but with fewer lanes a group and sizes that differ, 1 to 40, 5: 26.1 and 27.0;  20 000, 8,
-//                         32: 25.8 and 26.0
-//   more:                 20 000, 32, 16: 26.7 and 27.2;  100, 12: 34.7 and 36.6
-//   weights:              20 000, 12, 8 (one): 24.0 and 22.4, 16 (two): 25.7 and 25.5;  32, 24 (four): 33.1 and 31.5;  33 000, 32,
-//                         20 (six): 35.0 and 37.0;  80, 8 (five): 47.3 and 44.4, 16 (nine): 49.3 and 59.0
-//   two tiles, one turn:  65 536, 32, 1: 27.9 and 26.4, 2: 28.4 and 27.4;  50 000, 32, 2: 27.5 and 26.1;  8, 2: 25.9 and 26.3;  100, 1:
-//                         37.1 and 38.9;  weights, 32, 4: 34.3 and 35.7
+// (V, members, sequences of pcg_verify or rows of pcg_group_probs; turns: of the CSR's workgroups):
+//   one tile, one turn:   verify 12 000, 8, 3: 21.6 and 20.9;  20 000, 32, 1: 23.4 and 21.3;  100, 1: 31.8 and 26.2;  40 000, 32, 2: 25.0
+//                         and 22.7;  rows 4100, 4, 1: 10.3 and 9.8, 16, 36: 12.3 and 11.0, 100, 5: 26.8 and 11.6;  14 000, 13, 9: 12.4 and 10.7
+//   two:                  with 8 lanes a group and one size, verify 20 011, 20, 12: 25.1 and 24.5, rows 8192, 24, 18: 13.0 and 12.4;
+//                         with 16, verify 12 000, 100, 8: 32.4 and 28.7, 30 000, 1 to 128, 3: 29.7 and 29.0;  but rows 10 000, 10, 48:
+//                         11.9 and 12.8;  verify 20 000, 8, 32: 26.5 and 27.5;  1 to 40, 5: 26.1 and 27.0
+//   three:                verify 14 000, 33, 9: 25.2 and 25.8, 64: 28.7 and 27.0 at 30 000, 5;  7000, 1 to 200, 18: 35.6 and 37.3
+//   weights, 8 lanes:     a turn takes as long for 17 members as for 32.  Two turns: rows 17 000, 20, 9: 15.0 and 14.3, 1 to 50, 36: 14.1
+//                         and 15.0 at 4500, up to 32 members, half of them 32: 13.9 and 12.3;  three: rows 7000, 18, 48: 12.9 and
+//                         14.2, 5000, 28, 64: 14.4 and 14.0, 20 to 40, verify 14 000, 18: 29.1 and 32.2;  four: rows 7000, 20, 64: 13.2
+//                         and 15.6, 28: 14.6 and 15.6, verify 20 011, 32, 24: 34.1 and 32.1
+//   weights, 16 lanes:    four: rows 20 011, 33, 12: 19.2 and 19.0, verify 17 000, 1 to 128, 12: 41.7 and 39.7;  five: verify 26 000, 56, 9: 37.2
+//                         and 33.7, but rows 14 000, 33, 18: 16.7 and 18.7, 4100, 1 to 128, 64: 21.9 and 24.3
+//   two tiles, one turn:  verify 65 536, 32, 1: 27.1 and 25.7;  24, 2: 26.8 and 26.3;  up to 32 members, half of them 32: 25.7 and 24.5 at
+//                         45 000, but 1 to 40: 27.4 and 29.1;  140, 1: 41.9 and 45.0 at 50 000;  12, 2: rows 17.1 and 17.8
 bool csr_is_faster(const pcg_groups &g, const CsrShape &p) {
   const int32_t turn = kCsrInFlight * (kGatherThreads / p.width), turns = (p.chunk_groups + turn - 1) / turn;
   if (g.G <= kScanGroups) return false;                // one chunk, whose totals finalize reads at once
   if (p.ntiles == 2) return p.width == 8 && !g.weights && turns == 1;
-  const int32_t most = g.weights ? (p.width >= 16 ? 5 : p.width == 8 ? 4 : 1)
-                                 : (p.width >= 16 || (p.width == 8 && even_size(g) > 0) ? 2 : 1);
+  const bool even = even_size(g) > 0;
+  const double mean = (double) g.nnz / (double) g.G;
+  int32_t most = 1;
+  if (p.width >= 16) most = !g.weights ? 2 : even && mean > 44 ? 5 : 4;
+  else if (p.width == 8 && g.weights) most = !even ? 2 : mean > 28 ? 4 : mean > 24 ? 3 : 2;
+  else if (p.width == 8 && even) most = 2;
   return p.ntiles == 1 && turns <= most;
 }
 

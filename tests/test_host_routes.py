@@ -1,0 +1,31 @@
+"""Which calls take which route, on both sides of the lines that were measured.  No GPU needed."""
+import pytest
+
+import routes
+
+
+# members: one size, or (smallest, largest)
+def nnz_of(G, members):
+    return G * members if isinstance(members, int) else G * (members[0] + members[1]) // 2 + 1 - G % 2
+
+
+@pytest.mark.parametrize("V,members,weighted,rows,csr", [
+    (4100, 100, False, 5, True), (14000, 13, False, 9, True), (8192, 24, False, 18, True), (10000, 10, False, 48, False),
+    (20011, 20, False, 60, False), (30000, 33, False, 9, False), (20000, 32, False, 64, False), (4096, 32, False, 1, False),
+    # with weights: 8 lanes a group, two to four turns
+    (17000, 20, True, 9, True), (7000, 18, True, 48, False), (7000, 20, True, 64, False), (5000, 28, True, 64, True),
+    (7000, 28, True, 64, False), (20000, 32, True, 18, True), (20011, (1, 60), True, 18, False), (9000, (1, 60), True, 36, False),
+    (4500, (1, 60), True, 1, True),
+    # 16 lanes, four and five
+    (20011, 33, True, 12, True), (14000, 33, True, 18, False), (26000, 56, True, 9, True), (4100, (1, 128), True, 64, False),
+    (5000, (1, 128), True, 36, True)])
+def test_rows_of_a_prepared_membership(V, members, weighted, rows, csr):
+    assert routes.rows_from_csr(V, V, nnz_of(V, members), weighted, rows) == csr
+
+
+@pytest.mark.parametrize("V,members,weighted,B,K,csr", [
+    (20000, 32, False, 1, 8, True), (20011, 20, False, 12, 8, True), (20000, 8, False, 32, 8, False), (20000, 32, False, 16, 8, False),
+    (65536, 32, False, 1, 8, True), (65536, 32, False, 3, 8, False), (50000, 140, False, 1, 8, False), (65536, 32, True, 1, 8, False),
+    (20011, 32, True, 24, 8, True), (14000, (20, 40), True, 18, 8, False), (26000, 56, True, 9, 8, True)])
+def test_steps_of_a_prepared_membership(V, members, weighted, B, K, csr):
+    assert routes.step_from_csr(V, V, nnz_of(V, members), weighted, B, K) == csr
