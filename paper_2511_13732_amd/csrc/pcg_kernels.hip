@@ -1151,17 +1151,22 @@ __device__ __forceinline__ u32x4 load_mult(const int32_t *mult, int32_t at, int3
 }
 
 // Four entries of the table from their exponentials: the product with the scale, a double, rounded once (two floats hold
-// enough of it), and, if divide, with 1 / N(t).
-__device__ __forceinline__ void store_piece(float *out, const float *e, double scale, bool divide, const u32x4 n, int32_t at,
-                                            int32_t V, bool whole) {
+// enough of it); and divided by N(t).
+__device__ __forceinline__ f32x4_any scaled(const float *e, double scale) {
   const float f_hi = (float) scale, f_lo = (float) (scale - (double) f_hi);
-  const int32_t t = min(at, V - 4);
   f32x4_any v;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    v[k] = fmaf(e[k], f_hi, e[k] * f_lo);
-    if (divide) v[k] *= __builtin_amdgcn_rcpf((float) (int32_t) n[k]);      // uniform
-  }
+  for (int k = 0; k < 4; ++k) v[k] = fmaf(e[k], f_hi, e[k] * f_lo);
+  return v;
+}
+__device__ __forceinline__ f32x4_any divided(f32x4_any v, const u32x4 n) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] *= __builtin_amdgcn_rcpf((float) (int32_t) n[k]);
+  return v;
+}
+
+__device__ __forceinline__ void store_piece(float *out, const f32x4_any v, int32_t at, int32_t V, bool whole) {
+  const int32_t t = min(at, V - 4);
   if (whole || at <= V - 4) {
     *reinterpret_cast<f32x4_any *>(out + t) = v;
   } else {
@@ -1223,9 +1228,9 @@ __global__ __launch_bounds__(kRowTableThreads) void row_weights_kernel(RowSet rs
 #pragma unroll
     for (int j = 0; j < kTablePieces; ++j) {
       const int32_t at = piece_token(p, j, lane);
-      u32x4 n = {1, 1, 1, 1};
-      if (mult) n = load_mult<WIDE>(mult, at, V);
-      store_piece(out, e[q] + 4 * j, f, mult, n, at, V, whole);
+      f32x4_any v = scaled(e[q] + 4 * j, f);
+      if (mult) v = divided(v, load_mult<WIDE>(mult, at, V));      // uniform
+      store_piece(out, v, at, V, whole);
     }
   }
 }
@@ -1250,7 +1255,7 @@ __global__ __launch_bounds__(kStatsWaves *kWave) void weights_parts_kernel(RowSe
 // The table from those, a part by one workgroup.
 constexpr int kTableThreads = 256;
 
-template <bool BF16>
+template <bool BF16, bool DIVIDE>
 __global__ __launch_bounds__(kTableThreads) void weights_kernel(RowSet rs, int32_t V, int32_t nparts, float c, float c_lo,
                                                                 double cd, const StatPart *parts, const int32_t *mult,
                                                                 float *table) {
@@ -1261,8 +1266,8 @@ __global__ __launch_bounds__(kTableThreads) void weights_kernel(RowSet rs, int32
   const void *rowp = row_base(rs, row, BF16);
   Piece<BF16> w[kMine];
   load_pieces<BF16, false>(w, rowp, p, wave * kMine, V, lane);
-  u32x4 n[kMine] = {};
-  if (mult)
+  u32x4 n[kMine];
+  if constexpr (DIVIDE)
 #pragma unroll
     for (int j = 0; j < kMine; ++j) n[j] = load_mult<true>(mult, piece_token(p, wave * kMine + j, lane), V);
   // the row's maximum and total as above; a lane's first part stays in registers (V <= 131 072: all of them)
@@ -1287,7 +1292,11 @@ __global__ __launch_bounds__(kTableThreads) void weights_kernel(RowSet rs, int32
 #pragma unroll
   for (int k = 0; k < 4 * kMine; ++k) e[k] = part_exp(e[k], m, c, c_lo);
 #pragma unroll
-  for (int j = 0; j < kMine; ++j) store_piece(out, e + 4 * j, scale, mult, n[j], piece_token(p, wave * kMine + j, lane), V, whole);
+  for (int j = 0; j < kMine; ++j) {
+    f32x4_any v = scaled(e + 4 * j, scale);
+    if constexpr (DIVIDE) v = divided(v, n[j]);
+    store_piece(out, v, piece_token(p, wave * kMine + j, lane), V, whole);
+  }
 }
 
 // =============================================================================================
@@ -2767,7 +2776,8 @@ hipError_t launch_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int3
   auto launch = [&](auto kernel) {
     kernel<<<dim3((unsigned) nparts, (unsigned) nrows), kTableThreads, 0, stream>>>(rs, g.V, nparts, c, c_lo, cd, parts, mult, table);
   };
-  if (bf16) launch(weights_kernel<true>); else launch(weights_kernel<false>);
+  if (bf16) { if (mult) launch(weights_kernel<true, true>); else launch(weights_kernel<true, false>); }
+  else { if (mult) launch(weights_kernel<false, true>); else launch(weights_kernel<false, false>); }
   return hipGetLastError();
 }
 
