@@ -444,9 +444,8 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
   int64_t csum_stride;
   // The CSR gather may cut a row finer than csum has room for; its chunk totals then go where the
   // sequence's row parts were, which nothing reads after the accept scan.
-  const int64_t room = (groups->G + kChunkStep - 1) / kChunkStep;
-  const int64_t parts_room = (2 * K + 1) * (int64_t) nparts * (sizeof(StatPart) / sizeof(double));
-  const CsrShape cut = csr_shape(V, groups->G, groups->nnz, B, std::max(room, parts_room));
+  const int64_t room = csum_room(groups->G);
+  const CsrShape cut = step_csr_shape(*groups, B, K);
   if (groups->prepared && !csr_is_faster(*groups, cut)) {
     csum_stride = nchunks = groups->prepared_info->nchunks;
     chunk_groups = groups->prepared_info->chunk_groups;
@@ -454,7 +453,7 @@ int verify_impl(const pcg_groups *groups, const void *target_logits, const void 
   } else {
     nchunks = cut.nchunks;
     chunk_groups = cut.chunk_groups;
-    csum_stride = nchunks <= room ? room : parts_room;
+    csum_stride = nchunks <= room ? room : csum_room_in_parts(V, K);
     if (nchunks > room) csum = (double *) parts;
     e = launch_gather(*groups, cut, B, table, nullptr, csum, csum_stride, runs, stream);
   }

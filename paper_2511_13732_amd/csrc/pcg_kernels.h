@@ -7,6 +7,7 @@
 
 #include "../../include/pcg.h"
 #include "pcg_device.h"
+#include "pcg_layout.h"
 
 namespace pcg {
 
@@ -58,6 +59,13 @@ struct CsrShape {
   int32_t width, nchunks, chunk_groups, ntiles, tile_len;
 };
 CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max_chunks);
+// Chunk totals of a sequence that a step has room for, in their own region and, once the accept scan is over, where the
+// sequence's row parts were; and the cut of a step's gather, which uses the larger.
+inline int64_t csum_room(int32_t G) { return (G + kChunkStep - 1) / kChunkStep; }
+inline int64_t csum_room_in_parts(int32_t V, int32_t K) {
+  return (2 * K + 1) * (int64_t) stats_nparts(V) * (int64_t) (sizeof(StatPart) / sizeof(double));
+}
+CsrShape step_csr_shape(const pcg_groups &g, int32_t B, int32_t K);
 // Whether a gather so cut is ahead of one from the prepared layout of the same groups.
 bool csr_is_faster(const pcg_groups &g, const CsrShape &p);
 

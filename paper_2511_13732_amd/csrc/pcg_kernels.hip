@@ -2845,6 +2845,10 @@ CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max
   return p;
 }
 
+CsrShape step_csr_shape(const pcg_groups &g, int32_t B, int32_t K) {
+  return csr_shape(g.V, g.G, g.nnz, B, std::max(csum_room(g.G), csum_room_in_parts(g.V, K)));
+}
+
 // How the XCDs share rows and chunks.  All chunks of a row on one XCD, unless another split saves each of them 1 MiB
 // to bring in (the rows, which everything waits for, counted twice).  Whole calls, or the gather alone, in us, all
 // on one and split (V, members, rows):
@@ -2888,8 +2892,12 @@ static unsigned gather_grid(const GatherMap &m, int32_t nrows) {
 //                         and 33.7, but rows 14 000, 33, 18: 16.7 and 18.7, 4100, 1 to 128, 64: 21.9 and 24.3
 //   two tiles, one turn:  verify 65 536, 32, 1: 27.1 and 25.7;  24, 2: 26.8 and 26.3;  up to 32 members, half of them 32: 25.7 and 24.5 at
 //                         45 000, but 1 to 40: 27.4 and 29.1;  140, 1: 41.9 and 45.0 at 50 000;  12, 2: rows 17.1 and 17.8
+static int32_t csr_turns(const CsrShape &p) {
+  const int32_t turn = kCsrInFlight * (kGatherThreads / p.width);
+  return (p.chunk_groups + turn - 1) / turn;
+}
 bool csr_is_faster(const pcg_groups &g, const CsrShape &p) {
-  const int32_t turn = kCsrInFlight * (kGatherThreads / p.width), turns = (p.chunk_groups + turn - 1) / turn;
+  const int32_t turns = csr_turns(p);
   if (g.G <= kScanGroups) return false;                // one chunk, whose totals finalize reads at once
   if (p.ntiles == 2) return p.width == 8 && !g.weights && turns == 1;
   const bool even = even_size(g) > 0;
@@ -2992,20 +3000,28 @@ StepShape step_shape(const pcg_groups &g, int32_t B, int32_t K) {
   // 157 and 90, 16 384, 4, 160: 60 and 57, 16 384, 128 with weights, 224: 316 and 295.
   if (B > 128) return small;
   if (g.prepared) {
-    // With one chunk of groups a sequence's gather is one workgroup in any case, and this wins throughout:
-    // 4096, 64, 1: 27.2 and 20.8, 4096, 128 with weights, 128: 61 and 50, chunks of 16 384 groups 16 384, 4, 1: 23.6
-    // and 21.2, 16 384, 100, 1: 56.9 and 51.4.  Several are walked one after the other here, and side by side
-    // there: what counts is the table (tokens) and the slots, padding and all, that one unit reads, three
-    // times as many bytes each with weights.
-    //   B < 128:  load 128: 8192, 32, 1: 24.1 and 23.2, 64: 27.6 and 25.2;  117: 12 000, 8, 1: 23.1 and 23.8, 64:
-    //             29.1 and 28.0;  140: 12 000, 16, 1: 23.4 and 25.2;  144: 16 384, 4, 1: 22.7 and 26.8;  192: 8192, 32
-    //             with weights, 1: 26.0 and 26.1;  320: 8192, 64 with weights, 64: 43.7 and 49.1
+    // What counts here is the table (tokens) and the slots, padding and all, that one unit reads, three times as many
+    // bytes each with weights: the load.
+    // With one chunk of groups a sequence's gather from the prepared layout is one workgroup in any case, and this wins
+    // over that throughout: 8192, 64, 64: 36.1 and 27.2, 16 384, 100, 64: 64.9 and 56.3, with weights 126.5 and 116.8.  But few
+    // sequences are gathered from the CSR by four launches (csr_is_faster), which takes longer by its turns:
+    //   one turn:   load 144: 16 384, 4, 1: 19.8 and 18.3;  160: 16 384, 8, 1: 19.9 and 19.7;  172: 16 000, 6 with weights, 1: 21.5
+    //               and 19.3;  187: 12 000, 32, 1: 20.2 and 23.2;  192: 8192, 64, 8: 22.1 and 24.6, 16 384, 16, 1: 20.0 and 22.2,
+    //               16 384, 8 with weights, 1: 19.8 and 20.4;  528: 16 384, 100, 1: 23.6 and 48.1, with weights (928) 25.4 and 126.6
+    //   more:       three, load 142: 6000, 32 with weights, 64: 27.0 and 24.6;  four, 236: 4500, 1 to 128 with weights, 48: 36.6 and
+    //               31.8;  two, 281: 12 000, 64, 8: 24.5 and 30.6
+    // Several chunks are walked one after the other here, and side by side there.
+    //   B < 128:  load 128: 8192, 32, 1: 19.1 and 20.3, 64: 25.7 and 22.5;  116: 12 000, 8, 1: 19.2 and 20.8, 64: 27.1 and
+    //             25.6;  140: 12 000, 16, 1: 19.3 and 22.2, 64: 28.0 and 27.2;  144: 16 384, 4, 1: 19.6 and 23.3, 64: 27.9 and 29.5;
+    //             192: 8192, 32 with weights, 1: 20.5 and 24.4, 64: 30.7 and 30.3;  320: 8192, 64 with weights, 64: 40.8 and 46.9
     //   B = 128:  load 256: 16 384, 16 with weights: 44.2 and 43.3, 8192, 48 with weights: 43.3 and 43.7;  192:
     //             8192, 64: 37.0 and 35.0;  320: 8192, 64 with weights: 48.3 and 51.0
     const pcg_prepared &p = *g.prepared_info;
     const int64_t slots = ((p.off_weights ? p.off_weights : p.bytes) - p.off_data) / 2;
     const int64_t load = g.V / 128 + slots / (g.weights ? 2048 : 4096);
-    return p.nchunks == 1 || load <= (B == 128 ? 256 : 130) ? small : StepShape::kFour;
+    if (p.nchunks > 1) return load <= (B == 128 ? 256 : 130) ? small : StepShape::kFour;
+    const CsrShape cut = step_csr_shape(g, B, K);
+    return !csr_is_faster(g, cut) || load <= 176 + 30 * (csr_turns(cut) - 1) ? small : StepShape::kFour;
   }
   // The CSR is read by 256 sub-waves of four lanes: trips are the turns of 1024 groups times those of 16
   // entries that the mean group needs.  The four kernels spread them.

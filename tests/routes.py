@@ -43,3 +43,12 @@ def step_from_csr(V, G, nnz, weighted, B, K):
     """Whether the four launches of pcg_verify do."""
     room = max((G + 4095) // 4096, (2 * K + 1) * ((V + 2047) // 2048) * 2)
     return _csr_is_faster(V, G, nnz, weighted, csr_shape(V, G, nnz, B, room))
+
+
+def step_launches(V, G, nnz, weighted, B, K, nchunks, slots):
+    """Launches of a pcg_verify step on a prepared membership of one tile, whose layout has so many slots."""
+    f = _function("_ZN3pcg10step_shapeERK10pcg_groupsii", C.c_int, C.c_void_p, C.c_int32, C.c_int32)
+    info = PreparedInfo(V=V, G=G, ntiles=1, tile_len=V, nchunks=nchunks, off_data=0, off_weights=2 * slots if weighted else 0,
+                        bytes=(6 if weighted else 2) * slots)
+    g = _groups(V, G, nnz, weighted, info)
+    return {0: 1, 1: 2, 2: 4}[f(C.addressof(g), B, K)]

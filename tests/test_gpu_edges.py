@@ -503,3 +503,11 @@ def test_rows_of_calls_of_different_sizes(V, n, some, weighted, dtype):
     out = pcg.group_probs(dg, x, 0.9)
     assert torch.equal(pcg.group_probs(dg, x[:some], 0.9), out[:some])
     assert torch.equal(pcg.group_probs(dg, x[n - some:], 0.9), out[n - some:])
+
+
+# few sequences of a prepared membership of one chunk: by four launches from the CSR, and on the other side of that line
+@pytest.mark.parametrize("V,G,size,B,K,weighted", [
+    (12000, 12000, 64, 1, 2, False), (16384, 16384, 40, 9, 1, False), (9001, 9001, 110, 3, 2, True), (16384, 16000, 200, 2, 8, True),
+    (16384, 16384, 12, 1, 2, False), (12001, 12001, 64, 40, 1, False)])
+def test_few_sequences_of_one_chunk(V, G, size, B, K, weighted):
+    check_step(V, G, size, B, K, "bf16", layout="prepared", weighted=weighted, thinning=False)

@@ -29,3 +29,19 @@ def test_rows_of_a_prepared_membership(V, members, weighted, rows, csr):
     (20011, 32, True, 24, 8, True), (14000, (20, 40), True, 18, 8, False), (26000, 56, True, 9, 8, True)])
 def test_steps_of_a_prepared_membership(V, members, weighted, B, K, csr):
     assert routes.step_from_csr(V, V, nnz_of(V, members), weighted, B, K) == csr
+
+
+# of one chunk, slots without padding: one launch or two where that was measured to be ahead of the four from the CSR, and
+# where those would take the prepared layout
+@pytest.mark.parametrize("V,members,weighted,B,K,launches", [
+    (16384, 4, False, 1, 8, 2), (12000, 32, False, 1, 8, 4), (8192, 64, False, 8, 8, 4), (16384, 100, False, 1, 8, 4),
+    (16384, 100, True, 1, 8, 4), (16384, 100, True, 8, 8, 4), (6000, 32, True, 64, 8, 2), (12000, 64, False, 8, 8, 4),
+    (8192, 64, False, 64, 8, 2), (16384, 100, False, 64, 8, 2), (4096, 100, True, 1, 8, 2), (1024, 8, False, 1, 4, 1),
+    (16384, 100, False, 129, 8, 1), (16384, 100, False, 100, 8, 2)])
+def test_launches_of_a_small_step(V, members, weighted, B, K, launches):
+    assert routes.step_launches(V, V, V * members, weighted, B, K, 1, V * members) == launches
+
+
+@pytest.mark.parametrize("V,members,B,launches", [(8192, 32, 1, 2), (12000, 16, 64, 4), (16384, 100, 8, 4), (8192, 64, 128, 2)])
+def test_launches_where_there_are_chunks(V, members, B, launches):
+    assert routes.step_launches(V, V, V * members, False, B, 8, (V + 4095) // 4096, V * members) == launches
