@@ -529,7 +529,8 @@ int build(int32_t V, int32_t G, const int32_t *row_ptr, const int32_t *members, 
   std::atomic<int64_t> next_block{0};
   auto worker = [&]() {
     std::vector<uint16_t> lists[32], sched;
-    std::vector<std::pair<uint16_t, float>> share[32];   // (slot, weight) of each lane's list, by slot
+    struct Entry { uint16_t slot; bool used; float weight; };
+    std::vector<Entry> share[32];                        // of each lane's list, by slot
     for (int64_t w = next_block.fetch_add(1); w < nblocks; w = next_block.fetch_add(1)) {
       const int32_t c = (int32_t) (w / BPC), bl = (int32_t) (w % BPC);
       const int32_t g0 = c * sh.chunk_groups;
@@ -548,9 +549,9 @@ int build(int32_t V, int32_t G, const int32_t *row_ptr, const int32_t *members, 
               for (int32_t j = row_ptr[g0 + k]; j < row_ptr[g0 + k + 1]; ++j)
                 if (members[j] / sh.tile_len == h) {
                   lists[l].push_back((uint16_t) (members[j] - h * sh.tile_len));
-                  if (weighted) share[l].emplace_back(lists[l].back(), weights[j]);
+                  if (weighted) share[l].push_back({lists[l].back(), false, weights[j]});
                 }
-              std::sort(share[l].begin(), share[l].end());
+              std::stable_sort(share[l].begin(), share[l].end(), [](const Entry &a, const Entry &b) { return a.slot < b.slot; });
             }
             schedule_half_wave(lists, (int) steps * 2, pad_base, sched);
             for (uint32_t q = 0; q < steps; ++q)
@@ -560,12 +561,15 @@ int build(int32_t V, int32_t G, const int32_t *row_ptr, const int32_t *members, 
                 const uint16_t s1 = sched[(size_t) (2 * q + 1) * 32 + l];
                 data[unit * 4 + r] = (uint32_t) s0 | ((uint32_t) s1 << 16);
                 if (!weighted) continue;
-                // a group's members are distinct, so a slot names one entry of the lane's list
+                // a slot names an entry of the lane's list; the entries of a token that the group
+                // lists several times are taken one after the other
                 auto weight_of = [&](uint16_t s) {
                   if (s >= pad_base) return 0.f;
-                  auto it = std::lower_bound(share[l].begin(), share[l].end(),
-                                             std::make_pair(s, -1.f));
-                  return it->second;
+                  auto it = std::lower_bound(share[l].begin(), share[l].end(), s,
+                                             [](const Entry &e, uint16_t slot) { return e.slot < slot; });
+                  while (it->used) ++it;
+                  it->used = true;
+                  return it->weight;
                 };
                 wdata[(unit * 4 + r) * 2] = weight_of(s0);
                 wdata[(unit * 4 + r) * 2 + 1] = weight_of(s1);

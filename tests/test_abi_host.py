@@ -277,6 +277,20 @@ def test_weighted_prepared_layout_carries_every_entrys_weight(V, G, smin, smax, 
                                              blob.ctypes.data, n - 1, C.byref(info)) == WS_SMALL
 
 
+def test_weights_of_a_token_that_a_group_lists_twice():
+    """Each entry keeps its own weight, also where a group lists one token several times."""
+    V, G = 700, 400
+    rng = np.random.default_rng(3)
+    rp = np.arange(0, 13 * G + 1, 13, dtype=np.int32)
+    mem = np.sort(rng.integers(0, 40, (G, 13)) * 17 % V, axis=1).astype(np.int32).ravel()
+    rp, mem, _ = pcg.groups_canonicalize_host(V, rp, mem)
+    w = W.random_weights(V, mem, seed=5)
+    blob, info = pcg.groups_prepare_host(V, rp, mem, 0, weights=w)
+    got, _, wgot = decode_prepared(blob, info, V, len(rp) - 1)
+    for g in range(len(rp) - 1):
+        assert sorted(zip(got[g], wgot[g])) == sorted(zip(mem[rp[g]:rp[g + 1]].tolist(), w[rp[g]:rp[g + 1]].tolist())), g
+
+
 def test_prepare_rejects_bad_arguments():
     rp, mem = np.array([0, 2, 4], np.int32), np.array([0, 1, 2, 3], np.int32)
     L = pcg.lib()
