@@ -481,7 +481,8 @@ int pcg_groups_prepare_weights_host(int32_t V, int32_t G, const int32_t *row_ptr
  * event pair adds, which is included in every other stage's figure.  A step that is small enough
  * to run as one or two kernels has everything after row_stats (or with it) recorded under "gather";
  * the stages so absorbed then read as event_overhead.  pcg_propose on rows of up to 131 072 logits is
- * one kernel, recorded under "propose": row_stats then reads 0.
+ * one kernel, recorded under "propose": row_stats then reads 0.  pcg_group_probs records its first batch of rows;
+ * where one kernel forms their statistics and their table it is recorded under "weights", and row_stats reads 0.
  * Not thread-safe; one profile at a time.
  */
 int pcg_profile_begin(int32_t max_calls);

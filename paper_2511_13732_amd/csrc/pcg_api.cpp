@@ -205,14 +205,15 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
   for (int64_t r0 = 0; r0 < rows; r0 += batch) {
     const int32_t n = (int32_t) std::min(batch, rows - r0);
     const bool by_rows = weights_by_rows(groups->V, n);      // statistics and table in one launch
-    if (r0 == 0) tm.begin(kStageStats);
+    if (r0 == 0 && !by_rows) tm.begin(kStageStats);
     RowSet some = rs;
     some.base0 = static_cast<const char *>(logits) + r0 * row_stride * (bf16 ? 2 : 4);
     some.nrows0 = n;
     if (!by_rows &&
         (e = launch_weights_parts(some, bf16, groups->V, n, f.c, f.c_lo, parts, stream)) != hipSuccess)
       return hip_fail(e);
-    if (r0 == 0) { tm.end(kStageStats); tm.begin(kStageTable); }
+    if (r0 == 0 && !by_rows) tm.end(kStageStats);
+    if (r0 == 0) tm.begin(kStageTable);
     e = by_rows ? launch_row_weights(some, bf16, *groups, n, f.c, f.c_lo, f.cd, table, stream)
                 : launch_weights(some, bf16, *groups, n, f.c, f.c_lo, f.cd, parts, table, stream);
     if (e != hipSuccess) return hip_fail(e);

@@ -511,3 +511,18 @@ def test_rows_of_calls_of_different_sizes(V, n, some, weighted, dtype):
     (16384, 16384, 12, 1, 2, False), (12001, 12001, 64, 40, 1, False)])
 def test_few_sequences_of_one_chunk(V, G, size, B, K, weighted):
     check_step(V, G, size, B, K, "bf16", layout="prepared", weighted=weighted, thinning=False)
+
+
+@pytest.mark.parametrize("V,n,by_rows", [(4096, 3, True), (20000, 2, False), (65536, 257, True), (65536, 100, False)])
+def test_stage_times_of_group_probs(V, n, by_rows):
+    """Statistics and table by one kernel are one stage; by two, two.  Of the first batch."""
+    rp, mem = W.random_groups(V, 500, 1, 9, seed=1)
+    dg = pcg.Groups.from_csr(V, rp, mem, "cuda")
+    x = torch.randn((n, V), device="cuda")
+    pcg.group_probs(dg, x)
+    pcg.profile_begin(3)
+    for _ in range(3):
+        pcg.group_probs(dg, x)
+    ms, calls = pcg.profile_end()
+    assert calls == 3 and (ms["row_stats"] == 0.0) == by_rows
+    assert ms["weights"] > ms["event_overhead"] > 0.0 and ms["gather"] > ms["event_overhead"] and ms["finalize"] == 0.0
