@@ -41,8 +41,11 @@ def test_no_kernel_uses_scratch():
     found = kernels(pcg.lib_path())
     names = {k[".name"] for k in found}
     for part in ("row_stats_kernel", "accept_delta_kernel", "gather_kernel", "gather_prepared_kernel", "finalize_kernel",
-                 "small_step_kernel", "accept_thin_kernel", "propose_row_kernel", "weights_kernel", "asg_similarity_kernel"):
-        assert any(part in n for n in names), part
+                 "finalize_sums_kernel", "small_step_kernel", "accept_thin_kernel", "propose_row_kernel", "propose_kernel",
+                 "row_weights_kernel", "weights_parts_kernel", "weights_kernel", "asg_normalize_kernel",
+                 "asg_similarity_kernel", "asg_refine_kernel", "asg_sort_kernel", "asg_compact_kernel"):
+        # as a whole name: mangled, its length stands in front of it
+        assert any(f"{len(part)}{part}" in n for n in names), part
     bad = [(k[".name"], k[".vgpr_count"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in found
            if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"] or k.get(".uses_dynamic_stack")]
     assert not bad, f"{len(bad)} of {len(found)} kernels: {bad[:3]}"
