@@ -45,3 +45,16 @@ def test_launches_of_a_small_step(V, members, weighted, B, K, launches):
 @pytest.mark.parametrize("V,members,B,launches", [(8192, 32, 1, 2), (12000, 16, 64, 4), (16384, 100, 8, 4), (8192, 64, 128, 2)])
 def test_launches_where_there_are_chunks(V, members, B, launches):
     assert routes.step_launches(V, V, V * members, False, B, 8, (V + 4095) // 4096, V * members) == launches
+
+
+def test_the_calls_compared_on_the_gpu_take_both_routes():
+    """The sizes of the GPU tests around the lines of few rows lie on the sides they were chosen for."""
+    import test_gpu_edges as edges
+    params = lambda f: next(m.args[1] for m in f.pytestmark if m.name == "parametrize")
+    steps = [routes.step_from_csr(V, G, nnz_of(G, (1, size)), w, B, K) for V, G, size, B, K, _, w in params(edges.test_few_rows)]
+    assert steps == [True] * 4 + [False, True, False, True, True, True, False, False, False, False]
+    rows = [routes.rows_from_csr(V, V, V * size, False, n) for V, size, n in params(edges.test_few_rows_of_groups_of_one_size)]
+    assert rows == [True, False, True, False, True]
+    some = [routes.rows_from_csr(V, V, nnz_of(V, (1, 12)), w, n)
+            for V, _, n, w in params(edges.test_rows_of_calls_of_different_sizes)]
+    assert not any(some)
