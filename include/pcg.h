@@ -105,7 +105,8 @@ typedef struct {
    * gives the same results but re-reads the 4-byte member ids from L2 for every row: at
    * V = G = 65 536 with 32-member groups and 64 sequences a step takes about 0.21 ms from the
    * CSR against about 0.07 ms from the prepared form.  (For a few rows the library may read the CSR
-   * although the prepared form is there, where that is faster.) */
+   * although the prepared form is there, where that is faster.)  The two sum a group's members in different
+   * orders, so that sums differ in their last bits; see pcg_group_probs. */
   const void *prepared;
   const pcg_prepared *prepared_info;
   /* Optional reverse index token -> groups (the paper's S(t); see pcg_groups_reverse_host),
@@ -188,6 +189,10 @@ typedef struct {
  * Accuracy: a group's sum is one float32 running sum over its entries, so next to the 1e-5
  * relative error of the terms themselves it carries up to n 2^-24 of rounding for a group of n
  * entries (measured: within 1e-5 in total for groups of up to a few hundred entries).
+ * Rows of one call that hold the same logits give the same sums, to the bit.  Between calls the number of
+ * rows can decide how a membership is read (a few rows from the CSR, more from `prepared`; from the CSR,
+ * by how many lanes and in how many tiles), and with it the order in which members are added: the last bits of
+ * a row's sums may then differ from call to call.  The terms themselves do not depend on it.
  */
 int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, int64_t rows,
                     int64_t row_stride, float temperature, float *out, void *workspace,
@@ -220,6 +225,9 @@ size_t pcg_group_probs_workspace_bytes(int32_t V, int64_t rows);
  * rejects).  Inverse-CDF draws take the first index whose running sum strictly exceeds
  * u * total; zero-mass groups and tokens are never chosen.  The accept test never reads
  * prop_tokens, so token-in-group consistency of the proposal is the caller's business.
+ * The number of sequences decides among kernels that add up the same terms in different orders, so
+ * that a draw within rounding of a threshold (those that diag counts as near) may come out
+ * differently for the same sequence in a batch of another size.
  * B == 0 is a no-op; 1 <= K <= PCG_MAX_K.
  */
 int pcg_verify(const pcg_groups *groups, const void *target_logits, const void *draft_logits,
@@ -351,7 +359,8 @@ int pcg_asg_normalize(const float *emb, int32_t V, int32_t d, uint16_t *unit_bf1
  * product with t's above theta (fp32 accumulation of the exact bf16 products), and t itself;
  * the distinct sets, each once, in order of first appearance (ascending t), as the CSR that
  * pcg_groups reads: members ascending inside a group, mult = entry counts.
- *   unit_bf16     DEVICE uint16 [V, d], 16-byte aligned, d a multiple of 64, V * d < 2^31
+ *   unit_bf16     DEVICE uint16 [V, d], 16-byte aligned, d a multiple of 64, V * d < 2^31, V <= 16 776 960
+ *                 (65 535 tiles of 256 tokens; PCG_ERR_BAD_SHAPE beyond)
  *   theta         strict threshold of Eq. (1); values below -1 put everything in one group
  *   cap           room for one group while it is collected, 1 .. PCG_ASG_MAX_CAP
  *   row_ptr       DEVICE int32 [V + 1]: the first *out_G + 1 entries are written
@@ -380,7 +389,7 @@ size_t pcg_asg_build_workspace_bytes(int32_t V, int32_t cap);
  * farthest that rounding has moved any of the unit vectors (measured; typically 2.1e-4: the band is how
  * far rounding and summing in fp32 can move it), is decided by the double-precision
  * cosine, every other pair by the rounded one.  Outputs, order of the groups, waiting for the
- * stream and PCG_ERR_CAPACITY as for pcg_asg_build, except that cap must hold every candidate
+ * stream, PCG_ERR_CAPACITY and the limit on V as for pcg_asg_build, except that cap must hold every candidate
  * of a group (the pairs above theta minus that band) while it is collected; *out_max_size is
  * the largest G(t) after the decision when everything fitted.
  *   emb           DEVICE float [V, d], 16-byte aligned, d a multiple of 64, V * d < 2^31

@@ -640,10 +640,12 @@ int pcg_verify_thinning(const pcg_groups *groups, const void *target_logits,
   hipError_t e;
   tm.begin(kStageStats);
   // Cached pass: every trial is a chain of small reads into the same rows.  Streamed for large batches of bf16 logits,
-  // of which a trial reads half the bytes again.  Whole calls in us, cached and streamed, on logits last touched
-  // 430 MB or more ago, and repeated on the same:
-  //   bf16, V = 65 536, K = 8:  111 MB 33.8 and 33.5, 31.4 and 29.7;  143 MB 39.3 and 38.3, 35.5 and 34.8;  178 MB 45.1 and
-  //             43.2, 40.5 and 40.5
+  // of which a trial reads half the bytes again; what that gives shows on logits that are still in the caches, on others it
+  // is within what two runs differ by.  Whole calls in us, cached and streamed, on four sets of logits in turn, and repeated
+  // on the same:
+  //   bf16, V = 65 536, K = 8:  111 MB 33.4 and 33.3, 31.0 and 29.7;  125 MB 35.9 and 35.5, 33.3 and 32.0;  143 MB 46.3 and
+  //             46.9, 43.3 and 41.9;  178 MB 44.2 and 43.0, 40.1 and 40.8;  V = 32 768:  111 MB 32.7 and 33.3, 31.0 and 30.6;
+  //             V = 40 000:  174 MB 44.2 and 44.2, 40.6 and 42.8
   //   fp32, V = 32 768, K = 6:  109 MB 34.1 and 34.9, 31.0 and 30.4;  179 MB 50.1 and 49.7, 41.4 and 42.7;  218 MB 56.5 and
   //             55.0, 54.2 and 56.0;  V = 65 536, K = 8:  160 MB 47.6 and 48.2, 39.6 and 38.4
   const bool streaming = bf16 && rows * V * 2 > kStreamBytes;

@@ -23,7 +23,8 @@ constexpr size_t kAsgAlign = 256;
 size_t asg_align(size_t n) { return (n + kAsgAlign - 1) / kAsgAlign * kAsgAlign; }
 
 // ---------------------------------------------------------------------------------------------
-// Unit vectors: emb[v] / ||emb[v]|| in double, rounded once to bfloat16 (nearest, ties to even).
+// Unit vectors: emb[v] / ||emb[v]|| in double, rounded once to bfloat16 (nearest, ties to even); for the exact form, whose
+// filter they are, to fp32, times 2^8 and to fp16, with what is then subnormal set to 0.
 // ---------------------------------------------------------------------------------------------
 
 __device__ __forceinline__ uint16_t round_to_bf16(double x) {
@@ -530,10 +531,10 @@ __global__ __launch_bounds__(kSimThreads, 1) void asg_similarity_kernel(
 // wave's own pairs are those with a larger token, whatever has happened to the others it reads.
 // The wave's own row stays in registers (up to kRowRegs * 256 elements), the other's comes from
 // memory, with its norm and the first 64 entries of its list, while the pair before is summed.  Bound
-// by the gather of those rows, 4 d bytes a pair: 65 536 x 1024, 0.7 M undecided pairs, 471 us (1711
-// when both tokens' waves computed each pair and read both rows for it).  With few tokens, all of whose
-// waves run at once, it is the longest chain of pairs that counts: 2048 x 128 5.1 us (5.3 with the
-// list fetched after the sum).
+// by the gather of those rows, 4 d bytes a pair: 65 536 x 1024, 0.12 M undecided pairs, 119 us (with the
+// 0.7 M of a filter in bf16 471, and 1711 when both tokens' waves computed each pair and read both rows for
+// it).  With few tokens, all of whose waves run at once, it is the longest chain of pairs that counts: 2048 x 128,
+// bf16 filter, 5.1 us (5.3 with the list fetched after the sum).
 // Lists that did not fit into cap stay undecided: their count stays above cap and the call reports
 // PCG_ERR_CAPACITY.
 // ---------------------------------------------------------------------------------------------

@@ -2824,9 +2824,11 @@ CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max
   const double mean = (double) nnz / (double) G;
   p.width = 2;
   while (p.width < 16 && 4 * p.width < mean) p.width *= 2;
-  // More lanes for long groups only where every workgroup then has one pass and they all run at once (a
-  // row's workgroups share the 32 compute units of an XCD): V = 4096, 100 members, 8 rows 6.0 us with 32, 8.1
-  // with 16.  Elsewhere it loses: 32 rows 31.4 and 30.6, V = 20 000, 1 row 54.7 and 49.6.
+  // More lanes for long groups only where G times an XCD's rows is one pass of its 32 compute units: there they were
+  // never behind.  Calls with 16 lanes and with 32 (V, members, rows): 4096, 100, 1: 21.1 and 19.8;  2048, 1 to 128 with weights,
+  // 2: 19.1 and 17.9;  4096, 40, 1: 18.4 and 18.4.  Beyond, gains (20 000, 100, 1: 24.7 and 24.1;  8192, 100, 1: 24.5 and 23.1) and
+  // losses (16 384, 40, 16: 27.9 and 33.2;  30 000, 40 with weights, 4: 25.3 and 28.8;  65 536, 140, 2: 57.4 and 64.3) mix: of 640
+  // shapes 148 gain more than 2 %, 382 lose as much.
   const int64_t rows_per_xcd = (nrows + 7) / 8;
   if (mean > 32 && (int64_t) G * rows_per_xcd <= 32 * 4 * (kGatherThreads / 32)) p.width = 32;
   // Chunks per row: a workgroup for every compute unit, each with at least one pass of groups, at most
@@ -2852,9 +2854,9 @@ CsrShape step_csr_shape(const pcg_groups &g, int32_t B, int32_t K) {
 // How the XCDs share rows and chunks.  All chunks of a row on one XCD, unless another split saves each of them 1 MiB
 // to bring in (the rows, which everything waits for, counted twice).  Whole calls, or the gather alone, in us, all
 // on one and split (V, members, rows):
-//   prepared:  65 536, 32, 8: gather 15.8 and 14.3;  16: 15.8 and 14.7;  weights, 16: 26.2 and 20.6, 64: 50.7 and 46.6;
-//              64 (no saving): 25.4 and 27.0;  32 768, 1 to 128, 128 (none): 47.6 and 51.9
-//   CSR:       65 536, 32, 1: call 58.8 and 25.9;  30 000, 100, 8: 49.7 and 38.7;  16 384, 32, 32 (0.5 MiB): gather 12.6 and
+//   prepared:  65 536, 32, 8: call 34.0 and 32.8;  16: 37.1 and 35.7;  weights, 16: 47.5 and 40.8, 64: 88.3 and 87.3 (gather 46.8 and
+//              44.9);  64 (no saving): gather 25.4 and 27.0;  32 768, 1 to 128, 128 (none): 47.6 and 51.9
+//   CSR:       65 536, 32, 1: call 54.7 and 25.6;  30 000, 100, 8: 48.5 and 37.8;  16 384, 32, 32 (0.5 MiB): gather 12.6 and
 //              12.2, but finalize, which finds a row's totals in its own XCD's L2 if they were formed there, 6.2 and 6.5
 static GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes) {
   GatherMap best{3, nchunks};
