@@ -1179,9 +1179,9 @@ __device__ __forceinline__ void store_piece(float *out, const f32x4_any v, int32
 // A row by one workgroup: its exponentials stay in registers until its total is known.  NP: row parts a wave holds (64
 // exponentials a lane with two; longer rows take the two kernels below).  A row is read once and its
 // exponentials are formed once, where the two kernels read it twice and form them twice.  256 rows of 65 536
-// bf16 logits 26.0 us against 6.3 + 27.4, fp32 29.4 against 11.7 + 29.5; what is written (67 MB) and read takes 20 at
-// the rate of a copy, and one row, by one compute unit, 17: 20 issue slots an element, of which the
-// exponential and the reciprocal of N(t) take four each.
+// bf16 logits 19.7 us against 7.5 + 20.2, fp32 24.3 against 11.4 + 21.9; what is written (67 MB) and read takes 20 and 27 at
+// the rate of a copy.  64 rows, which leave most of the chip to others, take 16.2 against 4.2 + 10.3: a row's instructions on
+// one compute unit, of which the exponential and the reciprocal of N(t) take four issue slots each.
 constexpr int kRowTableThreads = 1024;
 constexpr int kRowTableParts = 2 * kRowTableThreads / kWave;      // V <= 65 536
 
