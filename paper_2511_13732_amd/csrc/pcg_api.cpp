@@ -218,7 +218,8 @@ int pcg_group_probs(const pcg_groups *groups, const void *logits, pcg_dtype dt, 
                 : launch_weights(some, bf16, *groups, n, f.c, f.c_lo, f.cd, parts, table, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (r0 == 0) { tm.end(kStageTable); tm.begin(kStageGather); }
-    CsrShape cut = csr_shape(groups->V, groups->G, groups->nnz, n, 256);      // no larger chunks than `first`
+    CsrShape cut = csr_shape(groups->V, groups->G, groups->nnz, n, 256);
+    if (cut.chunk_groups > first.chunk_groups) cut = first;      // the LDS beside a tile of `first` holds no more sums
     cut.width = first.width;
     cut.ntiles = first.ntiles;
     cut.tile_len = first.tile_len;

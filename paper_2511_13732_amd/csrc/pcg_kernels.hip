@@ -2834,17 +2834,30 @@ CsrShape csr_shape(int32_t V, int32_t G, int64_t nnz, int64_t nrows, int64_t max
   // Chunks per row: a workgroup for every compute unit, each with at least one pass of groups, at most
   // kMaxChunkGroups and, where that allows it, at most max_chunks.
   const int64_t pass = 4 * (kGatherThreads / p.width);
-  int64_t nchunks = std::min<int64_t>({csr_chunks_at_once(nrows), max_chunks, (G + pass - 1) / pass});
-  nchunks = std::max<int64_t>(nchunks, ((int64_t) G + kMaxChunkGroups - 1) / kMaxChunkGroups);
-  int64_t gpc = (G + nchunks - 1) / nchunks;
-  gpc = (gpc + kRunGroups - 1) / kRunGroups * kRunGroups;
-  p.chunk_groups = (int32_t) gpc;
-  p.nchunks = (int32_t) ((G + gpc - 1) / gpc);
-  // LDS: the chunk's sums, then as much of the table row as fits (a tile and its zero slot)
-  const int32_t room = (kTileMax - p.chunk_groups - 64) / 64 * 64;
-  p.ntiles = (V + room - 1) / room;
-  p.tile_len = std::min(room, ((V + p.ntiles - 1) / p.ntiles + 63) / 64 * 64);
-  return p;
+  auto cut = [&](int64_t want) {
+    CsrShape c = p;
+    int64_t nchunks = std::min<int64_t>({want, max_chunks, (G + pass - 1) / pass});
+    nchunks = std::max<int64_t>(nchunks, ((int64_t) G + kMaxChunkGroups - 1) / kMaxChunkGroups);
+    int64_t gpc = (G + nchunks - 1) / nchunks;
+    gpc = (gpc + kRunGroups - 1) / kRunGroups * kRunGroups;
+    c.chunk_groups = (int32_t) gpc;
+    c.nchunks = (int32_t) ((G + gpc - 1) / gpc);
+    // LDS: the chunk's sums, then as much of the table row as fits (a tile and its zero slot)
+    const int32_t room = (kTileMax - c.chunk_groups - 64) / 64 * 64;
+    c.ntiles = (V + room - 1) / room;
+    c.tile_len = std::min(room, ((V + c.ntiles - 1) / c.ntiles + 63) / 64 * 64);
+    return c;
+  };
+  // As many chunks as all run at once, or a few more of them, the last in a second turn, where those leave room for a larger
+  // tile: every tile walks all entries of a chunk.  A workgroup's walks, and in us (V, members, rows; at once and more):
+  //   two tiles and one:    30 592, 68, 70: 2 x G / 3 and 2 turns of G / 4: 249 and 164;  33 720, 133, 55: 2 x G / 4 and 2 of G / 5:
+  //                         323 and 248;  31 736, 1 to 128, 84: 2 x G / 2 and 2 of G / 4: 361 and 163;  29 706, 4, 127: 47.5 and 35.7
+  //   three tiles and two:  57 588, 1 to 128, 49: 3 x G / 4 and 2 x 2 of G / 6: 523 and 475;  48 918, 64, 75: 3 x G / 3 and 2 x 2 of G / 4: 382
+  //                         and 382;  60 411, 32, 44: 3 x G / 5 and 2 x 2 of G / 6: 160 and 178
+  const int64_t at_once = csr_chunks_at_once(nrows);
+  auto walks = [&](const CsrShape &c) { return (int64_t) c.ntiles * c.chunk_groups * (c.nchunks > at_once ? 2 : 1); };
+  const CsrShape one = cut(at_once), two = cut((256 + nrows - 1) / nrows);
+  return two.ntiles < one.ntiles && walks(two) < walks(one) ? two : one;
 }
 
 CsrShape step_csr_shape(const pcg_groups &g, int32_t B, int32_t K) {

@@ -526,3 +526,10 @@ def test_stage_times_of_group_probs(V, n, by_rows):
     ms, calls = pcg.profile_end()
     assert calls == 3 and (ms["row_stats"] == 0.0) == by_rows
     assert ms["weights"] > ms["event_overhead"] > 0.0 and ms["gather"] > ms["event_overhead"] and ms["finalize"] == 0.0
+
+
+# from the CSR: more chunks of a row than run at once, the last in a second turn, where those spare a tile
+@pytest.mark.parametrize("V,G,size,B,weighted", [(28980, 28980, 7, 101, False), (29706, 29000, 4, 127, True), (48852, 48852, 4, 85, False),
+                                                 (27001, 27000, 12, 93, False)])
+def test_chunks_that_spare_a_tile(V, G, size, B, weighted):
+    check_step(V, G, size, B, 1, "bf16", layout="csr", weighted=weighted, thinning=False)

@@ -58,3 +58,24 @@ def test_the_calls_compared_on_the_gpu_take_both_routes():
     some = [routes.rows_from_csr(V, V, nnz_of(V, (1, 12)), w, n)
             for V, _, n, w in params(edges.test_rows_of_calls_of_different_sizes)]
     assert not any(some)
+
+
+# chunks of groups and tiles of the vocabulary from the CSR: a few chunks more than run at once where they spare a tile
+@pytest.mark.parametrize("V,members,rows,chunks,tiles", [
+    (30592, 68, 70, 4, 1), (33720, 133, 55, 5, 1), (27744, 10, 93, 3, 1), (28980, 7, 101, 3, 1), (29706, 4, 127, 3, 1),
+    (57588, 64, 49, 6, 2), (60411, 32, 44, 5, 3), (58163, 32, 46, 5, 3), (48852, 4, 85, 4, 2), (20000, 32, 12, 20, 1), (16384, 32, 32, 8, 1)])
+def test_chunks_and_tiles_from_the_csr(V, members, rows, chunks, tiles):
+    c = routes.csr_shape(V, V, V * members, rows, 256)
+    assert (c.nchunks, c.ntiles) == (chunks, tiles)
+    assert c.nchunks * c.chunk_groups >= V and c.ntiles * c.tile_len >= V and c.chunk_groups + c.tile_len + 64 <= 40704
+
+
+def test_every_cut_of_the_csr_fits():
+    """Chunks and tiles cover groups and tokens, and a chunk's sums and a tile fit the LDS together, at any number of rows."""
+    for V in (1, 63, 64, 4097, 20000, 27000, 30592, 33720, 40576, 40640, 40704, 65536, 81000, 131072, 1000003):
+        for G in (1, 33, 4097, 16384, 16385, 30000, V):
+            for rows in list(range(1, 140)) + [200, 255, 256, 257, 4096]:
+                for mean in (1, 40):
+                    c = routes.csr_shape(V, G, G * mean, rows, 256)
+                    assert c.nchunks * c.chunk_groups >= G > (c.nchunks - 1) * c.chunk_groups and c.chunk_groups % 16 == 0
+                    assert c.ntiles * c.tile_len >= V and c.chunk_groups + c.tile_len + 64 <= 40704 and c.chunk_groups <= 16384
