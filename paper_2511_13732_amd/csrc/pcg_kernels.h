@@ -53,6 +53,13 @@ bool weights_by_rows(int32_t V, int32_t nrows);
 hipError_t launch_row_weights(const RowSet &rs, bool bf16, const pcg_groups &g, int32_t nrows, float c, float c_lo, double cd,
                               float *table, hipStream_t stream);
 
+// How the XCDs share the rows and chunks of a gather: 2^row_shift parts of the rows, 8 / 2^row_shift of the chunks.
+struct GatherMap {
+  int32_t row_shift;
+  int32_t chunks_each;                  // of an XCD, at most
+};
+GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes, int32_t row_cost);
+
 // How the CSR gather cuts `nrows` rows: lanes per group, chunks of consecutive groups (a multiple of
 // kRunGroups; no more of them than max_chunks or ceil(G / kMaxChunkGroups)), tiles of the vocabulary.
 struct CsrShape {

@@ -52,3 +52,12 @@ def step_launches(V, G, nnz, weighted, B, K, nchunks, slots):
                         bytes=(6 if weighted else 2) * slots)
     g = _groups(V, G, nnz, weighted, info)
     return {0: 1, 1: 2, 2: 4}[f(C.addressof(g), B, K)]
+
+
+class GatherMap(C.Structure):
+    _fields_ = [("row_shift", C.c_int32), ("chunks_each", C.c_int32)]
+
+
+def gather_map(nrows, nchunks, row_bytes, chunk_bytes, row_cost):
+    return _function("_ZN3pcg10gather_mapEiilli", GatherMap, C.c_int32, C.c_int32, C.c_int64, C.c_int64, C.c_int32)(
+        nrows, nchunks, row_bytes, chunk_bytes, row_cost)

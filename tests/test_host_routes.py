@@ -79,3 +79,32 @@ def test_every_cut_of_the_csr_fits():
                     c = routes.csr_shape(V, G, G * mean, rows, 256)
                     assert c.nchunks * c.chunk_groups >= G > (c.nchunks - 1) * c.chunk_groups and c.chunk_groups % 16 == 0
                     assert c.ntiles * c.tile_len >= V and c.chunk_groups + c.tile_len + 64 <= 40704 and c.chunk_groups <= 16384
+
+
+# the split over the XCDs of a gather over the prepared layout (slots without padding): as many parts of the rows
+@pytest.mark.parametrize("V,members,weighted,rows,nchunks,parts", [
+    (65536, 32, False, 64, 4, 8), (65536, 32, True, 16, 4, (1, 2)), (65536, 32, False, 8, 8, (1, 2, 4)), (32768, 64, False, 128, 2, 8),
+    # not all at once: the split that leaves the least to the last turn, or saves bytes and leaves no more
+    (50945, 64, True, 49, 5, 8), (50464, 94, False, 33, 7, 8), (50979, 123, False, 38, 7, 8), (35648, 117, False, 54, 5, 8),
+    (36772, 115, False, 56, 5, 8), (25336, 24, False, 33, 7, 8), (51092, 128, False, 19, 13, 4), (65507, 32, True, 17, 16, (1, 2))])
+def test_split_over_the_chip(V, members, weighted, rows, nchunks, parts):
+    m = routes.gather_map(rows, nchunks, 4 * V, V * members * (6 if weighted else 2) // nchunks, 2 if weighted else 4)
+    assert (1 << m.row_shift) in (parts if isinstance(parts, tuple) else (parts,))
+
+
+def test_every_split_reaches_every_row_and_chunk():
+    """The kernels' arithmetic on every workgroup of the grid: each (row, chunk) once."""
+    for rows in list(range(1, 40)) + [63, 64, 65, 128, 257]:
+        for nchunks in (1, 2, 3, 5, 7, 8, 9, 16, 33):
+            for row_bytes, chunk_bytes in ((4096, 1 << 22), (262144, 1 << 20), (1 << 20, 64)):
+                m = routes.gather_map(rows, nchunks, row_bytes, chunk_bytes, 4)
+                grid = 8 * -(-rows // (1 << m.row_shift)) * m.chunks_each
+                seen = []
+                for b in range(grid):
+                    xcd, y = b & 7, b >> 3
+                    turn = y // m.chunks_each
+                    row = (xcd & ((1 << m.row_shift) - 1)) + (turn << m.row_shift)
+                    chunk = (xcd >> m.row_shift) + ((y - turn * m.chunks_each) << (3 - m.row_shift))
+                    if row < rows and chunk < nchunks:
+                        seen.append((row, chunk))
+                assert sorted(seen) == [(r, c) for r in range(rows) for c in range(nchunks)]
