@@ -3045,18 +3045,22 @@ StepShape step_shape(const pcg_groups &g, int32_t B, int32_t K) {
     const CsrShape cut = step_csr_shape(g, B, K);
     return !csr_is_faster(g, cut) || load <= 176 + 30 * (csr_turns(cut) - 1) ? small : StepShape::kFour;
   }
-  // The CSR is read by 256 sub-waves of four lanes: trips are the turns of 1024 groups times those of 16
-  // entries that the mean group needs.  The four kernels spread them.
-  //   B < 128:  2 trips: 1024, 32, 16: 18.3 and 16.0, 2048, 16, 16: 18.5 and 16.2;  4 and 5, one a turn: 4096, 16, 16:
-  //             20.4 and 19.4, 5000, 4, 32, K = 1: 23.2 and 20.2, K = 3: 22.8 and 21.6;  4, two a turn and more: 2048,
-  //             32, 16: 18.5 and 19.2, 1024, 64, 1: 17.0 and 17.7;  8: 8192, 4, 16: 23.0 and 26.3, K = 1: 23.0 and
-  //             25.2, 4096, 24, 16: 20.4 and 24.8
-  //   B = 128:  8 trips, up to 4096 groups: 4096, 24: 29.5 and 27.0, 1024, 128: 25.4 and 23.9, 2048, 64: 26.3 and 23.9;
-  //             beyond: 8192, 4: 30.2 and 31.3, 12 000, 8 with weights: 39.6 and 45.3;  16: 4096, 64 with weights:
-  //             42.2 and 46.7
+  // The CSR is read by 256 sub-waves of four lanes: a turn takes 1024 groups, and a trip in it 16 entries of each (as many
+  // trips as the mean group needs; four parts of a load of five for one).  The four kernels spread them over the chip, the less
+  // of it the more sequences there are.
+  //   load, B <= 64:   17: 1000, 64, 1: 16.0 and 14.7, 16: 17.4 and 15.2;  18: 2048, 24, 16: 17.2 and 15.7, with weights, 1: 16.2 and
+  //                    16.4;  20: 4096, 16, 16: 18.8 and 16.2, with weights, 1: 17.7 and 17.4;  25: 5000, 16, 1: 18.5 and 18.0, with weights,
+  //                    1: 18.7 and 19.4, K = 1, 64: 22.6 and 18.5;  27: 3000, 32, 1: 16.5 and 18.3, 64: 20.6 and 19.7;  29: 1000, 100, 1:
+  //                    17.1 and 18.4;  30: 6000, 8, 1: 19.1 and 19.3
+  //   65 to 96:        26: 2048, 48, 80: 21.3 and 17.8;  27: 3072, 32 with weights, 80: 21.8 and 22.0;  30: 6144, 12, 80: 23.1 and 21.0,
+  //                    4 with weights, 80: 22.0 and 23.2;  35: 7168, 4 with weights, 80: 25.1 and 26.1
+  //   97 to 128:       34: 2048, 64, 128: 23.9 and 19.8;  36: 4096, 32, 128: 26.7 and 24.2, with weights 29.0 and 28.6;  39: 3072, 48, 128:
+  //                    28.5 and 25.4;  40: 8192, 4, 128: 27.6 and 27.9, with weights 28.4 and 31.9;  45: 5120, 32 with weights, 128:
+  //                    32.7 and 34.8
+  // Groups far above the mean are not in it: 1130 tokens, 416 groups of 75 and some of 1000, weights, 64: 20.9 and 23.7.
   const int64_t turns = (g.G + 1023) / 1024, per_turn = (g.nnz + 16 * (int64_t) g.G - 1) / (16 * (int64_t) g.G);
-  const bool few = B == 128 ? g.G <= 4096 && turns * per_turn <= 8
-                            : turns * per_turn <= (per_turn > 1 ? 3 : one ? 5 : 4);
+  const int64_t load = turns * (4 * per_turn + 1);
+  const bool few = load <= (B <= 64 ? (g.weights && !one ? 21 : 25) : B <= 96 ? (g.weights ? 29 : 30) : (g.weights ? 36 : 39));
   return few ? small : StepShape::kFour;
 }
 

@@ -54,6 +54,13 @@ def step_launches(V, G, nnz, weighted, B, K, nchunks, slots):
     return {0: 1, 1: 2, 2: 4}[f(C.addressof(g), B, K)]
 
 
+def csr_step_launches(V, G, nnz, weighted, B, K):
+    """Launches of a pcg_verify step from the CSR."""
+    f = _function("_ZN3pcg10step_shapeERK10pcg_groupsii", C.c_int, C.c_void_p, C.c_int32, C.c_int32)
+    g = _groups(V, G, nnz, weighted)
+    return {0: 1, 1: 2, 2: 4}[f(C.addressof(g), B, K)]
+
+
 class GatherMap(C.Structure):
     _fields_ = [("row_shift", C.c_int32), ("chunks_each", C.c_int32)]
 

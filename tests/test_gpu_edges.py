@@ -533,3 +533,12 @@ def test_stage_times_of_group_probs(V, n, by_rows):
                                                  (27001, 27000, 12, 93, False)])
 def test_chunks_that_spare_a_tile(V, G, size, B, weighted):
     check_step(V, G, size, B, 1, "bf16", layout="csr", weighted=weighted, thinning=False)
+
+
+# from the CSR by one workgroup a sequence: the most trips it takes
+@pytest.mark.parametrize("V,G,size,B,K,dtype,weighted", [
+    (1024, 1024, 120, 5, 8, "f32", False), (2047, 2040, 60, 33, 4, "bf16", True), (5003, 5003, 25, 20, 8, "bf16", False),
+    (6100, 6001, 20, 70, 5, "bf16", False), (4096, 4096, 60, 100, 2, "f32", True), (7168, 7168, 12, 97, 4, "bf16", False),
+    (700, 640, 260, 100, 2, "bf16", False)])
+def test_small_steps_from_the_csr(V, G, size, B, K, dtype, weighted):
+    check_step(V, G, size, B, K, dtype, layout="csr", weighted=weighted, thinning=False)

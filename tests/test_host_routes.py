@@ -47,6 +47,17 @@ def test_launches_where_there_are_chunks(V, members, B, launches):
     assert routes.step_launches(V, V, V * members, False, B, 8, (V + 4095) // 4096, V * members) == launches
 
 
+# from the CSR: one workgroup a sequence, or four launches where that has too many trips
+@pytest.mark.parametrize("V,members,weighted,B,K,launches", [
+    (1000, 64, False, 16, 8, 1), (2048, 24, False, 16, 8, 1), (2048, 24, True, 64, 8, 1), (4096, 16, True, 16, 8, 2),
+    (5000, 16, False, 1, 8, 2), (5000, 16, True, 1, 8, 4), (5000, 16, True, 64, 1, 1), (3000, 32, False, 16, 8, 4),
+    (1000, 100, False, 1, 8, 4), (6000, 8, False, 1, 8, 4), (6144, 12, False, 80, 8, 2), (6144, 4, True, 80, 8, 4),
+    (5120, 12, True, 80, 8, 2), (7168, 4, False, 80, 8, 4), (7168, 12, False, 128, 8, 2), (3072, 48, False, 128, 8, 2),
+    (4096, 32, True, 128, 8, 2), (8192, 4, False, 128, 8, 4), (5120, 32, True, 128, 8, 4), (12000, 8, False, 130, 8, 1)])
+def test_launches_of_a_small_step_from_the_csr(V, members, weighted, B, K, launches):
+    assert routes.csr_step_launches(V, V, V * members, weighted, B, K) == launches
+
+
 def test_the_calls_compared_on_the_gpu_take_both_routes():
     """The sizes of the GPU tests around the lines of few rows lie on the sides they were chosen for."""
     import test_gpu_edges as edges
@@ -55,6 +66,8 @@ def test_the_calls_compared_on_the_gpu_take_both_routes():
     assert steps == [True] * 4 + [False, True, False, True, True, True, False, False, False, False]
     rows = [routes.rows_from_csr(V, V, V * size, False, n) for V, size, n in params(edges.test_few_rows_of_groups_of_one_size)]
     assert rows == [True, False, True, False, True]
+    small = [routes.csr_step_launches(V, G, nnz_of(G, (1, size)), w, B, K) for V, G, size, B, K, _, w in params(edges.test_small_steps_from_the_csr)]
+    assert small == [1, 1, 2, 2, 1, 2, 1]
     some = [routes.rows_from_csr(V, V, nnz_of(V, (1, 12)), w, n)
             for V, _, n, w in params(edges.test_rows_of_calls_of_different_sizes)]
     assert not any(some)
