@@ -58,7 +58,7 @@ struct GatherMap {
   int32_t row_shift;
   int32_t chunks_each;                  // of an XCD, at most
 };
-GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes, int32_t row_cost);
+GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes, bool csr, bool weights);
 
 // How the CSR gather cuts `nrows` rows: lanes per group, chunks of consecutive groups (a multiple of
 // kRunGroups; no more of them than max_chunks or ceil(G / kMaxChunkGroups)), tiles of the vocabulary.

@@ -2860,9 +2860,9 @@ CsrShape step_csr_shape(const pcg_groups &g, int32_t B, int32_t K) {
 }
 
 // How the XCDs share rows and chunks.  All chunks of a row on one XCD, unless another split saves each of them half a MiB
-// to bring in (the rows, which everything waits for, counted row_cost times: four, two beside a prepared stream with weights),
-// and, where not all workgroups run at once, leaves no more of them to the last turn.  Whole calls, or the gather alone, in us, all
-// on one and split (V, members, rows):
+// to bring in, a whole one from the CSR (the rows, which everything waits for, counted four times, twice beside a prepared stream
+// with weights), and, where not all workgroups run at once, from the prepared layout leaves no more of them to the last turn.  Whole
+// calls, or the gather alone, in us, all on one and split (V, members, rows):
 //   prepared:  65 536, 32, 8: call 34.0 and 32.8;  16: 37.1 and 35.7;  weights, 16: 47.5 and 40.8, 64: 88.3 and 87.3 (gather 46.8 and
 //              44.9);  64 (no saving): gather 25.4 and 27.0;  32 768, 1 to 128, 128 (none): 47.6 and 51.9;  59 549, 64, 18: 31.8 and 33.6
 //              (over two XCDs 32.3)
@@ -2870,8 +2870,10 @@ CsrShape step_csr_shape(const pcg_groups &g, int32_t B, int32_t K) {
 //              35 648, 117, 54 (18 or 34): 69.2 and 79.4;  51 092, 128, 19 (21 or 9): 50.5 and 43.0;  65 507, 1 to 64, 17 (16 either way):
 //              64.4 and 53.6
 //   CSR:       65 536, 32, 1: call 54.7 and 25.6;  30 000, 100, 8: 48.5 and 37.8;  16 384, 32, 32 (0.5 MiB): gather 12.6 and
-//              12.2, but finalize, which finds a row's totals in its own XCD's L2 if they were formed there, 6.2 and 6.5
-GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes, int32_t row_cost) {
+//              12.2, but finalize, which finds a row's totals in its own XCD's L2 if they were formed there, 6.2 and 6.5;  rows 14 987, 1 to 15 with weights, 1 (0.8): 12.3 and 13.1;
+//              turns: 28 456, 111 with weights, 86 (6 in a second turn, or 44): 300 and 288;  32 524, 72 with weights, 56 (24 or 40): 192 and 187
+GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t chunk_bytes, bool csr, bool weights) {
+  const int64_t row_cost = !csr && weights ? 2 : 4, saving = (int64_t) 1 << (csr ? 20 : 19);
   struct Split { int64_t turns, late, bytes; } best{}, one{};
   GatherMap map{3, nchunks};
   for (int32_t shift = 3; shift >= 0; --shift) {
@@ -2879,11 +2881,11 @@ GatherMap gather_map(int32_t nrows, int32_t nchunks, int64_t row_bytes, int64_t 
     Split s;
     s.turns = ((int64_t) rows * chunks + 31) / 32;         // of an XCD's compute units
     s.late = 0;                                            // workgroups in the last of several
-    for (int32_t x = 0; x < 8 && s.turns > 1; ++x) {
+    for (int32_t x = 0; x < 8 && s.turns > 1 && !csr; ++x) {
       const int64_t mine = (int64_t) ((nrows - (x & (rp - 1)) + rp - 1) / rp) * ((nchunks - (x >> shift) + cp - 1) / cp);
       s.late += std::max<int64_t>(0, mine - 32 * (s.turns - 1));
     }
-    s.bytes = row_cost * rows * row_bytes + chunks * chunk_bytes + (rp < 8 ? (int64_t) 1 << 19 : 0);
+    s.bytes = row_cost * rows * row_bytes + chunks * chunk_bytes + (rp < 8 ? saving : 0);
     if (shift == 3) { best = one = s; continue; }
     if (s.turns > one.turns || (s.turns == one.turns && s.late > one.late)) continue;
     if (s.turns < best.turns || (s.turns == best.turns && s.bytes < best.bytes)) {
@@ -2934,7 +2936,7 @@ bool csr_is_faster(const pcg_groups &g, const CsrShape &p) {
 hipError_t launch_gather(const pcg_groups &g, const CsrShape &p, int32_t nrows, const float *table, float *out,
                          double *csum, int64_t csum_stride, double *runs, hipStream_t stream) {
   if (nrows == 0) return hipSuccess;
-  const GatherMap map = gather_map(nrows, p.nchunks, (int64_t) g.V * 4, g.nnz * (g.weights ? 8 : 4) / p.nchunks, 4);
+  const GatherMap map = gather_map(nrows, p.nchunks, (int64_t) g.V * 4, g.nnz * (g.weights ? 8 : 4) / p.nchunks, true, g.weights);
   const dim3 grid(gather_grid(map, nrows));
   auto launch = [&](auto kernel) {
     kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, map, p.nchunks, p.chunk_groups, p.ntiles, p.tile_len,
@@ -2988,7 +2990,7 @@ hipError_t launch_gather_prepared(const pcg_groups &g, int32_t nrows, const floa
                                   double *csum, double *runs, hipStream_t stream) {
   if (nrows == 0) return hipSuccess;
   const PreparedView p = prepared_view(g);
-  const GatherMap map = gather_map(nrows, p.nchunks, (int64_t) g.V * 4, prepared_slot_bytes(g) / p.nchunks, g.weights ? 2 : 4);
+  const GatherMap map = gather_map(nrows, p.nchunks, (int64_t) g.V * 4, prepared_slot_bytes(g) / p.nchunks, false, g.weights);
   const dim3 grid(gather_grid(map, nrows));
   auto launch = [&](auto kernel) {
     kernel<<<grid, kGatherThreads, 0, stream>>>(g.V, g.G, nrows, map, p, table, out, csum, runs);

@@ -65,6 +65,6 @@ class GatherMap(C.Structure):
     _fields_ = [("row_shift", C.c_int32), ("chunks_each", C.c_int32)]
 
 
-def gather_map(nrows, nchunks, row_bytes, chunk_bytes, row_cost):
-    return _function("_ZN3pcg10gather_mapEiilli", GatherMap, C.c_int32, C.c_int32, C.c_int64, C.c_int64, C.c_int32)(
-        nrows, nchunks, row_bytes, chunk_bytes, row_cost)
+def gather_map(nrows, nchunks, row_bytes, chunk_bytes, csr, weighted):
+    return _function("_ZN3pcg10gather_mapEiillbb", GatherMap, C.c_int32, C.c_int32, C.c_int64, C.c_int64, C.c_bool, C.c_bool)(
+        nrows, nchunks, row_bytes, chunk_bytes, csr, weighted)

@@ -101,7 +101,17 @@ def test_every_cut_of_the_csr_fits():
     (50945, 64, True, 49, 5, 8), (50464, 94, False, 33, 7, 8), (50979, 123, False, 38, 7, 8), (35648, 117, False, 54, 5, 8),
     (36772, 115, False, 56, 5, 8), (25336, 24, False, 33, 7, 8), (51092, 128, False, 19, 13, 4), (65507, 32, True, 17, 16, (1, 2))])
 def test_split_over_the_chip(V, members, weighted, rows, nchunks, parts):
-    m = routes.gather_map(rows, nchunks, 4 * V, V * members * (6 if weighted else 2) // nchunks, 2 if weighted else 4)
+    m = routes.gather_map(rows, nchunks, 4 * V, V * members * (6 if weighted else 2) // nchunks, False, weighted)
+    assert (1 << m.row_shift) in (parts if isinstance(parts, tuple) else (parts,))
+
+
+# the same from the CSR
+@pytest.mark.parametrize("V,members,weighted,rows,parts", [
+    (65536, 32, False, 1, 1), (30000, 100, False, 8, (1, 2)), (16384, 32, False, 32, 8), (14987, 8, True, 1, 8), (15569, 10, False, 1, 8),
+    (28456, 111, True, 86, 4), (32524, 72, True, 56, 4), (29622, 39, False, 33, 8)])
+def test_split_over_the_chip_from_the_csr(V, members, weighted, rows, parts):
+    c = routes.csr_shape(V, V, V * members, rows, 256)
+    m = routes.gather_map(rows, c.nchunks, 4 * V, V * members * (8 if weighted else 4) // c.nchunks, True, weighted)
     assert (1 << m.row_shift) in (parts if isinstance(parts, tuple) else (parts,))
 
 
@@ -110,7 +120,7 @@ def test_every_split_reaches_every_row_and_chunk():
     for rows in list(range(1, 40)) + [63, 64, 65, 128, 257]:
         for nchunks in (1, 2, 3, 5, 7, 8, 9, 16, 33):
             for row_bytes, chunk_bytes in ((4096, 1 << 22), (262144, 1 << 20), (1 << 20, 64)):
-                m = routes.gather_map(rows, nchunks, row_bytes, chunk_bytes, 4)
+                m = routes.gather_map(rows, nchunks, row_bytes, chunk_bytes, rows % 2 == 0, False)
                 grid = 8 * -(-rows // (1 << m.row_shift)) * m.chunks_each
                 seen = []
                 for b in range(grid):
